@@ -31,8 +31,9 @@ SHAPES = {
 EPS = 1e-5
 
 
-def _step(name, shape, layers, vocab, B, k, ctx, ctx_max=0, tree=False):
-    c = dict(kind="step", shape=shape, layers=layers, vocab=vocab, B=B, k=k, ctx=ctx, ctx_max=ctx_max or ctx, tree=tree)
+def _step(name, shape, layers, vocab, B, k, ctx, ctx_max=0, tree=False, room=0):
+    """room: cache rows per sequence beyond the longest context and the new rows (a server reserves for growth)."""
+    c = dict(kind="step", shape=shape, layers=layers, vocab=vocab, B=B, k=k, ctx=ctx, ctx_max=ctx_max or ctx, tree=tree, room=room)
     return dict(c, name=name) if name else c
 
 
@@ -44,14 +45,14 @@ def listed():
         _step("8b_whole_b1_k8", "8b", 32, 128256, 1, 8, 2048),
         # plain decoding (no drafts) of a batch on the 70B shape: one layer, 16 rows
         _step("70b_layer_b16_k0", "70b", 1, 1024, 16, 0, 2048),
-        # the same batch with eight drafts each: 144 rows
-        _step("70b_layer_b16_k8", "70b", 1, 1024, 16, 8, 2048),
+        # the same batch with eight drafts each, in a cache that has room for 8192 positions a sequence: 144 rows
+        _step("70b_layer_b16_k8", "70b", 1, 1024, 16, 8, 2048, room=6135),
         # long context, few sequences: attention over 32768 cached positions and 36-row matrices
         _step("8b_layers_b4_k8_long", "8b", 2, 1024, 4, 8, 32768),
         # a serving batch of ragged sequences: 160 rows
         _step("8b_layers_b32_k4_ragged", "8b", 2, 1024, 32, 4, 1024, 4096),
-        # prompts prefilled through the verify step in chunks of 32 tokens: 512 rows
-        _step("8b_layers_prefill_b16_k31", "8b", 2, 1024, 16, 31, 479),
+        # prompts prefilled through the verify step in chunks of 32 tokens, room for 4096 positions: 512 rows
+        _step("8b_layers_prefill_b16_k31", "8b", 2, 1024, 16, 31, 479, room=3585),
         # draft trees of 13 nodes on seven sequences with the real vocabulary: 91 rows, LM head and arg-max
         _step("8b_layer_head_tree_b7_k12", "8b", 1, 128256, 7, 12, 700, 1500, True),
         # attention alone, an odd context, a wide tree of drafts (five row tiles)
@@ -88,8 +89,9 @@ def draw(rng):
     if kind == "attention":
         return dict(kind=kind, shape=shape, B=B, k=k, ctx=lo, ctx_max=ctx)
     layers = 1 if shape == "70b" else rng.choice([1, 2])
+    room = rng.choice([0, 0, 1, 3]) * ctx
     vocab = rng.choice([1024, 1024, 32000, 128256])
-    return _step("", shape, layers, vocab, B, k, lo, ctx, rng.random() < 0.4)
+    return _step("", shape, layers, vocab, B, k, lo, ctx, rng.random() < 0.4, room)
 
 
 # ---------------------------------------------------------------- inputs ----
@@ -194,7 +196,7 @@ def prepare(case, seed):
         out = torch.zeros(B, k + 1, s.n_q_heads * s.head_dim, device=DEV)
         return dict(kind=kind, ctx=ctx, q=q, lens=torch.tensor(lens, dtype=torch.int32, device=DEV), out=out)
     s, tokens, parents, layers, top, g = _step_inputs(case, seed)
-    ctx = sv.VerifyContext(sv.make_config(s, B, k, max(lens) + k + 1), layers, top, in_place=case["shape"] == "70b")
+    ctx = sv.VerifyContext(sv.make_config(s, B, k, max(lens) + k + 1 + case["room"]), layers, top, in_place=case["shape"] == "70b")
     for l in range(s.n_layers):
         for b, (K, V) in enumerate(_kv(g, s, lens)):
             ctx.sssd_kv_import(l, b, 0, K, V)
