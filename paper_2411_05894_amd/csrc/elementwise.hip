@@ -134,7 +134,88 @@ __global__ void rollback_kernel(int B, int32_t *lens, const int32_t *accepted_le
     else lens[b] = new_lens[b];
 }
 
-// grid = (n_rows, nkv), block = d.  ext layout [nkv][n_rows][d]; Kc/Vc: the layer's pools.
+// grid = (blocks of 32 positions that the rows touch, nkv), 256 threads.  ext layout [nkv][n_rows][HD]; Kc/Vc: the
+// layer's pools.  One workgroup moves one (block, kv head): HD*64 bytes of K, contiguous on both sides, and as many of V,
+// whose block is stored transposed (8 positions of one channel per 16-byte record) and turns through LDS.  Everything in
+// memory is read and written 16 bytes at a time, all loads of a thread in flight together: the kernel is bound by the
+// copy rate (read + write) of the memory.  A pitch of HD + 8 elements keeps the 2-byte column accesses of a wave in
+// separate banks (four rows 4 apart, 16 channels each).  4001 rows x 8 heads x 128, in or out: 17.4 -> 8.0 us (4.1 TB/s of reads and writes).
+// A block that the rows cover only in part keeps its other rows: K rows and V elements outside are not written.
+// Blocks that the table sends outside the pool are skipped (nothing written on either side) and raise the sticky flag.
+template <int HD, bool IMPORT>
+__global__ __launch_bounds__(256) void kv_block_copy_kernel(KvGeom kv, uint16_t *Kc, uint16_t *Vc, int b, int t0, int n_rows, uint16_t *k_ext,
+                                                            uint16_t *v_ext, int32_t *err_flag)
+{
+    constexpr int CPR = HD / 8, NREC = 32 * CPR, N = NREC / 256, PITCH = HD + 8;
+    __shared__ __align__(16) uint16_t tile[32 * PITCH];
+    const int blk = (t0 >> 5) + blockIdx.x, kvh = blockIdx.y;
+    const int first = 32 * blk;                                   // position of the block's row 0
+    if (!kv_pages_ok(kv, b, first, first)) {
+        if (threadIdx.x == 0 && kvh == 0) *err_flag = 1;
+        return;
+    }
+    const int lo = t0 > first ? t0 - first : 0, hi = min(32, t0 + n_rows - first);   // rows [lo, hi) of the block
+    const size_t base = kv_block_offset(kv, kv_page(kv, b, blk), kvh);
+    u32x4 *kc = reinterpret_cast<u32x4 *>(Kc + base), *vc = reinterpret_cast<u32x4 *>(Vc + base);
+    // 16-byte records of the block's rows in the plain layout (row r, channels 8x..8x+7 at record r * CPR + x)
+    const ptrdiff_t e0 = ((ptrdiff_t)kvh * n_rows + (first - t0)) * CPR;
+    u32x4 *ke = reinterpret_cast<u32x4 *>(k_ext) + e0, *ve = reinterpret_cast<u32x4 *>(v_ext) + e0;
+    u32x4 k[N], v[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        const int rec = threadIdx.x + 256 * i, row = rec / CPR;
+        const bool in = row >= lo && row < hi;
+        k[i] = v[i] = u32x4{0u, 0u, 0u, 0u};
+        if (in) k[i] = IMPORT ? ke[rec] : kc[rec];
+        if (IMPORT) { if (in) v[i] = ve[rec]; }
+        else v[i] = vc[rec];
+    }
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        const int rec = threadIdx.x + 256 * i, row = rec / CPR;
+        if (row >= lo && row < hi) (IMPORT ? kc : ke)[rec] = k[i];
+    }
+    // record rec of a V block: channel (rec / 64) * 16 + rec % 16, positions 4q..4q+3 and 16+4q..16+4q+3, q = (rec / 16) % 4
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        const int rec = threadIdx.x + 256 * i;
+        if (IMPORT) {
+            *reinterpret_cast<u32x4 *>(&tile[(rec / CPR) * PITCH + (rec % CPR) * 8]) = v[i];
+        } else {
+            const int ch = (rec >> 6) * 16 + (rec & 15), q = (rec >> 4) & 3;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) tile[(4 * q + (e & 3) + 16 * (e >> 2)) * PITCH + ch] = (uint16_t)(v[i][e >> 1] >> (16 * (e & 1)));
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        const int rec = threadIdx.x + 256 * i;
+        if (!IMPORT) {
+            const int row = rec / CPR;
+            if (row >= lo && row < hi) ve[rec] = *reinterpret_cast<const u32x4 *>(&tile[row * PITCH + (rec % CPR) * 8]);
+            continue;
+        }
+        const int ch = (rec >> 6) * 16 + (rec & 15), q = (rec >> 4) & 3;
+        uint16_t x[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) x[e] = tile[(4 * q + (e & 3) + 16 * (e >> 2)) * PITCH + ch];
+        if (lo == 0 && hi == 32) {
+            u32x4 r;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) r[e] = (uint32_t)x[2 * e] | ((uint32_t)x[2 * e + 1] << 16);
+            vc[rec] = r;
+        } else {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const int row = 4 * q + (e & 3) + 16 * (e >> 2);
+                if (row >= lo && row < hi) reinterpret_cast<uint16_t *>(vc + rec)[e] = x[e];
+            }
+        }
+    }
+}
+
+// The same copy element by element, for caller arrays that are not 16-byte aligned: grid = (n_rows, nkv), block = d.
 // A row whose block the table sends outside the pool is skipped (nothing written on either side) and
 // raises the sticky flag.
 __global__ void kv_copy_kernel(Dims D, KvGeom kv, uint16_t *Kc, uint16_t *Vc, int b, int t0, int n_rows, uint16_t *k_ext,
@@ -379,6 +460,14 @@ hipError_t launch_kv_copy(const Dims &D, const KvGeom &kv, uint16_t *Kc_layer, u
                           uint16_t *k_ext, uint16_t *v_ext, bool import, int32_t *err_flag, hipStream_t s)
 {
     if (n_rows <= 0) return hipSuccess;
+    if (((uintptr_t)k_ext | (uintptr_t)v_ext) % 16 == 0) {   // rows are 128 or 256 bytes: every row is aligned then
+        const dim3 grid(((t0 + n_rows - 1) >> 5) - (t0 >> 5) + 1, D.nkv);
+#define SSSD_KVLAUNCH(HD, IN) hipLaunchKernelGGL((kv_block_copy_kernel<HD, IN>), grid, dim3(256), 0, s, kv, Kc_layer, Vc_layer, b, t0, n_rows, k_ext, v_ext, err_flag)
+        if (D.d == 128) { if (import) SSSD_KVLAUNCH(128, true); else SSSD_KVLAUNCH(128, false); }
+        else { if (import) SSSD_KVLAUNCH(64, true); else SSSD_KVLAUNCH(64, false); }
+#undef SSSD_KVLAUNCH
+        return hipGetLastError();
+    }
     hipLaunchKernelGGL(kv_copy_kernel, dim3(n_rows, D.nkv), dim3(D.d), 0, s, D, kv, Kc_layer, Vc_layer, b, t0, n_rows, k_ext,
                        v_ext, import, err_flag);
     return hipGetLastError();

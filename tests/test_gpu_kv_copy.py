@@ -1,0 +1,56 @@
+"""Cache import / export against a plain tensor: ranges that start and end inside blocks of 32 positions, both head
+sizes, a shuffled block table, and caller arrays that are 16-byte aligned or not (each has its own kernel)."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+from paper_2411_05894_amd import binding as sv
+from sssd_synth import MODEL_SHAPES, global_weight_specs, layer_weight_specs, normal_bf16, uniform_int
+
+DEV = "cuda:0"
+
+
+def make_ctx(shape_name, max_seq):
+    s = MODEL_SHAPES[shape_name]
+    s = type(s)(**{**s.__dict__, "n_layers": 1, "vocab": 1024, "hidden": 64, "ffn": 64})
+    layers = [{n: torch.zeros(shp, dtype=torch.bfloat16, device=DEV) for n, _, shp in layer_weight_specs(s)}]
+    g = {n: torch.zeros(shp, dtype=torch.bfloat16, device=DEV) for n, _, shp in global_weight_specs(s)}
+    return s, sv.VerifyContext(sv.make_config(s, 2, 0, max_seq), layers, g)
+
+
+def shifted(t, by):
+    """A contiguous copy of t whose storage starts `by` elements after a 16-byte boundary."""
+    buf = torch.empty(t.numel() + 8, dtype=t.dtype, device=t.device)
+    out = buf[by:by + t.numel()].view(t.shape)
+    out.copy_(t)
+    assert out.data_ptr() % 16 == 2 * by
+    return out
+
+
+@pytest.mark.parametrize("shape_name", ["tiny", "8b"])            # head sizes 64 and 128
+@pytest.mark.parametrize("t0,n", [(0, 1), (0, 32), (31, 1), (31, 2), (5, 20), (5, 27), (5, 28), (32, 64), (17, 111), (0, 129), (63, 66)])
+@pytest.mark.parametrize("by", [0, 1])
+def test_import_export_any_range(shape_name, t0, n, by):
+    max_seq = 130
+    s, ctx = make_ctx(shape_name, max_seq)
+    print(f"kv copy {shape_name} t0={t0} n={n} shift={by}", flush=True)
+    blocks = (max_seq + 31) // 32
+    ctx.sssd_kv_set_block_table(torch.tensor([[3, 8, 0, 6, 2], [9, 1, 7, 5, 4]], dtype=torch.int32, device=DEV)[:, :blocks].contiguous())
+    full = [normal_bf16(5, i, (s.n_kv_heads, max_seq, s.head_dim), 1.0, device=DEV) for i in range(2)]
+    other = [normal_bf16(6, i, (s.n_kv_heads, max_seq, s.head_dim), 1.0, device=DEV) for i in range(2)]
+    new = [normal_bf16(7, i, (s.n_kv_heads, n, s.head_dim), 1.0, device=DEV) for i in range(2)]
+    ctx.sssd_kv_import(0, 0, 0, *other)
+    ctx.sssd_kv_import(0, 1, 0, *full)
+    ctx.sssd_kv_import(0, 1, t0, *[shifted(x, by) for x in new])
+    want = [x.clone() for x in full]
+    for w, x in zip(want, new):
+        w[:, t0:t0 + n] = x
+    for b, ref in ((1, want), (0, other)):                          # the other sequence's pages keep their bits
+        got = [torch.full_like(x, 7.0) for x in ref]
+        ctx.sssd_kv_export(0, b, 0, *got)
+        assert all(torch.equal(g.view(torch.int16), r.view(torch.int16)) for g, r in zip(got, ref))
+    part = [shifted(torch.full_like(x, 7.0), by) for x in new]
+    ctx.sssd_kv_export(0, 1, t0, *part)
+    assert all(torch.equal(p.view(torch.int16), x.view(torch.int16)) for p, x in zip(part, new))
+    assert ctx.sssd_verify_sync() == 0
