@@ -195,3 +195,32 @@ def test_sampling_argument_checks():
                 sv.SamplingParams(1.0, 0, 1.5)):
         with pytest.raises(sv.SssdError):
             sv.sssd_op_sample(z, bad, u)
+
+
+@pytest.mark.parametrize("V,rows", [(4099, 1), (4099, 17), (8192, 129), (32004, 9)])   # clusters of 16, 8, 1 and 16 workgroups
+def test_list_selections_at_their_edges(V, rows):
+    """The largest top_k of either bound search and one more, ties taken in part by both selections, rows whose length
+    is no multiple of four."""
+    smooth = (normal_bf16(111, V, (rows, V), 1.0).float() * 2.0 + 2.0 ** -9 * normal_bf16(112, V, (rows, V), 1.0).float()).contiguous()
+    coarse = (smooth * 4).round() / 4                                # hundreds of equal logits at every threshold
+    u = uniforms(113, rows)
+    for T, k, p in ((0.8, 64, 0.9), (0.8, 65, 0.9), (1.0, 256, 0.99), (1.0, 257, 0.99), (0.9, 2, 0.5), (1.0, 0, 1e-6), (0.7, 0, 0.97)):
+        params = sv.SamplingParams(T, k, p)
+        for logits in (smooth, coarse):
+            say(f"V={V} rows={rows} T={T} top_k={k} top_p={p}")
+            check_rows(logits, params, u, rows // 2)
+
+
+def test_lists_that_overflow_take_the_general_path():
+    """Flat rows, and likely tokens that all lie in one workgroup's share of the row: closed-form answers."""
+    u = torch.tensor([0.0, 0.3, 0.999])
+    for V, top_k, top_p, n in ((16384, 0, 0.5, 8192), (16384, 100, 1.0, 100)):
+        flat = torch.zeros(3, V)
+        for call in (sv.sssd_op_sample, sv.sssd_op_sample_wide):
+            assert call(flat.to(DEV), sv.SamplingParams(1.0, top_k, top_p), u.to(DEV)).cpu().tolist() == [int(x * n) for x in u.tolist()]
+    V = 128256
+    heap = torch.full((1, V), -10.0)
+    heap[0, 300:1100] = 5.0
+    for x in u.tolist():
+        got = sv.sssd_op_sample_wide(heap.to(DEV), sv.SamplingParams(1.0, 50, 1.0), torch.tensor([x]).to(DEV))
+        assert got.cpu().tolist() == [300 + int(x * 50)]
