@@ -7,8 +7,10 @@
 // ones named by a 32-bit word per query node -- itself and its ancestors in the draft
 // tree (Sec. 3.1); for a linear chain that is "row j sees new rows 0..j".
 //
-// One workgroup owns one (sequence, kv head, position chunk).  All g*(k+1) query rows
-// that share the kv head are processed against the chunk, one 16-row tile per wave,
+// One workgroup owns one segment of one sequence's positions for one kv head.  The segments are cut
+// once per step from the device's own lens (attn_schedule in elementwise.hip), so that ragged batches
+// and caches with room to grow keep every compute unit about equally busy.  All g*(k+1) query rows
+// that share the kv head are processed against the segment, one 16-row tile per wave,
 // so every cached byte is read from HBM once per step: the waves stage each block of
 // 32 positions through LDS together (double buffered, the next block's loads in flight
 // during the current block's arithmetic) and every wave reads its operands from there.
@@ -21,7 +23,8 @@
 //                         B operand = the lane's own probabilities)
 // The transposed forms are chosen so that the lane that owns a query row's
 // statistics also owns that row's accumulator columns: no shuffles to rescale.
-// Chunks are merged by a second kernel in fixed order (deterministic).
+// The segments of a sequence are merged by a second kernel in fixed order (deterministic); a
+// sequence that lies in one segment is finished by its workgroup itself.
 #include "kernels.h"
 
 namespace {
@@ -34,11 +37,13 @@ __device__ __forceinline__ f32x4 mfma(const u32x4 &a, const u32x4 &b, f32x4 c)
 constexpr float NEG_BIG = -1.0e30f;
 constexpr int MAX_WAVES = 6;   // query-row tiles per launch
 
-// grid = (splits, kv heads, sequences); block = NW waves; wave w owns query-row tile rt_base + w.
+// grid = (a.wgs * kv heads, passes over the row tiles); block = NW waves; wave w owns query-row tile pass * NW + w.
+// Workgroups 8 apart run on one die, where the heads of a segment follow each other: they read one page (64 KiB of K at
+// eight heads of 128) at about the same time (B = 4, context 32768: 101 us with the heads 64 workgroups apart, 96 us so).
 // The kernel is bound by bytes in flight, i.e. by resident workgroups: with three or more waves the
 // register allocator is held to three waves per SIMD (four workgroups per compute unit).
 template <int HD, int NW>
-__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW >= 3 ? 3 : NW, 3))) void attn_partial_kernel(Dims D, AttnArgs a, int q_rows_pad, int rt_base)
+__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW >= 3 ? 3 : NW, 3))) void attn_partial_kernel(Dims D, AttnArgs a, int q_rows_pad)
 {
     constexpr int KS = HD / 32, DT = HD / 16;
     constexpr int CPR = HD / 8;          // 16-byte records per cached K row
@@ -49,16 +54,34 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW >= 3
     __shared__ u32x4 Ks[2][32 * KROW];
     __shared__ u32x4 Vs[2][NREC];
 
-    const int split = blockIdx.x, kvh = blockIdx.y, b = blockIdx.z;
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    int kvh, wg;
+    {
+        const int id = blockIdx.x, whole = a.wgs & ~7;
+        if (id < whole * D.nkv) {
+            wg = id / (8 * D.nkv) * 8 + (id & 7);
+            kvh = (id >> 3) % D.nkv;
+        } else {
+            const int r = id - whole * D.nkv;
+            wg = whole + r / D.nkv;
+            kvh = r % D.nkv;
+        }
+    }
+    const int4 rec = reinterpret_cast<const int4 *>(a.wg_rec)[wg];   // sequence, first block, blocks, segments of the sequence
+    const int b = rec.x;
+    if (b < 0) return;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int q = lane >> 4, c = lane & 15;
+    const int rt = min((int)blockIdx.y * NW + wave, (q_rows_pad >> 4) - 1);   // the last pass may have waves to spare: they repeat a tile
+    const bool row_tile_ok = (int)blockIdx.y * NW + wave < a.row_tiles;
     const int len = max(a.pos_base[b], 0);   // a rejected sequence (< 0) is read as empty
     const int total = len + a.k + 1;
-    const int t_begin = split * a.chunk;
-    if (t_begin >= total) return;
-    const int t_end = min(total, t_begin + a.chunk);
+    const int t_begin = rec.y * 32;
+    // The segments of a rejected sequence were cut from its own length: those past the rows it is read with see one block
+    // with every position masked.
+    const int t_end = max(min(total, t_begin + rec.z * 32), t_begin + 1);
+    const int n_seg = rec.w;
 
-    // Pages of the chunk's blocks: lane l keeps the page of block first_blk + 64*group + l, so the
+    // Pages of the segment's blocks: lane l keeps the page of block first_blk + 64*group + l, so the
     // page of any block of the current group of 64 is one cross-lane read away.
     const u32x4 *Kpool = reinterpret_cast<const u32x4 *>(a.Kc), *Vpool = reinterpret_cast<const u32x4 *>(a.Vc);
     const int first_blk = t_begin >> 5;
@@ -78,7 +101,6 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW >= 3
         const int page = __shfl(pg, rel & 63);
         return (((size_t)page * D.nkv + kvh) * 32 * HD) >> 3;
     };
-    const int rt = rt_base + wave;
     const u32x4 *Qs = reinterpret_cast<const u32x4 *>(a.Qp + ((size_t)b * D.nkv + kvh) * q_rows_pad * HD) + (size_t)rt * KS * 64 + lane;
     const u32x4 *Ql = reinterpret_cast<const u32x4 *>(a.Qp_lo + ((size_t)b * D.nkv + kvh) * q_rows_pad * HD) + (size_t)rt * KS * 64 + lane;
 
@@ -86,13 +108,13 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW >= 3
     // Two register stages: while block i is processed out of LDS, block i+1 sits in one stage
     // (loaded during the previous iteration, moved to LDS at the end of this one) and block i+2 is
     // being fetched into the other, so two blocks (32 KiB with d = 128) are in flight per workgroup.
-    // Every load is issued unconditionally -- past the chunk's end all lanes re-read one record of the
+    // Every load is issued unconditionally -- past the segment's end all lanes re-read one record of the
     // last block (a single cache line of traffic), which is never stored -- because a load under a
     // branch would make every later wait a full drain.
     struct Stage {
         u32x4 k[SPT], v[SPT];
     };
-    const int t_last = t_begin + ((t_end - t_begin - 1) & ~31);   // first position of the chunk's last block
+    const int t_last = t_begin + ((t_end - t_begin - 1) & ~31);   // first position of the segment's last block
     auto stage_load = [&](Stage &st, int t0) {
         const bool past = t0 > t_last;   // nothing left to fetch: every lane reads one and the same record
         if (past) t0 = t_last;
@@ -217,17 +239,36 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW >= 3
     }
 
     // o[dt][r] of lane (q, c): channel dt*16 + 4q + r of query row rt*16 + c.
-    const size_t slot = ((size_t)b * D.nkv + kvh) * a.n_splits + split;
     float l = l_run;
     l += __shfl_xor(l, 16);
     l += __shfl_xor(l, 32);
-    const size_t row = slot * q_rows_pad + (size_t)rt * 16 + c;
-    float *po = a.part_o + row * HD;
+    const int row = rt * 16 + c;
+    if (n_seg == 1) {   // the whole sequence: the packed operands of the O projection
+        const int jj = row / D.g, hl = row - jj * D.g;
+        if (row_tile_ok && jj <= a.k) {
+            const float inv = 1.f / l;
+            const int m = b * (a.k + 1) + jj, KTq = (D.qd + 31) >> 5;
+            const size_t idx = packed_index(m, (kvh * D.g + hl) * HD + 4 * q, KTq);
 #pragma unroll
-    for (int dt = 0; dt < DT; ++dt) *reinterpret_cast<f32x4 *>(po + dt * 16 + 4 * q) = o[dt];
-    if (q == 0) {
-        a.part_ml[row * 2] = m_run;
-        a.part_ml[row * 2 + 1] = l;
+            for (int dt = 0; dt < DT; ++dt) {
+                uint32_t h0, l0, h1, l1;
+                split_bf16x2(o[dt][0] * inv, o[dt][1] * inv, h0, l0);
+                split_bf16x2(o[dt][2] * inv, o[dt][3] * inv, h1, l1);
+                // channels dt*16 + 4q ..+3: half of lane record 2*(dt%2) + q/2 of k-tile dt/2 of the head
+                const size_t at = idx + (size_t)(dt >> 1) * 512 + (size_t)(dt & 1) * 256;
+                *reinterpret_cast<uint2 *>(a.out_hi + at) = uint2{h0, h1};
+                *reinterpret_cast<uint2 *>(a.out_lo + at) = uint2{l0, l1};
+            }
+        }
+    } else if (row_tile_ok) {
+        const size_t at = ((size_t)kvh * a.wgs + wg) * q_rows_pad + row;
+        float *po = a.part_o + at * HD;
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt) *reinterpret_cast<f32x4 *>(po + dt * 16 + 4 * q) = o[dt];
+        if (q == 0) {
+            a.part_ml[at * 2] = m_run;
+            a.part_ml[at * 2 + 1] = l;
+        }
     }
 }
 
@@ -238,7 +279,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW >= 3
 template <int HD>
 __global__ __launch_bounds__(256) void attn_combine_kernel(Dims D, AttnArgs a, int q_rows_pad)
 {
-    constexpr int BATCH = 9;
+    constexpr int BATCH = 5;
     constexpr int LPR = HD / 8;   // lanes that cover a row of HD channels, 8 each
     const int lane = threadIdx.x & 63, k = a.k;
     const int R = D.g * (k + 1);
@@ -248,9 +289,10 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(Dims D, AttnArgs a, i
     const int KTq = (D.qd + 31) >> 5;
     const int sg = lane >> 4, cl = lane & 15;
     const int r = task % R, kvh = (task / R) % D.nkv, b = task / (R * D.nkv);
-    const int total = max(a.pos_base[b], 0) + k + 1;
-    const int n_splits = (total + a.chunk - 1) / a.chunk;   // at most 64 (launch_attention)
-    const size_t slot0 = ((size_t)b * D.nkv + kvh) * a.n_splits;
+    const int2 seg = *reinterpret_cast<const int2 *>(a.seq_seg + 2 * b);
+    const int n_splits = seg.y;            // at most ATTN_MAX_SEGMENTS
+    if (n_splits == 1) return;             // finished by its workgroup
+    const size_t slot0 = (size_t)kvh * a.wgs + seg.x;
 
     float2 ml = float2{NEG_BIG, 0.f};
     if (lane < n_splits) ml = *reinterpret_cast<const float2 *>(a.part_ml + ((slot0 + lane) * q_rows_pad + r) * 2);
@@ -309,86 +351,58 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(Dims D, AttnArgs a, i
     }
 }
 
-template <int HD, int NW> void launch_nw(const Dims &D, const AttnArgs &a, int q_rows_pad, int rt0, dim3 grid, hipStream_t s)
-{
-    hipLaunchKernelGGL((attn_partial_kernel<HD, NW>), grid, dim3(NW * 64), 0, s, D, a, q_rows_pad, rt0);
-}
-
 template <int HD> hipError_t launch_partial(const Dims &D, const AttnArgs &a, int q_rows_pad, hipStream_t s)
 {
-    const int rows = D.g * (a.k + 1);
-    const int rt_total = (rows + 15) / 16;
-    const dim3 grid(a.n_splits, D.nkv, a.B);
-    // One wave per query-row tile; more than MAX_WAVES tiles take further passes over the cache.
-    for (int rt0 = 0; rt0 < rt_total; rt0 += MAX_WAVES) {
-        const int nw = rt_total - rt0 < MAX_WAVES ? rt_total - rt0 : MAX_WAVES;
-        switch (nw) {
-        case 1: launch_nw<HD, 1>(D, a, q_rows_pad, rt0, grid, s); break;
-        case 2: launch_nw<HD, 2>(D, a, q_rows_pad, rt0, grid, s); break;
-        case 3: launch_nw<HD, 3>(D, a, q_rows_pad, rt0, grid, s); break;
-        case 4: launch_nw<HD, 4>(D, a, q_rows_pad, rt0, grid, s); break;
-        case 5: launch_nw<HD, 5>(D, a, q_rows_pad, rt0, grid, s); break;
-        default: launch_nw<HD, 6>(D, a, q_rows_pad, rt0, grid, s); break;
-        }
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
+    // One wave per query-row tile; more than MAX_WAVES tiles are spread evenly over several passes over the cache.
+    const int passes = (a.row_tiles + MAX_WAVES - 1) / MAX_WAVES, nw = (a.row_tiles + passes - 1) / passes;
+    const dim3 grid(a.wgs * D.nkv, passes);
+#define SSSD_ALAUNCH(NW) hipLaunchKernelGGL((attn_partial_kernel<HD, NW>), grid, dim3(NW * 64), 0, s, D, a, q_rows_pad)
+    switch (nw) {
+    case 1: SSSD_ALAUNCH(1); break;
+    case 2: SSSD_ALAUNCH(2); break;
+    case 3: SSSD_ALAUNCH(3); break;
+    case 4: SSSD_ALAUNCH(4); break;
+    case 5: SSSD_ALAUNCH(5); break;
+    default: SSSD_ALAUNCH(6); break;
     }
-    return hipSuccess;
+#undef SSSD_ALAUNCH
+    return hipGetLastError();
 }
 
 }  // namespace
 
-// Positions per workgroup for a step of B sequences with `rows` query rows per kv head.  The device
-// holds four workgroups per compute unit with up to three waves (row tiles) each, three with four
-// waves, two with five or six, i.e. 1024 / 768 / 512 at once, and a launch is kept to one such round
-// at most (a round and a half measured 8 % slower than one or two).  Within that, fewer and longer
-// chunks are faster -- every chunk is a partial result of g*(k+1) rows to write and merge, and HBM
-// serves 512 concurrent streams better than 1024 -- as long as ragged batches still even out:
-//   target = max(512, 3 chunks per (sequence, kv head)), capped at the round.
-// Measured, 8B shape, ms per step at 512 / 768 / 1024 workgroups: B = 4, context 32768, k = 8 (three
-// waves) 7.47 / 7.71 / 8.23; k = 4 (two) 6.79 / 6.95 / 6.98; k = 12 (four) 7.84 / 7.95 / 8.41; B = 16,
-// context 4096, k = 8: 9.12 / 9.22 / 9.42; 32 ragged sequences of 1024..4096 at k = 4: 9.89 / 9.54 /
-// 9.59 (two chunks per sequence leave the compute units unevenly loaded).  70B shape at k = 8, five
-// waves: 13 chunks of 160 positions per sequence -> 4 of 544: attention 7.3 -> 5.3 ms per step.  With five or
-// six waves and long caches, 256 workgroups beat 512 (70B shape, 16 layers, B = 8, context 8192, k = 8:
-// 8.21 against 8.55 ms; 8B shape, B = 4, context 16384, k = 23: 8.09 against 8.45; context 32768, k = 16:
-// 9.82 against 10.09), while at B = 16, context 2048 (chunks of 1030 positions) 512 stay 1 % ahead.
-// In whole 32-position blocks, at most 64 chunks per sequence (128 measured 4 % slower per step at
-// B = 1, context 32768) and at least 128 positions per chunk (shorter chunks only add partial
-// results for the merge: at B = 1, context 2048 the merge takes 6.8 us with 64-position chunks, 5.6 us
-// with 128, the partial kernel the same).
-int attention_chunk(const Dims &D, int B, int rows)
+AttnPlan attention_plan(const Dims &D, int B, int k)
 {
-    const int waves = (rows + 15) / 16 < MAX_WAVES ? (rows + 15) / 16 : MAX_WAVES;
-    const long round = waves <= 3 ? 1024 : (waves == 4 ? 768 : 512);
-    const long positions = (long)D.seq_pad * B * D.nkv;
-    long target = 3L * B * D.nkv;
-    // five or six waves: one workgroup per compute unit when that still leaves it 2048 positions or more
-    const long least = (waves >= 5 && positions >= 256L * 2048) ? 256 : 512;
-    if (target < least) target = least;
-    if (target > round) target = round;
-    long chunk = (positions + target - 1) / target;
-    const long floor64 = (D.seq_pad + 63) / 64;
-    if (chunk < floor64) chunk = floor64;
-    chunk = (chunk + 31) / 32 * 32;
-    if (chunk < 128) chunk = 128;
-    return (int)chunk;
+    const int tiles = (D.g * (k + 1) + 15) / 16;
+    const int passes = (tiles + MAX_WAVES - 1) / MAX_WAVES, waves = (tiles + passes - 1) / passes;
+    const long pairs = (long)B * D.nkv;
+    long target;
+    if (waves >= 5) target = 3 * pairs > 256 ? 512 : 256;
+    else {
+        target = 3 * pairs > 512 ? 3 * pairs : 512;
+        const long round = waves == 4 ? 768 : 1024;
+        if (target > round) target = round;
+    }
+    target = (target + passes - 1) / passes;
+    AttnPlan p;
+    const int w = (int)((target + D.nkv - 1) / D.nkv);
+    p.wgs = w > B ? w : B;
+    p.min_blocks = 4;
+    p.long_blocks = 0x7FFFFFFF;
+    if (tiles > 4) p.long_blocks = (16 * 256 + D.nkv * passes - 1) / (D.nkv * passes);
+    p.wg_rec = p.seq_seg = nullptr;
+    return p;
 }
 
-// Chunks per sequence at the narrowest step (the most chunks any step of B sequences uses): what the
-// partial-result buffers are sized for.
-int attention_splits(const Dims &D, int B)
-{
-    const int chunk = attention_chunk(D, B, 1);
-    return (D.seq_pad + chunk - 1) / chunk;
-}
+// Partial results a step of B sequences can leave, all kv heads: most at the narrowest step.
+size_t attention_slots(const Dims &D, int B) { return (size_t)D.nkv * attention_plan(D, B, 0).wgs; }
 
 hipError_t launch_attention(const Dims &D, const AttnArgs &a_in, hipStream_t s)
 {
     AttnArgs a = a_in;
-    a.chunk = attention_chunk(D, a.B, D.g * (a.k + 1));
-    a.n_splits = (D.seq_pad + a.chunk - 1) / a.chunk;
     const int q_rows_pad = round_up(D.g * (D.max_k + 1), 16);
+    a.row_tiles = (D.g * (a.k + 1) + 15) / 16;
+    a.wgs = attention_plan(D, a.B, a.k).wgs;
     hipError_t e = D.d == 128 ? launch_partial<128>(D, a, q_rows_pad, s) : launch_partial<64>(D, a, q_rows_pad, s);
     if (e != hipSuccess) return e;
     const int n_tasks = a.B * D.nkv * D.g * (a.k + 1);

@@ -2,6 +2,8 @@
 #pragma once
 #include "common.h"
 
+struct AttnPlan;
+
 // ---------------------------------------------------------- elementwise ----
 // Reorder a row-major bf16 matrix [N][K] into packed tiles (K padded to 32 with zeros).
 hipError_t launch_pack_weight(const uint16_t *src, uint16_t *dst, int N, int K, hipStream_t s);
@@ -74,7 +76,7 @@ hipError_t launch_stream_gemm(FusedGemmArgs &a, int epilogue, hipStream_t s, boo
 hipError_t launch_stream_epilogue(const FusedGemmArgs &a, int epilogue, hipStream_t s);
 hipError_t launch_fused_embed(const Dims &D, const StepIO &io, const KvGeom &kv, const uint16_t *embed, const uint16_t *gamma,
                               float *X, uint16_t *A_hi, uint16_t *A_lo, float *ssq, int32_t *pos_base, int32_t *rope_pos,
-                              uint32_t *anc, int32_t *err_flag, hipStream_t s);
+                              uint32_t *anc, int32_t *err_flag, const AttnPlan &plan, hipStream_t s);
 
 // Merge per-tile arg-max partials, then greedy acceptance (longest matching prefix of a chain, or
 // the walk from the root of a draft tree when io.parents is set).
@@ -110,7 +112,7 @@ constexpr int STREAM_READ_SINK_WORDS = 4096;
 hipError_t launch_stream_read(const void *src, size_t bytes, uint32_t *sink, int n_cu, hipStream_t s);
 hipError_t launch_q_pack(const Dims &D, const float *q, int B, int k, uint16_t *Qp, uint16_t *Qp_lo, hipStream_t s);
 hipError_t launch_lens(const Dims &D, int B, int k, const int32_t *lens, int32_t *pos_base, int32_t *rope_pos,
-                       uint32_t *anc, int32_t *err_flag, hipStream_t s);
+                       uint32_t *anc, int32_t *err_flag, const AttnPlan &plan, hipStream_t s);
 
 // ------------------------------------------------------------ attention ----
 struct AttnArgs {
@@ -120,14 +122,25 @@ struct AttnArgs {
     KvGeom kv;                 // page geometry
     const int32_t *pos_base;   // validated lens
     const uint32_t *anc;       // [B*(k+1)] visible new rows of each query row (bit i = row pos_base + i)
-    float *part_o;             // [b][kv head][n_splits][q_rows_pad][d]
-    float *part_ml;            // [b][kv head][n_splits][q_rows_pad][2]  (running max in log2 units, sum)
+    float *part_o;             // [kv head][wgs][q_rows_pad][d]
+    float *part_ml;            // [kv head][wgs][q_rows_pad][2]  (running max in log2 units, sum)
+    const int32_t *wg_rec;     // the step's segments (AttnPlan)
+    const int32_t *seq_seg;
     uint16_t *out_hi, *out_lo; // packed activations for the O projection (K = nq*d)
     int B, k;
-    int chunk, n_splits;       // filled in by launch_attention: positions per workgroup, partial slots per (b, kv head)
+    int wgs, row_tiles;        // filled in by launch_attention: workgroups per kv head, 16-row tiles of query rows
 };
-// Positions per workgroup for a step of B sequences with `rows` query rows per kv head, and the most
-// chunks per sequence any such step uses (sizes the partial buffers).
-int attention_chunk(const Dims &D, int B, int rows);
-int attention_splits(const Dims &D, int B);
+// How a step of B sequences x k drafts is cut into segments: at most wgs of them per kv head, of min_blocks blocks of 32
+// positions or more, at most ATTN_MAX_SEGMENTS per sequence (what the merge takes).  The device cuts them from lens once
+// per step (fused_embed_kernel, lens_kernel) into
+//   wg_rec   int32 [wgs][4]: sequence (-1: none), first block, blocks, segments of that sequence
+//   seq_seg  int32 [B][2]: first segment and number of segments of a sequence
+struct AttnPlan {
+    int wgs, min_blocks, long_blocks;   // 16 blocks or more once the head's list is long_blocks long
+    int32_t *wg_rec, *seq_seg;
+};
+constexpr int ATTN_MAX_SEGMENTS = 64;
+AttnPlan attention_plan(const Dims &D, int B, int k);   // without the arrays
+// Partial slots of a step of B sequences, all kv heads (sizes the buffers).
+size_t attention_slots(const Dims &D, int B);
 hipError_t launch_attention(const Dims &D, const AttnArgs &a, hipStream_t s);
