@@ -54,8 +54,8 @@ int sssd_op_gemm_static(const void *a_hi, const void *a_lo, const void *w_packed
  * large-M kernels (qgemm_kernel up to 48 rows, qgemm16_kernel above).  For benchmarks. */
 int32_t sssd_op_gemm_small_step_rows(void);
 
-/* Name of the weight-streaming kernel that a GEMM of M rows launches (static string; for M > 160, of its
- * first pass of 160 rows): "pgemm_kernel", "qgemm_kernel" or "qgemm16_kernel". */
+/* Name of the weight-streaming kernel that a GEMM of M rows launches (static string): "pgemm_kernel",
+ * "qgemm_kernel" or "qgemm16_kernel". */
 const char *sssd_op_gemm_kernel_name(int32_t M);
 
 /* Measurement aid: one read-only pass over `bytes` (>= 16, src 16-byte aligned) of device memory by a

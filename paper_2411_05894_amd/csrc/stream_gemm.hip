@@ -12,13 +12,13 @@
 //                  are refilled for the NEXT tile right after the MFMA that consumed them: a
 //                  rolling prefetch with a constant number of bytes in flight per wave and no
 //                  bubble at tile boundaries.  The k-split is reduced through LDS in fixed order.
-//   qgemm16_kernel M > 48 rows (up to 160 per pass).  v_mfma_f32_16x16x32_bf16 tiles: each wave of a
+//   qgemm16_kernel M > 48 rows (in blocks of up to 160).  v_mfma_f32_16x16x32_bf16 tiles: each wave of a
 //                  workgroup of eight (four for the small matrices) owns 32 output columns and streams
 //                  their weights HBM -> registers (rolling prefetch, every weight byte read once), while
 //                  the activation k-tiles of the workgroup's k-slice, which all its waves need, are staged
 //                  through a register ring and a two-deep LDS ring.  Results go to split-K partials for
 //                  epi_kernel.
-//   qgemm_kernel   33..48 rows (and the rows a pass of 160 leaves over): the same launch on
+//   qgemm_kernel   33..48 rows: the same launch on
 //                  v_mfma_f32_32x32x16_bf16, the 16-row operand tiles of the packed layout read as the
 //                  halves of 32-row MFMA operands, so one weight layout serves every kernel.
 //   epi_kernel     Sums split-K partial results (when K is split over workgroups) in fixed order
@@ -444,14 +444,14 @@ constexpr int QDW = 4;   // weight k-tiles in flight per wave
 // k-slots pair up.
 __device__ __forceinline__ int half_record(int lane, int hh) { return (lane & 15) + 16 * ((lane >> 5) + 2 * hh); }
 
-// grid = n_groups * J workgroups of QW waves; rows [m_base, m_base + 32*MT32) of the packed
+// grid = n_groups * J workgroups of QW waves; rows [0, 32*MT32) of the packed
 // activations; writes partials[j][row][col].  One 32-column tile per wave, so two or more waves
 // share a SIMD and cover each other's LDS and barrier waits; QW = 8 (256 columns per workgroup)
 // for the large matrices, QW = 4 for the small ones, whose K then splits half as often (measured:
 // 8 waves 15 % faster on gate/up and down at M = 160, 4 waves 10-15 % faster on QKV and O, and on
 // every matrix at up to 64 rows).
 template <int MT32, int QW>
-__global__ __launch_bounds__(QW * 64) void qgemm_kernel(FusedGemmArgs a, int m_base, int NT16)
+__global__ __launch_bounds__(QW * 64) void qgemm_kernel(FusedGemmArgs a, int NT16)
 {
     constexpr int MT16 = 2 * MT32;
     constexpr int CHUNK = MT16 * 2 * 64;          // lane records of one activation k-tile (hi and lo)
@@ -478,7 +478,6 @@ __global__ __launch_bounds__(QW * 64) void qgemm_kernel(FusedGemmArgs a, int m_b
     const int r0 = half_record(lane, 0), r1 = half_record(lane, 1);
 
     // activation staging: thread t moves records t, t+256, ... of each k-tile chunk
-    const size_t mt_base = (size_t)(m_base >> 4);
     const u32x4 *asrc[APT];
 #pragma unroll
     for (int i = 0; i < APT; ++i) {
@@ -486,7 +485,7 @@ __global__ __launch_bounds__(QW * 64) void qgemm_kernel(FusedGemmArgs a, int m_b
         if (!AFULL && q >= CHUNK) q = CHUNK - 1;  // surplus threads re-read the last record, never stored
         const int tile = q >> 6, rec = q & 63;    // tile = mt16 * 2 + (0: hi, 1: lo)
         const u32x4 *base = (tile & 1) ? a.A_lo : a.A_hi;
-        asrc[i] = base + ((mt_base + (tile >> 1)) * KT) * 64 + rec;
+        asrc[i] = base + ((size_t)(tile >> 1) * KT) * 64 + rec;
     }
     auto stage_load = [&](int kt, u32x4 (&v)[APT]) {
 #pragma unroll
@@ -574,7 +573,7 @@ __global__ __launch_bounds__(QW * 64) void qgemm_kernel(FusedGemmArgs a, int m_b
         for (int i = 0; i < MT32; ++i)
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
-                const int row = m_base + 32 * i + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
+                const int row = 32 * i + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
                 if (row < a.part_rows) a.partials[((size_t)j * a.part_rows + row) * a.Ntot + col] = acc[i][g][v];
             }
     }
@@ -589,8 +588,12 @@ __global__ __launch_bounds__(QW * 64) void qgemm_kernel(FusedGemmArgs a, int m_b
 // 6.20 -> 5.93, 112 rows 6.93 -> 6.72, 144 rows 8.02 -> 7.80, 64 / 96 / 128 / 160 rows 0-1.5 % ahead; 70B shape
 // (16 layers) 80 rows 7.67 -> 7.03, 144 rows 10.79 -> 10.28, 64 / 160 rows 3 % ahead; at 36 rows the 32 x 32 form
 // stays 4 % ahead on the 8B shape (same on the 70B shape at 48), so up to 48 rows keep it.
-template <int MT16, int QW>
-__global__ __launch_bounds__(QW * 64) void qgemm16_kernel(FusedGemmArgs a, int m_base, int NT16)
+//
+// More than 160 rows are cut into RB blocks of MT16 row tiles, all in one launch: blocks 8 apart in the grid run on one
+// die, where the row blocks of a (column group, slice) follow each other and share the weights through its L2 (ordinary
+// loads then, not streaming ones).
+template <int MT16, int QW, bool BLOCKS>
+__global__ __launch_bounds__(QW * 64) void qgemm16_kernel(FusedGemmArgs a, int RB, int NT16)
 {
     constexpr int QDW = 4;
     constexpr int CHUNK = MT16 * 2 * 64;          // lane records of one activation k-tile (hi and lo)
@@ -598,7 +601,20 @@ __global__ __launch_bounds__(QW * 64) void qgemm16_kernel(FusedGemmArgs a, int m
     constexpr bool AFULL = CHUNK % (QW * 64) == 0;
     __shared__ u32x4 ring[2][CHUNK];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-    const int J = a.J, j = blockIdx.x % J, grp = blockIdx.x / J;
+    int gj = blockIdx.x, rb = 0;
+    if (BLOCKS) {
+        const int n = gridDim.x / RB, whole = n & ~7;     // (column group, slice) pairs; those in full sets of 8
+        if ((int)blockIdx.x < whole * RB) {
+            rb = (blockIdx.x >> 3) % RB;
+            gj = (blockIdx.x >> 3) / RB * 8 + (blockIdx.x & 7);
+        } else {
+            const int x = blockIdx.x - whole * RB;
+            rb = x / (n - whole);
+            gj = whole + x % (n - whole);
+        }
+    }
+    const int m_base = rb * MT16 * 16;
+    const int J = a.J, j = gj % J, grp = gj / J;
     const int KT = a.KT;
     const int kps = a.kps;
     const int kt_begin = j * kps, kt_end = kt_begin + kps < KT ? kt_begin + kps : KT;
@@ -643,8 +659,9 @@ __global__ __launch_bounds__(QW * 64) void qgemm16_kernel(FusedGemmArgs a, int m
     auto issue = [&](int u, int it) {   // activation chunk and weights of iteration `it` into slot u
         const int kt = kt_begin + (it < n_iter ? it : n_iter - 1);
         stage_load(kt, apre[u]);
-        w[u][0] = __builtin_nontemporal_load(wp[0] + (size_t)kt * 64);
-        w[u][1] = __builtin_nontemporal_load(wp[1] + (size_t)kt * 64);
+#pragma unroll
+        for (int ct = 0; ct < 2; ++ct)
+            w[u][ct] = BLOCKS ? wp[ct][(size_t)kt * 64] : __builtin_nontemporal_load(wp[ct] + (size_t)kt * 64);
     };
 #pragma unroll
     for (int u = 0; u < QDW; ++u) issue(u, u);
@@ -730,6 +747,26 @@ __host__ QPlan q_plan(int Ntot, int K, int M)
         if (fill > best_fill + 1e-9) { best_fill = fill; best = J; }
         if (fill >= 0.85) { best = J; break; }
     }
+    if (M > 160) {
+        // Row blocks fill the device as well as slices do, without partial sums: the split with the least estimated time
+        //   rounds x (k-tiles per slice x row tiles x 0.099 us + 10.6 us) + 0.13 us per MB of partial sums to read back,
+        // fitted to the 8B shapes at 256 and 512 rows, eight waves throughout.  Measured there, GEMM and epilogue launch at
+        // 512 rows, J = 1 / 2 / 3 / 4 / 6 / 8: QKV 103 / 66 / 95 / 75 / 88 / 82 us, O 100 / 61 / 50 / 45 / 61 / 58, gate/up
+        // 290 / 301 / 315 / 324 / 385 / 451, down 322 / 174 / 133 / 109 / 142 / 122 (four passes of up to 160 rows took 126,
+        // 101, 294 + 30 and 190 + 19 us).  No split needs more than SPLIT_BYTES of partial sums unless the rule above did.
+        constexpr size_t SPLIT_BYTES = (size_t)32 << 20;
+        const int was = best, mt16 = (M + 15) / 16, RB = (mt16 + 9) / 10, mt = (mt16 + RB - 1) / RB;
+        p.qw = 8;
+        p.groups = (NT32 + p.qw * QNG - 1) / (p.qw * QNG);
+        double least = 0.0;
+        for (int J = 1; J <= jmax; ++J) {
+            const size_t sums = (size_t)J * mt16 * 16 * Ntot * sizeof(float);
+            if (J > was && sums > SPLIT_BYTES) break;
+            const long tasks = (long)p.groups * RB * J, rounds = (tasks + slots - 1) / slots;
+            const double us = (double)rounds * ((KT + J - 1) / J * mt * 0.099 + 10.6) + 0.13e-6 * (double)sums;
+            if (J == 1 || us < least) { least = us; best = J; }
+        }
+    }
     p.kps = (KT + best - 1) / best;
     p.J = (KT + p.kps - 1) / p.kps;
     return p;
@@ -747,43 +784,32 @@ template <int EPI> hipError_t launch_large(FusedGemmArgs &a, hipStream_t s, bool
     else if (EPI == FEPI_SWIGLU) { a.seg0 = a.NT; a.seg1 = a.NT; }
     else { a.seg0 = NT16; a.seg1 = 0; }
     if ((size_t)a.J * a.part_rows * a.Ntot * sizeof(float) > a.partial_bytes) return hipErrorInvalidValue;
-    const dim3 grid(p.groups * a.J), block(p.qw * 64);
-    for (int m_base = 0; m_base < a.M; m_base += 160) {
-        const int mt32 = (a.M - m_base + 31) / 32;
-        const int mt16 = (a.M - m_base + 15) / 16;
-        hipEvent_t e0 = m_base == 0 ? t0 : nullptr, e1 = m_base + 160 >= a.M ? t1 : nullptr;   // first pass starts, last pass stops
-        if (mt16 >= 4) {   // 49 rows and more: the 16 x 16 x 32 form (measured ahead at every tile count from 4 up)
-#define SSSD_Q16LAUNCH(MT)                                                                                      \
-    do {                                                                                                        \
-        if (p.qw == 8) hipExtLaunchKernelGGL((qgemm16_kernel<MT, 8>), grid, block, 0, s, e0, e1, 0, a, m_base, NT16); \
-        else hipExtLaunchKernelGGL((qgemm16_kernel<MT, 4>), grid, block, 0, s, e0, e1, 0, a, m_base, NT16);     \
+    const int mt16 = (a.M + 15) / 16, RB = (mt16 + 9) / 10;
+    const dim3 grid(p.groups * a.J * RB), block(p.qw * 64);
+    if (mt16 >= 4) {   // 49 rows and more: the 16 x 16 x 32 form (measured ahead at every tile count from 4 up)
+#define SSSD_Q16LAUNCH(MT, QW, BLOCKS) hipExtLaunchKernelGGL((qgemm16_kernel<MT, QW, BLOCKS>), grid, block, 0, s, t0, t1, 0, a, RB, NT16)
+#define SSSD_Q16ROWS(MT)                                        \
+    do {                                                        \
+        if (RB > 1) SSSD_Q16LAUNCH((MT > 6 ? MT : 6), 8, true); \
+        else if (p.qw == 8) SSSD_Q16LAUNCH(MT, 8, false);       \
+        else SSSD_Q16LAUNCH(MT, 4, false);                      \
     } while (0)
-            switch (mt16) {
-            case 4: SSSD_Q16LAUNCH(4); break;
-            case 5: SSSD_Q16LAUNCH(5); break;
-            case 6: SSSD_Q16LAUNCH(6); break;
-            case 7: SSSD_Q16LAUNCH(7); break;
-            case 8: SSSD_Q16LAUNCH(8); break;
-            case 9: SSSD_Q16LAUNCH(9); break;
-            default: SSSD_Q16LAUNCH(10); break;
-            }
-#undef SSSD_Q16LAUNCH
-            hipError_t e16 = hipGetLastError();
-            if (e16 != hipSuccess) return e16;
-            continue;
+        switch ((mt16 + RB - 1) / RB) {   // several row blocks have at least six tiles each
+        case 4: SSSD_Q16ROWS(4); break;
+        case 5: SSSD_Q16ROWS(5); break;
+        case 6: SSSD_Q16ROWS(6); break;
+        case 7: SSSD_Q16ROWS(7); break;
+        case 8: SSSD_Q16ROWS(8); break;
+        case 9: SSSD_Q16ROWS(9); break;
+        default: SSSD_Q16ROWS(10); break;
         }
-#define SSSD_QLAUNCH(MT)                                                                                        \
-    do {                                                                                                        \
-        if (p.qw == 8) hipExtLaunchKernelGGL((qgemm_kernel<MT, 8>), grid, block, 0, s, e0, e1, 0, a, m_base, NT16); \
-        else hipExtLaunchKernelGGL((qgemm_kernel<MT, 4>), grid, block, 0, s, e0, e1, 0, a, m_base, NT16);       \
-    } while (0)
-        if (mt32 == 1) SSSD_QLAUNCH(1);   // the rows left over by a pass of 160
-        else SSSD_QLAUNCH(2);             // 33..48 rows
-#undef SSSD_QLAUNCH
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
+#undef SSSD_Q16ROWS
+#undef SSSD_Q16LAUNCH
+    } else {   // 33..48 rows
+        if (p.qw == 8) hipExtLaunchKernelGGL((qgemm_kernel<2, 8>), grid, block, 0, s, t0, t1, 0, a, NT16);
+        else hipExtLaunchKernelGGL((qgemm_kernel<2, 4>), grid, block, 0, s, t0, t1, 0, a, NT16);
     }
-    return hipSuccess;
+    return hipGetLastError();
 }
 
 // k-tiles per wave: 7 when K is a multiple of 16*7*32 but not of 16*8*32 (the FFN widths of the
@@ -840,7 +866,7 @@ int stream_gemm_max_rows() { return 32; }
 const char *stream_gemm_kernel_name(int M)
 {
     if (M <= stream_gemm_max_rows()) return "pgemm_kernel";
-    return (M < 160 ? M : 160) > 48 ? "qgemm16_kernel" : "qgemm_kernel";
+    return M > 48 ? "qgemm16_kernel" : "qgemm_kernel";
 }
 
 // Split-K scratch needed for M rows: the largest J * rows * Ntot over the model's GEMMs.
@@ -858,13 +884,11 @@ size_t stream_gemm_partial_bytes(const Dims &D, int M)
     consider(D.h, 2 * (size_t)D.f);
     consider(D.f, D.h);
     consider(D.h, D.V);
-    // larger steps: the K split depends on the row count's class (32-row tiles), so take the worst
-    // case over every step size up to M
-    for (int mc = 32; M > stream_gemm_max_rows(); mc += 32) {
-        const int rows_c = mc < M ? mc : M;
-        const size_t rows = (size_t)round_up(rows_c, 16);
+    // larger steps: the K split depends on the number of row tiles, so take the worst case over every step size up to M
+    for (int rows_c = 48; M > stream_gemm_max_rows(); rows_c += 16) {
+        const int rows = rows_c < round_up(M, 16) ? rows_c : round_up(M, 16);
         auto large = [&](int K, size_t ntot) {
-            const size_t need = (size_t)q_plan((int)ntot, K, rows_c).J * rows * ntot;
+            const size_t need = (size_t)q_plan((int)ntot, K, rows).J * rows * ntot;
             if (need > best) best = need;
         };
         large(D.h, (size_t)D.qd + 2 * D.kd);
@@ -872,7 +896,7 @@ size_t stream_gemm_partial_bytes(const Dims &D, int M)
         large(D.h, 2 * (size_t)D.f);
         large(D.f, D.h);
         large(D.h, D.V);
-        if (mc >= M) break;
+        if (rows_c >= M) break;
     }
     return best * sizeof(float);
 }
