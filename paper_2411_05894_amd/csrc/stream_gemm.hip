@@ -12,15 +12,12 @@
 //                  are refilled for the NEXT tile right after the MFMA that consumed them: a
 //                  rolling prefetch with a constant number of bytes in flight per wave and no
 //                  bubble at tile boundaries.  The k-split is reduced through LDS in fixed order.
-//   qgemm16_kernel M > 48 rows (in blocks of up to 160).  v_mfma_f32_16x16x32_bf16 tiles: each wave of a
-//                  workgroup of eight (four for the small matrices) owns 32 output columns and streams
-//                  their weights HBM -> registers (rolling prefetch, every weight byte read once), while
-//                  the activation k-tiles of the workgroup's k-slice, which all its waves need, are staged
-//                  through a register ring and a two-deep LDS ring.  Results go to split-K partials for
-//                  epi_kernel.
-//   qgemm_kernel   33..48 rows: the same launch on
-//                  v_mfma_f32_32x32x16_bf16, the 16-row operand tiles of the packed layout read as the
-//                  halves of 32-row MFMA operands, so one weight layout serves every kernel.
+//   qgemm16_kernel More rows, in blocks of up to 160, and the matrices whose K pgemm_kernel would have to split
+//                  (is_small).  v_mfma_f32_16x16x32_bf16 tiles: each wave of a workgroup of eight (four for the small
+//                  matrices) owns 32 output columns and streams their weights HBM -> registers (rolling prefetch,
+//                  every weight byte read once), while the activation k-tiles of the workgroup's k-slice, which all
+//                  its waves need, are staged through a register ring and a four-deep LDS ring.  Results go to
+//                  split-K partials for epi_kernel.
 //   epi_kernel     Sums split-K partial results (when K is split over workgroups) in fixed order
 //                  and applies the epilogue.
 //
@@ -411,13 +408,6 @@ template <int EPI> hipError_t launch_epi(const FusedGemmArgs &a, hipStream_t s)
 }
 
 // ------------------------------------------------------------------- M > 32 ----
-typedef __attribute__((ext_vector_type(16))) float f32x16;
-
-__device__ __forceinline__ f32x16 mfma32(const u32x4 &a, const u32x4 &b, f32x16 c)
-{
-    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
-}
-
 // Packed weights of concatenated 16-column tile gt for any epilogue: the output is up to three
 // matrices side by side, the first two of seg0 and seg1 tiles.
 __device__ __forceinline__ const u32x4 *tile_weights_seg(const FusedGemmArgs &a, int gt)
@@ -435,172 +425,45 @@ __device__ __forceinline__ const u32x4 *tile_weights_seg(const FusedGemmArgs &a,
     return base + gt * stride;
 }
 
-constexpr int QNG = 1;   // 32-column tiles per wave
-constexpr int QDW = 4;   // weight k-tiles in flight per wave
-
-// A 32 x 16 MFMA operand (rows l%32, k-slots 8*(l/32)..+7) assembled from two packed 16 x 32
-// tiles T0 (rows 0..15) and T1 (rows 16..31): for k-half hh of the k-tile, lane l takes lane
-// record (l%16) + 16*(l/32 + 2*hh) of tile T[(l/16)%2].  Both operands use the same rule, so the
-// k-slots pair up.
-__device__ __forceinline__ int half_record(int lane, int hh) { return (lane & 15) + 16 * ((lane >> 5) + 2 * hh); }
-
-// grid = n_groups * J workgroups of QW waves; rows [0, 32*MT32) of the packed
-// activations; writes partials[j][row][col].  One 32-column tile per wave, so two or more waves
-// share a SIMD and cover each other's LDS and barrier waits; QW = 8 (256 columns per workgroup)
-// for the large matrices, QW = 4 for the small ones, whose K then splits half as often (measured:
-// 8 waves 15 % faster on gate/up and down at M = 160, 4 waves 10-15 % faster on QKV and O, and on
-// every matrix at up to 64 rows).
-template <int MT32, int QW>
-__global__ __launch_bounds__(QW * 64) void qgemm_kernel(FusedGemmArgs a, int NT16)
-{
-    constexpr int MT16 = 2 * MT32;
-    constexpr int CHUNK = MT16 * 2 * 64;          // lane records of one activation k-tile (hi and lo)
-    constexpr int APT = (CHUNK + QW * 64 - 1) / (QW * 64);   // records staged per thread
-    constexpr bool AFULL = CHUNK % (QW * 64) == 0;
-    __shared__ u32x4 ring[2][CHUNK];
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-    const int J = a.J, j = blockIdx.x % J, grp = blockIdx.x / J;
-    const int KT = a.KT;
-    const int kps = a.kps;
-    const int kt_begin = j * kps, kt_end = kt_begin + kps < KT ? kt_begin + kps : KT;
-    const int n_iter = kt_end - kt_begin;
-
-    // this wave's weight tiles
-    const u32x4 *wp[QNG];
-    int n32[QNG];
-#pragma unroll
-    for (int g = 0; g < QNG; ++g) {
-        n32[g] = (grp * QW + wave) * QNG + g;
-        int t16 = 2 * n32[g] + ((lane >> 4) & 1);
-        if (t16 >= NT16) t16 = NT16 - 1;          // columns past the matrix re-read the last tile, never stored
-        wp[g] = tile_weights_seg(a, t16);
-    }
-    const int r0 = half_record(lane, 0), r1 = half_record(lane, 1);
-
-    // activation staging: thread t moves records t, t+256, ... of each k-tile chunk
-    const u32x4 *asrc[APT];
-#pragma unroll
-    for (int i = 0; i < APT; ++i) {
-        int q = threadIdx.x + i * QW * 64;
-        if (!AFULL && q >= CHUNK) q = CHUNK - 1;  // surplus threads re-read the last record, never stored
-        const int tile = q >> 6, rec = q & 63;    // tile = mt16 * 2 + (0: hi, 1: lo)
-        const u32x4 *base = (tile & 1) ? a.A_lo : a.A_hi;
-        asrc[i] = base + ((size_t)(tile >> 1) * KT) * 64 + rec;
-    }
-    auto stage_load = [&](int kt, u32x4 (&v)[APT]) {
-#pragma unroll
-        for (int i = 0; i < APT; ++i) v[i] = asrc[i][(size_t)kt * 64];
-    };
-    auto stage_store = [&](int buf, const u32x4 (&v)[APT]) {
-#pragma unroll
-        for (int i = 0; i < APT; ++i)
-            if (AFULL || threadIdx.x + i * QW * 64 < CHUNK) ring[buf][threadIdx.x + i * QW * 64] = v[i];
-    };
-
-    f32x16 acc[MT32][QNG];
-#pragma unroll
-    for (int i = 0; i < MT32; ++i)
-#pragma unroll
-        for (int g = 0; g < QNG; ++g)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[i][g][v] = 0.f;
-
-    // All loads of a wave retire in issue order, so the activation loads (L2 hits) are issued
-    // QDW k-tiles ahead, each right before the weight loads of the same k-tile, and parked in
-    // registers: by the time chunk c moves to LDS (iteration c-1) everything issued before it has
-    // been consumed already, and waiting for it never waits for a weight load still in flight.
-    u32x4 w[QDW][QNG][2], apre[QDW][APT];
-    auto issue = [&](int u, int it) {   // activation chunk and weights of iteration `it` into slot u
-        const int kt = kt_begin + (it < n_iter ? it : n_iter - 1);
-        stage_load(kt, apre[u]);
-#pragma unroll
-        for (int g = 0; g < QNG; ++g) {
-            w[u][g][0] = __builtin_nontemporal_load(wp[g] + (size_t)kt * 64 + r0);
-            w[u][g][1] = __builtin_nontemporal_load(wp[g] + (size_t)kt * 64 + r1);
-        }
-    };
-#pragma unroll
-    for (int u = 0; u < QDW; ++u) issue(u, u);
-    stage_store(0, apre[0]);
-    __syncthreads();
-
-    // One k-tile: MFMAs on LDS slot it&1 with weight slot u, refill both register slots for
-    // iteration it+QDW, move chunk it+1 to the other LDS slot.  The steady-state loop below runs it
-    // with every branch resolved at compile time: a load that is only conditionally issued would
-    // force the wait counters in front of every later use down to "nothing outstanding".
-    auto ktile = [&](int u, int it, bool refill, bool next_chunk) {
-        const u32x4 *buf = ring[it & 1];
-#pragma unroll
-        for (int hh = 0; hh < 2; ++hh) {
-            const int rec = hh ? r1 : r0;
-#pragma unroll
-            for (int i = 0; i < MT32; ++i) {
-                // tile index in the chunk: (mt16 * 2 + hi/lo) with mt16 = 2i + (lane/16)%2
-                const int t_hi = ((2 * i + ((lane >> 4) & 1)) * 2) * 64 + rec;
-                const u32x4 xh = buf[t_hi], xl = buf[t_hi + 64];
-#pragma unroll
-                for (int g = 0; g < QNG; ++g) {
-                    acc[i][g] = mfma32(xh, w[u][g][hh], acc[i][g]);
-                    acc[i][g] = mfma32(xl, w[u][g][hh], acc[i][g]);
-                }
-            }
-        }
-        if (refill) issue(u, it + QDW);
-        // LDS slot (it+1)&1 held chunk it-1, which every wave finished before the barrier that
-        // ended iteration it-1.
-        if (next_chunk) stage_store((it + 1) & 1, apre[(u + 1) % QDW]);
-        __syncthreads();
-    };
-    int it0 = 0;
-    for (; it0 + 2 * QDW <= n_iter; it0 += QDW) {   // every iteration of the group refills
-#pragma unroll
-        for (int u = 0; u < QDW; ++u) ktile(u, it0 + u, true, true);
-    }
-    for (; it0 < n_iter; it0 += QDW) {              // the last groups drain the pipeline
-#pragma unroll
-        for (int u = 0; u < QDW; ++u) {
-            const int it = it0 + u;
-            if (it < n_iter) ktile(u, it, it + QDW < n_iter, it + 1 < n_iter);
-        }
-    }
-
-    // acc[i][g][v] of lane l: row 32i + 8*(v/4) + 4*(l/32) + v%4, column 32*n32[g] + l%32
-#pragma unroll
-    for (int g = 0; g < QNG; ++g) {
-        const int col = n32[g] * 32 + (lane & 31);
-        if (col >= a.Ntot) continue;
-#pragma unroll
-        for (int i = 0; i < MT32; ++i)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int row = 32 * i + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
-                if (row < a.part_rows) a.partials[((size_t)j * a.part_rows + row) * a.Ntot + col] = acc[i][g][v];
-            }
-    }
-}
-
-// The same launch with v_mfma_f32_16x16x32_bf16 on MT16 row tiles of 16: the form used from 49 rows up.  An
-// odd number of 16-row tiles spends no MFMA on a half-empty 32-row tile (144 rows: 36 instead of 40 units of MFMA
-// time per k-tile and wave, 18 instead of 20 operand reads from LDS, nine instead of ten tiles staged), and both
-// operands are the packed tiles as stored -- lane l holds (row or column l%16, k-slots 8*(l/16)..+7) of a 16 x 32
-// tile -- so a wave's weight loads are two whole 1 KiB records per k-tile.  Staging, prefetch distance and the K
-// split are those of qgemm_kernel.  Measured against it, whole steps in one session (ms): 8B shape 80 rows
-// 6.20 -> 5.93, 112 rows 6.93 -> 6.72, 144 rows 8.02 -> 7.80, 64 / 96 / 128 / 160 rows 0-1.5 % ahead; 70B shape
-// (16 layers) 80 rows 7.67 -> 7.03, 144 rows 10.79 -> 10.28, 64 / 160 rows 3 % ahead; at 36 rows the 32 x 32 form
-// stays 4 % ahead on the 8B shape (same on the 70B shape at 48), so up to 48 rows keep it.
+// grid = row blocks * column groups * J workgroups of QW waves on MT16 row tiles of 16; writes partials[j][row][col].
+// Both operands are the packed tiles as stored: lane l holds (row or column l%16, k-slots 8*(l/16)..+7) of a 16 x 32 tile.
+// One 32-column tile pair per wave, so two waves share a SIMD at QW = 8 (256 columns per workgroup, the large matrices);
+// QW = 4 for the small ones, whose K then splits half as often.
+//
+// What bounds it: below about 100 rows the weight stream, above that the matrix pipes, which at 512 rows are busy 70 % of
+// the cycles of a compute unit that has work (and the clock falls to 2.0 GHz under that load); the rest goes into operand
+// reads, stores and barriers between the MFMAs.  So the instruction stream of a k-tile is fixed by hand: operand
+// tiles are read from LDS AHEAD MFMA groups before their use, straight across the k-tile boundary; the chunk of the next
+// k-tile is stored early in the current one, and the barrier that publishes it stands just before the first read of it,
+// so that waves may be most of a k-tile apart without waiting and no read latency follows a barrier.  Left to the
+// compiler, most reads were issued right before their use.  Measured against that form, GEMM and epilogue, us: 8B gate/up
+// 160 rows 84 -> 82, 512 rows 240 -> 225; 70B gate/up 144 rows 274 -> 262, 512 rows 894 -> 825; 70B down 144 rows 147 -> 135.
+// Against v_mfma_f32_32x32x16_bf16, which 33..48 rows used to take: 8B 36 rows gate/up 48.7 -> 45.3, down 32.4 -> 29.4,
+// 70B gate/up 157 -> 143.
 //
 // More than 160 rows are cut into RB blocks of MT16 row tiles, all in one launch: blocks 8 apart in the grid run on one
 // die, where the row blocks of a (column group, slice) follow each other and share the weights through its L2 (ordinary
-// loads then, not streaming ones).
+// loads then, not streaming ones).  There the matrix pipes bound everything and two waves share 64 columns, each on half
+// of the rows: half the operand reads per MFMA for a second fetch of the weights from the die's L2 (8B gate/up at 512 rows
+// 235 -> 220 us, but 84 -> 100 us at 160 rows, which are still bound by what a compute unit can fetch).
 template <int MT16, int QW, bool BLOCKS>
 __global__ __launch_bounds__(QW * 64) void qgemm16_kernel(FusedGemmArgs a, int RB, int NT16)
 {
     constexpr int QDW = 4;
-    constexpr int CHUNK = MT16 * 2 * 64;          // lane records of one activation k-tile (hi and lo)
-    constexpr int APT = (CHUNK + QW * 64 - 1) / (QW * 64);
-    constexpr bool AFULL = CHUNK % (QW * 64) == 0;
-    __shared__ u32x4 ring[2][CHUNK];
+    constexpr int RH = BLOCKS ? 2 : 1;       // waves that share a column group, each on its part of the rows
+    static_assert(MT16 % RH == 0, "every wave has the same number of row tiles");
+    constexpr int CW = QW / RH;                   // column groups per workgroup
+    constexpr int NC = 2 * RH;                    // 16-column tiles per wave
+    constexpr int MTW = MT16 / RH;                // row tiles per wave
+    constexpr int TILES = MT16 * 2;               // activation tiles (hi and lo) of one k-tile
+    constexpr int APT = (TILES + QW - 1) / QW;    // tiles staged per wave; surplus waves fill the padding of the ring
+    constexpr int RECS = 2 * MTW;                 // operand tiles every wave reads per k-tile
+    constexpr int AHEAD = (RECS - 1) / 2 < 6 ? (RECS - 1) / 2 : 6;   // of them read before their use
+    constexpr int BAR = RECS - AHEAD;             // the first read of the next k-tile
+    constexpr int PUT = BAR - AHEAD - 1;          // chunk stores: at least AHEAD reads lie between them and the barrier
+    __shared__ u32x4 ring[QDW][APT * QW * 64];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int half = wave / CW, cg = wave % CW;
     int gj = blockIdx.x, rb = 0;
     if (BLOCKS) {
         const int n = gridDim.x / RB, whole = n & ~7;     // (column group, slice) pairs; those in full sets of 8
@@ -620,94 +483,106 @@ __global__ __launch_bounds__(QW * 64) void qgemm16_kernel(FusedGemmArgs a, int R
     const int kt_begin = j * kps, kt_end = kt_begin + kps < KT ? kt_begin + kps : KT;
     const int n_iter = kt_end - kt_begin;
 
-    const int n32 = grp * QW + wave;
-    const u32x4 *wp[2];
+    const int c16 = (grp * CW + cg) * NC;         // this wave's first 16-column tile
+    const u32x4 *wp[NC];
 #pragma unroll
-    for (int ct = 0; ct < 2; ++ct) {
-        int t16 = 2 * n32 + ct;
+    for (int ct = 0; ct < NC; ++ct) {
+        int t16 = c16 + ct;
         if (t16 >= NT16) t16 = NT16 - 1;          // columns past the matrix re-read the last tile, never stored
         wp[ct] = tile_weights_seg(a, t16) + lane;
     }
-
-    const size_t mt_base = (size_t)(m_base >> 4);
     const u32x4 *asrc[APT];
 #pragma unroll
     for (int i = 0; i < APT; ++i) {
-        int q = threadIdx.x + i * QW * 64;
-        if (!AFULL && q >= CHUNK) q = CHUNK - 1;  // surplus threads re-read the last record, never stored
-        const int tile = q >> 6, rec = q & 63;    // tile = mt16 * 2 + (0: hi, 1: lo)
-        const u32x4 *base = (tile & 1) ? a.A_lo : a.A_hi;
-        asrc[i] = base + ((mt_base + (tile >> 1)) * KT) * 64 + rec;
+        int t = wave + i * QW;                    // row tile t / 2, part t % 2 (0: hi, 1: lo)
+        if (t >= TILES) t = TILES - 1;
+        asrc[i] = ((t & 1) ? a.A_lo : a.A_hi) + (size_t)(rb * MT16 + (t >> 1)) * KT * 64 + lane;
     }
-    auto stage_load = [&](int kt, u32x4 (&v)[APT]) {
+    f32x4 acc[MTW][NC];
 #pragma unroll
-        for (int i = 0; i < APT; ++i) v[i] = asrc[i][(size_t)kt * 64];
-    };
-    auto stage_store = [&](int buf, const u32x4 (&v)[APT]) {
+    for (int i = 0; i < MTW; ++i)
 #pragma unroll
-        for (int i = 0; i < APT; ++i)
-            if (AFULL || threadIdx.x + i * QW * 64 < CHUNK) ring[buf][threadIdx.x + i * QW * 64] = v[i];
-    };
+        for (int ct = 0; ct < NC; ++ct) acc[i][ct] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-    f32x4 acc[MT16][2];
+    u32x4 w[QDW][NC], apre[QDW][APT];
+    auto load_a = [&](int u, int it) {
+        const size_t kt = (size_t)(kt_begin + (it < n_iter ? it : n_iter - 1)) * 64;
 #pragma unroll
-    for (int i = 0; i < MT16; ++i)
+        for (int i = 0; i < APT; ++i) apre[u][i] = asrc[i][kt];
+    };
+    auto load_w = [&](int u, int it) {
+        const size_t kt = (size_t)(kt_begin + (it < n_iter ? it : n_iter - 1)) * 64;
 #pragma unroll
-        for (int ct = 0; ct < 2; ++ct) acc[i][ct] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-    u32x4 w[QDW][2], apre[QDW][APT];
-    auto issue = [&](int u, int it) {   // activation chunk and weights of iteration `it` into slot u
-        const int kt = kt_begin + (it < n_iter ? it : n_iter - 1);
-        stage_load(kt, apre[u]);
+        for (int ct = 0; ct < NC; ++ct) w[u][ct] = BLOCKS ? wp[ct][kt] : __builtin_nontemporal_load(wp[ct] + kt);
+    };
+    auto stage = [&](int u) {
 #pragma unroll
-        for (int ct = 0; ct < 2; ++ct)
-            w[u][ct] = BLOCKS ? wp[ct][(size_t)kt * 64] : __builtin_nontemporal_load(wp[ct] + (size_t)kt * 64);
+        for (int i = 0; i < APT; ++i) ring[u][(wave + i * QW) * 64 + lane] = apre[u][i];
     };
 #pragma unroll
-    for (int u = 0; u < QDW; ++u) issue(u, u);
-    stage_store(0, apre[0]);
+    for (int u = 0; u < QDW; ++u) {
+        load_a(u, u);
+        load_w(u, u);
+    }
+    stage(0);
     __syncthreads();
+    const int a_at = half * MTW * 128 + lane;
+    u32x4 x[RECS + AHEAD];
+#pragma unroll
+    for (int r = 0; r < AHEAD; ++r) x[r] = ring[0][a_at + r * 64];
 
-    auto ktile = [&](int u, int it, bool refill, bool next_chunk) {
-        const u32x4 *buf = ring[it & 1] + lane;
+    auto ktile = [&](int u, int it, bool refill) {
+        const int un = (u + 1) % QDW;
 #pragma unroll
-        for (int i = 0; i < MT16; ++i) {
-            const u32x4 xh = buf[(2 * i) * 64], xl = buf[(2 * i + 1) * 64];
+        for (int r = 0; r < RECS; ++r) {
+            if (r == BAR) {
+                // lgkmcnt counts LDS operations in order: with at least AHEAD reads issued since the stores of the next
+                // chunk, AHEAD or fewer outstanding means that the stores are done.
+                asm volatile("s_waitcnt lgkmcnt(%0)" ::"n"(AHEAD) : "memory");
+                asm volatile("s_barrier" ::: "memory");
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            x[r + AHEAD] = r < BAR ? ring[u][a_at + (r + AHEAD) * 64] : ring[un][a_at + (r + AHEAD - RECS) * 64];
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int ct = 0; ct < 2; ++ct) {
-                acc[i][ct] = mfma(xh, w[u][ct], acc[i][ct]);
-                acc[i][ct] = mfma(xl, w[u][ct], acc[i][ct]);
+            for (int ct = 0; ct < NC; ++ct) acc[r >> 1][ct] = mfma(x[r], w[u][ct], acc[r >> 1][ct]);
+            __builtin_amdgcn_sched_barrier(0);
+            if (r == PUT) {
+                stage(un);
+                if (refill) load_a(u, it + QDW);
+                __builtin_amdgcn_sched_barrier(0);
             }
         }
-        if (refill) issue(u, it + QDW);
-        if (next_chunk) stage_store((it + 1) & 1, apre[(u + 1) % QDW]);
-        __syncthreads();
+        if (refill) load_w(u, it + QDW);
+#pragma unroll
+        for (int r = 0; r < AHEAD; ++r) x[r] = x[RECS + r];
     };
     int it0 = 0;
     for (; it0 + 2 * QDW <= n_iter; it0 += QDW) {
 #pragma unroll
-        for (int u = 0; u < QDW; ++u) ktile(u, it0 + u, true, true);
+        for (int u = 0; u < QDW; ++u) ktile(u, it0 + u, true);
     }
     for (; it0 < n_iter; it0 += QDW) {
 #pragma unroll
         for (int u = 0; u < QDW; ++u) {
             const int it = it0 + u;
-            if (it < n_iter) ktile(u, it, it + QDW < n_iter, it + 1 < n_iter);
+            if (it < n_iter) ktile(u, it, it + QDW < n_iter);
         }
     }
 
-    // acc[i][ct][v] of lane l: row 16i + 4*(l/16) + v, column 32*n32 + 16*ct + l%16
+    // acc[i][ct][v] of lane l: row 16 * (half * MTW + i) + 4*(l/16) + v, column 16 * (c16 + ct) + l%16
 #pragma unroll
-    for (int ct = 0; ct < 2; ++ct) {
-        const int col = n32 * 32 + ct * 16 + (lane & 15);
+    for (int ct = 0; ct < NC; ++ct) {
+        const int col = (c16 + ct) * 16 + (lane & 15);
         if (col >= a.Ntot) continue;
 #pragma unroll
-        for (int i = 0; i < MT16; ++i)
+        for (int i = 0; i < MTW; ++i) {
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
-                const int row = m_base + 16 * i + 4 * (lane >> 4) + v;
+                const int row = m_base + 16 * (half * MTW + i) + 4 * (lane >> 4) + v;
                 if (row < a.part_rows) a.partials[((size_t)j * a.part_rows + row) * a.Ntot + col] = acc[i][ct][v];
             }
+        }
     }
 }
 
@@ -734,7 +609,7 @@ __host__ QPlan q_plan(int Ntot, int K, int M)
     // on the 940 MB gate/up matrix of the 70B shape they win at 48 rows already: 189 -> 153 us without a split).
     p.qw = (bytes < ((size_t)64 << 20) || (mt32 <= 2 && bytes < ((size_t)512 << 20))) ? 4 : 8;
     const int slots = 256;
-    p.groups = (NT32 + p.qw * QNG - 1) / (p.qw * QNG);
+    p.groups = (NT32 + p.qw - 1) / p.qw;
     int jmax = KT / 8;
     if (jmax > 16) jmax = 16;
     if (jmax < 1) jmax = 1;
@@ -757,7 +632,7 @@ __host__ QPlan q_plan(int Ntot, int K, int M)
         constexpr size_t SPLIT_BYTES = (size_t)32 << 20;
         const int was = best, mt16 = (M + 15) / 16, RB = (mt16 + 9) / 10, mt = (mt16 + RB - 1) / RB;
         p.qw = 8;
-        p.groups = (NT32 + p.qw * QNG - 1) / (p.qw * QNG);
+        p.groups = (NT32 + p.qw - 1) / p.qw;
         double least = 0.0;
         for (int J = 1; J <= jmax; ++J) {
             const size_t sums = (size_t)J * mt16 * 16 * Ntot * sizeof(float);
@@ -770,6 +645,13 @@ __host__ QPlan q_plan(int Ntot, int K, int M)
     p.kps = (KT + best - 1) / best;
     p.J = (KT + p.kps - 1) / p.kps;
     return p;
+}
+
+// Which kernel: true for pgemm_kernel.
+__host__ bool is_small(int M, int Ntot, int K)
+{
+    (void)Ntot; (void)K;
+    return M <= 32;
 }
 
 template <int EPI> hipError_t launch_large(FusedGemmArgs &a, hipStream_t s, bool *needs_epilogue, hipEvent_t t0, hipEvent_t t1)
@@ -786,15 +668,20 @@ template <int EPI> hipError_t launch_large(FusedGemmArgs &a, hipStream_t s, bool
     if ((size_t)a.J * a.part_rows * a.Ntot * sizeof(float) > a.partial_bytes) return hipErrorInvalidValue;
     const int mt16 = (a.M + 15) / 16, RB = (mt16 + 9) / 10;
     const dim3 grid(p.groups * a.J * RB), block(p.qw * 64);
-    if (mt16 >= 4) {   // 49 rows and more: the 16 x 16 x 32 form (measured ahead at every tile count from 4 up)
 #define SSSD_Q16LAUNCH(MT, QW, BLOCKS) hipExtLaunchKernelGGL((qgemm16_kernel<MT, QW, BLOCKS>), grid, block, 0, s, t0, t1, 0, a, RB, NT16)
-#define SSSD_Q16ROWS(MT)                                        \
-    do {                                                        \
-        if (RB > 1) SSSD_Q16LAUNCH((MT > 6 ? MT : 6), 8, true); \
-        else if (p.qw == 8) SSSD_Q16LAUNCH(MT, 8, false);       \
-        else SSSD_Q16LAUNCH(MT, 4, false);                      \
+#define SSSD_Q16ROWS(MT)                                  \
+    do {                                                  \
+        if (p.qw == 8) SSSD_Q16LAUNCH(MT, 8, false);      \
+        else SSSD_Q16LAUNCH(MT, 4, false);                \
     } while (0)
-        switch ((mt16 + RB - 1) / RB) {   // several row blocks have at least six tiles each
+    const int mt = (mt16 + RB - 1) / RB;
+    if (RB > 1) {   // six to ten tiles per block, an even number (two halves of the rows)
+        if (mt <= 6) SSSD_Q16LAUNCH(6, 8, true);
+        else if (mt <= 8) SSSD_Q16LAUNCH(8, 8, true);
+        else SSSD_Q16LAUNCH(10, 8, true);
+    } else {
+        switch (mt) {
+        case 3: SSSD_Q16ROWS(3); break;
         case 4: SSSD_Q16ROWS(4); break;
         case 5: SSSD_Q16ROWS(5); break;
         case 6: SSSD_Q16ROWS(6); break;
@@ -803,12 +690,9 @@ template <int EPI> hipError_t launch_large(FusedGemmArgs &a, hipStream_t s, bool
         case 9: SSSD_Q16ROWS(9); break;
         default: SSSD_Q16ROWS(10); break;
         }
+    }
 #undef SSSD_Q16ROWS
 #undef SSSD_Q16LAUNCH
-    } else {   // 33..48 rows
-        if (p.qw == 8) hipExtLaunchKernelGGL((qgemm_kernel<2, 8>), grid, block, 0, s, t0, t1, 0, a, NT16);
-        else hipExtLaunchKernelGGL((qgemm_kernel<2, 4>), grid, block, 0, s, t0, t1, 0, a, NT16);
-    }
     return hipGetLastError();
 }
 
@@ -865,8 +749,7 @@ int stream_gemm_max_rows() { return 32; }
 
 const char *stream_gemm_kernel_name(int M)
 {
-    if (M <= stream_gemm_max_rows()) return "pgemm_kernel";
-    return M > 48 ? "qgemm16_kernel" : "qgemm_kernel";
+    return M <= 32 ? "pgemm_kernel" : "qgemm16_kernel";
 }
 
 // Split-K scratch needed for M rows: the largest J * rows * Ntot over the model's GEMMs.
@@ -885,10 +768,11 @@ size_t stream_gemm_partial_bytes(const Dims &D, int M)
     consider(D.f, D.h);
     consider(D.h, D.V);
     // larger steps: the K split depends on the number of row tiles, so take the worst case over every step size up to M
-    for (int rows_c = 48; M > stream_gemm_max_rows(); rows_c += 16) {
+    for (int rows_c = 16;; rows_c += 16) {
         const int rows = rows_c < round_up(M, 16) ? rows_c : round_up(M, 16);
         auto large = [&](int K, size_t ntot) {
-            const size_t need = (size_t)q_plan((int)ntot, K, rows).J * rows * ntot;
+            if (is_small(rows, (int)ntot, round_up(K, 32))) return;
+            const size_t need = (size_t)q_plan((int)ntot, round_up(K, 32), rows).J * rows * ntot;
             if (need > best) best = need;
         };
         large(D.h, (size_t)D.qd + 2 * D.kd);
@@ -904,7 +788,7 @@ size_t stream_gemm_partial_bytes(const Dims &D, int M)
 size_t stream_gemm_scratch_bytes(int M, int N, int K)
 {
     const int KT = (K + 31) / 32;
-    if (M > stream_gemm_max_rows()) return (size_t)q_plan(N, K, M).J * round_up(M, 16) * N * sizeof(float);
+    if (!is_small(M, N, KT * 32)) return (size_t)q_plan(N, KT * 32, M).J * round_up(M, 16) * N * sizeof(float);
     const int ks = PW * small_kpw(KT);
     const size_t j = (size_t)((KT + ks - 1) / ks);
     return j > 1 ? j * (M <= 16 ? 16 : 32) * N * sizeof(float) : 0;
@@ -913,7 +797,7 @@ size_t stream_gemm_scratch_bytes(int M, int N, int K)
 hipError_t launch_stream_gemm(FusedGemmArgs &a, int epilogue, hipStream_t s, bool *needs_epilogue, hipEvent_t t0,
                               hipEvent_t t1)
 {
-    if (a.M > stream_gemm_max_rows()) {
+    if (!is_small(a.M, a.Ntot, a.KT * 32)) {
         switch (epilogue) {
         case FEPI_QKV: return launch_large<FEPI_QKV>(a, s, needs_epilogue, t0, t1);
         case FEPI_RESID: return launch_large<FEPI_RESID>(a, s, needs_epilogue, t0, t1);

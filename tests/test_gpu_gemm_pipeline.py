@@ -1,0 +1,33 @@
+"""The pipelined GEMM kernel at every row-tile count up to ten: slices of one, two and three k-tiles (fewer than are in
+flight), odd k-tile counts, split and unsplit K, four and eight waves, a last column group partly inside the matrix."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+import oracle
+from paper_2411_05894_amd import binding as sv
+from sssd_synth import normal_bf16
+
+DEV = "cuda:0"
+
+
+def check(N, K, M):
+    print(f"gemm N={N} K={K} M={M}", flush=True)
+    w = normal_bf16(71, N * 3 + K, (N, K), 0.02, device=DEV)
+    x = normal_bf16(72, M * 7 + K, (M, K), 1.0, device=DEV).float() * 1.25
+    x += 2.0 ** -10 * normal_bf16(73, M + K, (M, K), 1.0, device=DEV).float()     # not bf16-representable
+    hi, lo = sv.sssd_op_pack_activation(x)
+    y = sv.sssd_op_gemm(hi, lo, sv.sssd_op_pack_weight(w), M, N, K)
+    full = x.double() @ w.double().t().contiguous()
+    # x = hi + lo to 2^-17 of x, products and sums in fp32: the bound of the other GEMM parity tests
+    assert (y - full).abs().max().item() <= 3e-5 * full.abs().max().item() + 1e-6
+    cols = slice(max(0, N - 96), N)                                                # the oracle runs on the host
+    ref = oracle.linear(x[[0, M - 1]].cpu(), w[cols].cpu())
+    assert (y[[0, M - 1]][:, cols].cpu() - ref).abs().max().item() <= 3e-5 * ref.abs().max().item() + 1e-6
+
+
+@pytest.mark.parametrize("N,K", [(16, 32), (96, 64), (144, 96), (272, 352), (2064, 1056), (8208, 4128)])
+@pytest.mark.parametrize("M", [33, 47, 48, 49, 64, 80, 81, 112, 113, 128, 144, 145, 160])
+def test_row_tiles(N, K, M):
+    check(N, K, M)
