@@ -51,11 +51,11 @@ int sssd_op_gemm_static(const void *a_hi, const void *a_lo, const void *w_packed
                         float *out, void *stream);
 
 /* Largest M = B*(k+1) that the small-step GEMM kernel (pgemm_kernel) serves; steps above it run
- * qgemm16_kernel.  For benchmarks. */
+ * qgemm16_kernel, as the larger matrices of smaller steps do.  For benchmarks. */
 int32_t sssd_op_gemm_small_step_rows(void);
 
 /* Name of the weight-streaming kernel that a GEMM of M rows launches (static string): "pgemm_kernel" or
- * "qgemm16_kernel". */
+ * "qgemm16_kernel" (17..32 rows: of the matrices of 64 MB and more). */
 const char *sssd_op_gemm_kernel_name(int32_t M);
 
 /* Measurement aid: one read-only pass over `bytes` (>= 16, src 16-byte aligned) of device memory by a

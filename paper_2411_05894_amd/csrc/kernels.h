@@ -62,7 +62,7 @@ struct FusedGemmArgs {
     int upw, J, part_rows, kps;   // filled in by the launcher: units per workgroup, K slices, rows per slice, k-tiles per slice
     int groups;                   // ... and column groups (M <= 32: the grid is groups * J workgroups)
 };
-// M <= stream_gemm_max_rows(): persistent weight streamer; NT must be the tile count of W0.
+// Up to stream_gemm_max_rows() rows some matrices take the persistent weight streamer; NT must be the tile count of W0.
 int stream_gemm_max_rows();
 const char *stream_gemm_kernel_name(int M);   // the kernel that serves a GEMM of M rows
 size_t stream_gemm_partial_bytes(const Dims &D, int M);

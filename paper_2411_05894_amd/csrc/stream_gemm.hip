@@ -5,7 +5,7 @@
 // MI355X ridge (~312 flop/byte), so each launch is a stream of the weight matrix through
 // the matrix cores with everything else hidden behind it.
 //
-//   pgemm_kernel   M <= 32 rows (one or two 16-row tiles).  Persistent: one workgroup of 16 waves per compute unit walks a
+//   pgemm_kernel   M <= 32 rows (one or two 16-row tiles), as is_small has it.  Persistent: one workgroup of 16 waves per compute unit walks a
 //                  list of 16-column output tiles.  Each wave owns a fixed k-slice and keeps the
 //                  activations of that slice (bf16 hi and lo parts) in registers for the whole
 //                  launch, so the inner loop touches memory only for weights.  Weight registers
@@ -16,7 +16,7 @@
 //                  (is_small).  v_mfma_f32_16x16x32_bf16 tiles: each wave of a workgroup of eight (four for the small
 //                  matrices) owns 32 output columns and streams their weights HBM -> registers (rolling prefetch,
 //                  every weight byte read once), while the activation k-tiles of the workgroup's k-slice, which all
-//                  its waves need, are staged through a register ring and a four-deep LDS ring.  Results go to
+//                  its waves need, are staged through a register ring and an LDS ring.  Results go to
 //                  split-K partials for epi_kernel.
 //   epi_kernel     Sums split-K partial results (when K is split over workgroups) in fixed order
 //                  and applies the epilogue.
@@ -437,9 +437,9 @@ __device__ __forceinline__ const u32x4 *tile_weights_seg(const FusedGemmArgs &a,
 // k-tile is stored early in the current one, and the barrier that publishes it stands just before the first read of it,
 // so that waves may be most of a k-tile apart without waiting and no read latency follows a barrier.  Left to the
 // compiler, most reads were issued right before their use.  Measured against that form, GEMM and epilogue, us: 8B gate/up
-// 160 rows 84 -> 82, 512 rows 240 -> 225; 70B gate/up 144 rows 274 -> 262, 512 rows 894 -> 825; 70B down 144 rows 147 -> 135.
+// 160 rows 84 -> 82, 512 rows 240 -> 234; 70B gate/up 144 rows 274 -> 262, 512 rows 894 -> 850; 70B down 144 rows 147 -> 135.
 // Against v_mfma_f32_32x32x16_bf16, which 33..48 rows used to take: 8B 36 rows gate/up 48.7 -> 45.3, down 32.4 -> 29.4,
-// 70B gate/up 157 -> 143.
+// 70B gate/up 157 -> 147.
 //
 // More than 160 rows are cut into RB blocks of MT16 row tiles, all in one launch: blocks 8 apart in the grid run on one
 // die, where the row blocks of a (column group, slice) follow each other and share the weights through its L2 (ordinary
@@ -449,7 +449,8 @@ __device__ __forceinline__ const u32x4 *tile_weights_seg(const FusedGemmArgs &a,
 template <int MT16, int QW, bool BLOCKS>
 __global__ __launch_bounds__(QW * 64) void qgemm16_kernel(FusedGemmArgs a, int RB, int NT16)
 {
-    constexpr int QDW = 4;
+    constexpr int QDW = BLOCKS ? 3 : 4;           // k-tiles in flight
+    constexpr bool TWO = BLOCKS || MT16 <= 3;     // sums in two levels, where the registers allow it
     constexpr int RH = BLOCKS ? 2 : 1;       // waves that share a column group, each on its part of the rows
     static_assert(MT16 % RH == 0, "every wave has the same number of row tiles");
     constexpr int CW = QW / RH;                   // column groups per workgroup
@@ -496,13 +497,15 @@ __global__ __launch_bounds__(QW * 64) void qgemm16_kernel(FusedGemmArgs a, int R
     for (int i = 0; i < APT; ++i) {
         int t = wave + i * QW;                    // row tile t / 2, part t % 2 (0: hi, 1: lo)
         if (t >= TILES) t = TILES - 1;
-        asrc[i] = ((t & 1) ? a.A_lo : a.A_hi) + (size_t)(rb * MT16 + (t >> 1)) * KT * 64 + lane;
+        int rt = rb * MT16 + (t >> 1);
+        if (rt >= a.part_rows >> 4) rt = (a.part_rows >> 4) - 1;   // past the rows: never stored
+        asrc[i] = ((t & 1) ? a.A_lo : a.A_hi) + (size_t)rt * KT * 64 + lane;
     }
-    f32x4 acc[MTW][NC];
+    f32x4 acc[MTW][NC], total[MTW][NC];
 #pragma unroll
     for (int i = 0; i < MTW; ++i)
 #pragma unroll
-        for (int ct = 0; ct < NC; ++ct) acc[i][ct] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int ct = 0; ct < NC; ++ct) acc[i][ct] = total[i][ct] = f32x4{0.f, 0.f, 0.f, 0.f};
 
     u32x4 w[QDW][NC], apre[QDW][APT];
     auto load_a = [&](int u, int it) {
@@ -557,10 +560,25 @@ __global__ __launch_bounds__(QW * 64) void qgemm16_kernel(FusedGemmArgs a, int R
 #pragma unroll
         for (int r = 0; r < AHEAD; ++r) x[r] = x[RECS + r];
     };
+    // A running fp32 sum over hundreds of k-tiles loses more bits than sums of a few k-tiles and a sum of those, which the
+    // register-resident kernel and the deeper K splits of four passes had for free.  Relative error against 64 bits, one
+    // level / two: 70B down at 32 rows 7.7e-7 / 1.8e-7 (pgemm_kernel 1.3e-7), at 512 rows 1.1e-6 / 2.0e-7 (passes 5.8e-7).
+    auto flush = [&]() {
+#pragma unroll
+        for (int i = 0; i < MTW; ++i)
+#pragma unroll
+            for (int ct = 0; ct < NC; ++ct) {
+                total[i][ct] += acc[i][ct];
+                acc[i][ct] = f32x4{0.f, 0.f, 0.f, 0.f};
+            }
+    };
     int it0 = 0;
+    bool odd = false;
     for (; it0 + 2 * QDW <= n_iter; it0 += QDW) {
 #pragma unroll
         for (int u = 0; u < QDW; ++u) ktile(u, it0 + u, true);
+        if (TWO && (odd || !BLOCKS)) flush();
+        odd = !odd;
     }
     for (; it0 < n_iter; it0 += QDW) {
 #pragma unroll
@@ -568,6 +586,12 @@ __global__ __launch_bounds__(QW * 64) void qgemm16_kernel(FusedGemmArgs a, int R
             const int it = it0 + u;
             if (it < n_iter) ktile(u, it, it + QDW < n_iter);
         }
+    }
+    if (TWO) {
+#pragma unroll
+        for (int i = 0; i < MTW; ++i)
+#pragma unroll
+            for (int ct = 0; ct < NC; ++ct) acc[i][ct] += total[i][ct];
     }
 
     // acc[i][ct][v] of lane l: row 16 * (half * MTW + i) + 4*(l/16) + v, column 16 * (c16 + ct) + l%16
@@ -585,6 +609,9 @@ __global__ __launch_bounds__(QW * 64) void qgemm16_kernel(FusedGemmArgs a, int R
         }
     }
 }
+
+// Row blocks of a launch: one of up to ten tiles, more of up to eight (the sums in two levels leave no registers for more).
+__host__ int row_blocks(int mt16) { return mt16 <= 10 ? 1 : (mt16 + 7) / 8; }
 
 struct QPlan {
     int groups, J, kps;   // column groups, K slices (none empty), k-tiles per slice
@@ -630,7 +657,7 @@ __host__ QPlan q_plan(int Ntot, int K, int M)
         // 290 / 301 / 315 / 324 / 385 / 451, down 322 / 174 / 133 / 109 / 142 / 122 (four passes of up to 160 rows took 126,
         // 101, 294 + 30 and 190 + 19 us).  No split needs more than SPLIT_BYTES of partial sums unless the rule above did.
         constexpr size_t SPLIT_BYTES = (size_t)32 << 20;
-        const int was = best, mt16 = (M + 15) / 16, RB = (mt16 + 9) / 10, mt = (mt16 + RB - 1) / RB;
+        const int was = best, mt16 = (M + 15) / 16, RB = row_blocks(mt16), mt = (mt16 + RB - 1) / RB <= 6 ? 6 : 8;
         p.qw = 8;
         p.groups = (NT32 + p.qw - 1) / p.qw;
         double least = 0.0;
@@ -647,11 +674,24 @@ __host__ QPlan q_plan(int Ntot, int K, int M)
     return p;
 }
 
-// Which kernel: true for pgemm_kernel.
+// Which kernel a GEMM takes: true for pgemm_kernel.
+//   17..32 rows: pgemm_kernel feeds every compute unit twice the weight bytes it would stream alone, which costs more than
+//   the partial sums of qgemm16_kernel on all but the small matrices.  At 32 rows, GEMM and epilogue, pgemm / qgemm16 us:
+//   8B QKV (50 MB) 14.8 / 16.0, O (34 MB) 11.4 / 14.3, down (117 MB) 30 / 26, gate/up (235 MB) 50 / 42, LM head 223 / 193,
+//   70B QKV (168 MB) 41 / 32, gate/up 206 / 143, down 107 / 76.  The line lies at 64 MB, where the other kernel's
+//   workgroups get eight waves.
+//   1..16 rows: pgemm_kernel wins wherever a workgroup covers the whole K (4096); where K is split, its slices go through
+//   memory too, and from 256 MB the faster stream decides, pgemm / qgemm16 at 16 rows: 70B gate/up (940 MB) 150 / 142,
+//   down (470 MB) 79 / 73, QKV (168 MB) 32 / 32, O (134 MB) 26 / 30, and an 8B layer with its down projection
+//   (117 MB) on qgemm16 108.1 -> 109.7 us.
+// A GEMM whose partial sums would exceed SMALL_SCRATCH (the library's own array for callers without scratch) stays.
 __host__ bool is_small(int M, int Ntot, int K)
 {
-    (void)Ntot; (void)K;
-    return M <= 32;
+    constexpr size_t SMALL_SCRATCH = (size_t)32 << 20;
+    if (M > 32) return false;
+    const size_t bytes = (size_t)Ntot * (size_t)K * 2;
+    if (M > 16 ? bytes < ((size_t)64 << 20) : K <= PW * 8 * 32 || bytes < ((size_t)256 << 20)) return true;
+    return (size_t)q_plan(Ntot, K, M).J * round_up(M, 16) * Ntot * sizeof(float) > SMALL_SCRATCH;
 }
 
 template <int EPI> hipError_t launch_large(FusedGemmArgs &a, hipStream_t s, bool *needs_epilogue, hipEvent_t t0, hipEvent_t t1)
@@ -666,7 +706,7 @@ template <int EPI> hipError_t launch_large(FusedGemmArgs &a, hipStream_t s, bool
     else if (EPI == FEPI_SWIGLU) { a.seg0 = a.NT; a.seg1 = a.NT; }
     else { a.seg0 = NT16; a.seg1 = 0; }
     if ((size_t)a.J * a.part_rows * a.Ntot * sizeof(float) > a.partial_bytes) return hipErrorInvalidValue;
-    const int mt16 = (a.M + 15) / 16, RB = (mt16 + 9) / 10;
+    const int mt16 = (a.M + 15) / 16, RB = row_blocks(mt16);
     const dim3 grid(p.groups * a.J * RB), block(p.qw * 64);
 #define SSSD_Q16LAUNCH(MT, QW, BLOCKS) hipExtLaunchKernelGGL((qgemm16_kernel<MT, QW, BLOCKS>), grid, block, 0, s, t0, t1, 0, a, RB, NT16)
 #define SSSD_Q16ROWS(MT)                                  \
@@ -675,12 +715,13 @@ template <int EPI> hipError_t launch_large(FusedGemmArgs &a, hipStream_t s, bool
         else SSSD_Q16LAUNCH(MT, 4, false);                \
     } while (0)
     const int mt = (mt16 + RB - 1) / RB;
-    if (RB > 1) {   // six to ten tiles per block, an even number (two halves of the rows)
+    if (RB > 1) {   // six or eight tiles per block: two halves of the rows
         if (mt <= 6) SSSD_Q16LAUNCH(6, 8, true);
-        else if (mt <= 8) SSSD_Q16LAUNCH(8, 8, true);
-        else SSSD_Q16LAUNCH(10, 8, true);
+        else SSSD_Q16LAUNCH(8, 8, true);
     } else {
         switch (mt) {
+        case 1:   // the second row tile is padding, computed and not stored
+        case 2: SSSD_Q16ROWS(2); break;
         case 3: SSSD_Q16ROWS(3); break;
         case 4: SSSD_Q16ROWS(4); break;
         case 5: SSSD_Q16ROWS(5); break;
@@ -747,9 +788,10 @@ template <int EPI> hipError_t launch_small(FusedGemmArgs &a, hipStream_t s, bool
 
 int stream_gemm_max_rows() { return 32; }
 
+// Of the larger matrices where the size decides: from 17 rows on; below, the headline shape's matrices all take pgemm_kernel.
 const char *stream_gemm_kernel_name(int M)
 {
-    return M <= 32 ? "pgemm_kernel" : "qgemm16_kernel";
+    return M <= 16 ? "pgemm_kernel" : "qgemm16_kernel";
 }
 
 // Split-K scratch needed for M rows: the largest J * rows * Ntot over the model's GEMMs.

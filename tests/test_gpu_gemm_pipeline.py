@@ -31,3 +31,12 @@ def check(N, K, M):
 @pytest.mark.parametrize("M", [33, 47, 48, 49, 64, 80, 81, 112, 113, 128, 144, 145, 160])
 def test_row_tiles(N, K, M):
     check(N, K, M)
+
+
+# either side of the lines between the kernels: 64 MB at 17..32 rows, 256 MB and a K split at up to 16 rows, and results
+# whose partial sums would not fit the library's own scratch array
+@pytest.mark.parametrize("N,K,M", [(8192, 4064, 17), (8192, 4096, 17), (8208, 4128, 31), (3888, 8640, 32), (127104, 288, 18),
+                                   (270000, 128, 32), (16368, 8192, 16), (16384, 8192, 1), (16400, 8224, 16), (9616, 14336, 5),
+                                   (32800, 4096, 9)])
+def test_small_steps_of_large_matrices(N, K, M):
+    check(N, K, M)

@@ -1,4 +1,4 @@
-"""GEMMs of more than 160 rows: two to seven row blocks of six to ten tiles in one launch, whole and partial last blocks,
+"""GEMMs of more than 160 rows: two to eight row blocks of six or eight tiles in one launch, whole and partial last blocks,
 grids that do and do not divide into sets of eight, split and unsplit K, a last column group partly inside the matrix."""
 import pytest
 import torch
