@@ -1,6 +1,8 @@
 """GPU parity of target-only speculative sampling (Sec. 4.4) against the fp64 oracle: the row sampler
 on its own (same logits on both sides, so only the fp32 arithmetic of the weights differs), its tie
 rules, its sampling frequencies, and the sampled tree step of the tiny model."""
+import ctypes as C
+
 import numpy as np
 import pytest
 import torch
@@ -224,3 +226,23 @@ def test_lists_that_overflow_take_the_general_path():
     for x in u.tolist():
         got = sv.sssd_op_sample_wide(heap.to(DEV), sv.SamplingParams(1.0, 50, 1.0), torch.tensor([x]).to(DEV))
         assert got.cpu().tolist() == [300 + int(x * 50)]
+
+
+@pytest.mark.parametrize("V,rows", [(8192, 3), (4099, 129)])     # clusters of 16 workgroups and of one
+@pytest.mark.parametrize("T", [1e-40, 4e-39])                    # 1 / T overflows; only its product with log2(e) does
+def test_temperatures_without_any_mass_give_the_argmax(V, rows, T):
+    """The limit of T towards 0 is the arg-max, also where no weight can be represented any more.  Every token is written:
+    the outputs hold a sentinel before the call."""
+    z = (normal_bf16(121, V, (rows, V), 1.0).float() * 2.0).contiguous()
+    z[torch.arange(rows), (torch.arange(rows) * 997) % V] = 20.0
+    z, u = z.to(DEV), uniforms(122, rows).to(DEV)
+    need = sv.lib().sssd_op_sample_scratch_bytes(rows)
+    scratch = torch.empty(max(need, 16), dtype=torch.uint8, device=DEV)
+    for k, p in ((5, 1.0), (5, 0.9), (0, 0.95), (0, 1.0)):
+        say(f"V={V} rows={rows} T={T} top_k={k} top_p={p}")
+        params = sv.SamplingParams(T, k, p)
+        one, wide = (torch.full((rows,), -7, dtype=torch.int32, device=DEV) for _ in range(2))
+        at = (z.data_ptr(), rows, V, C.byref(params), u.data_ptr())
+        assert sv.lib().sssd_op_sample(*at, one.data_ptr(), None) == 0
+        assert sv.lib().sssd_op_sample_wide(*at, wide.data_ptr(), scratch.data_ptr() if need else None, need, None) == 0
+        assert torch.equal(one, z.argmax(-1).to(torch.int32)) and torch.equal(wide, one)
