@@ -447,10 +447,11 @@ __device__ __forceinline__ const u32x4 *tile_weights_seg(const FusedGemmArgs &a,
 // of the rows: half the operand reads per MFMA for a second fetch of the weights from the die's L2 (8B gate/up at 512 rows
 // 235 -> 220 us, but 84 -> 100 us at 160 rows, which are still bound by what a compute unit can fetch).
 template <int MT16, int QW, bool BLOCKS>
-__global__ __launch_bounds__(QW * 64) void qgemm16_kernel(FusedGemmArgs a, int RB, int NT16)
+__global__ __launch_bounds__(QW * 64) __attribute__((amdgpu_waves_per_eu(MT16 <= 2 ? 4 : 1))) void qgemm16_kernel(FusedGemmArgs a, int RB, int NT16)
 {
     constexpr int QDW = BLOCKS ? 3 : 4;           // k-tiles in flight
     constexpr bool TWO = BLOCKS || MT16 <= 3;     // sums in two levels, where the registers allow it
+    constexpr bool COMP = !BLOCKS && MT16 <= 2;   // ... the upper one compensated
     constexpr int RH = BLOCKS ? 2 : 1;       // waves that share a column group, each on its part of the rows
     static_assert(MT16 % RH == 0, "every wave has the same number of row tiles");
     constexpr int CW = QW / RH;                   // column groups per workgroup
@@ -501,11 +502,11 @@ __global__ __launch_bounds__(QW * 64) void qgemm16_kernel(FusedGemmArgs a, int R
         if (rt >= a.part_rows >> 4) rt = (a.part_rows >> 4) - 1;   // past the rows: never stored
         asrc[i] = ((t & 1) ? a.A_lo : a.A_hi) + (size_t)rt * KT * 64 + lane;
     }
-    f32x4 acc[MTW][NC], total[MTW][NC];
+    f32x4 acc[MTW][NC], total[MTW][NC], lost[MTW][NC];
 #pragma unroll
     for (int i = 0; i < MTW; ++i)
 #pragma unroll
-        for (int ct = 0; ct < NC; ++ct) acc[i][ct] = total[i][ct] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int ct = 0; ct < NC; ++ct) acc[i][ct] = total[i][ct] = lost[i][ct] = f32x4{0.f, 0.f, 0.f, 0.f};
 
     u32x4 w[QDW][NC], apre[QDW][APT];
     auto load_a = [&](int u, int it) {
@@ -562,13 +563,23 @@ __global__ __launch_bounds__(QW * 64) void qgemm16_kernel(FusedGemmArgs a, int R
     };
     // A running fp32 sum over hundreds of k-tiles loses more bits than sums of a few k-tiles and a sum of those, which the
     // register-resident kernel and the deeper K splits of four passes had for free.  Relative error against 64 bits, one
-    // level / two: 70B down at 32 rows 7.7e-7 / 1.8e-7 (pgemm_kernel 1.3e-7), at 512 rows 1.1e-6 / 2.0e-7 (passes 5.8e-7).
+    // level / two: 70B down at 32 rows 7.7e-7 / 1.8e-7, at 512 rows 1.1e-6 / 2.0e-7 (passes 5.8e-7).  Up to 32 rows, which
+    // share their sizes with pgemm_kernel, the sum of sums is compensated: two levels / compensated / pgemm_kernel 70B down
+    // 1.77e-7 / 1.16e-7 / 1.29e-7, 8B down 1.38e-7 / 1.20e-7 / 1.21e-7, K = 4096 1.46e-7 / 1.07e-7 / 1.18e-7, in the same time
+    // as long as four waves fit a SIMD (LM head of 128256 at 32 rows 192 us; with the lo products in sums of their own the
+    // error is 0.7e-7, but three waves fit: 199 us).
     auto flush = [&]() {
 #pragma unroll
         for (int i = 0; i < MTW; ++i)
 #pragma unroll
             for (int ct = 0; ct < NC; ++ct) {
-                total[i][ct] += acc[i][ct];
+                if (COMP) {   // `lost`: what the last sum rounded away
+                    const f32x4 add = acc[i][ct] - lost[i][ct], sum = total[i][ct] + add;
+                    lost[i][ct] = (sum - total[i][ct]) - add;
+                    total[i][ct] = sum;
+                } else {
+                    total[i][ct] += acc[i][ct];
+                }
                 acc[i][ct] = f32x4{0.f, 0.f, 0.f, 0.f};
             }
     };
@@ -591,7 +602,10 @@ __global__ __launch_bounds__(QW * 64) void qgemm16_kernel(FusedGemmArgs a, int R
 #pragma unroll
         for (int i = 0; i < MTW; ++i)
 #pragma unroll
-            for (int ct = 0; ct < NC; ++ct) acc[i][ct] += total[i][ct];
+            for (int ct = 0; ct < NC; ++ct) {
+                if (COMP) acc[i][ct] -= lost[i][ct];
+                acc[i][ct] += total[i][ct];
+            }
     }
 
     // acc[i][ct][v] of lane l: row 16 * (half * MTW + i) + 4*(l/16) + v, column 16 * (c16 + ct) + l%16

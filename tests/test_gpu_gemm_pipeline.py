@@ -40,3 +40,29 @@ def test_row_tiles(N, K, M):
                                    (32800, 4096, 9)])
 def test_small_steps_of_large_matrices(N, K, M):
     check(N, K, M)
+
+
+# up to 32 rows either kernel may serve a matrix, so neither may round worse than the other
+@pytest.mark.parametrize("N,K", [(28672, 4096), (4096, 14336), (57344, 8192), (8192, 28672)])
+@pytest.mark.parametrize("M", [5, 16, 17, 32])
+def test_rounding_of_small_steps(N, K, M):
+    """Against 64 bits on the operands as they are stored.  A chain of n fp32 additions of like terms has a relative error
+    of sqrt(n / 2) * 2^-24 / sqrt(3) (every sum rounds once, and is sqrt(i / n) of the last).  The small-step kernel adds 8
+    k-tiles, 16 waves and J slices of 128 k-tiles: sqrt(4 + 8 + J / 2).  The error averages over M * N >= 20480 elements."""
+    print(f"gemm rounding N={N} K={K} M={M}", flush=True)
+    w = normal_bf16(74, N * 3 + K, (N, K), 0.02, device=DEV)
+    x = normal_bf16(75, M * 7 + K, (M, K), 1.0, device=DEV).float() * 1.25
+    hi, lo = sv.sssd_op_pack_activation(x)
+    y = sv.sssd_op_gemm(hi, lo, sv.sssd_op_pack_weight(w), M, N, K)
+    xh = x.to(torch.bfloat16)
+    stored = xh.double() + (x - xh.float()).to(torch.bfloat16).double()
+    err = size = 0.0
+    for n in range(0, N, 8192):
+        full = stored @ w[n:n + 8192].double().t().contiguous()
+        err += (y[:, n:n + 8192] - full).square().sum().item()
+        size += full.square().sum().item()
+    J = -(-K // 4096)
+    bound = (12 + J / 2) ** 0.5 * 2.0 ** -24 / 3 ** 0.5
+    rel = (err / size) ** 0.5
+    print(f"relative error {rel:.3e}, bound {bound:.3e}", flush=True)
+    assert rel <= bound
