@@ -24,8 +24,9 @@ struct Buffers {
     uint16_t *Qp, *Qp_lo;
     float *part_o, *part_ml, *part_val;
     int *part_idx;
-    int32_t *pos_base, *seq_seg, *wg_rec, *err_flag, *that_dbg, *rope_pos;
+    int32_t *pos_base, *err_flag, *that_dbg, *rope_pos;
     int *tail_count;   // TAIL_SLOTS split-K arrival counters, zero between launches
+    AttnCut *cut;
     uint32_t *anc;
     float *rope_cs, *ssq1;
     uint8_t *staging;
@@ -34,7 +35,7 @@ struct Buffers {
     size_t partial_bytes;
     void *sample_scratch;         // sampled steps of few rows: the row sampler's cluster scratch
     size_t sample_scratch_bytes;
-    size_t attn_slots;   // attention partial slots ([kv head][workgroup]) the buffers behind part_o / part_ml hold
+    size_t attn_slots;   // attention partial slots ([kv head][sequence][segment]) the buffers behind part_o / part_ml hold
 };
 
 struct Sizes {
@@ -139,8 +140,7 @@ size_t layout(const Dims &D, Sizes &S, Buffers *B, uint8_t *base)
     b.part_val = (float *)take((size_t)S.m_alloc * NTv * 4);
     b.part_idx = (int *)take((size_t)S.m_alloc * NTv * 4);
     b.pos_base = (int32_t *)take((size_t)D.max_batch * 4);
-    b.seq_seg = (int32_t *)take((size_t)D.max_batch * 8);
-    b.wg_rec = (int32_t *)take(b.attn_slots / D.nkv * 16);
+    b.cut = (AttnCut *)take((size_t)D.max_batch * sizeof(AttnCut));
     b.rope_pos = (int32_t *)take((size_t)S.m_alloc * 4);
     b.anc = (uint32_t *)take((size_t)S.m_alloc * 4);
     b.err_flag = (int32_t *)take(4);
@@ -235,14 +235,6 @@ int drain_prof(sssd_ctx *c)
 
 bool valid(const sssd_ctx *c) { return c && c->magic == MAGIC; }
 
-AttnPlan attn_plan(const sssd_ctx *c, int B, int k)
-{
-    AttnPlan p = attention_plan(c->D, B, k);
-    p.wg_rec = c->W.wg_rec;
-    p.seq_seg = c->W.seq_seg;
-    return p;
-}
-
 KvGeom kv_geom(const sssd_ctx *c) { return KvGeom{c->block_table, c->D.blocks_per_seq, c->D.n_pages, c->D.nkv, c->D.d}; }
 
 }  // namespace
@@ -293,8 +285,8 @@ int sssd_verify_plan_check(const sssd_model_config *cfg, int32_t B, int32_t k)
     const int kin[5] = {D.h, D.qd, D.h, D.f, D.h};
     for (int i = 0; i < 5; ++i)
         if (stream_gemm_scratch_bytes(M, (int)ntot[i], kin[i]) > W.partial_bytes) return SSSD_ECAPACITY;
-    // attention partial slots: [kv heads][workgroups] x q_rows_pad rows, laid out behind part_o / part_ml
-    if ((size_t)D.nkv * attention_plan(D, B, k).wgs > W.attn_slots) return SSSD_ECAPACITY;
+    // attention partial slots: [kv heads][B][segments] x q_rows_pad rows, laid out behind part_o / part_ml
+    if ((size_t)D.nkv * B * attention_plan(D, B, k).share > W.attn_slots) return SSSD_ECAPACITY;
     return SSSD_OK;
 }
 
@@ -474,7 +466,7 @@ int run_step(sssd_ctx *c, int32_t B, int32_t k, const int32_t *tokens, const int
     {
         Prof p(c, s, SSSD_PROF_ELEM);
         HIP_TRY(launch_fused_embed(D, io, kv_geom(c), c->embed, c->layers[0].attn_norm, W.X, W.Ah_hi, W.Ah_lo, W.ssq1, W.pos_base,
-                                   W.rope_pos, W.anc, W.err_flag, attn_plan(c, B, k), s));
+                                   W.cut, W.rope_pos, W.anc, W.err_flag, s));
     }
     FusedGemmArgs f{};
     f.M = M; f.h = D.h; f.d = D.d; f.nq = D.nq; f.nkv = D.nkv; f.seq_pad = D.seq_pad; f.k = k;
@@ -535,7 +527,7 @@ int run_step(sssd_ctx *c, int32_t B, int32_t k, const int32_t *tokens, const int
     for (int l = 0; l < D.L; ++l) {
         uint16_t *Kl = c->Kc + (size_t)l * c->S.kv_layer_elems, *Vl = c->Vc + (size_t)l * c->S.kv_layer_elems;
         {
-            AttnArgs a{W.Qp, W.Qp_lo, Kl, Vl, kv_geom(c), W.pos_base, W.anc, W.part_o, W.part_ml, W.wg_rec, W.seq_seg, W.Aq_hi, W.Aq_lo, B, k, 0, 0};
+            AttnArgs a{W.Qp, W.Qp_lo, Kl, Vl, kv_geom(c), W.pos_base, W.cut, W.anc, W.part_o, W.part_ml, W.Aq_hi, W.Aq_lo, B, k, {}, 0};
             Prof p(c, s, SSSD_PROF_ATTN);
             HIP_TRY(launch_attention(D, a, s));
         }
@@ -859,10 +851,10 @@ int sssd_op_attention(sssd_ctx *c, int32_t layer, int32_t B, int32_t k, const fl
     if (B > D.max_batch || k > D.max_k) return SSSD_ECAPACITY;
     hipStream_t s = (hipStream_t)stream;
     Buffers &W = c->W;
-    HIP_TRY(launch_lens(D, B, k, lens, W.pos_base, W.rope_pos, W.anc, W.err_flag, attn_plan(c, B, k), s));
+    HIP_TRY(launch_lens(D, B, k, lens, W.pos_base, W.cut, W.rope_pos, W.anc, W.err_flag, s));
     HIP_TRY(launch_q_pack(D, q, B, k, W.Qp, W.Qp_lo, s));
     uint16_t *Kl = c->Kc + (size_t)layer * c->S.kv_layer_elems, *Vl = c->Vc + (size_t)layer * c->S.kv_layer_elems;
-    AttnArgs a{W.Qp, W.Qp_lo, Kl, Vl, kv_geom(c), W.pos_base, W.anc, W.part_o, W.part_ml, W.wg_rec, W.seq_seg, W.Aq_hi, W.Aq_lo, B, k, 0, 0};
+    AttnArgs a{W.Qp, W.Qp_lo, Kl, Vl, kv_geom(c), W.pos_base, W.cut, W.anc, W.part_o, W.part_ml, W.Aq_hi, W.Aq_lo, B, k, {}, 0};
     HIP_TRY(launch_attention(D, a, s));
     HIP_TRY(launch_unpack_act(W.Aq_hi, W.Aq_lo, B * (k + 1), D.qd, out, s));
     return SSSD_OK;

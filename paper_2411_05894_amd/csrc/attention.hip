@@ -7,9 +7,9 @@
 // ones named by a 32-bit word per query node -- itself and its ancestors in the draft
 // tree (Sec. 3.1); for a linear chain that is "row j sees new rows 0..j".
 //
-// One workgroup owns one segment of one sequence's positions for one kv head.  The segments are cut
-// once per step from the device's own lens (attn_schedule in elementwise.hip), so that ragged batches
-// and caches with room to grow keep every compute unit about equally busy.  All g*(k+1) query rows
+// One workgroup owns one segment of one sequence's positions for one kv head.  A sequence is cut by
+// its own length (attention_cut, by the kernel that validates the lens): caches with room to grow cost
+// nothing, and what the other sequences hold changes no bit.  All g*(k+1) query rows
 // that share the kv head are processed against the segment, one 16-row tile per wave,
 // so every cached byte is read from HBM once per step: the waves stage each block of
 // 32 positions through LDS together (double buffered, the next block's loads in flight
@@ -37,7 +37,7 @@ __device__ __forceinline__ f32x4 mfma(const u32x4 &a, const u32x4 &b, f32x4 c)
 constexpr float NEG_BIG = -1.0e30f;
 constexpr int MAX_WAVES = 6;   // query-row tiles per launch
 
-// grid = (a.wgs * kv heads, passes over the row tiles); block = NW waves; wave w owns query-row tile pass * NW + w.
+// grid = (B * share * kv heads, passes over the row tiles); block = NW waves; wave w owns query-row tile pass * NW + w.
 // Workgroups 8 apart run on one die, where the heads of a segment follow each other: they read one page (64 KiB of K at
 // eight heads of 128) at about the same time (B = 4, context 32768: 101 us with the heads 64 workgroups apart, 96 us so).
 // The kernel is bound by bytes in flight, i.e. by resident workgroups: with three or more waves the
@@ -54,9 +54,9 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW >= 3
     __shared__ u32x4 Ks[2][32 * KROW];
     __shared__ u32x4 Vs[2][NREC];
 
-    int kvh, wg;
+    int kvh, wg;   // kv head; (sequence, segment)
     {
-        const int id = blockIdx.x, whole = a.wgs & ~7;
+        const int id = blockIdx.x, whole = (a.B * a.plan.share) & ~7;
         if (id < whole * D.nkv) {
             wg = id / (8 * D.nkv) * 8 + (id & 7);
             kvh = (id >> 3) % D.nkv;
@@ -66,20 +66,17 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW >= 3
             kvh = r % D.nkv;
         }
     }
-    const int4 rec = reinterpret_cast<const int4 *>(a.wg_rec)[wg];   // sequence, first block, blocks, segments of the sequence
-    const int b = rec.x;
-    if (b < 0) return;
+    const int b = wg / a.plan.share, segment = wg % a.plan.share;
+    const int len = max(a.pos_base[b], 0);   // a rejected sequence (< 0) is read as empty
+    const int total = len + a.k + 1;
+    const AttnCut cut = a.cut[b];
+    if (segment >= cut.n) return;
+    const int t_begin = segment * cut.each * 32;
+    const int t_end = min(total, t_begin + cut.each * 32);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int q = lane >> 4, c = lane & 15;
     const int rt = min((int)blockIdx.y * NW + wave, (q_rows_pad >> 4) - 1);   // the last pass may have waves to spare: they repeat a tile
     const bool row_tile_ok = (int)blockIdx.y * NW + wave < a.row_tiles;
-    const int len = max(a.pos_base[b], 0);   // a rejected sequence (< 0) is read as empty
-    const int total = len + a.k + 1;
-    const int t_begin = rec.y * 32;
-    // The segments of a rejected sequence were cut from its own length: those past the rows it is read with see one block
-    // with every position masked.
-    const int t_end = max(min(total, t_begin + rec.z * 32), t_begin + 1);
-    const int n_seg = rec.w;
 
     // Pages of the segment's blocks: lane l keeps the page of block first_blk + 64*group + l, so the
     // page of any block of the current group of 64 is one cross-lane read away.
@@ -243,7 +240,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW >= 3
     l += __shfl_xor(l, 16);
     l += __shfl_xor(l, 32);
     const int row = rt * 16 + c;
-    if (n_seg == 1) {   // the whole sequence: the packed operands of the O projection
+    if (cut.n == 1) {   // the whole sequence: the packed operands of the O projection
         const int jj = row / D.g, hl = row - jj * D.g;
         if (row_tile_ok && jj <= a.k) {
             const float inv = 1.f / l;
@@ -261,7 +258,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW >= 3
             }
         }
     } else if (row_tile_ok) {
-        const size_t at = ((size_t)kvh * a.wgs + wg) * q_rows_pad + row;
+        const size_t at = ((size_t)kvh * a.B * a.plan.share + wg) * q_rows_pad + row;
         float *po = a.part_o + at * HD;
 #pragma unroll
         for (int dt = 0; dt < DT; ++dt) *reinterpret_cast<f32x4 *>(po + dt * 16 + 4 * q) = o[dt];
@@ -289,10 +286,9 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(Dims D, AttnArgs a, i
     const int KTq = (D.qd + 31) >> 5;
     const int sg = lane >> 4, cl = lane & 15;
     const int r = task % R, kvh = (task / R) % D.nkv, b = task / (R * D.nkv);
-    const int2 seg = *reinterpret_cast<const int2 *>(a.seq_seg + 2 * b);
-    const int n_splits = seg.y;            // at most ATTN_MAX_SEGMENTS
+    const int n_splits = a.cut[b].n;       // at most ATTN_MAX_SEGMENTS
     if (n_splits == 1) return;             // finished by its workgroup
-    const size_t slot0 = (size_t)kvh * a.wgs + seg.x;
+    const size_t slot0 = ((size_t)kvh * a.B + b) * a.plan.share;
 
     float2 ml = float2{NEG_BIG, 0.f};
     if (lane < n_splits) ml = *reinterpret_cast<const float2 *>(a.part_ml + ((slot0 + lane) * q_rows_pad + r) * 2);
@@ -355,7 +351,7 @@ template <int HD> hipError_t launch_partial(const Dims &D, const AttnArgs &a, in
 {
     // One wave per query-row tile; more than MAX_WAVES tiles are spread evenly over several passes over the cache.
     const int passes = (a.row_tiles + MAX_WAVES - 1) / MAX_WAVES, nw = (a.row_tiles + passes - 1) / passes;
-    const dim3 grid(a.wgs * D.nkv, passes);
+    const dim3 grid(a.B * a.plan.share * D.nkv, passes);
 #define SSSD_ALAUNCH(NW) hipLaunchKernelGGL((attn_partial_kernel<HD, NW>), grid, dim3(NW * 64), 0, s, D, a, q_rows_pad)
     switch (nw) {
     case 1: SSSD_ALAUNCH(1); break;
@@ -371,38 +367,47 @@ template <int HD> hipError_t launch_partial(const Dims &D, const AttnArgs &a, in
 
 }  // namespace
 
+// Segments per sequence.  The device holds four workgroups per compute unit with up to three waves (row tiles) each, three
+// with four waves, two with five or six, i.e. 1024 / 768 / 512 at once, and a launch is kept to one such round.  Within it
+// fewer and longer segments are faster, as long as ragged batches still even out.
 AttnPlan attention_plan(const Dims &D, int B, int k)
 {
     const int tiles = (D.g * (k + 1) + 15) / 16;
     const int passes = (tiles + MAX_WAVES - 1) / MAX_WAVES, waves = (tiles + passes - 1) / passes;
-    const long pairs = (long)B * D.nkv;
+    const long pairs = (long)B * D.nkv, units = pairs * passes;   // workgroups per segment of every sequence
     long target;
-    if (waves >= 5) target = 3 * pairs > 256 ? 512 : 256;
-    else {
-        target = 3 * pairs > 512 ? 3 * pairs : 512;
+    if (waves >= 5) {
+        target = 3 * pairs > 256 ? 512 : 256;
+    } else {
         const long round = waves == 4 ? 768 : 1024;
+        target = 3 * pairs > 512 ? 3 * pairs : 512;
         if (target > round) target = round;
     }
-    target = (target + passes - 1) / passes;
+    const long share = target / units;
     AttnPlan p;
-    const int w = (int)((target + D.nkv - 1) / D.nkv);
-    p.wgs = w > B ? w : B;
-    p.min_blocks = 4;
-    p.long_blocks = 0x7FFFFFFF;
-    if (tiles > 4) p.long_blocks = (16 * 256 + D.nkv * passes - 1) / (D.nkv * passes);
-    p.wg_rec = p.seq_seg = nullptr;
+    p.share = share < 1 ? 1 : (share > ATTN_MAX_SEGMENTS ? ATTN_MAX_SEGMENTS : (int)share);
+    p.long_blocks = tiles > 4 ? (int)((16 * 256 + units - 1) / units) : 0x7FFFFFFF;
     return p;
 }
 
-// Partial results a step of B sequences can leave, all kv heads: most at the narrowest step.
-size_t attention_slots(const Dims &D, int B) { return (size_t)D.nkv * attention_plan(D, B, 0).wgs; }
+// Most partial results that any step of up to B sequences leaves, all kv heads.
+size_t attention_slots(const Dims &D, int B)
+{
+    size_t most = 0;
+    for (int b = 1; b <= B; ++b)
+        for (int k = 0; k <= D.max_k; ++k) {
+            const size_t n = (size_t)D.nkv * b * attention_plan(D, b, k).share;
+            if (n > most) most = n;
+        }
+    return most;
+}
 
 hipError_t launch_attention(const Dims &D, const AttnArgs &a_in, hipStream_t s)
 {
     AttnArgs a = a_in;
     const int q_rows_pad = round_up(D.g * (D.max_k + 1), 16);
     a.row_tiles = (D.g * (a.k + 1) + 15) / 16;
-    a.wgs = attention_plan(D, a.B, a.k).wgs;
+    a.plan = attention_plan(D, a.B, a.k);
     hipError_t e = D.d == 128 ? launch_partial<128>(D, a, q_rows_pad, s) : launch_partial<64>(D, a, q_rows_pad, s);
     if (e != hipSuccess) return e;
     const int n_tasks = a.B * D.nkv * D.g * (a.k + 1);

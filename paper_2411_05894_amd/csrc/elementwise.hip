@@ -276,80 +276,10 @@ __global__ void q_pack_kernel(Dims D, const float *q, int k, uint16_t *Qp, uint1
     Qp_lo[idx] = lo;
 }
 
-// Cuts the cached positions of all sequences into the attention kernel's segments (AttnPlan), from the lens as the caller
-// gave them; whole workgroup.  The segment length is the smallest of 64 candidates whose segments fit plan.wgs, evened out
-// per sequence.  Lengths of 16 blocks and more are made odd: an even one puts the segments' streams a multiple of a large
-// power of two apart, where they meet on the same memory channels (B = 4, context 32768, eight heads of 128: 96 us of
-// attention with segments of 65 blocks, 104 us with 64).
-__device__ void attn_schedule(const Dims &D, int B, int k, const int32_t *lens, const AttnPlan &plan)
+// Validated lens and the row geometry of linear chains (kernel-level attention entry point).
+__global__ void lens_kernel(Dims D, int B, int k, const int32_t *lens, int32_t *pos_base, AttnCut *cut, int32_t *rope_pos,
+                            uint32_t *anc, int32_t *err_flag, AttnPlan plan)
 {
-    __shared__ int total, longest, fits[64], pick;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, waves = blockDim.x >> 6;
-    auto blocks = [&](int b) {
-        int len = lens[b];
-        if (len < 0 || len + k + 1 > D.max_seq) len = 0;
-        return (len + k + 1 + 31) >> 5;
-    };
-    auto ceil_div = [](int x, int y) { return (int)(((unsigned)x + (unsigned)y - 1u) / (unsigned)y); };
-    auto streamable = [](int n) { return n >= 16 ? n | 1 : n; };
-    if (tid < 64) fits[tid] = 0;
-    if (tid == 0) total = longest = pick = 0;
-    __syncthreads();
-    int sum = 0, most = 0;
-    for (int b = tid; b < B; b += blockDim.x) {
-        const int n = blocks(b);
-        sum += n;
-        most = max(most, n);
-    }
-    if (sum) { atomicAdd(&total, sum); atomicMax(&longest, most); }
-    __syncthreads();
-    const int least = max(total >= plan.long_blocks ? 16 : plan.min_blocks, max(ceil_div(total, plan.wgs), ceil_div(longest, ATTN_MAX_SEGMENTS)));
-    const int step = max(1, ceil_div(longest - min(longest, least), 62));
-    const int mine = streamable(least + lane * step);
-    int count = 0;
-    for (int b = wave; b < B; b += waves) count += ceil_div(blocks(b), mine);
-    atomicAdd(&fits[lane], count);
-    __syncthreads();
-    if (wave != 0) return;
-    // the last candidate is as long as the longest sequence: B segments, which always fit
-    const unsigned long long ok = __ballot(fits[lane] <= plan.wgs);
-    const int len = __shfl(mine, ok ? __ffsll((long long)ok) - 1 : 63);
-    int used = 0;
-    int4 *rec = reinterpret_cast<int4 *>(plan.wg_rec);
-    for (int b0 = 0; b0 < B; b0 += 64) {
-        const int b = b0 + lane;
-        int n = 0, each = 1, nb = 0;
-        if (b < B) {
-            nb = blocks(b);
-            each = streamable(ceil_div(nb, ceil_div(nb, len)));
-            n = ceil_div(nb, each);
-        }
-        int upto = n;
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            const int o = __shfl_up(upto, off);
-            if (lane >= off) upto += o;
-        }
-        const int first = used + upto - n;
-        if (b < B) {
-            plan.seq_seg[2 * b] = first;
-            plan.seq_seg[2 * b + 1] = n;
-        }
-        for (int i = 0; i < n && first + i < plan.wgs; ++i) rec[first + i] = int4{b, i * each, min(each, nb - i * each), n};
-        used += __shfl(upto, 63);
-    }
-    for (int w = used + lane; w < plan.wgs; w += 64) rec[w] = int4{-1, 0, 0, 0};
-}
-
-// Validated lens and the row geometry of linear chains (kernel-level attention entry point); the last workgroup cuts the
-// segments.
-__global__ void lens_kernel(Dims D, int B, int k, const int32_t *lens, int32_t *pos_base, int32_t *rope_pos, uint32_t *anc,
-                            int32_t *err_flag, AttnPlan plan)
-{
-    if (blockIdx.x == gridDim.x - 1) {
-        attn_schedule(D, B, k, lens, plan);
-        return;
-    }
     const int b = blockIdx.x * blockDim.x + threadIdx.x;
     if (b >= B) return;
     int len = lens[b];
@@ -358,6 +288,7 @@ __global__ void lens_kernel(Dims D, int B, int k, const int32_t *lens, int32_t *
         len = 0;
     }
     pos_base[b] = len;
+    cut[b] = attention_cut(plan, (len + k + 32) >> 5);
     for (int j = 0; j <= k; ++j) {
         rope_pos[b * (k + 1) + j] = len + j;
         anc[b * (k + 1) + j] = 0xFFFFFFFFu >> (31 - j);
@@ -387,17 +318,13 @@ __global__ void pack_weight_kernel(const uint16_t *src, u32x4 *dst, int N, int K
 }
 
 
-// grid = M + 1, 512 threads: one row each, and one workgroup that cuts the attention segments.  Validates lens/tokens/parents; row geometry (depth and visible new
+// grid = M rows, 512 threads.  Validates lens/tokens/parents; row geometry (depth and visible new
 // rows of the node, from the draft tree or the chain); x = E[token]; packed x*gamma; sums of squares.
 __global__ __launch_bounds__(512) void fused_embed_kernel(Dims D, StepIO io, KvGeom kv, const uint16_t *embed, const uint16_t *gamma,
                                                           float *X, uint16_t *A_hi, uint16_t *A_lo, float *ssq,
-                                                          int32_t *pos_base, int32_t *rope_pos, uint32_t *anc,
+                                                          int32_t *pos_base, AttnCut *cut, int32_t *rope_pos, uint32_t *anc,
                                                           int32_t *err_flag, AttnPlan plan)
 {
-    if (blockIdx.x == gridDim.x - 1) {
-        attn_schedule(D, io.B, io.k, io.lens, plan);
-        return;
-    }
     const int m = blockIdx.x, b = m / (io.k + 1), j = m % (io.k + 1);
     int tok = io.tokens[m];
     if (tok < 0 || tok >= D.V) {
@@ -421,6 +348,7 @@ __global__ __launch_bounds__(512) void fused_embed_kernel(Dims D, StepIO io, KvG
             }
             // pos_base < 0 marks the rejected sequence for the K/V writers; readers take it as length 0
             pos_base[b] = reject ? -1 : len;
+            cut[b] = attention_cut(plan, ((reject ? 0 : len) + io.k + 32) >> 5);
         }
         if (reject) *err_flag = 1;
         int depth = j;
@@ -566,10 +494,11 @@ hipError_t launch_q_pack(const Dims &D, const float *q, int B, int k, uint16_t *
     return hipGetLastError();
 }
 
-hipError_t launch_lens(const Dims &D, int B, int k, const int32_t *lens, int32_t *pos_base, int32_t *rope_pos, uint32_t *anc,
-                       int32_t *err_flag, const AttnPlan &plan, hipStream_t s)
+hipError_t launch_lens(const Dims &D, int B, int k, const int32_t *lens, int32_t *pos_base, AttnCut *cut, int32_t *rope_pos,
+                       uint32_t *anc, int32_t *err_flag, hipStream_t s)
 {
-    hipLaunchKernelGGL(lens_kernel, dim3((B + 63) / 64 + 1), dim3(64), 0, s, D, B, k, lens, pos_base, rope_pos, anc, err_flag, plan);
+    hipLaunchKernelGGL(lens_kernel, dim3((B + 63) / 64), dim3(64), 0, s, D, B, k, lens, pos_base, cut, rope_pos, anc, err_flag,
+                       attention_plan(D, B, k));
     return hipGetLastError();
 }
 
@@ -584,10 +513,10 @@ hipError_t launch_pack_weight(const uint16_t *src, uint16_t *dst, int N, int K, 
 }
 
 hipError_t launch_fused_embed(const Dims &D, const StepIO &io, const KvGeom &kv, const uint16_t *embed, const uint16_t *gamma,
-                              float *X, uint16_t *A_hi, uint16_t *A_lo, float *ssq, int32_t *pos_base, int32_t *rope_pos,
-                              uint32_t *anc, int32_t *err_flag, const AttnPlan &plan, hipStream_t s)
+                              float *X, uint16_t *A_hi, uint16_t *A_lo, float *ssq, int32_t *pos_base, AttnCut *cut, int32_t *rope_pos,
+                              uint32_t *anc, int32_t *err_flag, hipStream_t s)
 {
-    hipLaunchKernelGGL(fused_embed_kernel, dim3(io.B * (io.k + 1) + 1), dim3(512), 0, s, D, io, kv, embed, gamma, X, A_hi, A_lo, ssq,
-                       pos_base, rope_pos, anc, err_flag, plan);
+    hipLaunchKernelGGL(fused_embed_kernel, dim3(io.B * (io.k + 1)), dim3(512), 0, s, D, io, kv, embed, gamma, X, A_hi, A_lo, ssq,
+                       pos_base, cut, rope_pos, anc, err_flag, attention_plan(D, io.B, io.k));
     return hipGetLastError();
 }

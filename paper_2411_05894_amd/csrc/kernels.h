@@ -2,7 +2,32 @@
 #pragma once
 #include "common.h"
 
-struct AttnPlan;
+// -------------------------------------------------- attention segments ----
+// How a sequence's positions are cut into segments, one workgroup per segment and kv head.  The cut follows from the
+// sequence's own length and from B, k and the model alone, so that a sequence's results do not depend, not even in their
+// rounding, on the sequences beside it.
+struct AttnPlan {
+    int share;         // segments of a sequence at most
+    int long_blocks;   // a sequence of so many blocks of 32 positions or more has segments of at least 16 blocks, not 4
+};
+constexpr int ATTN_MAX_SEGMENTS = 64;   // per sequence: what the merge takes
+AttnPlan attention_plan(const Dims &D, int B, int k);
+struct AttnCut {       // of one sequence, once per step, beside pos_base
+    int each, n;       // blocks per segment (the last may be shorter), segments
+};
+// The sequence is shared out evenly.  Lengths of 16 blocks and more are made odd: an even one puts the segments' streams a
+// multiple of a large power of two apart, where they meet on the same memory channels (B = 4, context 32768, eight heads
+// of 128: 96 us of attention with segments of 65 blocks, 104 us with 64).
+__host__ __device__ __forceinline__ AttnCut attention_cut(const AttnPlan &p, int blocks)
+{
+    auto ceil_div = [](int x, int y) { return (int)(((unsigned)x + (unsigned)y - 1u) / (unsigned)y); };
+    const int fair = ceil_div(blocks, p.share), least = blocks >= p.long_blocks ? 16 : 4;
+    AttnCut c;
+    c.each = ceil_div(blocks, ceil_div(blocks, fair > least ? fair : least));
+    if (c.each >= 16) c.each |= 1;
+    c.n = ceil_div(blocks, c.each);
+    return c;
+}
 
 // ---------------------------------------------------------- elementwise ----
 // Reorder a row-major bf16 matrix [N][K] into packed tiles (K padded to 32 with zeros).
@@ -75,8 +100,8 @@ hipError_t launch_stream_gemm(FusedGemmArgs &a, int epilogue, hipStream_t s, boo
                               hipEvent_t t1);
 hipError_t launch_stream_epilogue(const FusedGemmArgs &a, int epilogue, hipStream_t s);
 hipError_t launch_fused_embed(const Dims &D, const StepIO &io, const KvGeom &kv, const uint16_t *embed, const uint16_t *gamma,
-                              float *X, uint16_t *A_hi, uint16_t *A_lo, float *ssq, int32_t *pos_base, int32_t *rope_pos,
-                              uint32_t *anc, int32_t *err_flag, const AttnPlan &plan, hipStream_t s);
+                              float *X, uint16_t *A_hi, uint16_t *A_lo, float *ssq, int32_t *pos_base, AttnCut *cut, int32_t *rope_pos,
+                              uint32_t *anc, int32_t *err_flag, hipStream_t s);
 
 // Merge per-tile arg-max partials, then greedy acceptance (longest matching prefix of a chain, or
 // the walk from the root of a draft tree when io.parents is set).
@@ -111,8 +136,8 @@ hipError_t launch_unpack_act(const uint16_t *A_hi, const uint16_t *A_lo, int M, 
 constexpr int STREAM_READ_SINK_WORDS = 4096;
 hipError_t launch_stream_read(const void *src, size_t bytes, uint32_t *sink, int n_cu, hipStream_t s);
 hipError_t launch_q_pack(const Dims &D, const float *q, int B, int k, uint16_t *Qp, uint16_t *Qp_lo, hipStream_t s);
-hipError_t launch_lens(const Dims &D, int B, int k, const int32_t *lens, int32_t *pos_base, int32_t *rope_pos,
-                       uint32_t *anc, int32_t *err_flag, const AttnPlan &plan, hipStream_t s);
+hipError_t launch_lens(const Dims &D, int B, int k, const int32_t *lens, int32_t *pos_base, AttnCut *cut, int32_t *rope_pos,
+                       uint32_t *anc, int32_t *err_flag, hipStream_t s);
 
 // ------------------------------------------------------------ attention ----
 struct AttnArgs {
@@ -121,26 +146,15 @@ struct AttnArgs {
     const uint16_t *Kc, *Vc;   // this layer's cache pools
     KvGeom kv;                 // page geometry
     const int32_t *pos_base;   // validated lens
+    const AttnCut *cut;        // [B]
     const uint32_t *anc;       // [B*(k+1)] visible new rows of each query row (bit i = row pos_base + i)
-    float *part_o;             // [kv head][wgs][q_rows_pad][d]
-    float *part_ml;            // [kv head][wgs][q_rows_pad][2]  (running max in log2 units, sum)
-    const int32_t *wg_rec;     // the step's segments (AttnPlan)
-    const int32_t *seq_seg;
+    float *part_o;             // [kv head][B][share][q_rows_pad][d]
+    float *part_ml;            // [kv head][B][share][q_rows_pad][2]  (running max in log2 units, sum)
     uint16_t *out_hi, *out_lo; // packed activations for the O projection (K = nq*d)
     int B, k;
-    int wgs, row_tiles;        // filled in by launch_attention: workgroups per kv head, 16-row tiles of query rows
+    AttnPlan plan;             // filled in by launch_attention
+    int row_tiles;             // ... 16-row tiles of query rows
 };
-// How a step of B sequences x k drafts is cut into segments: at most wgs of them per kv head, of min_blocks blocks of 32
-// positions or more, at most ATTN_MAX_SEGMENTS per sequence (what the merge takes).  The device cuts them from lens once
-// per step (fused_embed_kernel, lens_kernel) into
-//   wg_rec   int32 [wgs][4]: sequence (-1: none), first block, blocks, segments of that sequence
-//   seq_seg  int32 [B][2]: first segment and number of segments of a sequence
-struct AttnPlan {
-    int wgs, min_blocks, long_blocks;   // 16 blocks or more once the head's list is long_blocks long
-    int32_t *wg_rec, *seq_seg;
-};
-constexpr int ATTN_MAX_SEGMENTS = 64;
-AttnPlan attention_plan(const Dims &D, int B, int k);   // without the arrays
 // Partial slots of a step of B sequences, all kv heads (sizes the buffers).
 size_t attention_slots(const Dims &D, int B);
 hipError_t launch_attention(const Dims &D, const AttnArgs &a, hipStream_t s);

@@ -1,6 +1,7 @@
 """Attention over segments cut from the device's own lens: ragged batches in caches with room to grow, more sequences than a
 wave has lanes, sequences of one segment (finished without a merge) beside long ones, several passes over the row tiles, and
-sequences that the step rejects.  Reference: softmax in 64 bits."""
+sequences that the step rejects.  Reference: softmax in 64 bits.  A sequence's results are the same bits whatever the others
+hold."""
 import math
 
 import pytest
@@ -8,8 +9,9 @@ import torch
 
 pytestmark = pytest.mark.gpu
 
+from harness import Pair
 from paper_2411_05894_amd import binding as sv
-from sssd_synth import MODEL_SHAPES, global_weight_specs, layer_weight_specs, normal_bf16
+from sssd_synth import MODEL_SHAPES, global_weight_specs, layer_weight_specs, normal_bf16, uniform_int
 
 DEV = "cuda:0"
 CASES = [  # shape, k, lens, max_seq
@@ -35,14 +37,20 @@ def reference(q, K, V, n_old, g):
     return out
 
 
-@pytest.mark.parametrize("shape_name,k,lens,max_seq", CASES)
-def test_ragged_batches(shape_name, k, lens, max_seq):
+def attention_context(shape_name, B, k, max_seq):
+    """A context of which only the cache matters: the matrices are small and zero."""
     s = MODEL_SHAPES[shape_name]
     s = type(s)(**{**s.__dict__, "n_layers": 1, "vocab": 1024, "hidden": 64, "ffn": 64})
     layers = [{n: torch.zeros(shp, dtype=torch.bfloat16, device=DEV) for n, _, shp in layer_weight_specs(s)}]
     g = {n: torch.zeros(shp, dtype=torch.bfloat16, device=DEV) for n, _, shp in global_weight_specs(s)}
-    B, sq, d, grp = len(lens), k + 1, s.head_dim, s.n_q_heads // s.n_kv_heads
-    ctx = sv.VerifyContext(sv.make_config(s, B, k, max_seq), layers, g)
+    return s, sv.VerifyContext(sv.make_config(s, B, k, max_seq), layers, g)
+
+
+@pytest.mark.parametrize("shape_name,k,lens,max_seq", CASES)
+def test_ragged_batches(shape_name, k, lens, max_seq):
+    B = len(lens)
+    s, ctx = attention_context(shape_name, B, k, max_seq)
+    sq, d, grp = k + 1, s.head_dim, s.n_q_heads // s.n_kv_heads
     q = (normal_bf16(41, 1, (B, sq, s.n_q_heads, d), 1.0, device=DEV).float() * 1.28).contiguous()
     kv = []
     for b, n in enumerate(lens):
@@ -67,3 +75,66 @@ def test_ragged_batches(shape_name, k, lens, max_seq):
         assert rc == sv.SSSD_ENOSPACE
         for b in (0, 2):
             assert (other[b] - reference(q[b], *kv[b], lens[b], grp)).abs().max().item() <= 1e-4, b
+
+
+@pytest.mark.parametrize("shape_name,k", [("8b", 8), ("8b", 0), ("8b", 31), ("70b", 8), ("tiny", 4)])
+def test_the_other_sequences_change_no_bit(shape_name, k):
+    """One sequence's rows are cut, summed and merged alike whatever its neighbours hold, and wherever it stands in the batch."""
+    max_seq, mine = 20000, 3000
+    s, ctx = attention_context(shape_name, 4, k, max_seq)
+    sq = k + 1
+    q = (normal_bf16(43, 1, (4, sq, s.n_q_heads, s.head_dim), 1.0, device=DEV).float() * 1.28).contiguous()
+    q[2] = q[0]
+    kv = [normal_bf16(44, i, (s.n_kv_heads, max_seq, s.head_dim), 1.0, device=DEV) for i in range(2)]
+    for b in range(4):
+        ctx.sssd_kv_import(0, b, 0, *kv)
+    out = torch.empty(4, sq, s.n_q_heads * s.head_dim, dtype=torch.float32, device=DEV)
+    seen = []
+    for lens in ([mine, 10, mine, 0], [mine, 15000, mine, max_seq - sq], [mine, mine, mine, mine], [mine, 700, mine, 9000], [mine, max_seq, mine, 5]):
+        print(f"attention beside others {shape_name} k={k} lens={lens}", flush=True)
+        ctx.sssd_op_attention(0, q, torch.tensor(lens, dtype=torch.int32, device=DEV), out)
+        assert ctx.sssd_verify_sync() == (0 if max(lens) + sq <= max_seq else sv.SSSD_ENOSPACE)
+        seen += [out[0].clone(), out[2].clone()]
+    assert all(torch.equal(o, seen[0]) for o in seen)
+
+
+def test_a_long_sequence_with_a_bad_page_is_read_as_empty():
+    """A sequence of several segments whose table names a page outside the pool, beside healthy ones: the error is reported,
+    the others' logits and every cached row keep their bits."""
+    s = MODEL_SHAPES["tiny"]
+    B, k, max_seq = 3, 4, 1700
+    p = Pair(s, seed=91, max_batch=B, max_k=k, max_seq=max_seq)
+    _, bps, n_pages = sv.sssd_kv_geometry(p.cfg)
+    table = torch.arange(n_pages, dtype=torch.int32).flip(0).view(B, bps).contiguous()
+    good, bad = table.to(DEV), table.clone()
+    bad[1, 30] = n_pages + 5
+    p.ctx.sssd_kv_set_block_table(good)
+    ctxs = [300, 1600, 45]
+    for b in range(B):
+        p.prefill_random_kv(92, b, ctxs[b])
+    lens = torch.tensor(ctxs, dtype=torch.int32)
+    tokens = uniform_int(93, 1, (B, k + 1), 0, s.vocab - 1)
+
+    def cache():
+        got = []
+        for l in range(s.n_layers):
+            for b in range(B):
+                kv = [torch.empty(s.n_kv_heads, max_seq, s.head_dim, dtype=torch.bfloat16, device=DEV) for _ in range(2)]
+                p.ctx.sssd_kv_export(l, b, 0, *kv)
+                got += [x.view(torch.int16) for x in kv]
+        return got
+
+    healthy = p.step(tokens, lens)["logits"]
+    before = cache()
+    p.ctx.sssd_kv_set_block_table(bad.to(DEV))
+    dev = torch.zeros(B, dtype=torch.int32, device=DEV), torch.zeros(B, dtype=torch.int32, device=DEV)
+    logits = torch.zeros(B * (k + 1), s.vocab, device=DEV)
+    p.ctx.sssd_debug_logits(logits)
+    p.ctx.sssd_verify_step(tokens.to(DEV), lens.to(DEV), *dev)
+    assert p.ctx.sssd_verify_sync() == sv.SSSD_ENOSPACE
+    p.ctx.sssd_kv_set_block_table(good)
+    logits = logits.cpu().view(B, k + 1, s.vocab)
+    for b in (0, 2):
+        assert torch.equal(logits[b], healthy[b])
+    assert torch.isfinite(logits[1]).all()
+    assert all(torch.equal(x, y) for x, y in zip(cache(), before))
