@@ -276,7 +276,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW >= 3
 template <int HD>
 __global__ __launch_bounds__(256) void attn_combine_kernel(Dims D, AttnArgs a, int q_rows_pad)
 {
-    constexpr int BATCH = 5;
+    constexpr int BATCH = 5;      // nine cost registers: B = 12, k = 31, context 900..2700 81 us of attention, five 78
     constexpr int LPR = HD / 8;   // lanes that cover a row of HD channels, 8 each
     const int lane = threadIdx.x & 63, k = a.k;
     const int R = D.g * (k + 1);
@@ -369,21 +369,37 @@ template <int HD> hipError_t launch_partial(const Dims &D, const AttnArgs &a, in
 
 // Segments per sequence.  The device holds four workgroups per compute unit with up to three waves (row tiles) each, three
 // with four waves, two with five or six, i.e. 1024 / 768 / 512 at once, and a launch is kept to one such round.  Within it
-// fewer and longer segments are faster, as long as ragged batches still even out.
+// fewer and longer segments are faster (every segment is a partial result of g*(k+1) rows to write and merge, and HBM
+// serves 512 concurrent streams better than 1024), until compute units stand idle.  Measured as sssd_op_attention over the
+// caches of enough layers (1 GB) that nothing stays in a cache, us, all sequences at 4000 / at 1333..4000, by segments per
+// sequence (workgroups):
+//   up to four waves, 512 workgroups, or 768 where more than a fifth of 512 would be missing.  8B shape:
+//     k = 8, B = 13: 2 (208) 83 / 83, 4 (416) 66 / 65, 7 (728) 67 / 62, 9 (936) 69 / 63
+//     k = 8, B = 24: 2 (384) 103 / 97, 3 (576) 102 / 83, 4 (768) 98 / 83, 5 (960) 106 / 88
+//     k = 4, B = 32: 1 (256) 122 / 120, 2 (512) 105 / 91, 3 (768) 111 / 90, 4 (1024) 112 / 91
+//     k = 4, B = 4: 8 (256) 35 / 35, 16 (512) 33 / 33, 24 (768) 36 / 34, 32 (1024) 38 / 36
+//   one wave and fewer than six segments by that, 768, or 1024 for three: it needs them to even out ragged batches:
+//     k = 0, B = 16: 2 (256) 79 / 79, 4 (512) 60 / 54, 6 (768) 60 / 50, 8 (1024) 62 / 50
+//     k = 0, B = 40, 2000 / 667..2000: 1 (320) 82 / 79, 2 (640) 70 / 60, 3 (960) 70 / 56
+//   five and six waves, 256, where that leaves at most a quarter of the compute units idle, else 512.  70B shape, k = 8:
+//     B = 4: 8 (256) 50 / 50, 12 (384) 57 / 56, 16 (512) 53 / 53; B = 16: 2 (256) 101 / 100, 3 (384) 123 / 105, 4 (512) 107 / 96
+//     B = 11: 2 (176) 97 / 96, 4 (352) 104 / 89, 5 (440) 94 / 81; B = 24: 1 (192) 155 / 153, 2 (384) 169 / 148
+// At least four blocks per segment: 2 / 4 / 8 blocks at B = 1, k = 8 8B context 2048 26.4 / 25.2 / 27.8, 70B B = 2 context
+// 1000 35.0 / 34.1 / 36.9, 8B context 300 22.0 / 23.0 / 24.2.  More than four row tiles make partial results dear: at least
+// 16 blocks as soon as segments of that length fill the compute units (B = 16, k = 31, context 479 58 -> 56).
 AttnPlan attention_plan(const Dims &D, int B, int k)
 {
     const int tiles = (D.g * (k + 1) + 15) / 16;
     const int passes = (tiles + MAX_WAVES - 1) / MAX_WAVES, waves = (tiles + passes - 1) / passes;
-    const long pairs = (long)B * D.nkv, units = pairs * passes;   // workgroups per segment of every sequence
-    long target;
+    const long units = (long)B * D.nkv * passes;   // workgroups for one segment of every sequence
+    long share;
     if (waves >= 5) {
-        target = 3 * pairs > 256 ? 512 : 256;
+        share = 256 / units * units >= 192 ? 256 / units : 512 / units;
     } else {
-        const long round = waves == 4 ? 768 : 1024;
-        target = 3 * pairs > 512 ? 3 * pairs : 512;
-        if (target > round) target = round;
+        share = 512 / units;
+        if (share * units < 400 || (waves == 1 && share < 6)) share = 768 / units;
+        if (waves == 1 && share < 3) share = 1024 / units;
     }
-    const long share = target / units;
     AttnPlan p;
     p.share = share < 1 ? 1 : (share > ATTN_MAX_SEGMENTS ? ATTN_MAX_SEGMENTS : (int)share);
     p.long_blocks = tiles > 4 ? (int)((16 * 256 + units - 1) / units) : 0x7FFFFFFF;
