@@ -205,8 +205,8 @@ def main() -> int:
         ctx.sssd_verify_step(tok, lens, acc, nxt)
     prof = ctx.sssd_profile_read()
     ctx.sssd_profile_enable(False)
-    # dominant kernel: the weight streamer (one launch per GEMM; every weight byte is read once)
-    kname, launches = sv.sssd_op_gemm_kernel_name(M), prof["gemm"]["launches"] / prof_steps
+    # dominant kernel: the weight streamer (one launch per GEMM; every weight byte is read once), as the gate/up matrix takes it
+    kname, launches = sv.sssd_op_gemm_kernel_of(M, 2 * shape.ffn, shape.hidden), prof["gemm"]["launches"] / prof_steps
     ms_per_launch = prof["gemm"]["ms"] / prof["gemm"]["launches"]
     bytes_per_launch = bytes_alg["weights"] / launches
     achieved = bytes_per_launch / (ms_per_launch * 1e-3) / 1e9

@@ -54,8 +54,12 @@ int sssd_op_gemm_static(const void *a_hi, const void *a_lo, const void *w_packed
  * qgemm16_kernel, as the larger matrices of smaller steps do.  For benchmarks. */
 int32_t sssd_op_gemm_small_step_rows(void);
 
-/* Name of the weight-streaming kernel that a GEMM of M rows launches (static string): "pgemm_kernel" or
- * "qgemm16_kernel" (17..32 rows: of the matrices of 64 MB and more). */
+/* Name of the weight-streaming kernel that a GEMM of M rows with a matrix [N][K] launches (static string):
+ * "pgemm_kernel" or "qgemm16_kernel"; "" for sizes sssd_op_gemm refuses.  Up to 32 rows the size of the matrix decides. */
+const char *sssd_op_gemm_kernel_of(int32_t M, int32_t N, int32_t K);
+
+/* The same for one matrix of a common size, the gate/up matrix of the 8B shape (N = 28672, K = 4096).  Other matrices of a
+ * step of up to 32 rows may take the other kernel: sssd_op_gemm_kernel_of tells. */
 const char *sssd_op_gemm_kernel_name(int32_t M);
 
 /* Measurement aid: one read-only pass over `bytes` (>= 16, src 16-byte aligned) of device memory by a

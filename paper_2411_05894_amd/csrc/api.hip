@@ -743,7 +743,13 @@ int sssd_op_gemm(const void *a_hi, const void *a_lo, const void *w_packed, int32
 
 int32_t sssd_op_gemm_small_step_rows(void) { return stream_gemm_max_rows(); }
 
-const char *sssd_op_gemm_kernel_name(int32_t M) { return stream_gemm_kernel_name(M); }
+const char *sssd_op_gemm_kernel_of(int32_t M, int32_t N, int32_t K)
+{
+    if (M <= 0 || N <= 0 || K <= 0 || N % 16) return "";
+    return stream_gemm_kernel_name(M, N, K);
+}
+
+const char *sssd_op_gemm_kernel_name(int32_t M) { return stream_gemm_kernel_name(M, 28672, 4096); }
 
 }  // extern "C"
 

@@ -802,10 +802,9 @@ template <int EPI> hipError_t launch_small(FusedGemmArgs &a, hipStream_t s, bool
 
 int stream_gemm_max_rows() { return 32; }
 
-// Of the larger matrices where the size decides: from 17 rows on; below, the headline shape's matrices all take pgemm_kernel.
-const char *stream_gemm_kernel_name(int M)
+const char *stream_gemm_kernel_name(int M, int N, int K)
 {
-    return M <= 16 ? "pgemm_kernel" : "qgemm16_kernel";
+    return is_small(M, N, (K + 31) / 32 * 32) ? "pgemm_kernel" : "qgemm16_kernel";
 }
 
 // Split-K scratch needed for M rows: the largest J * rows * Ntot over the model's GEMMs.

@@ -70,3 +70,18 @@ def test_plan_check_covers_every_step_of_a_configuration_without_gpu():
         assert lib.sssd_verify_plan_check(C.byref(cfg), 1, mk + 1) == sv.SSSD_ECAPACITY
         assert lib.sssd_verify_plan_check(C.byref(cfg), 0, 0) == sv.SSSD_EINVAL
     assert lib.sssd_verify_plan_check(None, 1, 0) == sv.SSSD_EINVAL
+
+
+def test_the_gemm_kernel_of_a_matrix_follows_from_its_size_without_gpu():
+    """Up to 32 rows the matrix decides which kernel a GEMM takes: 64 MB at 17..32 rows; below, 256 MB and a K beyond what
+    one workgroup covers.  pgemm_kernel with an unsplit K is the one form that needs no scratch."""
+    of = sv.sssd_op_gemm_kernel_of
+    for M, N, K, want in ((9, 28672, 4096, "pgemm_kernel"), (16, 57344, 8192, "qgemm16_kernel"), (16, 8192, 28672, "qgemm16_kernel"),
+                          (16, 10240, 8192, "pgemm_kernel"), (1, 128256, 4096, "pgemm_kernel"), (32, 6144, 4096, "pgemm_kernel"),
+                          (17, 28672, 4096, "qgemm16_kernel"), (32, 4096, 14336, "qgemm16_kernel"), (33, 16, 32, "qgemm16_kernel")):
+        assert of(M, N, K) == want, (M, N, K)
+        if K <= 4096:
+            assert (sv.lib().sssd_op_gemm_scratch_bytes(M, N, K) == 0) == (want == "pgemm_kernel")
+    assert of(0, 16, 32) == of(1, 8, 32) == of(1, 16, 0) == ""
+    for M in (1, 16, 17, 32, 33, 160, 512):
+        assert sv.sssd_op_gemm_kernel_name(M) == of(M, 28672, 4096)
