@@ -195,7 +195,7 @@ struct SampleScratch {                    // one per cluster; the two counters a
     uint32_t chist[HIST_PASSES][256];
     uint64_t mhist[HIST_PASSES][256];
     // short path
-    uint64_t fine[FINE_BINS];             // cleared when a row begins
+    uint64_t fine[FINE_BINS];             // cleared when the row begins
     uint32_t kmax[MAX_CLUSTER], bound_k[MAX_CLUSTER], bound_1[MAX_CLUSTER], count[MAX_CLUSTER];
     uint64_t mass[MAX_CLUSTER];
     uint64_t sub[MAX_SUB];
@@ -700,40 +700,30 @@ __device__ int short_row(ShortLds &L, Cluster &cl, const float *z, int V, int se
     return SHORT_DONE;
 }
 
-// grid = clusters * C workgroups of 1024 threads; cluster g takes rows g, g + clusters, ...
-__global__ __launch_bounds__(ST) void sample_rows_kernel(const float *logits, int rows, int V, float inv_temperature, int top_k, float top_p,
-                                                         const float *uniforms, int32_t *sampled, int C, SampleScratch *scratch,
-                                                         int32_t *err)
+// One row, by the workgroups of a cluster (or one workgroup): the row's token to sampled[row].
+__device__ __forceinline__ void sample_row(Cluster &cl, const float *logits, int row, int V, float inv_temperature, int top_k, float top_p,
+                                           const float *uniforms, int32_t *sampled, int32_t *err)
 {
     __shared__ uint32_t chist[256];
     __shared__ uint64_t mhist[256];
     __shared__ float red_f[16];
     __shared__ uint32_t red_c[16];
     __shared__ uint32_t sh_prefix, sh_need, sh_count_b;
-    __shared__ uint64_t sh_above, sh_total, sh_target;
+    __shared__ uint64_t sh_above, sh_target;
     __shared__ int sh_wave, sh_batch, sh_token;
     __shared__ uint64_t sub[16][MAX_BATCH];   // mass of S per (wave, batch of 512 ids)
     __shared__ ShortLds short_lds;
 
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    const int n_clusters = gridDim.x / C;
-    Cluster cl{C > 1 ? scratch + blockIdx.x / C : nullptr, C, (int)(blockIdx.x % C), 0u, false};
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, C = cl.C;
     // this workgroup's token ids: [seg_lo, seg_hi), whole groups of four so that 16-byte loads stay aligned
     const int seg_len = ((V + C - 1) / C + 3) & ~3;
     const int seg_lo = min(V, cl.c * seg_len), seg_hi = min(V, seg_lo + seg_len), Vs = seg_hi - seg_lo;
-
-  for (int row = blockIdx.x / C; row < rows; row += n_clusters) {
     RowCtx r;
     r.z = logits + (size_t)row * V;
     r.V = V;
     const float *zs = r.z + seg_lo;   // the segment
     auto give_up = [&]() { if (cl.c == 0 && tid == 0) sampled[row] = -1; };
-    if (cl.failed) {                  // an earlier wait ran out: nothing more is sampled by this cluster
-        give_up();
-        continue;
-    }
-    // the cluster's bins of the previous row are dead (everyone left that row through a barrier that
-    // came after its last read of them): clear them for this row
+    // The scratch's bins start at zero; a barrier (of the maxima) comes before anything is added to them.
     if (C > 1) {
         uint32_t *w = &cl.s->chist[0][0];
         constexpr int WORDS = HIST_PASSES * 256 * 3;
@@ -745,10 +735,7 @@ __global__ __launch_bounds__(ST) void sample_rows_kernel(const float *logits, in
     const int done = short_row(short_lds, cl, r.z, V, seg_lo, seg_len, Vs, vec4, 1.4426950408889634f * inv_temperature, top_k, top_p,
                                uniforms[row], sampled + row, err);
     if (done == SHORT_LOST) give_up();
-    if (done != SHORT_GENERAL) {
-        __syncthreads();   // the shared words are rewritten by the next row
-        continue;
-    }
+    if (done != SHORT_GENERAL) return;
 
     // ---- max ----
     float mx = -INFINITY;
@@ -762,7 +749,7 @@ __global__ __launch_bounds__(ST) void sample_rows_kernel(const float *logits, in
     __syncthreads();
     if (C > 1) {
         if (tid == 0) __hip_atomic_store(&cl.s->gmax[cl.c], mx, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (!cluster_sync(cl, err)) { give_up(); continue; }
+        if (!cluster_sync(cl, err)) { give_up(); return; }
         for (int w = 0; w < C; ++w) mx = fmaxf(mx, __hip_atomic_load(&cl.s->gmax[w], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
     }
     r.mx = mx;
@@ -804,7 +791,7 @@ __global__ __launch_bounds__(ST) void sample_rows_kernel(const float *logits, in
         total_a = sh_count_b;
         __syncthreads();
     }
-    if (lost) { give_up(); continue; }
+    if (lost) { give_up(); return; }
 
     // the n_a kept tokens at the top-k threshold all carry the same logit, hence the same mass
     uint64_t mass_a = 0;
@@ -851,7 +838,7 @@ __global__ __launch_bounds__(ST) void sample_rows_kernel(const float *logits, in
                     target = (uint64_t)((double)top_p * (double)tot);
                     if (target < 1) target = 1;
                     if (target > tot) target = tot;
-                    if (lane == 0) { sh_total = tot; sh_target = target; }
+                    if (lane == 0) sh_target = target;
                 }
                 if (nucleus) {
                     uint64_t higher;
@@ -883,7 +870,7 @@ __global__ __launch_bounds__(ST) void sample_rows_kernel(const float *logits, in
             total_b = (use_k && key_b == key_a) ? total_a : count_b;
         }
     }
-    if (lost) { give_up(); continue; }
+    if (lost) { give_up(); return; }
     const bool all_kept = !use_k && !(top_p < 1.f);   // S is the whole vocabulary
 
     // ---- sample in token-id order.  Wave w of this workgroup owns ids [lo, hi) of the segment; lanes stride by 64. ----
@@ -904,7 +891,7 @@ __global__ __launch_bounds__(ST) void sample_rows_kernel(const float *logits, in
         uint32_t mine = 0;
         for (int w = 0; w < 16; ++w) mine += red_c[w];
         if (tid == 0) __hip_atomic_store(&cl.s->gties[cl.c], mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (!cluster_sync(cl, err)) { give_up(); continue; }
+        if (!cluster_sync(cl, err)) { give_up(); return; }
         for (int w = 0; w < cl.c; ++w) tie_base += __hip_atomic_load(&cl.s->gties[w], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     // (2) mass of S inside each wave
@@ -950,7 +937,7 @@ __global__ __launch_bounds__(ST) void sample_rows_kernel(const float *logits, in
             for (int w = 0; w < 16; ++w)
                 for (int bt = 0; bt < n_batch; ++bt) mine += sub[w][bt];
         if (tid == 0) __hip_atomic_store((unsigned long long *)&cl.s->gsub[cl.c], (unsigned long long)mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (!cluster_sync(cl, err)) { give_up(); continue; }
+        if (!cluster_sync(cl, err)) { give_up(); return; }
         for (int w = 0; w < C; ++w) {
             const uint64_t m = __hip_atomic_load((unsigned long long *)&cl.s->gsub[w], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             if (w < cl.c) wg_before += m;
@@ -1026,11 +1013,20 @@ __global__ __launch_bounds__(ST) void sample_rows_kernel(const float *logits, in
         }
         sampled[row] = t;
     }
-    __syncthreads();   // the shared words above are rewritten by the next row
-  }
+}
+
+// grid = rows * C workgroups of 1024 threads, cluster g on row g.  A cluster takes one row only: most of its workgroups are
+// done while the first still reads their scratch, which nobody may clear for another row then.
+__global__ __launch_bounds__(ST) void sample_rows_kernel(const float *logits, int V, float inv_temperature, int top_k, float top_p,
+                                                         const float *uniforms, int32_t *sampled, int C, SampleScratch *scratch,
+                                                         int32_t *err)
+{
+    const int row = blockIdx.x / C;
+    Cluster cl{C > 1 ? scratch + row : nullptr, C, (int)(blockIdx.x % C), 0u, false};
+    sample_row(cl, logits, row, V, inv_temperature, top_k, top_p, uniforms, sampled, err);
     // Leave the counters at zero for the next launch on this scratch (a cluster that gave up leaves them as
     // they are: the launcher's caller learns of it through *err and clears the scratch).
-    if (C > 1 && !cl.failed && tid == 0) {
+    if (C > 1 && !cl.failed && threadIdx.x == 0) {
         const uint32_t old = __hip_atomic_fetch_add(&cl.s->departures, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (old == (uint32_t)C - 1) {
             __hip_atomic_store(&cl.s->arrivals, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -1075,7 +1071,7 @@ hipError_t launch_sample_rows(const float *logits, int rows, int V, float temper
     if (C > 1 && !scratch_clean) {
         hipLaunchKernelGGL(sample_scratch_clear_kernel, dim3((rows + 63) / 64), dim3(64), 0, s, (SampleScratch *)scratch, rows);
     }
-    hipLaunchKernelGGL(sample_rows_kernel, dim3(rows * C), dim3(ST), 0, s, logits, rows, V, 1.f / temperature, top_k, top_p, uniforms,
+    hipLaunchKernelGGL(sample_rows_kernel, dim3(rows * C), dim3(ST), 0, s, logits, V, 1.f / temperature, top_k, top_p, uniforms,
                        sampled, C, (SampleScratch *)scratch, err);
     return hipGetLastError();
 }
