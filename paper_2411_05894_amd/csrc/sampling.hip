@@ -701,6 +701,7 @@ __device__ int short_row(ShortLds &L, Cluster &cl, const float *z, int V, int se
 }
 
 // One row, by the workgroups of a cluster (or one workgroup): the row's token to sampled[row].
+template <bool SHORT>
 __device__ __forceinline__ void sample_row(Cluster &cl, const float *logits, int row, int V, float inv_temperature, int top_k, float top_p,
                                            const float *uniforms, int32_t *sampled, int32_t *err)
 {
@@ -712,8 +713,6 @@ __device__ __forceinline__ void sample_row(Cluster &cl, const float *logits, int
     __shared__ uint64_t sh_above, sh_target;
     __shared__ int sh_wave, sh_batch, sh_token;
     __shared__ uint64_t sub[16][MAX_BATCH];   // mass of S per (wave, batch of 512 ids)
-    __shared__ ShortLds short_lds;
-
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, C = cl.C;
     // this workgroup's token ids: [seg_lo, seg_hi), whole groups of four so that 16-byte loads stay aligned
     const int seg_len = ((V + C - 1) / C + 3) & ~3;
@@ -732,10 +731,13 @@ __device__ __forceinline__ void sample_row(Cluster &cl, const float *logits, int
     }
 
     const bool vec4 = (V & 3) == 0 && (reinterpret_cast<uintptr_t>(r.z) & 15) == 0;
-    const int done = short_row(short_lds, cl, r.z, V, seg_lo, seg_len, Vs, vec4, 1.4426950408889634f * inv_temperature, top_k, top_p,
-                               uniforms[row], sampled + row, err);
-    if (done == SHORT_LOST) give_up();
-    if (done != SHORT_GENERAL) return;
+    if (SHORT) {
+        __shared__ ShortLds short_lds;
+        const int done = short_row(short_lds, cl, r.z, V, seg_lo, seg_len, Vs, vec4, 1.4426950408889634f * inv_temperature, top_k, top_p,
+                                   uniforms[row], sampled + row, err);
+        if (done == SHORT_LOST) give_up();
+        if (done != SHORT_GENERAL) return;
+    }
 
     // ---- max ----
     float mx = -INFINITY;
@@ -1017,13 +1019,14 @@ __device__ __forceinline__ void sample_row(Cluster &cl, const float *logits, int
 
 // grid = rows * C workgroups of 1024 threads, cluster g on row g.  A cluster takes one row only: most of its workgroups are
 // done while the first still reads their scratch, which nobody may clear for another row then.
+template <bool SHORT>
 __global__ __launch_bounds__(ST) void sample_rows_kernel(const float *logits, int V, float inv_temperature, int top_k, float top_p,
                                                          const float *uniforms, int32_t *sampled, int C, SampleScratch *scratch,
                                                          int32_t *err)
 {
     const int row = blockIdx.x / C;
     Cluster cl{C > 1 ? scratch + row : nullptr, C, (int)(blockIdx.x % C), 0u, false};
-    sample_row(cl, logits, row, V, inv_temperature, top_k, top_p, uniforms, sampled, err);
+    sample_row<SHORT>(cl, logits, row, V, inv_temperature, top_k, top_p, uniforms, sampled, err);
     // Leave the counters at zero for the next launch on this scratch (a cluster that gave up leaves them as
     // they are: the launcher's caller learns of it through *err and clears the scratch).
     if (C > 1 && !cl.failed && threadIdx.x == 0) {
@@ -1071,7 +1074,7 @@ hipError_t launch_sample_rows(const float *logits, int rows, int V, float temper
     if (C > 1 && !scratch_clean) {
         hipLaunchKernelGGL(sample_scratch_clear_kernel, dim3((rows + 63) / 64), dim3(64), 0, s, (SampleScratch *)scratch, rows);
     }
-    hipLaunchKernelGGL(sample_rows_kernel, dim3(rows * C), dim3(ST), 0, s, logits, V, 1.f / temperature, top_k, top_p, uniforms,
+    hipLaunchKernelGGL((top_k > SHORT_K_MAX && top_k < V ? sample_rows_kernel<false> : sample_rows_kernel<true>), dim3(rows * C), dim3(ST), 0, s, logits, V, 1.f / temperature, top_k, top_p, uniforms,
                        sampled, C, (SampleScratch *)scratch, err);
     return hipGetLastError();
 }
