@@ -136,16 +136,17 @@ __device__ __forceinline__ void for_row(const float *z, int begin, int end, int 
     }
 }
 
-// The whole row, any order: 16-byte loads (four tokens per thread and load) when the row allows it.
-template <typename F> __device__ __forceinline__ void for_whole_row(const float *z, int V, bool vec4, int tid, F body)
+// The whole row, any order: 16-byte loads (four tokens per thread and load) when the row allows it.  `more` (wave-uniform)
+// is asked before every round of loads and ends the walk.
+template <typename F, typename P> __device__ __forceinline__ void for_whole_row(const float *z, int V, bool vec4, int tid, F body, P more)
 {
     if (!vec4) {
-        for_row(z, 0, V, tid, ST, body);
+        for (int base = 0; base < V && more(); base += ST * SU) for_row(z, base, min(V, base + ST * SU), tid, ST, body);
         return;
     }
     const f32x4 *z4 = reinterpret_cast<const f32x4 *>(z);
     const int V4 = V >> 2;
-    for (int base = 0; base < V4; base += ST * SU) {
+    for (int base = 0; base < V4 && more(); base += ST * SU) {
         f32x4 zz[SU];
 #pragma unroll
         for (int u = 0; u < SU; ++u) {
@@ -159,6 +160,10 @@ template <typename F> __device__ __forceinline__ void for_whole_row(const float 
             for (int e = 0; e < 4; ++e) body(4 * i + e, zz[u][e], i < V4);
         }
     }
+}
+template <typename F> __device__ __forceinline__ void for_whole_row(const float *z, int V, bool vec4, int tid, F body)
+{
+    for_whole_row(z, V, vec4, tid, body, [] { return true; });
 }
 
 // ---- several workgroups per row ----
@@ -196,7 +201,7 @@ struct SampleScratch {                    // one per cluster; the two counters a
     uint64_t mhist[HIST_PASSES][256];
     // short path
     uint64_t fine[FINE_BINS];             // cleared when the row begins
-    uint32_t kmax[MAX_CLUSTER], bound_k[MAX_CLUSTER], bound_1[MAX_CLUSTER], count[MAX_CLUSTER];
+    uint32_t kmax[MAX_CLUSTER], kmin[MAX_CLUSTER], bound_k[MAX_CLUSTER], bound_1[MAX_CLUSTER], count[MAX_CLUSTER];
     uint64_t mass[MAX_CLUSTER];
     uint64_t sub[MAX_SUB];
     uint32_t keys[LIST_MAX], ids[LIST_MAX];   // workgroup c of C: LIST_MAX / C entries from c * LIST_MAX / C on
@@ -269,11 +274,16 @@ __device__ __forceinline__ bool merge_bins(Cluster &cl, int pass, uint32_t *chis
 //           sums the tokens above that bin per batch of 512 ids and collects the tokens inside it, whose radix select runs
 //           in LDS.
 //   neither  passes 1 and 3, every token counting as above the bin.
-// Masses, targets and ties are those of the general path, integer for integer, so the token is the same one.  A list that
-// overflows (very many equal or nearly equal logits), a top_k above SHORT_K_MAX, rows with an infinite or NaN maximum and
-// temperatures whose reciprocal overflows go to the general path.  Measured at vocabulary 128256 (before -> after): 160 rows
-// top-k 20 + top-p 0.8 212 -> 43 us, top-p 0.95 173 -> 71 us, or on nearly
-// flat logits 195 -> 87 us; 9 rows 60 -> 35 us, 46 -> 36 us and 47 -> 40 us.
+// Masses, targets and ties are those of the general path, integer for integer, so the token is the same one.  Rows whose
+// list would overflow (very many equal or nearly equal logits), rows with an infinite or NaN maximum and temperatures whose
+// reciprocal overflows go to the general path, with what is known by then (Known): the maximum, and the digits that all
+// keys in question share, which need no pass.  They are told early, since a pass more is what it would cost them: by the
+// range of the logits (pass 1), by the mass of the last bin (pass 2), or when the top-k list is full.  top_k above
+// SHORT_K_MAX is a kernel of its own, without the lists' registers.
+// Measured at vocabulary 128256, us, without lists -> with: 160 rows top-k 20 + top-p 0.8 212 -> 36, top-p 0.9 on N(0, 2)
+// 192 -> 77, neither 65 -> 46; 9 rows top-p 0.95 46 -> 30, neither 24 -> 16.  On the general path, 160 rows: top-p 0.9 on
+// equal logits 224 -> 216, on N(0, 0.1) 186 -> 188, on logits rounded to quarters 245 -> 218, top-k 50 on equal logits
+// 164 -> 102, top-k 300 167 -> 159.
 struct ShortLds {
     uint64_t fine[FINE_COPIES][FINE_BINS];
     uint32_t keys[LIST_MAX], ids[LIST_MAX];
@@ -285,6 +295,15 @@ struct ShortLds {
     uint32_t n, prefix, bound, bound1;
     int bin;
 };
+
+// The leading 8-bit digits that two keys share, at most three: into prefix; returns the first digit (3 .. 0) below them.
+__device__ __forceinline__ int common_digits(uint32_t a, uint32_t b, uint32_t &prefix)
+{
+    const uint32_t diff = a ^ b;
+    const int d = diff >> 24 ? 3 : diff >> 16 ? 2 : diff >> 8 ? 1 : 0;
+    prefix = d == 3 ? 0u : a >> (8 * (d + 1));
+    return d;
+}
 
 __device__ __forceinline__ float key_logit(uint32_t key) { return bits_f32((key & 0x80000000u) ? (key & 0x7FFFFFFFu) : ~key); }
 
@@ -382,29 +401,52 @@ __device__ __forceinline__ void kth_of_groups(ShortLds &L, int n, int rank, int 
 
 enum { SHORT_DONE = 1, SHORT_GENERAL = 0, SHORT_LOST = -1 };
 
-// One row.  zs: this workgroup's ids [seg_lo, seg_lo + Vs) of the row z.  Every workgroup of the cluster returns the same.
-__device__ int short_row(ShortLds &L, Cluster &cl, const float *z, int V, int seg_lo, int seg_len, int Vs, bool vec4, float scale, int top_k,
-                         float top_p, float uniform, int32_t *out, int32_t *err)
+// What the short path found out about a row that it leaves to the general path.
+struct Known {
+    uint32_t kmax = 0;             // key of the maximum, if it is finite; else 0
+    uint32_t bound = 0;            // top-k: a lower bound of the selection's last key; 0: none
+    int bin = -1;                  // top-p without top-k: the bin of the nucleus' last token, with
+    uint64_t above = 0, target = 0;   // the mass above that bin and the nucleus' mass
+};
+
+// Bin of a token that has any mass: 1/16 octave of weight, 0 at the maximum, below 497 (weights above 2^-31).
+__device__ __forceinline__ int fine_bin(const RowCtx &r, float x) { return (int)((r.mx - x) * r.scale * 16.f); }
+
+// One row.  zs: this workgroup's ids [seg_lo, seg_lo + Vs) of the row z; top_k at most SHORT_K_MAX.  Every workgroup of the
+// cluster returns the same.
+__device__ __forceinline__ int short_row(ShortLds &L, Cluster &cl, const float *z, int V, int seg_lo, int seg_len, int Vs, bool vec4, float scale, int top_k,
+                         float top_p, float uniform, int32_t *out, int32_t *err, Known &known)
 {
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const bool use_k = top_k > 0 && top_k < V, nucleus = top_p < 1.f;
-    if (use_k && top_k > SHORT_K_MAX) return SHORT_GENERAL;
     const float *zs = z + seg_lo;
 
-    // ---- pass 1: the maximum, and (top-k) maxima per group of threads ----
-    uint32_t kmax = 0;
-    for_whole_row(zs, Vs, vec4, tid, [&](int, float x, bool ok) { if (ok) kmax = max(kmax, order_key(x)); });
+    // ---- pass 1: the maximum, (top-k) maxima per group of threads, (top-p) the minimum ----
+    uint32_t kmax = 0, kmin = 0xFFFFFFFFu;
+    if (use_k || !nucleus)
+        for_whole_row(zs, Vs, vec4, tid, [&](int, float x, bool ok) { if (ok) kmax = max(kmax, order_key(x)); });
+    else
+        for_whole_row(zs, Vs, vec4, tid, [&](int, float x, bool ok) {
+            if (ok) { kmax = max(kmax, order_key(x)); kmin = min(kmin, order_key(x)); }
+        });
     L.gmax[tid] = kmax;
     if (tid == 0) L.n = 0;
     if (!use_k && nucleus)
         for (int i = tid; i < FINE_COPIES * FINE_BINS; i += ST) (&L.fine[0][0])[i] = 0;
 #pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) kmax = max(kmax, (uint32_t)__shfl_xor((int)kmax, off));
-    if (lane == 0) L.red[wave] = kmax;
+    for (int off = 32; off >= 1; off >>= 1) {
+        kmax = max(kmax, (uint32_t)__shfl_xor((int)kmax, off));
+        kmin = min(kmin, (uint32_t)__shfl_xor((int)kmin, off));
+    }
+    if (lane == 0) L.red[wave] = (uint64_t)kmin << 32 | kmax;
     __syncthreads();
     kmax = (uint32_t)L.red[lane & 15];
+    kmin = (uint32_t)(L.red[lane & 15] >> 32);
 #pragma unroll
-    for (int off = 8; off >= 1; off >>= 1) kmax = max(kmax, (uint32_t)__shfl_xor((int)kmax, off));
+    for (int off = 8; off >= 1; off >>= 1) {
+        kmax = max(kmax, (uint32_t)__shfl_xor((int)kmax, off));
+        kmin = min(kmin, (uint32_t)__shfl_xor((int)kmin, off));
+    }
     uint32_t bound = 0;
     if (use_k) {
         int groups = ST;
@@ -421,16 +463,18 @@ __device__ int short_row(ShortLds &L, Cluster &cl, const float *z, int V, int se
         if (cl.C > 1 && tid == 0) { dev_store(&cl.s->bound_k[cl.c], bound); dev_store(&cl.s->bound_1[cl.c], L.bound1); }
     }
     if (cl.C > 1) {
-        if (tid == 0) dev_store(&cl.s->kmax[cl.c], kmax);
+        if (tid == 0) { dev_store(&cl.s->kmax[cl.c], kmax); dev_store(&cl.s->kmin[cl.c], kmin); }
         if (!cluster_sync(cl, err)) return SHORT_LOST;
         uint32_t lo1 = 0xFFFFFFFFu;
         if (lane < cl.C) {
             kmax = dev_load(&cl.s->kmax[lane]);
+            kmin = dev_load(&cl.s->kmin[lane]);
             if (use_k) { bound = dev_load(&cl.s->bound_k[lane]); lo1 = dev_load(&cl.s->bound_1[lane]); }
         }
 #pragma unroll
         for (int off = 32; off >= 1; off >>= 1) {
             kmax = max(kmax, (uint32_t)__shfl_xor((int)kmax, off));
+            kmin = min(kmin, (uint32_t)__shfl_xor((int)kmin, off));
             bound = max(bound, (uint32_t)__shfl_xor((int)bound, off));
             lo1 = min(lo1, (uint32_t)__shfl_xor((int)lo1, off));
         }
@@ -440,13 +484,15 @@ __device__ int short_row(ShortLds &L, Cluster &cl, const float *z, int V, int se
     // then exp2(0 * inf), no token has any mass, and the general path answers with the arg-max
     if (kmax >= 0xFF800000u || kmax <= 0x007FFFFFu || scale == INFINITY) return SHORT_GENERAL;
     RowCtx r{z, V, key_logit(kmax), scale};
+    known.kmax = kmax;
+    known.bound = bound;
 
     if (use_k) {
         // ---- pass 2: the tokens at or above the bound; the first workgroup does the rest ----
         for_whole_row(zs, Vs, vec4, tid, [&](int i, float x, bool ok) {
             const uint32_t key = order_key(x);
             list_push(L, ok && key >= bound, key, seg_lo + i, lane);
-        });
+        }, [&] { return __builtin_amdgcn_readfirstlane(*(volatile uint32_t *)&L.n) <= LIST_K_MAX; });
         list_publish(L, cl, tid);
         if (cl.C > 1) { if (!cluster_sync(cl, err)) return SHORT_LOST; }
         else __syncthreads();
@@ -502,13 +548,13 @@ __device__ int short_row(ShortLds &L, Cluster &cl, const float *z, int V, int se
     int bin = 0x7FFFFFFF;   // no nucleus: every token counts as above the bin, and the list stays empty
     uint64_t target = 0;
     if (nucleus) {
+        // So many tokens on so few bins that the last one's list would overflow: a quarter of LIST_MAX per bin on average
+        // are LIST_MAX in the middle of a normal distribution.
+        if ((float)V > ((r.mx - key_logit(kmin)) * r.scale * 16.f + 1.f) * (LIST_MAX / 4)) return SHORT_GENERAL;
         uint64_t sum = 0;
         for_whole_row(zs, Vs, vec4, tid, [&](int, float x, bool ok) {
             const uint64_t m = ok ? fix_mass(r, x) : 0;
-            if (m) {   // weight above 2^-31: the bin number is below 497
-                const int b = (int)((r.mx - x) * r.scale * 16.f);
-                atomicAdd((unsigned long long *)&L.fine[lane & (FINE_COPIES - 1)][b], (unsigned long long)m);
-            }
+            if (m) atomicAdd((unsigned long long *)&L.fine[lane & (FINE_COPIES - 1)][fine_bin(r, x)], (unsigned long long)m);
             sum += m;
         });
         sum = wave_sum(sum);
@@ -554,6 +600,11 @@ __device__ int short_row(ShortLds &L, Cluster &cl, const float *z, int V, int se
         }
         __syncthreads();
         bin = L.bin;
+        known.bin = bin;
+        known.above = L.above;
+        known.target = target;
+        // at least so many tokens: none of the bin's weights is above exp2(-bin / 16)
+        if ((float)L.fine[0][bin] > (LIST_MAX * 1.001f) * 2147483648.f * __builtin_amdgcn_exp2f(bin * -0.0625f)) return SHORT_GENERAL;
     }
 
     // ---- pass 3: sums per batch of the tokens above the bin, and the bin's own tokens ----
@@ -563,7 +614,7 @@ __device__ int short_row(ShortLds &L, Cluster &cl, const float *z, int V, int se
     const int lo = min(Vs, wave * per), hi = min(Vs, lo + per);
     auto visit = [&](int i, float x, bool ok) -> uint64_t {
         const uint64_t m = ok ? fix_mass(r, x) : 0;
-        const int b = (int)((r.mx - x) * r.scale * 16.f);
+        const int b = fine_bin(r, x);
         list_push(L, m != 0 && b == bin, order_key(x), seg_lo + i, lane);
         return m != 0 && b < bin ? m : 0;
     };
@@ -731,28 +782,32 @@ __device__ __forceinline__ void sample_row(Cluster &cl, const float *logits, int
     }
 
     const bool vec4 = (V & 3) == 0 && (reinterpret_cast<uintptr_t>(r.z) & 15) == 0;
+    Known known;
     if (SHORT) {
         __shared__ ShortLds short_lds;
         const int done = short_row(short_lds, cl, r.z, V, seg_lo, seg_len, Vs, vec4, 1.4426950408889634f * inv_temperature, top_k, top_p,
-                                   uniforms[row], sampled + row, err);
+                                   uniforms[row], sampled + row, err, known);
         if (done == SHORT_LOST) give_up();
         if (done != SHORT_GENERAL) return;
     }
 
     // ---- max ----
-    float mx = -INFINITY;
-    for_whole_row(zs, Vs, vec4, tid, [&](int, float z, bool ok) { if (ok) mx = fmaxf(mx, z); });
+    float mx = key_logit(known.kmax);
+    if (!SHORT || !known.kmax) {
+        mx = -INFINITY;
+        for_whole_row(zs, Vs, vec4, tid, [&](int, float z, bool ok) { if (ok) mx = fmaxf(mx, z); });
 #pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
-    if (lane == 0) red_f[wave] = mx;
-    __syncthreads();
-    mx = red_f[0];
-    for (int w = 1; w < 16; ++w) mx = fmaxf(mx, red_f[w]);
-    __syncthreads();
-    if (C > 1) {
-        if (tid == 0) __hip_atomic_store(&cl.s->gmax[cl.c], mx, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (!cluster_sync(cl, err)) { give_up(); return; }
-        for (int w = 0; w < C; ++w) mx = fmaxf(mx, __hip_atomic_load(&cl.s->gmax[w], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+        for (int off = 32; off >= 1; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
+        if (lane == 0) red_f[wave] = mx;
+        __syncthreads();
+        mx = red_f[0];
+        for (int w = 1; w < 16; ++w) mx = fmaxf(mx, red_f[w]);
+        __syncthreads();
+        if (C > 1) {
+            if (tid == 0) __hip_atomic_store(&cl.s->gmax[cl.c], mx, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (!cluster_sync(cl, err)) { give_up(); return; }
+            for (int w = 0; w < C; ++w) mx = fmaxf(mx, __hip_atomic_load(&cl.s->gmax[w], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+        }
     }
     r.mx = mx;
     r.scale = 1.4426950408889634f * inv_temperature;
@@ -763,7 +818,9 @@ __device__ __forceinline__ void sample_row(Cluster &cl, const float *logits, int
     bool lost = false;
     if (use_k) {
         uint32_t prefix = 0, need = (uint32_t)top_k;
-        for (int d = 3; d >= 0 && !lost; --d) {
+        int first = 3;   // leading digits that every key from the bound to the maximum has are known
+        if (SHORT && known.bound) first = common_digits(known.bound, known.kmax, prefix);
+        for (int d = first; d >= 0 && !lost; --d) {
             if (tid < 256) chist[tid] = 0;
             __syncthreads();
             BinRun run{0, 0, 0, false};
@@ -809,18 +866,32 @@ __device__ __forceinline__ void sample_row(Cluster &cl, const float *logits, int
     uint32_t total_b = total_a;   // tokens of the row with key == key_b
     {
         const bool nucleus = top_p < 1.f;
-        uint64_t target = 0, above = 0;
+        const bool in_bin = SHORT && known.bin >= 0;   // only the tokens of one bin are left to look through
+        uint64_t target = in_bin ? known.target : 0, above = in_bin ? known.above : 0;
         uint32_t prefix = 0;
-        for (int d = 3; nucleus && d >= 0 && !lost; --d) {
+        int first = 3;
+        if (in_bin) {
+            // logits of the bin, a hundredth of a bin and a few units of rounding wider than it is
+            const float width = 1.f / (16.f * r.scale), slack = fabsf(r.mx) * 1e-6f;
+            const float low = r.mx - ((float)known.bin + 1.01f) * width - slack, high = r.mx - ((float)known.bin - 0.01f) * width + slack;
+            if (low > -INFINITY && high < INFINITY) first = common_digits(order_key(low), order_key(high), prefix);
+        } else if (SHORT && use_k && known.kmax) {
+            first = common_digits(key_a, known.kmax, prefix);
+        }
+        for (int d = first; nucleus && d >= 0 && !lost; --d) {
             if (tid < 256) { mhist[tid] = 0; chist[tid] = 0; }
             __syncthreads();
             BinRun run{0, 0, 0, false};
             uint32_t *cbins = d == 0 ? chist : nullptr;   // counts matter only for the exact key (the ties at key_b)
-            for_whole_row(zs, Vs, vec4, tid, [&](int, float z, bool ok) {
-                const uint32_t key = order_key(z);
-                if (ok && (!use_k || key > key_a) && (d == 3 || (key >> (8 * (d + 1))) == prefix))
-                    run_add(run, (key >> (8 * d)) & 255u, fix_mass(r, z), cbins, mhist);
-            });
+            auto look = [&](auto &&mass_of) {
+                for_whole_row(zs, Vs, vec4, tid, [&](int, float z, bool ok) {
+                    const uint32_t key = order_key(z);
+                    if (ok && (!use_k || key > key_a) && (d == 3 || (key >> (8 * (d + 1))) == prefix))
+                        run_add(run, (key >> (8 * d)) & 255u, mass_of(z), cbins, mhist);
+                });
+            };
+            if (in_bin) look([&](float z) { return fine_bin(r, z) == known.bin ? fix_mass(r, z) : 0ull; });
+            else look([&](float z) { return fix_mass(r, z); });
             run_flush(run, cbins, mhist);
             // the kept tokens at the top-k threshold are added once per row, by the cluster's first workgroup
             if (tid == 0 && cl.c == 0 && use_k && (d == 3 || (key_a >> (8 * (d + 1))) == prefix)) {
@@ -831,7 +902,7 @@ __device__ __forceinline__ void sample_row(Cluster &cl, const float *logits, int
             __syncthreads();
             if (!merge_bins(cl, 4 + (3 - d), chist, mhist, d == 0, true, tid, err)) { lost = true; break; }
             if (wave == 0) {
-                if (d == 3) {   // Z_k = the sum of all bins; the nucleus target follows from it
+                if (d == first && !in_bin) {   // Z_k = the sum of all bins; the nucleus target follows from it
                     uint64_t tot = 0;
 #pragma unroll
                     for (int e = 0; e < 4; ++e) tot += mhist[4 * lane + e];
@@ -853,7 +924,7 @@ __device__ __forceinline__ void sample_row(Cluster &cl, const float *logits, int
                 }
             }
             __syncthreads();
-            target = sh_target;
+            if (!in_bin) target = sh_target;
             if (nucleus) {
                 prefix = sh_prefix;
                 above = sh_above;

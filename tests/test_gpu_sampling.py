@@ -246,3 +246,27 @@ def test_temperatures_without_any_mass_give_the_argmax(V, rows, T):
         assert sv.lib().sssd_op_sample(*at, one.data_ptr(), None) == 0
         assert sv.lib().sssd_op_sample_wide(*at, wide.data_ptr(), scratch.data_ptr() if need else None, need, None) == 0
         assert torch.equal(one, z.argmax(-1).to(torch.int32)) and torch.equal(wide, one)
+
+
+@pytest.mark.parametrize("V,rows", [(128256, 3), (32003, 130)])    # clusters of 16 and of one; rows of 16-byte loads and not
+@pytest.mark.parametrize("kind", ["equal", "narrow", "narrow_high", "narrow_low", "quarters", "two_values"])
+def test_rows_that_the_lists_leave_to_the_general_path(V, rows, kind):
+    """The general path starts from what the lists' passes found: the maximum, the digits that the keys between a bound and
+    the maximum or within one bin share, the mass above that bin.  Logits whose keys share one to three digits or none, ties
+    cut by either selection; every token against the sort that the definition states."""
+    z = (normal_bf16(131, V, (rows, V), 1.0).float() + 2.0 ** -9 * normal_bf16(132, V, (rows, V), 1.0).float())
+    z = {"equal": torch.full_like(z, 1.7), "narrow": z * 0.1, "narrow_high": z * 0.05 + 900.0, "narrow_low": z * 0.02 - 37.0,
+         "quarters": (z * 8).round() / 4, "two_values": (z > 0).float() * 3 - 1}[kind].contiguous()
+    u = uniforms(133, rows)
+    checked = 0
+    for T, k, p in ((1.0, 0, 0.9), (1.0, 0, 0.3), (0.3, 0, 0.99), (1.0, 50, 1.0), (1.0, 256, 0.9), (1.0, 257, 0.9)):
+        params = sv.SamplingParams(T, k, p)
+        say(f"{kind} V={V} rows={rows} T={T} top_k={k} top_p={p}")
+        n = min(rows, 3)                                            # the oracle sorts the whole row on the host
+        checked += check_rows(z[:n].contiguous(), params, u[:n].contiguous(), 0)[0]
+        one = sv.sssd_op_sample(z.to(DEV), params, u.to(DEV))
+        assert torch.equal(one, sv.sssd_op_sample_wide(z.to(DEV), params, u.to(DEV)))
+        if k:                                                       # order O on the host: by logit, then by id
+            order = torch.sort(z[0], descending=True, stable=True).indices[:k]
+            assert int(one[0]) in set(order.tolist())
+    assert checked >= 10    # of 18; a flat distribution over 128256 tokens has steps of 8e-6, so several rows lie within the exemption
