@@ -446,10 +446,19 @@ __device__ __forceinline__ const u32x4 *tile_weights_seg(const FusedGemmArgs &a,
 // loads then, not streaming ones).  There the matrix pipes bound everything and two waves share 64 columns, each on half
 // of the rows: half the operand reads per MFMA for a second fetch of the weights from the die's L2 (8B gate/up at 512 rows
 // 235 -> 220 us, but 84 -> 100 us at 160 rows, which are still bound by what a compute unit can fetch).
+template <int MT16, int QW, bool BLOCKS> struct QShape {
+    static constexpr int QDW = BLOCKS ? 3 : 4;                  // k-tiles in flight
+    static constexpr int TILES = MT16 * 2;                      // activation tiles (hi and lo) of one k-tile
+    static constexpr int APT = (TILES + QW - 1) / QW;           // tiles staged per wave; surplus waves fill the padding of the ring
+    static constexpr int SLOT = APT * QW * 64;                  // records of a ring slot
+};
+
+// Rows 16 * tile0 .. 16 * (tile0 + MT16) - 1; gj: column group and slice.  ring: QDW slots.
 template <int MT16, int QW, bool BLOCKS>
-__global__ __launch_bounds__(QW * 64) __attribute__((amdgpu_waves_per_eu(MT16 <= 2 ? 4 : 1))) void qgemm16_kernel(FusedGemmArgs a, int RB, int NT16)
+__device__ __forceinline__ void qgemm16_rows(const FusedGemmArgs &a, int NT16, int tile0, int gj, u32x4 (*ring)[QShape<MT16, QW, BLOCKS>::SLOT])
 {
-    constexpr int QDW = BLOCKS ? 3 : 4;           // k-tiles in flight
+    using S = QShape<MT16, QW, BLOCKS>;
+    constexpr int QDW = S::QDW, TILES = S::TILES, APT = S::APT;
     constexpr bool TWO = BLOCKS || MT16 <= 3;     // sums in two levels, where the registers allow it
     constexpr bool COMP = !BLOCKS && MT16 <= 2;   // ... the upper one compensated
     constexpr int RH = BLOCKS ? 2 : 1;       // waves that share a column group, each on its part of the rows
@@ -457,28 +466,13 @@ __global__ __launch_bounds__(QW * 64) __attribute__((amdgpu_waves_per_eu(MT16 <=
     constexpr int CW = QW / RH;                   // column groups per workgroup
     constexpr int NC = 2 * RH;                    // 16-column tiles per wave
     constexpr int MTW = MT16 / RH;                // row tiles per wave
-    constexpr int TILES = MT16 * 2;               // activation tiles (hi and lo) of one k-tile
-    constexpr int APT = (TILES + QW - 1) / QW;    // tiles staged per wave; surplus waves fill the padding of the ring
     constexpr int RECS = 2 * MTW;                 // operand tiles every wave reads per k-tile
     constexpr int AHEAD = (RECS - 1) / 2 < 6 ? (RECS - 1) / 2 : 6;   // of them read before their use
     constexpr int BAR = RECS - AHEAD;             // the first read of the next k-tile
     constexpr int PUT = BAR - AHEAD - 1;          // chunk stores: at least AHEAD reads lie between them and the barrier
-    __shared__ u32x4 ring[QDW][APT * QW * 64];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int half = wave / CW, cg = wave % CW;
-    int gj = blockIdx.x, rb = 0;
-    if (BLOCKS) {
-        const int n = gridDim.x / RB, whole = n & ~7;     // (column group, slice) pairs; those in full sets of 8
-        if ((int)blockIdx.x < whole * RB) {
-            rb = (blockIdx.x >> 3) % RB;
-            gj = (blockIdx.x >> 3) / RB * 8 + (blockIdx.x & 7);
-        } else {
-            const int x = blockIdx.x - whole * RB;
-            rb = x / (n - whole);
-            gj = whole + x % (n - whole);
-        }
-    }
-    const int m_base = rb * MT16 * 16;
+    const int m_base = tile0 * 16;
     const int J = a.J, j = gj % J, grp = gj / J;
     const int KT = a.KT;
     const int kps = a.kps;
@@ -498,7 +492,7 @@ __global__ __launch_bounds__(QW * 64) __attribute__((amdgpu_waves_per_eu(MT16 <=
     for (int i = 0; i < APT; ++i) {
         int t = wave + i * QW;                    // row tile t / 2, part t % 2 (0: hi, 1: lo)
         if (t >= TILES) t = TILES - 1;
-        int rt = rb * MT16 + (t >> 1);
+        int rt = tile0 + (t >> 1);
         if (rt >= a.part_rows >> 4) rt = (a.part_rows >> 4) - 1;   // past the rows: never stored
         asrc[i] = ((t & 1) ? a.A_lo : a.A_hi) + (size_t)rt * KT * 64 + lane;
     }
@@ -624,8 +618,48 @@ __global__ __launch_bounds__(QW * 64) __attribute__((amdgpu_waves_per_eu(MT16 <=
     }
 }
 
-// Row blocks of a launch: one of up to ten tiles, more of up to eight (the sums in two levels leave no registers for more).
-__host__ int row_blocks(int mt16) { return mt16 <= 10 ? 1 : (mt16 + 7) / 8; }
+// BLOCKS: RB blocks of rows, of MT16 tiles, or (MT16 = 0) the first n8 of eight tiles and the others of six.  Blocks of one
+// size have kernels of their own: in the mixed one they are 2 % slower.
+template <int MT16, int QW, bool BLOCKS>
+__global__ __launch_bounds__(QW * 64) __attribute__((amdgpu_waves_per_eu(!BLOCKS && MT16 <= 2 ? 4 : 1))) void qgemm16_kernel(FusedGemmArgs a, int RB, int n8, int NT16)
+{
+    if constexpr (BLOCKS) {
+        using S = QShape<MT16 ? MT16 : 8, QW, true>;
+        static_assert(QShape<6, QW, true>::SLOT == QShape<8, QW, true>::SLOT);
+        __shared__ u32x4 ring[S::QDW][S::SLOT];
+        int gj, rb;
+        const int n = gridDim.x / RB, whole = n & ~7;     // (column group, slice) pairs; those in full sets of 8
+        if ((int)blockIdx.x < whole * RB) {
+            rb = (blockIdx.x >> 3) % RB;
+            gj = (blockIdx.x >> 3) / RB * 8 + (blockIdx.x & 7);
+        } else {
+            const int x = blockIdx.x - whole * RB;
+            rb = x / (n - whole);
+            gj = whole + x % (n - whole);
+        }
+        if constexpr (MT16 != 0) qgemm16_rows<MT16, QW, true>(a, NT16, MT16 * rb, gj, ring);
+        else if (rb < n8) qgemm16_rows<8, QW, true>(a, NT16, 8 * rb, gj, ring);
+        else qgemm16_rows<6, QW, true>(a, NT16, 8 * n8 + 6 * (rb - n8), gj, ring);
+    } else {
+        using S = QShape<MT16, QW, false>;
+        __shared__ u32x4 ring[S::QDW][S::SLOT];
+        qgemm16_rows<MT16, QW, false>(a, NT16, 0, blockIdx.x, ring);
+    }
+}
+
+// Row blocks of a launch: one of up to ten tiles, more of eight (the sums in two levels leave no registers for more), as many
+// of them of six as the rows allow: 20 tiles are 8 + 6 + 6, not three of eight.  Three of eight / 8 + 6 + 6 / two passes of
+// ten with sums in one level, us: 320 rows 8B gate/up 180 / 171 / 164, 70B gate/up 618 / 582 / 563, down 312 / 291 / 298; 400
+// rows (four of eight / 8 + 6 + 6 + 6) 70B gate/up 794 / 744 / 732, LM head of 128256 924 / 850 / 906.
+struct RowBlocks {
+    int RB, n8;   // blocks, those of eight tiles
+};
+__host__ RowBlocks row_blocks(int mt16)
+{
+    if (mt16 <= 10) return RowBlocks{1, 0};
+    const int RB = (mt16 + 7) / 8, spare = (8 * RB - mt16) / 2;
+    return RowBlocks{RB, RB - (spare < RB ? spare : RB)};
+}
 
 struct QPlan {
     int groups, J, kps;   // column groups, K slices (none empty), k-tiles per slice
@@ -671,7 +705,10 @@ __host__ QPlan q_plan(int Ntot, int K, int M)
         // 290 / 301 / 315 / 324 / 385 / 451, down 322 / 174 / 133 / 109 / 142 / 122 (four passes of up to 160 rows took 126,
         // 101, 294 + 30 and 190 + 19 us).  No split needs more than SPLIT_BYTES of partial sums unless the rule above did.
         constexpr size_t SPLIT_BYTES = (size_t)32 << 20;
-        const int was = best, mt16 = (M + 15) / 16, RB = row_blocks(mt16), mt = (mt16 + RB - 1) / RB <= 6 ? 6 : 8;
+        const int was = best, mt16 = (M + 15) / 16;
+        const RowBlocks rows = row_blocks(mt16);
+        const int RB = rows.RB;
+        const double mt = (8.0 * rows.n8 + 6.0 * (RB - rows.n8)) / RB;
         p.qw = 8;
         p.groups = (NT32 + p.qw - 1) / p.qw;
         double least = 0.0;
@@ -720,20 +757,21 @@ template <int EPI> hipError_t launch_large(FusedGemmArgs &a, hipStream_t s, bool
     else if (EPI == FEPI_SWIGLU) { a.seg0 = a.NT; a.seg1 = a.NT; }
     else { a.seg0 = NT16; a.seg1 = 0; }
     if ((size_t)a.J * a.part_rows * a.Ntot * sizeof(float) > a.partial_bytes) return hipErrorInvalidValue;
-    const int mt16 = (a.M + 15) / 16, RB = row_blocks(mt16);
-    const dim3 grid(p.groups * a.J * RB), block(p.qw * 64);
-#define SSSD_Q16LAUNCH(MT, QW, BLOCKS) hipExtLaunchKernelGGL((qgemm16_kernel<MT, QW, BLOCKS>), grid, block, 0, s, t0, t1, 0, a, RB, NT16)
+    const int mt16 = (a.M + 15) / 16;
+    const RowBlocks rows = row_blocks(mt16);
+    const dim3 grid(p.groups * a.J * rows.RB), block(p.qw * 64);
+#define SSSD_Q16LAUNCH(MT, QW, BLOCKS) hipExtLaunchKernelGGL((qgemm16_kernel<MT, QW, BLOCKS>), grid, block, 0, s, t0, t1, 0, a, rows.RB, rows.n8, NT16)
 #define SSSD_Q16ROWS(MT)                                  \
     do {                                                  \
         if (p.qw == 8) SSSD_Q16LAUNCH(MT, 8, false);      \
         else SSSD_Q16LAUNCH(MT, 4, false);                \
     } while (0)
-    const int mt = (mt16 + RB - 1) / RB;
-    if (RB > 1) {   // six or eight tiles per block: two halves of the rows
-        if (mt <= 6) SSSD_Q16LAUNCH(6, 8, true);
-        else SSSD_Q16LAUNCH(8, 8, true);
+    if (rows.RB > 1) {
+        if (rows.n8 == 0) SSSD_Q16LAUNCH(6, 8, true);
+        else if (rows.n8 == rows.RB) SSSD_Q16LAUNCH(8, 8, true);
+        else SSSD_Q16LAUNCH(0, 8, true);
     } else {
-        switch (mt) {
+        switch (mt16) {
         case 1:   // the second row tile is padding, computed and not stored
         case 2: SSSD_Q16ROWS(2); break;
         case 3: SSSD_Q16ROWS(3); break;
