@@ -449,13 +449,13 @@ __device__ __forceinline__ const u32x4 *tile_weights_seg(const FusedGemmArgs &a,
 template <int MT16, int QW, bool BLOCKS> struct QShape {
     static constexpr int QDW = BLOCKS ? 3 : 4;                  // k-tiles in flight
     static constexpr int TILES = MT16 * 2;                      // activation tiles (hi and lo) of one k-tile
-    static constexpr int APT = (TILES + QW - 1) / QW;           // tiles staged per wave; surplus waves fill the padding of the ring
-    static constexpr int SLOT = APT * QW * 64;                  // records of a ring slot
+    static constexpr int APT = (TILES + QW - 1) / QW;           // tiles fetched per wave; surplus waves re-read the last one
+    static constexpr int SLOT = TILES * 64;                     // records of a ring slot
 };
 
 // Rows 16 * tile0 .. 16 * (tile0 + MT16) - 1; gj: column group and slice.  ring: QDW slots.
 template <int MT16, int QW, bool BLOCKS>
-__device__ __forceinline__ void qgemm16_rows(const FusedGemmArgs &a, int NT16, int tile0, int gj, u32x4 (*ring)[QShape<MT16, QW, BLOCKS>::SLOT])
+__device__ __forceinline__ void qgemm16_rows(const FusedGemmArgs a, int NT16, int tile0, int gj, u32x4 (*ring)[QShape<MT16, QW, BLOCKS>::SLOT])
 {
     using S = QShape<MT16, QW, BLOCKS>;
     constexpr int QDW = S::QDW, TILES = S::TILES, APT = S::APT;
@@ -515,7 +515,8 @@ __device__ __forceinline__ void qgemm16_rows(const FusedGemmArgs &a, int NT16, i
     };
     auto stage = [&](int u) {
 #pragma unroll
-        for (int i = 0; i < APT; ++i) ring[u][(wave + i * QW) * 64 + lane] = apre[u][i];
+        for (int i = 0; i < APT; ++i)   // without the padding: at nine tiles and eight waves a quarter of the stores
+            if (TILES % QW == 0 || i < APT - 1 || wave + i * QW < TILES) ring[u][(wave + i * QW) * 64 + lane] = apre[u][i];
     };
 #pragma unroll
     for (int u = 0; u < QDW; ++u) {
@@ -621,25 +622,21 @@ __device__ __forceinline__ void qgemm16_rows(const FusedGemmArgs &a, int NT16, i
 // BLOCKS: RB blocks of rows, of MT16 tiles, or (MT16 = 0) the first n8 of eight tiles and the others of six.  Blocks of one
 // size have kernels of their own: in the mixed one they are 2 % slower.
 template <int MT16, int QW, bool BLOCKS>
-__global__ __launch_bounds__(QW * 64) __attribute__((amdgpu_waves_per_eu(!BLOCKS && MT16 <= 2 ? 4 : 1))) void qgemm16_kernel(FusedGemmArgs a, int RB, int n8, int NT16)
+// Registers: two workgroups of four waves per compute unit up to nine tiles (tiny shape with a vocabulary of 128256, 144 rows:
+// 276 registers and one workgroup 69 us, 256 and two 66), four waves per SIMD up to two tiles.
+__global__ __launch_bounds__(QW * 64) __attribute__((amdgpu_waves_per_eu(!BLOCKS && MT16 <= 2 ? 4 : (QW == 4 && MT16 <= 9 ? 2 : 1)))) void qgemm16_kernel(FusedGemmArgs a, int RB, int n8, int NT16)
 {
     if constexpr (BLOCKS) {
         using S = QShape<MT16 ? MT16 : 8, QW, true>;
-        static_assert(QShape<6, QW, true>::SLOT == QShape<8, QW, true>::SLOT);
         __shared__ u32x4 ring[S::QDW][S::SLOT];
-        int gj, rb;
-        const int n = gridDim.x / RB, whole = n & ~7;     // (column group, slice) pairs; those in full sets of 8
-        if ((int)blockIdx.x < whole * RB) {
-            rb = (blockIdx.x >> 3) % RB;
-            gj = (blockIdx.x >> 3) / RB * 8 + (blockIdx.x & 7);
-        } else {
-            const int x = blockIdx.x - whole * RB;
-            rb = x / (n - whole);
-            gj = whole + x % (n - whole);
-        }
+        const int bid = blockIdx.x, n = gridDim.x / RB, whole = n & ~7;   // (column group, slice) pairs; those in full sets of 8
+        const bool in_set = bid < whole * RB;
+        const int x = in_set ? bid >> 3 : bid - whole * RB, by = in_set ? RB : n - whole;
+        const int q = x / by, r = x - q * by;
+        const int rb = in_set ? r : q, gj = in_set ? q * 8 + (bid & 7) : whole + r;
         if constexpr (MT16 != 0) qgemm16_rows<MT16, QW, true>(a, NT16, MT16 * rb, gj, ring);
         else if (rb < n8) qgemm16_rows<8, QW, true>(a, NT16, 8 * rb, gj, ring);
-        else qgemm16_rows<6, QW, true>(a, NT16, 8 * n8 + 6 * (rb - n8), gj, ring);
+        else qgemm16_rows<6, QW, true>(a, NT16, 8 * n8 + 6 * (rb - n8), gj, reinterpret_cast<u32x4 (*)[QShape<6, QW, true>::SLOT]>(ring));
     } else {
         using S = QShape<MT16, QW, false>;
         __shared__ u32x4 ring[S::QDW][S::SLOT];
