@@ -26,7 +26,8 @@ struct Buffers {
     int *part_idx;
     int32_t *pos_base, *err_flag, *that_dbg, *rope_pos;
     int *tail_count;   // TAIL_SLOTS split-K arrival counters, zero between launches
-    AttnCut *cut;
+    AttnSeq *seq;
+    int32_t *segments;
     uint32_t *anc;
     float *rope_cs, *ssq1;
     uint8_t *staging;
@@ -140,7 +141,8 @@ size_t layout(const Dims &D, Sizes &S, Buffers *B, uint8_t *base)
     b.part_val = (float *)take((size_t)S.m_alloc * NTv * 4);
     b.part_idx = (int *)take((size_t)S.m_alloc * NTv * 4);
     b.pos_base = (int32_t *)take((size_t)D.max_batch * 4);
-    b.cut = (AttnCut *)take((size_t)D.max_batch * sizeof(AttnCut));
+    b.seq = (AttnSeq *)take((size_t)D.max_batch * sizeof(AttnSeq));
+    b.segments = (int32_t *)take((size_t)D.max_batch * 4);
     b.rope_pos = (int32_t *)take((size_t)S.m_alloc * 4);
     b.anc = (uint32_t *)take((size_t)S.m_alloc * 4);
     b.err_flag = (int32_t *)take(4);
@@ -466,7 +468,7 @@ int run_step(sssd_ctx *c, int32_t B, int32_t k, const int32_t *tokens, const int
     {
         Prof p(c, s, SSSD_PROF_ELEM);
         HIP_TRY(launch_fused_embed(D, io, kv_geom(c), c->embed, c->layers[0].attn_norm, W.X, W.Ah_hi, W.Ah_lo, W.ssq1, W.pos_base,
-                                   W.cut, W.rope_pos, W.anc, W.err_flag, s));
+                                   W.seq, W.segments, W.rope_pos, W.anc, W.err_flag, s));
     }
     FusedGemmArgs f{};
     f.M = M; f.h = D.h; f.d = D.d; f.nq = D.nq; f.nkv = D.nkv; f.seq_pad = D.seq_pad; f.k = k;
@@ -527,7 +529,7 @@ int run_step(sssd_ctx *c, int32_t B, int32_t k, const int32_t *tokens, const int
     for (int l = 0; l < D.L; ++l) {
         uint16_t *Kl = c->Kc + (size_t)l * c->S.kv_layer_elems, *Vl = c->Vc + (size_t)l * c->S.kv_layer_elems;
         {
-            AttnArgs a{W.Qp, W.Qp_lo, Kl, Vl, kv_geom(c), W.pos_base, W.cut, W.anc, W.part_o, W.part_ml, W.Aq_hi, W.Aq_lo, B, k, {}, 0};
+            AttnArgs a{W.Qp, W.Qp_lo, Kl, Vl, kv_geom(c), W.seq, W.segments, W.anc, W.part_o, W.part_ml, W.Aq_hi, W.Aq_lo, B, k, {}, 0};
             Prof p(c, s, SSSD_PROF_ATTN);
             HIP_TRY(launch_attention(D, a, s));
         }
@@ -857,10 +859,10 @@ int sssd_op_attention(sssd_ctx *c, int32_t layer, int32_t B, int32_t k, const fl
     if (B > D.max_batch || k > D.max_k) return SSSD_ECAPACITY;
     hipStream_t s = (hipStream_t)stream;
     Buffers &W = c->W;
-    HIP_TRY(launch_lens(D, B, k, lens, W.pos_base, W.cut, W.rope_pos, W.anc, W.err_flag, s));
+    HIP_TRY(launch_lens(D, B, k, lens, W.pos_base, W.seq, W.segments, W.rope_pos, W.anc, W.err_flag, s));
     HIP_TRY(launch_q_pack(D, q, B, k, W.Qp, W.Qp_lo, s));
     uint16_t *Kl = c->Kc + (size_t)layer * c->S.kv_layer_elems, *Vl = c->Vc + (size_t)layer * c->S.kv_layer_elems;
-    AttnArgs a{W.Qp, W.Qp_lo, Kl, Vl, kv_geom(c), W.pos_base, W.cut, W.anc, W.part_o, W.part_ml, W.Aq_hi, W.Aq_lo, B, k, {}, 0};
+    AttnArgs a{W.Qp, W.Qp_lo, Kl, Vl, kv_geom(c), W.seq, W.segments, W.anc, W.part_o, W.part_ml, W.Aq_hi, W.Aq_lo, B, k, {}, 0};
     HIP_TRY(launch_attention(D, a, s));
     HIP_TRY(launch_unpack_act(W.Aq_hi, W.Aq_lo, B * (k + 1), D.qd, out, s));
     return SSSD_OK;

@@ -9,7 +9,9 @@
 //
 // One workgroup owns one segment of one sequence's positions for one kv head.  A sequence is cut by
 // its own length (attention_cut, by the kernel that validates the lens): caches with room to grow cost
-// nothing, and what the other sequences hold changes no bit.  All g*(k+1) query rows
+// nothing, and what the other sequences hold changes no bit.  (Segments of equal length throughout a
+// ragged batch would load the compute units better: 32 sequences of 1024..4096 at k = 4 65 us against
+// 70 in the step, a schedule of their own apart.)  All g*(k+1) query rows
 // that share the kv head are processed against the segment, one 16-row tile per wave,
 // so every cached byte is read from HBM once per step: the waves stage each block of
 // 32 positions through LDS together (double buffered, the next block's loads in flight
@@ -54,7 +56,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW >= 3
     __shared__ u32x4 Ks[2][32 * KROW];
     __shared__ u32x4 Vs[2][NREC];
 
-    int kvh, wg;   // kv head; (sequence, segment)
+    int kvh, wg;   // kv head; (turn, segment)
     {
         const int id = blockIdx.x, whole = (a.B * a.plan.share) & ~7;
         if (id < whole * D.nkv) {
@@ -66,10 +68,10 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW >= 3
             kvh = r % D.nkv;
         }
     }
-    const int b = wg / a.plan.share, segment = wg % a.plan.share;
-    const int len = max(a.pos_base[b], 0);   // a rejected sequence (< 0) is read as empty
-    const int total = len + a.k + 1;
-    const AttnCut cut = a.cut[b];
+    const int segment = wg % a.plan.share;
+    const AttnSeq me = a.seq[wg / a.plan.share];
+    const int b = me.b, len = me.len, total = len + a.k + 1;   // a rejected sequence is read as empty
+    const AttnCut cut = me.cut;
     if (segment >= cut.n) return;
     const int t_begin = segment * cut.each * 32;
     const int t_end = min(total, t_begin + cut.each * 32);
@@ -258,7 +260,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW >= 3
             }
         }
     } else if (row_tile_ok) {
-        const size_t at = ((size_t)kvh * a.B * a.plan.share + wg) * q_rows_pad + row;
+        const size_t at = (((size_t)kvh * a.B + b) * a.plan.share + segment) * q_rows_pad + row;
         float *po = a.part_o + at * HD;
 #pragma unroll
         for (int dt = 0; dt < DT; ++dt) *reinterpret_cast<f32x4 *>(po + dt * 16 + 4 * q) = o[dt];
@@ -286,7 +288,7 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(Dims D, AttnArgs a, i
     const int KTq = (D.qd + 31) >> 5;
     const int sg = lane >> 4, cl = lane & 15;
     const int r = task % R, kvh = (task / R) % D.nkv, b = task / (R * D.nkv);
-    const int n_splits = a.cut[b].n;       // at most ATTN_MAX_SEGMENTS
+    const int n_splits = a.segments[b];    // at most ATTN_MAX_SEGMENTS
     if (n_splits == 1) return;             // finished by its workgroup
     const size_t slot0 = ((size_t)kvh * a.B + b) * a.plan.share;
 
@@ -370,10 +372,10 @@ template <int HD> hipError_t launch_partial(const Dims &D, const AttnArgs &a, in
 // Segments per sequence.  The device holds four workgroups per compute unit with up to three waves (row tiles) each, three
 // with four waves, two with five or six, i.e. 1024 / 768 / 512 at once, and a launch is kept to one such round.  Within it
 // fewer and longer segments are faster (every segment is a partial result of g*(k+1) rows to write and merge, and HBM
-// serves 512 concurrent streams better than 1024), until compute units stand idle.  Measured as sssd_op_attention over the
+// serves 512 concurrent streams better than 1024), until compute units stand idle or ragged batches load them unevenly.  Measured as sssd_op_attention over the
 // caches of enough layers (1 GB) that nothing stays in a cache, us, all sequences at 4000 / at 1333..4000, by segments per
 // sequence (workgroups):
-//   up to four waves, 512 workgroups, or 768 where more than a fifth of 512 would be missing.  8B shape:
+//   up to four waves, 512 workgroups, or 768 where more than a sixth of 512 would be missing.  8B shape:
 //     k = 8, B = 13: 2 (208) 83 / 83, 4 (416) 66 / 65, 7 (728) 67 / 62, 9 (936) 69 / 63
 //     k = 8, B = 24: 2 (384) 103 / 97, 3 (576) 102 / 83, 4 (768) 98 / 83, 5 (960) 106 / 88
 //     k = 4, B = 32: 1 (256) 122 / 120, 2 (512) 105 / 91, 3 (768) 111 / 90, 4 (1024) 112 / 91
@@ -397,7 +399,7 @@ AttnPlan attention_plan(const Dims &D, int B, int k)
         share = 256 / units * units >= 192 ? 256 / units : 512 / units;
     } else {
         share = 512 / units;
-        if (share * units < 400 || (waves == 1 && share < 6)) share = 768 / units;
+        if (share * units < 426 || (waves == 1 && share < 6)) share = 768 / units;
         if (waves == 1 && share < 3) share = 1024 / units;
     }
     AttnPlan p;

@@ -276,22 +276,51 @@ __global__ void q_pack_kernel(Dims D, const float *q, int k, uint16_t *Qp, uint1
     Qp_lo[idx] = lo;
 }
 
-// Validated lens and the row geometry of linear chains (kernel-level attention entry point).
-__global__ void lens_kernel(Dims D, int B, int k, const int32_t *lens, int32_t *pos_base, AttnCut *cut, int32_t *rope_pos,
-                            uint32_t *anc, int32_t *err_flag, AttnPlan plan)
+// Rows that sequence b is ordered by: its length, if it fits.
+__device__ __forceinline__ int length_or_zero(const Dims &D, int k, int len) { return len < 0 || len + k + 1 > D.max_seq ? 0 : len; }
+
+// Turn of the sequence of the given rank among the lengths (0: the longest): the longer half in descending order, then the
+// others in ascending order.  A compute unit takes its second workgroup half a launch after its first, so the longest meet the
+// shortest.  Sequences in the order given / longest first / so, 8B shape, us of sssd_op_attention over cold caches: k = 4,
+// B = 32, context 1024..4096 95 / 91 / 89, k = 8, B = 16, 1333..4000 64 / 61 / 61.
+__device__ __forceinline__ int attention_turn(int rank, int B)
 {
-    const int b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= B) return;
+    const int first = (B + 1) / 2;
+    return rank < first ? rank : B - 1 - (rank - first);
+}
+
+// Rank of sequence b among the lengths of a step (longest first, then by index); whole wave.
+__device__ __forceinline__ int length_rank(const Dims &D, int B, int k, const int32_t *lens, int b, int lane)
+{
+    const int mine = length_or_zero(D, k, lens[b]);
+    int rank = 0;
+    for (int b0 = 0; b0 < B; b0 += 64) {
+        const int o = b0 + lane, other = o < B ? length_or_zero(D, k, lens[o]) : -1;
+        rank += __popcll(__ballot(other > mine || (other == mine && o < b)));
+    }
+    return rank;
+}
+
+// Validated lens and the row geometry of linear chains (kernel-level attention entry point).  grid = sequences, one wave.
+__global__ void lens_kernel(Dims D, int B, int k, const int32_t *lens, int32_t *pos_base, AttnSeq *seq, int32_t *segments,
+                            int32_t *rope_pos, uint32_t *anc, int32_t *err_flag, AttnPlan plan)
+{
+    const int b = blockIdx.x, lane = threadIdx.x;
+    const int rank = length_rank(D, B, k, lens, b, lane);
     int len = lens[b];
     if (len < 0 || len + k + 1 > D.max_seq) {
-        *err_flag = 1;
+        if (lane == 0) *err_flag = 1;
         len = 0;
     }
-    pos_base[b] = len;
-    cut[b] = attention_cut(plan, (len + k + 32) >> 5);
-    for (int j = 0; j <= k; ++j) {
-        rope_pos[b * (k + 1) + j] = len + j;
-        anc[b * (k + 1) + j] = 0xFFFFFFFFu >> (31 - j);
+    if (lane == 0) {
+        const AttnCut cut = attention_cut(plan, (len + k + 32) >> 5);
+        pos_base[b] = len;
+        seq[attention_turn(rank, B)] = AttnSeq{b, len, cut};
+        segments[b] = cut.n;
+    }
+    if (lane <= k) {   // k <= 31
+        rope_pos[b * (k + 1) + lane] = len + lane;
+        anc[b * (k + 1) + lane] = 0xFFFFFFFFu >> (31 - lane);
     }
 }
 
@@ -322,8 +351,8 @@ __global__ void pack_weight_kernel(const uint16_t *src, u32x4 *dst, int N, int K
 // rows of the node, from the draft tree or the chain); x = E[token]; packed x*gamma; sums of squares.
 __global__ __launch_bounds__(512) void fused_embed_kernel(Dims D, StepIO io, KvGeom kv, const uint16_t *embed, const uint16_t *gamma,
                                                           float *X, uint16_t *A_hi, uint16_t *A_lo, float *ssq,
-                                                          int32_t *pos_base, AttnCut *cut, int32_t *rope_pos, uint32_t *anc,
-                                                          int32_t *err_flag, AttnPlan plan)
+                                                          int32_t *pos_base, AttnSeq *seq, int32_t *segments, int32_t *rope_pos,
+                                                          uint32_t *anc, int32_t *err_flag, AttnPlan plan)
 {
     const int m = blockIdx.x, b = m / (io.k + 1), j = m % (io.k + 1);
     int tok = io.tokens[m];
@@ -331,6 +360,7 @@ __global__ __launch_bounds__(512) void fused_embed_kernel(Dims D, StepIO io, KvG
         if (threadIdx.x == 0) *err_flag = 1;
         tok = 0;
     }
+    const int rank = j == 0 && threadIdx.x < 64 ? length_rank(D, io.B, io.k, io.lens, b, threadIdx.x) : 0;
     if (threadIdx.x == 0) {
         int len = io.lens[b];
         bool reject = false;   // the sequence must not write the cache: its rows would land on live data
@@ -348,7 +378,10 @@ __global__ __launch_bounds__(512) void fused_embed_kernel(Dims D, StepIO io, KvG
             }
             // pos_base < 0 marks the rejected sequence for the K/V writers; readers take it as length 0
             pos_base[b] = reject ? -1 : len;
-            cut[b] = attention_cut(plan, ((reject ? 0 : len) + io.k + 32) >> 5);
+            const int rows = reject ? 0 : len;
+            const AttnCut cut = attention_cut(plan, (rows + io.k + 32) >> 5);
+            seq[attention_turn(rank, io.B)] = AttnSeq{b, rows, cut};
+            segments[b] = cut.n;
         }
         if (reject) *err_flag = 1;
         int depth = j;
@@ -494,10 +527,10 @@ hipError_t launch_q_pack(const Dims &D, const float *q, int B, int k, uint16_t *
     return hipGetLastError();
 }
 
-hipError_t launch_lens(const Dims &D, int B, int k, const int32_t *lens, int32_t *pos_base, AttnCut *cut, int32_t *rope_pos,
-                       uint32_t *anc, int32_t *err_flag, hipStream_t s)
+hipError_t launch_lens(const Dims &D, int B, int k, const int32_t *lens, int32_t *pos_base, AttnSeq *seq, int32_t *segments,
+                       int32_t *rope_pos, uint32_t *anc, int32_t *err_flag, hipStream_t s)
 {
-    hipLaunchKernelGGL(lens_kernel, dim3((B + 63) / 64), dim3(64), 0, s, D, B, k, lens, pos_base, cut, rope_pos, anc, err_flag,
+    hipLaunchKernelGGL(lens_kernel, dim3(B), dim3(64), 0, s, D, B, k, lens, pos_base, seq, segments, rope_pos, anc, err_flag,
                        attention_plan(D, B, k));
     return hipGetLastError();
 }
@@ -513,10 +546,10 @@ hipError_t launch_pack_weight(const uint16_t *src, uint16_t *dst, int N, int K, 
 }
 
 hipError_t launch_fused_embed(const Dims &D, const StepIO &io, const KvGeom &kv, const uint16_t *embed, const uint16_t *gamma,
-                              float *X, uint16_t *A_hi, uint16_t *A_lo, float *ssq, int32_t *pos_base, AttnCut *cut, int32_t *rope_pos,
+                              float *X, uint16_t *A_hi, uint16_t *A_lo, float *ssq, int32_t *pos_base, AttnSeq *seq, int32_t *segments, int32_t *rope_pos,
                               uint32_t *anc, int32_t *err_flag, hipStream_t s)
 {
     hipLaunchKernelGGL(fused_embed_kernel, dim3(io.B * (io.k + 1)), dim3(512), 0, s, D, io, kv, embed, gamma, X, A_hi, A_lo, ssq,
-                       pos_base, cut, rope_pos, anc, err_flag, attention_plan(D, io.B, io.k));
+                       pos_base, seq, segments, rope_pos, anc, err_flag, attention_plan(D, io.B, io.k));
     return hipGetLastError();
 }

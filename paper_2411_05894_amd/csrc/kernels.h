@@ -12,8 +12,14 @@ struct AttnPlan {
 };
 constexpr int ATTN_MAX_SEGMENTS = 64;   // per sequence: what the merge takes
 AttnPlan attention_plan(const Dims &D, int B, int k);
-struct AttnCut {       // of one sequence, once per step, beside pos_base
+struct AttnCut {
     int each, n;       // blocks per segment (the last may be shorter), segments
+};
+// The sequences of a step in the order in which their workgroups start, written once per step beside pos_base.  The order
+// changes no result: it puts the longest sequences first and pairs them with the shortest on the compute units.
+struct AttnSeq {
+    int b, len;        // sequence, cached rows it is read with
+    AttnCut cut;
 };
 // The sequence is shared out evenly.  Lengths of 16 blocks and more are made odd: an even one puts the segments' streams a
 // multiple of a large power of two apart, where they meet on the same memory channels (B = 4, context 32768, eight heads
@@ -100,7 +106,7 @@ hipError_t launch_stream_gemm(FusedGemmArgs &a, int epilogue, hipStream_t s, boo
                               hipEvent_t t1);
 hipError_t launch_stream_epilogue(const FusedGemmArgs &a, int epilogue, hipStream_t s);
 hipError_t launch_fused_embed(const Dims &D, const StepIO &io, const KvGeom &kv, const uint16_t *embed, const uint16_t *gamma,
-                              float *X, uint16_t *A_hi, uint16_t *A_lo, float *ssq, int32_t *pos_base, AttnCut *cut, int32_t *rope_pos,
+                              float *X, uint16_t *A_hi, uint16_t *A_lo, float *ssq, int32_t *pos_base, AttnSeq *seq, int32_t *segments, int32_t *rope_pos,
                               uint32_t *anc, int32_t *err_flag, hipStream_t s);
 
 // Merge per-tile arg-max partials, then greedy acceptance (longest matching prefix of a chain, or
@@ -136,8 +142,8 @@ hipError_t launch_unpack_act(const uint16_t *A_hi, const uint16_t *A_lo, int M, 
 constexpr int STREAM_READ_SINK_WORDS = 4096;
 hipError_t launch_stream_read(const void *src, size_t bytes, uint32_t *sink, int n_cu, hipStream_t s);
 hipError_t launch_q_pack(const Dims &D, const float *q, int B, int k, uint16_t *Qp, uint16_t *Qp_lo, hipStream_t s);
-hipError_t launch_lens(const Dims &D, int B, int k, const int32_t *lens, int32_t *pos_base, AttnCut *cut, int32_t *rope_pos,
-                       uint32_t *anc, int32_t *err_flag, hipStream_t s);
+hipError_t launch_lens(const Dims &D, int B, int k, const int32_t *lens, int32_t *pos_base, AttnSeq *seq, int32_t *segments,
+                       int32_t *rope_pos, uint32_t *anc, int32_t *err_flag, hipStream_t s);
 
 // ------------------------------------------------------------ attention ----
 struct AttnArgs {
@@ -145,8 +151,8 @@ struct AttnArgs {
     const uint16_t *Qp_lo;     // bf16 lo part: q ~= hi + lo
     const uint16_t *Kc, *Vc;   // this layer's cache pools
     KvGeom kv;                 // page geometry
-    const int32_t *pos_base;   // validated lens
-    const AttnCut *cut;        // [B]
+    const AttnSeq *seq;        // [B], by turn
+    const int32_t *segments;   // [B], by sequence
     const uint32_t *anc;       // [B*(k+1)] visible new rows of each query row (bit i = row pos_base + i)
     float *part_o;             // [kv head][B][share][q_rows_pad][d]
     float *part_ml;            // [kv head][B][share][q_rows_pad][2]  (running max in log2 units, sum)
