@@ -8,6 +8,9 @@
 
 namespace {
 
+// Room for the k + 1 new rows behind len cached ones (max_seq > k; the sum may not be representable).
+__device__ __forceinline__ bool length_fits(const Dims &D, int k, int len) { return len >= 0 && len <= D.max_seq - (k + 1); }
+
 // grid = M rows, block = 1024.  Row arg-max from the LM head's per-tile partials; the lowest
 // token id wins a tie.  The loads go out eight at a time (the kernel is one memory round trip long
 // per batch, not per element).
@@ -92,7 +95,7 @@ __global__ void kv_compact_kernel(Dims D, KvGeom kv, uint16_t *Kc, uint16_t *Vc,
 {
     const int kvh = blockIdx.x, b = blockIdx.y, l = blockIdx.z, i = threadIdx.x;
     const int len = lens[b], n = accepted_len[b];
-    if (len < 0 || n < 0 || n > k || len + k + 1 > D.max_seq) return;   // flagged by kv_commit_kernel
+    if (!length_fits(D, k, len) || n < 0 || n > k) return;   // flagged by kv_commit_kernel
     if (!kv_pages_ok(kv, b, len, len + k)) return;                       // likewise: nothing moves through a bad page
     uint16_t *kc = Kc + (size_t)l * kv_layer_elems, *vc = Vc + (size_t)l * kv_layer_elems;
     int prev = 0;
@@ -114,7 +117,7 @@ __global__ void kv_commit_kernel(Dims D, KvGeom kv, int B, int k, int32_t *lens,
     const int b = blockIdx.x * blockDim.x + threadIdx.x;
     if (b >= B) return;
     const int len = lens[b], n = accepted_len[b];
-    bool ok = len >= 0 && n >= 0 && n <= k && len + k + 1 <= D.max_seq;
+    bool ok = length_fits(D, k, len) && n >= 0 && n <= k;
     ok = ok && kv_pages_ok(kv, b, len, len + k);
     int prev = 0;
     for (int s = 1; ok && s <= n; ++s) {
@@ -277,7 +280,7 @@ __global__ void q_pack_kernel(Dims D, const float *q, int k, uint16_t *Qp, uint1
 }
 
 // Rows that sequence b is ordered by: its length, if it fits.
-__device__ __forceinline__ int length_or_zero(const Dims &D, int k, int len) { return len < 0 || len + k + 1 > D.max_seq ? 0 : len; }
+__device__ __forceinline__ int length_or_zero(const Dims &D, int k, int len) { return length_fits(D, k, len) ? len : 0; }
 
 // Turn of the sequence of the given rank among the lengths (0: the longest): the longer half in descending order, then the
 // others in ascending order.  A compute unit takes its second workgroup half a launch after its first, so the longest meet the
@@ -308,7 +311,7 @@ __global__ void lens_kernel(Dims D, int B, int k, const int32_t *lens, int32_t *
     const int b = blockIdx.x, lane = threadIdx.x;
     const int rank = length_rank(D, B, k, lens, b, lane);
     int len = lens[b];
-    if (len < 0 || len + k + 1 > D.max_seq) {
+    if (!length_fits(D, k, len)) {
         if (lane == 0) *err_flag = 1;
         len = 0;
     }
@@ -364,7 +367,7 @@ __global__ __launch_bounds__(512) void fused_embed_kernel(Dims D, StepIO io, KvG
     if (threadIdx.x == 0) {
         int len = io.lens[b];
         bool reject = false;   // the sequence must not write the cache: its rows would land on live data
-        if (len < 0 || len + io.k + 1 > D.max_seq) {
+        if (!length_fits(D, io.k, len)) {
             reject = true;
             len = 0;
         }

@@ -138,3 +138,34 @@ def test_a_long_sequence_with_a_bad_page_is_read_as_empty():
         assert torch.equal(logits[b], healthy[b])
     assert torch.isfinite(logits[1]).all()
     assert all(torch.equal(x, y) for x, y in zip(cache(), before))
+
+
+@pytest.mark.parametrize("length", [-1, -(1 << 31), (1 << 31) - 1, (1 << 31) - 3, 156])
+def test_lengths_that_do_not_fit_are_rejected(length):
+    """Negative, one too many and so large that the new rows' count takes them past 2^31: the call reports it, and neither the
+    step, the attention entry point nor the commit touches the cache."""
+    s = MODEL_SHAPES["tiny"]
+    B, k, max_seq = 2, 4, 160
+    p = Pair(s, seed=95, max_batch=B, max_k=k, max_seq=max_seq)
+    for b in range(B):
+        p.prefill_random_kv(96, b, max_seq)
+    print(f"length {length}", flush=True)
+
+    def row(b):
+        kv = [torch.empty(s.n_kv_heads, max_seq, s.head_dim, dtype=torch.bfloat16, device=DEV) for _ in range(2)]
+        p.ctx.sssd_kv_export(0, b, 0, *kv)
+        return [x.view(torch.int16) for x in kv]
+
+    before = row(1)
+    lens = torch.tensor([20, length], dtype=torch.int32, device=DEV)
+    acc, nxt = (torch.zeros(B, dtype=torch.int32, device=DEV) for _ in range(2))
+    p.ctx.sssd_verify_step(uniform_int(97, 1, (B, k + 1), 0, s.vocab - 1).to(DEV), lens, acc, nxt)
+    assert p.ctx.sssd_verify_sync() == sv.SSSD_ENOSPACE
+    q = torch.randn(B, k + 1, s.n_q_heads, s.head_dim, device=DEV)
+    p.ctx.sssd_op_attention(0, q, lens, torch.empty(B, k + 1, s.n_q_heads * s.head_dim, device=DEV))
+    assert p.ctx.sssd_verify_sync() == sv.SSSD_ENOSPACE
+    path = torch.tensor([[0, 2, -1, -1, -1]] * B, dtype=torch.int32, device=DEV)
+    p.ctx.sssd_kv_commit_tree(lens, torch.ones(B, dtype=torch.int32, device=DEV), path)
+    assert p.ctx.sssd_verify_sync() == sv.SSSD_ENOSPACE
+    assert lens.tolist() == [22, length]
+    assert all(torch.equal(x, y) for x, y in zip(row(1), before))
