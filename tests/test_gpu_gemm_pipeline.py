@@ -1,5 +1,6 @@
 """The pipelined GEMM kernel at every row-tile count up to ten: slices of one, two and three k-tiles (fewer than are in
-flight), odd k-tile counts, split and unsplit K, four and eight waves, a last column group partly inside the matrix."""
+flight), odd k-tile counts, split and unsplit K, four and eight waves (up to 64 rows eight from 512 MB on, a test of its own),
+a last column group partly inside the matrix."""
 import pytest
 import torch
 
@@ -39,6 +40,15 @@ def test_row_tiles(N, K, M):
                                    (270000, 128, 32), (16368, 8192, 16), (16384, 8192, 1), (16400, 8224, 16), (9616, 14336, 5),
                                    (32800, 4096, 9)])
 def test_small_steps_of_large_matrices(N, K, M):
+    check(N, K, M)
+
+
+# 514 MB: eight waves also at up to four row tiles, each count with its own staging, read-ahead and wait counts; the matrix
+# ends inside a column group of 256, and K, 257 k-tiles in seven slices, in a shorter slice
+@pytest.mark.parametrize("N,K", [(32784, 8224)])
+@pytest.mark.parametrize("M", [5, 16, 17, 32, 33, 48, 49, 64])
+def test_eight_waves_at_few_rows(N, K, M):
+    assert sv.sssd_op_gemm_kernel_of(M, N, K) == "qgemm16_kernel" and N * K * 2 >= 512 << 20
     check(N, K, M)
 
 
