@@ -16,6 +16,9 @@
  *    process memory.
  *  - All weights are bf16 (2 bytes, Table 2 caption), matrices row-major
  *    [out][in] (the transpose of the paper's X.W orientation, same product).
+ *  - A step of given B and k computes every sequence from that sequence's own
+ *    inputs alone, bit for bit: tokens, lengths and cache contents of the others
+ *    (rejected ones included) change nothing in its results.
  *  - Every function returns 0 (SSSD_OK) or a negative SSSD_E* code; nothing
  *    is printed and nothing aborts.  sssd_strerror() names a code.
  *  - Calls that take a `stream` only enqueue work on that hipStream_t (passed

@@ -117,7 +117,7 @@ size_t layout(const Dims &D, Sizes &S, Buffers *B, uint8_t *base)
         return p;
     };
     const int M = D.max_batch * (D.max_k + 1);
-    S.tiles_alloc = ((M + 15) / 16 + 9) / 10 * 10;
+    S.tiles_alloc = ((M + 15) / 16 + 9) / 10 * 10;   // whole tens: sizes callers may have stored; the kernels use (M + 15) / 16
     S.m_alloc = S.tiles_alloc * 16;
     S.q_rows_pad = round_up(D.g * (D.max_k + 1), 16);
     const size_t KTh = (D.h + 31) / 32, KTq = (D.qd + 31) / 32, KTf = (D.f + 31) / 32;
@@ -464,7 +464,7 @@ int run_step(sssd_ctx *c, int32_t B, int32_t k, const int32_t *tokens, const int
     StepIO io{tokens, lens, accepted_len, next_token, B, k, parents, path};
 
     // Six launches per layer (QKV, attention, merge, O, gate/up, down) plus an epilogue launch
-    // after every GEMM whose K is split over workgroups.
+    // after every GEMM on the pipelined kernel.
     {
         Prof p(c, s, SSSD_PROF_ELEM);
         HIP_TRY(launch_fused_embed(D, io, kv_geom(c), c->embed, c->layers[0].attn_norm, W.X, W.Ah_hi, W.Ah_lo, W.ssq1, W.pos_base,
@@ -703,7 +703,7 @@ size_t sssd_op_packed_weight_bytes(int32_t N, int32_t K)
 size_t sssd_op_packed_act_bytes(int32_t M, int32_t K)
 {
     if (M <= 0 || K <= 0) return 0;
-    const size_t tiles = (size_t)(((M + 15) / 16 + 9) / 10 * 10);  // whole GEMM passes of 10 row tiles
+    const size_t tiles = (size_t)(((M + 15) / 16 + 9) / 10 * 10);  // whole tens, as in the workspace; the kernels read (M + 15) / 16
     return tiles * ((K + 31) / 32) * 1024;
 }
 

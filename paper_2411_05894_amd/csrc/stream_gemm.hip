@@ -12,8 +12,8 @@
 //                  are refilled for the NEXT tile right after the MFMA that consumed them: a
 //                  rolling prefetch with a constant number of bytes in flight per wave and no
 //                  bubble at tile boundaries.  The k-split is reduced through LDS in fixed order.
-//   qgemm16_kernel More rows, in blocks of up to 160, and the matrices whose K pgemm_kernel would have to split
-//                  (is_small).  v_mfma_f32_16x16x32_bf16 tiles: each wave of a workgroup of eight (four for the small
+//   qgemm16_kernel More rows (up to 160 at once, beyond in row blocks of 96 and 128 within one launch), and the matrices
+//                  that is_small leaves to it.  v_mfma_f32_16x16x32_bf16 tiles: each wave of a workgroup of eight (four for the small
 //                  matrices) owns 32 output columns and streams their weights HBM -> registers (rolling prefetch,
 //                  every weight byte read once), while the activation k-tiles of the workgroup's k-slice, which all
 //                  its waves need, are staged through a register ring and an LDS ring.  Results go to
@@ -25,7 +25,8 @@
 //   QKV     RMSNorm scale, rotary embedding, Q -> packed hi/lo operand, K/V -> cache (in place)
 //   RESID   X += acc; packed X*gamma_next hi/lo; sums of squares per 16 columns
 //   SWIGLU  RMSNorm scale, silu(gate)*up -> packed hi/lo operand
-//   LM      RMSNorm scale, per-tile arg-max (logits are never materialised unless asked for)
+//   LM      RMSNorm scale, per-tile arg-max (pgemm_kernel with an unsplit K: logits are materialised only if asked for; else
+//           they pass through memory once as unscaled sums)
 // RMSNorm needs no pass of its own: the producer of the residual stream x writes x*gamma and
 // partial sums of squares, the consuming GEMM scales its fp32 results by rsqrt(mean(x^2)+eps),
 // which commutes with the matrix product.
@@ -441,7 +442,7 @@ __device__ __forceinline__ const u32x4 *tile_weights_seg(const FusedGemmArgs &a,
 // Against v_mfma_f32_32x32x16_bf16, which 33..48 rows used to take: 8B 36 rows gate/up 48.7 -> 45.3, down 32.4 -> 29.4,
 // 70B gate/up 157 -> 147.
 //
-// More than 160 rows are cut into RB blocks of MT16 row tiles, all in one launch: blocks 8 apart in the grid run on one
+// More than 160 rows are cut into blocks of eight or six row tiles, all in one launch: blocks 8 apart in the grid run on one
 // die, where the row blocks of a (column group, slice) follow each other and share the weights through its L2 (ordinary
 // loads then, not streaming ones).  There the matrix pipes bound everything and two waves share 64 columns, each on half
 // of the rows: half the operand reads per MFMA for a second fetch of the weights from the die's L2 (8B gate/up at 512 rows
@@ -726,8 +727,7 @@ __host__ QPlan q_plan(int Ntot, int K, int M)
 //   17..32 rows: pgemm_kernel feeds every compute unit twice the weight bytes it would stream alone, which costs more than
 //   the partial sums of qgemm16_kernel on all but the small matrices.  At 32 rows, GEMM and epilogue, pgemm / qgemm16 us:
 //   8B QKV (50 MB) 14.8 / 16.0, O (34 MB) 11.4 / 14.3, down (117 MB) 30 / 26, gate/up (235 MB) 50 / 42, LM head 223 / 193,
-//   70B QKV (168 MB) 41 / 32, gate/up 206 / 143, down 107 / 76.  The line lies at 64 MB, where the other kernel's
-//   workgroups get eight waves.
+//   70B QKV (168 MB) 41 / 32, gate/up 206 / 143, down 107 / 76.  The line lies between the 50 MB and the 117 MB of these.
 //   1..16 rows: pgemm_kernel wins wherever a workgroup covers the whole K (4096); where K is split, its slices go through
 //   memory too, and from 256 MB the faster stream decides, pgemm / qgemm16 at 16 rows: 70B gate/up (940 MB) 150 / 142,
 //   down (470 MB) 79 / 73, QKV (168 MB) 32 / 32, O (134 MB) 26 / 30, and an 8B layer with its down projection

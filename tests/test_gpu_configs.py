@@ -260,8 +260,8 @@ def test_cfg5_70b_b16_ctx2048_k8():
         check_exempt(ex, rows)
         # every sequence, not only the sampled one: the fused arg-max must be the arg-max of the step's logits
         assert torch.equal(gpu["that"], gpu["logits"].argmax(-1).to(torch.int32))
-    # k = 0 (16 rows: the small-step kernels, every GEMM with its K split over workgroups and summed by
-    # the last of them to arrive): 30 repetitions must give the same logits bit for bit
+    # k = 0 (16 rows: QKV and O on the small-step kernel with K split over workgroups and summed by the last
+    # of them to arrive, the larger matrices on the pipelined one): 30 repetitions must give the same logits bit for bit
     t1 = tokens[:, :1].contiguous().to(dev)
     first, bad = None, 0
     for rep in range(30):
