@@ -350,43 +350,53 @@ __global__ void pack_weight_kernel(const uint16_t *src, u32x4 *dst, int N, int K
 }
 
 
-// grid = M rows, 512 threads.  Validates lens/tokens/parents; row geometry (depth and visible new
+// One sequence of a step, by one wave: validates its length and pages, leaves its cache row, cut and turn.
+__device__ __forceinline__ void step_sequence(const Dims &D, const StepIO &io, const KvGeom &kv, const AttnPlan &plan, int b, int lane,
+                                              int32_t *pos_base, AttnSeq *seq, int32_t *segments, int32_t *err_flag)
+{
+    const int rank = length_rank(D, io.B, io.k, io.lens, b, lane);
+    const int len = io.lens[b];
+    bool reject = !length_fits(D, io.k, len);   // the sequence must not write the cache: its rows would land on live data
+    if (kv.table && !reject) {                  // every page the step reads or writes must lie in the pool
+        bool bad = false;
+        for (int blk = lane; blk <= (len + io.k) >> 5; blk += 64) {
+            const int page = kv.table[(size_t)b * kv.blocks_per_seq + blk];
+            bad = bad || page < 0 || page >= kv.n_pages;
+        }
+        reject = __any(bad);
+    }
+    if (lane != 0) return;
+    // pos_base < 0 marks the rejected sequence for the K/V writers; readers take it as length 0
+    pos_base[b] = reject ? -1 : len;
+    const int rows = reject ? 0 : len;
+    const AttnCut cut = attention_cut(plan, (rows + io.k + 32) >> 5);
+    seq[attention_turn(rank, io.B)] = AttnSeq{b, rows, cut};
+    segments[b] = cut.n;
+    if (reject) *err_flag = 1;
+}
+
+// grid = M rows and a workgroup for every eight sequences (a wave each, beside the rows: in the rows' own waves it took 2 us
+// longer), 512 threads.  Validates lens/tokens/parents; row geometry (depth and visible new
 // rows of the node, from the draft tree or the chain); x = E[token]; packed x*gamma; sums of squares.
 __global__ __launch_bounds__(512) void fused_embed_kernel(Dims D, StepIO io, KvGeom kv, const uint16_t *embed, const uint16_t *gamma,
                                                           float *X, uint16_t *A_hi, uint16_t *A_lo, float *ssq,
                                                           int32_t *pos_base, AttnSeq *seq, int32_t *segments, int32_t *rope_pos,
                                                           uint32_t *anc, int32_t *err_flag, AttnPlan plan)
 {
+    const int n_rows = io.B * (io.k + 1);
+    if ((int)blockIdx.x >= n_rows) {
+        const int of = ((int)blockIdx.x - n_rows) * 8 + (threadIdx.x >> 6);
+        if (of < io.B) step_sequence(D, io, kv, plan, of, threadIdx.x & 63, pos_base, seq, segments, err_flag);
+        return;
+    }
     const int m = blockIdx.x, b = m / (io.k + 1), j = m % (io.k + 1);
     int tok = io.tokens[m];
     if (tok < 0 || tok >= D.V) {
         if (threadIdx.x == 0) *err_flag = 1;
         tok = 0;
     }
-    const int rank = j == 0 && threadIdx.x < 64 ? length_rank(D, io.B, io.k, io.lens, b, threadIdx.x) : 0;
     if (threadIdx.x == 0) {
-        int len = io.lens[b];
-        bool reject = false;   // the sequence must not write the cache: its rows would land on live data
-        if (!length_fits(D, io.k, len)) {
-            reject = true;
-            len = 0;
-        }
-        if (j == 0) {
-            if (kv.table && !reject) {   // every page the step reads or writes must lie in the pool
-                const int last_blk = (len + io.k) >> 5;
-                for (int blk = 0; blk <= last_blk; ++blk) {
-                    const int page = kv.table[(size_t)b * kv.blocks_per_seq + blk];
-                    if (page < 0 || page >= kv.n_pages) reject = true;
-                }
-            }
-            // pos_base < 0 marks the rejected sequence for the K/V writers; readers take it as length 0
-            pos_base[b] = reject ? -1 : len;
-            const int rows = reject ? 0 : len;
-            const AttnCut cut = attention_cut(plan, (rows + io.k + 32) >> 5);
-            seq[attention_turn(rank, io.B)] = AttnSeq{b, rows, cut};
-            segments[b] = cut.n;
-        }
-        if (reject) *err_flag = 1;
+        const int len = length_or_zero(D, io.k, io.lens[b]);
         int depth = j;
         uint32_t vis = 0xFFFFFFFFu >> (31 - j);
         if (io.parents) {
@@ -552,7 +562,7 @@ hipError_t launch_fused_embed(const Dims &D, const StepIO &io, const KvGeom &kv,
                               float *X, uint16_t *A_hi, uint16_t *A_lo, float *ssq, int32_t *pos_base, AttnSeq *seq, int32_t *segments, int32_t *rope_pos,
                               uint32_t *anc, int32_t *err_flag, hipStream_t s)
 {
-    hipLaunchKernelGGL(fused_embed_kernel, dim3(io.B * (io.k + 1)), dim3(512), 0, s, D, io, kv, embed, gamma, X, A_hi, A_lo, ssq,
+    hipLaunchKernelGGL(fused_embed_kernel, dim3(io.B * (io.k + 1) + (io.B + 7) / 8), dim3(512), 0, s, D, io, kv, embed, gamma, X, A_hi, A_lo, ssq,
                        pos_base, seq, segments, rope_pos, anc, err_flag, attention_plan(D, io.B, io.k));
     return hipGetLastError();
 }
