@@ -474,7 +474,7 @@ __device__ __forceinline__ void qgemm16_rows(const FusedGemmArgs a, int NT16, in
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int half = wave / CW, cg = wave % CW;
     const int m_base = tile0 * 16;
-    const int J = a.J, j = gj % J, grp = gj / J;
+    const int J = a.J, grp = (int)((unsigned)gj / (unsigned)J), j = gj - grp * J;
     const int KT = a.KT;
     const int kps = a.kps;
     const int kt_begin = j * kps, kt_end = kt_begin + kps < KT ? kt_begin + kps : KT;
@@ -624,16 +624,17 @@ __device__ __forceinline__ void qgemm16_rows(const FusedGemmArgs a, int NT16, in
 // size have kernels of their own: in the mixed one they are 2 % slower.
 template <int MT16, int QW, bool BLOCKS>
 // Registers: two workgroups of four waves per compute unit up to nine tiles (tiny shape with a vocabulary of 128256, 144 rows:
-// 276 registers and one workgroup 69 us, 256 and two 66), four waves per SIMD up to two tiles.
-__global__ __launch_bounds__(QW * 64) __attribute__((amdgpu_waves_per_eu(!BLOCKS && MT16 <= 2 ? 4 : (QW == 4 && MT16 <= 9 ? 2 : 1)))) void qgemm16_kernel(FusedGemmArgs a, int RB, int n8, int NT16)
+// 276 registers and one workgroup 69 us, 256 and two 66), which at three tiles costs more than it gives (8B gate/up at 33 rows
+// 44.4 -> 45.2); four waves per SIMD up to two tiles.
+__global__ __launch_bounds__(QW * 64) __attribute__((amdgpu_waves_per_eu(!BLOCKS && MT16 <= 2 ? 4 : (QW == 4 && MT16 >= 4 && MT16 <= 9 ? 2 : 1)))) void qgemm16_kernel(FusedGemmArgs a, int RB, int n8, int NT16, int pairs)
 {
     if constexpr (BLOCKS) {
         using S = QShape<MT16 ? MT16 : 8, QW, true>;
         __shared__ u32x4 ring[S::QDW][S::SLOT];
-        const int bid = blockIdx.x, n = gridDim.x / RB, whole = n & ~7;   // (column group, slice) pairs; those in full sets of 8
+        const int bid = blockIdx.x, whole = pairs & ~7;   // (column group, slice) pairs; those in full sets of 8
         const bool in_set = bid < whole * RB;
-        const int x = in_set ? bid >> 3 : bid - whole * RB, by = in_set ? RB : n - whole;
-        const int q = x / by, r = x - q * by;
+        const int x = in_set ? bid >> 3 : bid - whole * RB, by = in_set ? RB : pairs - whole;
+        const int q = (int)((unsigned)x / (unsigned)by), r = x - q * by;
         const int rb = in_set ? r : q, gj = in_set ? q * 8 + (bid & 7) : whole + r;
         if constexpr (MT16 != 0) qgemm16_rows<MT16, QW, true>(a, NT16, MT16 * rb, gj, ring);
         else if (rb < n8) qgemm16_rows<8, QW, true>(a, NT16, 8 * rb, gj, ring);
@@ -757,7 +758,7 @@ template <int EPI> hipError_t launch_large(FusedGemmArgs &a, hipStream_t s, bool
     const int mt16 = (a.M + 15) / 16;
     const RowBlocks rows = row_blocks(mt16);
     const dim3 grid(p.groups * a.J * rows.RB), block(p.qw * 64);
-#define SSSD_Q16LAUNCH(MT, QW, BLOCKS) hipExtLaunchKernelGGL((qgemm16_kernel<MT, QW, BLOCKS>), grid, block, 0, s, t0, t1, 0, a, rows.RB, rows.n8, NT16)
+#define SSSD_Q16LAUNCH(MT, QW, BLOCKS) hipExtLaunchKernelGGL((qgemm16_kernel<MT, QW, BLOCKS>), grid, block, 0, s, t0, t1, 0, a, rows.RB, rows.n8, NT16, p.groups * a.J)
 #define SSSD_Q16ROWS(MT)                                  \
     do {                                                  \
         if (p.qw == 8) SSSD_Q16LAUNCH(MT, 8, false);      \
