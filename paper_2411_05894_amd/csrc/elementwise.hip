@@ -375,8 +375,8 @@ __device__ __forceinline__ void step_sequence(const Dims &D, const StepIO &io, c
     if (reject) *err_flag = 1;
 }
 
-// grid = M rows and a workgroup for every eight sequences (a wave each, beside the rows: in the rows' own waves it took 2 us
-// longer), 512 threads.  Validates lens/tokens/parents; row geometry (depth and visible new
+// grid = M rows and a workgroup for every eight sequences (a wave each, beside the rows: in the rows' own waves the launch took
+// 1 us longer), 512 threads.  Validates lens/tokens/parents; row geometry (depth and visible new
 // rows of the node, from the draft tree or the chain); x = E[token]; packed x*gamma; sums of squares.
 __global__ __launch_bounds__(512) void fused_embed_kernel(Dims D, StepIO io, KvGeom kv, const uint16_t *embed, const uint16_t *gamma,
                                                           float *X, uint16_t *A_hi, uint16_t *A_lo, float *ssq,
