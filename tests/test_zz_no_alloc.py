@@ -1,6 +1,7 @@
 """The GEMM entry point that allocates nothing (its split-K partial sums live in a device array inside
 the library image) against the entry point that takes the caller's scratch: same bits, on calls in a
 row that share the array, a larger problem first and a smaller one after it."""
+import gc
 import os
 import sys
 
@@ -34,6 +35,7 @@ def test_static_scratch_gemm_equals_the_workspace_gemm_on_calls_in_a_row():
     assert needs[0] > needs[1] and needs[2] > needs[3]
     outs = [torch.full((s[0], s[1]), float("nan"), dtype=torch.float32, device=DEV) for s in shapes]
     torch.cuda.synchronize()
+    gc.collect()      # tensors of earlier tests in reference cycles must not be freed between the two readings
     before = torch.cuda.memory_allocated()
     for (M, N, K), (w, x, hi, lo, wp), out in zip(shapes, cases, outs):          # back to back on one stream
         sv.sssd_op_gemm_static(hi, lo, wp, M, N, K, out)
