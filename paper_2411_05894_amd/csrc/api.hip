@@ -477,16 +477,23 @@ int run_step(sssd_ctx *c, int32_t B, int32_t k, const int32_t *tokens, const int
     f.logits = smp ? smp->logits : c->dbg_logits; f.part_val = W.part_val; f.part_idx = W.part_idx;
     const int KTh = (D.h + 31) / 32, KTq = (D.qd + 31) / 32, KTf = (D.f + 31) / 32;
     f.n_cu = c->n_cu; f.partials = W.partials; f.partial_bytes = W.partial_bytes;
+    int nss = embed_row_sums(D.h);   // sums of squares per row of the residual stream, as its last writer left them
     auto fgemm = [&](int epi) -> hipError_t {
         bool more = false;
+        f.nss_in = nss;
         f.tail_count = W.tail_count; f.tail_slots = TAIL_SLOTS;   // the launcher clears it when it does not apply
         {
             Prof p(c, s, SSSD_PROF_GEMM, true);
-            hipError_t e = launch_stream_gemm(f, epi, s, &more, p.start(), p.stop());
-            if (e != hipSuccess || !more) return e;
+            const hipError_t e = launch_stream_gemm(f, epi, s, &more, p.start(), p.stop());
+            if (e != hipSuccess) return e;
         }
-        Prof p(c, s, SSSD_PROF_ELEM);
-        return launch_stream_epilogue(f, epi, s);
+        if (more) {
+            Prof p(c, s, SSSD_PROF_ELEM);
+            const hipError_t e = launch_stream_epilogue(f, epi, s);
+            if (e != hipSuccess) return e;
+        }
+        if (epi == FEPI_RESID) nss = f.nss_out;
+        return hipSuccess;
     };
     auto set_qkv = [&](FusedGemmArgs &g, int l) {
         const LayerW &lw = c->layers[l];

@@ -377,7 +377,7 @@ __device__ __forceinline__ void step_sequence(const Dims &D, const StepIO &io, c
 
 // grid = M rows and a workgroup for every eight sequences (a wave each, beside the rows: in the rows' own waves the launch took
 // 1 us longer), 512 threads.  Validates lens/tokens/parents; row geometry (depth and visible new
-// rows of the node, from the draft tree or the chain); x = E[token]; packed x*gamma; sums of squares.
+// rows of the node, from the draft tree or the chain); x = E[token]; packed x*gamma; sums of squares, one per wave.
 __global__ __launch_bounds__(512) void fused_embed_kernel(Dims D, StepIO io, KvGeom kv, const uint16_t *embed, const uint16_t *gamma,
                                                           float *X, uint16_t *A_hi, uint16_t *A_lo, float *ssq,
                                                           int32_t *pos_base, AttnSeq *seq, int32_t *segments, int32_t *rope_pos,
@@ -418,7 +418,8 @@ __global__ __launch_bounds__(512) void fused_embed_kernel(Dims D, StepIO io, KvG
         anc[m] = vis;
     }
     const uint16_t *row = embed + (size_t)tok * D.h;
-    const int KT = (D.h + 31) >> 5, NSS = D.h >> 4;
+    const int KT = (D.h + 31) >> 5, NSS = embed_row_sums(D.h), wave = threadIdx.x >> 6;
+    float ss = 0.f;
     for (int i = threadIdx.x; i < D.h; i += blockDim.x) {
         const float x = bf16_to_f32(row[i]);
         X[(size_t)m * D.h + i] = x;
@@ -427,11 +428,11 @@ __global__ __launch_bounds__(512) void fused_embed_kernel(Dims D, StepIO io, KvG
         const size_t idx = packed_index(m, i, KT);
         A_hi[idx] = hi;
         A_lo[idx] = lo;
-        float ss = x * x;
-#pragma unroll
-        for (int off = 8; off >= 1; off >>= 1) ss += __shfl_xor(ss, off, 16);
-        if ((i & 15) == 0) ssq[(size_t)m * NSS + (i >> 4)] = ss;
+        ss += x * x;
     }
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) ss += __shfl_xor(ss, off);
+    if ((threadIdx.x & 63) == 0 && wave < NSS) ssq[(size_t)m * NSS + wave] = ss;
 }
 
 // Plain read-only stream over a buffer: workgroup b reads the 16 KiB pieces b, b + grid, b + 2 grid, ...,

@@ -143,10 +143,10 @@ __device__ __forceinline__ void epilogue(const FusedGemmArgs &a, int unit, int m
     }
 }
 
-// rsqrt(mean(x^2) + eps) of row m from the producer's per-16-column sums of squares; whole wave.
+// rsqrt(mean(x^2) + eps) of row m from the producer's sums of squares; whole wave.
 template <bool COH = false> __device__ __forceinline__ float row_rstd(const FusedGemmArgs &a, int m, int lane)
 {
-    const int NSS = a.h >> 4;
+    const int NSS = a.nss_in;
     float sum = 0.f;
     if (m < a.M)
         for (int t = lane; t < NSS; t += 64) sum += ld<COH>(a.ssq_in + (size_t)m * NSS + t);
@@ -223,44 +223,148 @@ __device__ __forceinline__ u32x4 round8(const Vec8 &x)
     return u32x4{h[0], h[1], h[2], h[3]};
 }
 
-// Sum of the J slices of 8 columns starting at (row m, column col), slices in order.
-template <bool COH = false> __device__ __forceinline__ Vec8 sum_slices(const FusedGemmArgs &a, int m, int col)
+// Sums of the J slices of 8 columns each at `col` (and at `col1`, with TWO) of row m, slices in order.  BATCH slices are
+// fetched at a time: one by one, every slice is a memory round trip of its own.
+template <int BATCH, bool TWO, bool COH = false>
+__device__ __forceinline__ void sum_slices(const FusedGemmArgs &a, int m, int col, int col1, Vec8 &s0, Vec8 &s1)
 {
-    const float *p = a.partials + (size_t)m * a.Ntot + col;
+    const float *p = a.partials + (size_t)m * a.Ntot + col, *p1 = a.partials + (size_t)m * a.Ntot + col1;
     const size_t jstride = (size_t)a.part_rows * a.Ntot;
-    Vec8 s = load8<COH>(p);
-    for (int j = 1; j < a.J; ++j) {
-        const Vec8 t = load8<COH>(p + j * jstride);
+    for (int j0 = 0; j0 < a.J; j0 += BATCH) {
+        Vec8 t0[BATCH], t1[BATCH];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) s.v[e] += t.v[e];
+        for (int u = 0; u < BATCH; ++u)
+            if (j0 + u < a.J) {
+                t0[u] = load8<COH>(p + (j0 + u) * jstride);
+                if (TWO) t1[u] = load8<COH>(p1 + (j0 + u) * jstride);
+            }
+#pragma unroll
+        for (int u = 0; u < BATCH; ++u)
+            if (j0 + u < a.J) {
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    s0.v[e] = j0 + u ? s0.v[e] + t0[u].v[e] : t0[u].v[e];
+                    if (TWO) s1.v[e] = j0 + u ? s1.v[e] + t1[u].v[e] : t1[u].v[e];
+                }
+            }
     }
-    return s;
 }
 
-// Residual epilogue on 8 columns (col..col+7 of row m) per thread, v0 = the projection's result there;
-// kg: which 8-column group of its 32-column block the thread holds (lanes kg and kg^1, 16 lanes
-// apart, share a 16-column sum of squares).  Whole waves call this.
-template <bool COH> __device__ __forceinline__ void resid_block(const FusedGemmArgs &a, int m, int col, bool live, int kg, const Vec8 &v0)
+// Epilogues on 8 consecutive columns per thread, which are one 16-byte lane record of a packed operand.
+
+// RESID: X += v0, packed X * gamma.  v0 = the projection's result at columns col..col+7 of row m.  Returns the sum of squares
+// of the updated columns.
+template <bool COH> __device__ __forceinline__ float resid8(const FusedGemmArgs &a, int m, int col, const Vec8 &v0)
 {
     float ss = 0.f;
-    if (live) {
-        const Vec8 x = load8<COH>(a.X + (size_t)m * a.h + col);
-        Vec8 xn, xg;
+    const Vec8 x = load8<COH>(a.X + (size_t)m * a.h + col);
+    Vec8 xn, xg;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            xn.v[e] = x.v[e] + v0.v[e];
-            xg.v[e] = xn.v[e] * bf16_to_f32(a.gamma_next[col + e]);   // caller's array: no alignment assumed
-            ss += xn.v[e] * xn.v[e];
-        }
-        store8<COH>(a.X + (size_t)m * a.h + col, xn);
-        u32x4 hi, lo;
-        split8(xg, hi, lo);
-        const size_t idx = packed_index(m, col, (a.h + 31) >> 5);
-        st_record<COH>(a.out_hi + idx, hi);
-        st_record<COH>(a.out_lo + idx, lo);
+    for (int e = 0; e < 8; ++e) {
+        xn.v[e] = x.v[e] + v0.v[e];
+        xg.v[e] = xn.v[e] * bf16_to_f32(a.gamma_next[col + e]);   // caller's array: no alignment assumed
+        ss += xn.v[e] * xn.v[e];
     }
+    store8<COH>(a.X + (size_t)m * a.h + col, xn);
+    u32x4 hi, lo;
+    split8(xg, hi, lo);
+    const size_t idx = packed_index(m, col, (a.h + 31) >> 5);
+    st_record<COH>(a.out_hi + idx, hi);
+    st_record<COH>(a.out_lo + idx, lo);
+    return ss;
+}
+
+// RESID with one sum of squares per 16 columns; whole waves call it.  kg: which 8-column group of its 32-column block the
+// thread holds (lanes kg and kg^1, 16 lanes apart, share a sum).
+template <bool COH> __device__ __forceinline__ void resid_block(const FusedGemmArgs &a, int m, int col, bool live, int kg, const Vec8 &v0)
+{
+    float ss = live ? resid8<COH>(a, m, col, v0) : 0.f;
     ss += __shfl_xor(ss, 16);   // the other 8 columns of the 16-column group
     if (live && !(kg & 1)) st<COH>(a.ssq_out + (size_t)m * (a.h >> 4) + (col >> 4), ss);
+}
+
+// QKV: v0 at channels ch..ch+7 of the first half of a head, v1 at the same channels of the second half.
+__device__ __forceinline__ void qkv8(const FusedGemmArgs &a, int m, int head, int ch, float rs, Vec8 v0, Vec8 v1)
+{
+    const int half = a.d >> 1;
+    const int b = m / (a.k + 1), j = m % (a.k + 1);
+    const int base = a.pos_base[b];               // < 0: a rejected sequence, which must not touch the cache
+    const int pos = base + j;                     // cache row of node j
+#pragma unroll
+    for (int e = 0; e < 8; ++e) { v0.v[e] *= rs; v1.v[e] *= rs; }
+    if (head < a.nq + a.nkv) {
+        const float *cs = a.rope_cs + ((size_t)a.rope_pos[m] * half + ch) * 2;
+        const Vec8 cs0 = load8(cs), cs1 = load8(cs + 8);   // (cos, sin) of channels ch..ch+3, ch+4..ch+7
+        Vec8 y0, y1;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const float co = e < 4 ? cs0.v[2 * e] : cs1.v[2 * (e - 4)], si = e < 4 ? cs0.v[2 * e + 1] : cs1.v[2 * (e - 4) + 1];
+            y0.v[e] = v0.v[e] * co - v1.v[e] * si;
+            y1.v[e] = v0.v[e] * si + v1.v[e] * co;
+        }
+        if (head < a.nq) {
+            const int g = a.nq / a.nkv, kvh = head / g, hl = head % g, rr = j * g + hl;
+            const size_t qs = ((size_t)b * a.nkv + kvh) * a.q_rows_pad * a.d;
+            u32x4 h0, l0, h1, l1;
+            split8(y0, h0, l0);
+            split8(y1, h1, l1);
+            const size_t i_0 = qs + packed_index(rr, ch, a.d >> 5), i_1 = qs + packed_index(rr, ch + half, a.d >> 5);
+            *reinterpret_cast<u32x4 *>(a.Qp + i_0) = h0; *reinterpret_cast<u32x4 *>(a.Qp_lo + i_0) = l0;
+            *reinterpret_cast<u32x4 *>(a.Qp + i_1) = h1; *reinterpret_cast<u32x4 *>(a.Qp_lo + i_1) = l1;
+        } else if (base >= 0) {
+            head -= a.nq;
+            uint16_t *kr = a.Kc + kcache_offset(a.kv, b, head, pos, 0);
+            *reinterpret_cast<u32x4 *>(kr + ch) = round8(y0);
+            *reinterpret_cast<u32x4 *>(kr + ch + half) = round8(y1);
+        }
+    } else if (base >= 0) {
+        head -= a.nq + a.nkv;
+        uint16_t *vv = a.Vc + kv_block_offset(a.kv, kv_page(a.kv, b, pos >> 5), head);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            vv[vblock_index(pos & 31, ch + e, a.d)] = f32_to_bf16(v0.v[e]);
+            vv[vblock_index(pos & 31, ch + half + e, a.d)] = f32_to_bf16(v1.v[e]);
+        }
+    }
+}
+
+// SWIGLU: gate v0, up v1 at columns col..col+7 of the FFN.
+__device__ __forceinline__ void swiglu8(const FusedGemmArgs &a, int m, int col, float rs, const Vec8 &v0, const Vec8 &v1)
+{
+    Vec8 hv;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        const float gg = v0.v[e] * rs;
+        hv.v[e] = gg / (1.f + __expf(-gg)) * (v1.v[e] * rs);
+    }
+    u32x4 hi, lo;
+    split8(hv, hi, lo);
+    const size_t idx = packed_index(m, col, a.KT_out);
+    *reinterpret_cast<u32x4 *>(a.out_hi + idx) = hi;
+    *reinterpret_cast<u32x4 *>(a.out_lo + idx) = lo;
+}
+
+// LM: logits (if asked for) and the arg-max of each 16 columns; whole waves call it, lanes 16 apart share 16 columns.
+__device__ __forceinline__ void lm8(const FusedGemmArgs &a, int m, int n0, bool live, int kg, float rs, Vec8 v0)
+{
+    float bv = -INFINITY;
+    int bi = n0;
+    if (live) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const float logit = v0.v[e] * rs;
+            v0.v[e] = logit;
+            if (logit > bv) { bv = logit; bi = n0 + e; }   // ascending columns: the lowest index keeps a tie
+        }
+        if (a.logits) store8(a.logits + (size_t)m * a.vocab + n0, v0);
+    }
+    const float ov = __shfl_xor(bv, 16);
+    const int oi = __shfl_xor(bi, 16);
+    if (ov > bv || (ov == bv && oi < bi)) { bv = ov; bi = oi; }
+    if (live && !(kg & 1)) {
+        a.part_val[(size_t)m * a.NT + (n0 >> 4)] = bv;
+        a.part_idx[(size_t)m * a.NT + (n0 >> 4)] = bi;
+    }
 }
 
 }  // namespace

@@ -68,8 +68,9 @@ struct FusedGemmArgs {
     int KT, NT, M;                // k tiles, n tiles of W0, valid rows
     int h, d, nq, nkv, seq_pad, k, q_rows_pad, vocab;
     float eps;
-    const float *ssq_in;          // [M][h/16] sums of squares of the consumed stream (not RESID)
-    float *X, *ssq_out;           // RESID: residual stream [M][h], sums of squares of the updated stream
+    const float *ssq_in;          // [M][nss_in] sums of squares of the consumed stream (not RESID)
+    float *X, *ssq_out;           // RESID: residual stream [M][h], [M][nss_out] sums of squares of the updated stream
+    int nss_in, nss_out;          // sums per row, at most h/16; nss_out is filled in by the launch that writes them
     const uint16_t *gamma_next;   // RESID: gains of the norm that consumes the updated stream
     uint16_t *out_hi, *out_lo;    // RESID (K = h) / SWIGLU (KT_out k-tiles): packed operands of the next GEMM
     int KT_out;
@@ -91,6 +92,7 @@ struct FusedGemmArgs {
     int tail_slots;               // the last workgroup of a column group sums the slices itself (null: epilogue launch)
     int seg0, seg1;               // tiles of W0 and of W1 in the concatenated output (qgemm16_kernel)
     int upw, J, part_rows, kps;   // filled in by the launcher: units per workgroup, K slices, rows per slice, k-tiles per slice
+    int epi;                      // ... epilogue (qgemm16_kernel)
     int groups;                   // ... and column groups (M <= 32: the grid is groups * J workgroups)
 };
 // Up to stream_gemm_max_rows() rows some matrices take the persistent weight streamer; NT must be the tile count of W0.
@@ -104,7 +106,9 @@ size_t stream_gemm_scratch_bytes(int M, int N, int K);   // one GEMM (kernel-lev
 // start and end (what a profiler reports as the kernel's duration).
 hipError_t launch_stream_gemm(FusedGemmArgs &a, int epilogue, hipStream_t s, bool *needs_epilogue, hipEvent_t t0,
                               hipEvent_t t1);
-hipError_t launch_stream_epilogue(const FusedGemmArgs &a, int epilogue, hipStream_t s);
+hipError_t launch_stream_epilogue(FusedGemmArgs &a, int epilogue, hipStream_t s);
+// Sums of squares per row that the embedding launch leaves: one per wave that has columns (at most h/16).
+__host__ __device__ __forceinline__ int embed_row_sums(int h) { return h > 512 ? 8 : (h + 63) / 64; }
 hipError_t launch_fused_embed(const Dims &D, const StepIO &io, const KvGeom &kv, const uint16_t *embed, const uint16_t *gamma,
                               float *X, uint16_t *A_hi, uint16_t *A_lo, float *ssq, int32_t *pos_base, AttnSeq *seq, int32_t *segments, int32_t *rope_pos,
                               uint32_t *anc, int32_t *err_flag, hipStream_t s);

@@ -16,8 +16,8 @@
 //                  that is_small leaves to it.  v_mfma_f32_16x16x32_bf16 tiles: each wave of a workgroup of eight (four for the small
 //                  matrices) owns 32 output columns and streams their weights HBM -> registers (rolling prefetch,
 //                  every weight byte read once), while the activation k-tiles of the workgroup's k-slice, which all
-//                  its waves need, are staged through a register ring and an LDS ring.  Results go to
-//                  split-K partials for epi_kernel.
+//                  its waves need, are staged through a register ring and an LDS ring.  With the whole K in one
+//                  workgroup it applies the epilogue itself; else its results go to split-K partials for epi_kernel.
 //   epi_kernel     Sums split-K partial results (when K is split over workgroups) in fixed order
 //                  and applies the epilogue.
 //
@@ -25,7 +25,7 @@
 //   QKV     RMSNorm scale, rotary embedding, Q -> packed hi/lo operand, K/V -> cache (in place)
 //   RESID   X += acc; packed X*gamma_next hi/lo; sums of squares per 16 columns
 //   SWIGLU  RMSNorm scale, silu(gate)*up -> packed hi/lo operand
-//   LM      RMSNorm scale, per-tile arg-max (pgemm_kernel with an unsplit K: logits are materialised only if asked for; else
+//   LM      RMSNorm scale, per-tile arg-max (with an unsplit K logits are materialised only if asked for; else
 //           they pass through memory once as unscaled sums)
 // RMSNorm needs no pass of its own: the producer of the residual stream x writes x*gamma and
 // partial sums of squares, the consuming GEMM scales its fp32 results by rsqrt(mean(x^2)+eps),
@@ -192,7 +192,7 @@ __global__ __launch_bounds__(PW * 64) void pgemm_kernel(FusedGemmArgs a)
                 const int m = m_base + r;
                 const bool live = i < n_mine && m < a.M;
                 Vec8 v0{};
-                if (live) v0 = sum_slices<true>(a, m, col);
+                if (live) sum_slices<4, false, true>(a, m, col, 0, v0, v0);
                 resid_block<false>(a, m, col, live, kg, v0);
             }
         } else {
@@ -229,8 +229,9 @@ template <int EPI> __device__ __host__ __forceinline__ int column_blocks(const F
 
 // grid = (column-block groups, row tiles of 16), 256 threads; each wave takes column blocks
 // cb0 + wave, cb0 + wave + 4, ...  The partial sums of a block are fetched one block ahead (the
-// first block's before the row scales are reduced), so the kernel's dependent memory round trips
-// overlap.
+// first block's before the row scales are reduced), all slices of a batch together, so the kernel's dependent memory round
+// trips overlap.  What is left is the traffic of the slices and the launch: RESID of 160 rows x 4096 in seven slices, 26 MB,
+// takes 10 us.  RESID leaves one sum of squares per row and workgroup: the launches that scale rows read few of them.
 template <int EPI>
 __global__ __launch_bounds__(256) void epi_kernel(FusedGemmArgs a, int blocks_per_wg)
 {
@@ -259,8 +260,7 @@ __global__ __launch_bounds__(256) void epi_kernel(FusedGemmArgs a, int blocks_pe
     auto fetch = [&](int cb, Vec8 &v0, Vec8 &v1) {
         const int col = cb < cb_end ? column(cb) : -1;
         if (col >= 0) {
-            v0 = sum_slices(a, m, col);
-            if (PAIRED) v1 = sum_slices(a, m, col + (EPI == FEPI_QKV ? half : a.Ntot >> 1));
+            sum_slices<PAIRED ? 4 : 8, PAIRED>(a, m, col, col + (EPI == FEPI_QKV ? half : a.Ntot >> 1), v0, v1);
         } else {
 #pragma unroll
             for (int e = 0; e < 8; ++e) v0.v[e] = v1.v[e] = 0.f;
@@ -269,8 +269,8 @@ __global__ __launch_bounds__(256) void epi_kernel(FusedGemmArgs a, int blocks_pe
 
     // Row scales: four rows per wave.  Their loads go out first and the first block's partial
     // sums right behind them, so the two dependent round trips overlap.
-    constexpr int SV = 8;                     // sums of squares per lane and row held in registers (h <= 8192)
-    const int NSS = a.h >> 4;
+    constexpr int SV = 2;                     // sums of squares per lane and row held in registers: all that a launch of this kernel leaves
+    const int NSS = a.nss_in;
     float sv[4][SV];
     if (SCALED) {
 #pragma unroll
@@ -302,100 +302,38 @@ __global__ __launch_bounds__(256) void epi_kernel(FusedGemmArgs a, int blocks_pe
     }
     const float rs = SCALED ? rstd_s[r] : 1.f;
 
+    float ss = 0.f;   // RESID: of this row, over the thread's columns
     for (int cb = cb_begin + wave; cb < cb_end; cb += 4) {
         Vec8 n0v, n1v;
         fetch(cb + 4, n0v, n1v);
         const int col = column(cb);
         const bool live = col >= 0;
         if (EPI == FEPI_QKV) {
-            if (live) {
-                int head = cb / bph;
-                const int ch = col - head * a.d;              // first-half channel of v0[0]
-                const int b = m / (a.k + 1), j = m % (a.k + 1);
-                const int base = a.pos_base[b];               // < 0: a rejected sequence, which must not touch the cache
-                const int pos = base + j;                     // cache row of node j
-#pragma unroll
-                for (int e = 0; e < 8; ++e) { v0.v[e] *= rs; v1.v[e] *= rs; }
-                if (head < a.nq + a.nkv) {
-                    const float *cs = a.rope_cs + ((size_t)a.rope_pos[m] * half + ch) * 2;
-                    const Vec8 cs0 = load8(cs), cs1 = load8(cs + 8);   // (cos, sin) of channels ch..ch+3, ch+4..ch+7
-                    Vec8 y0, y1;
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) {
-                        const float co = e < 4 ? cs0.v[2 * e] : cs1.v[2 * (e - 4)], si = e < 4 ? cs0.v[2 * e + 1] : cs1.v[2 * (e - 4) + 1];
-                        y0.v[e] = v0.v[e] * co - v1.v[e] * si;
-                        y1.v[e] = v0.v[e] * si + v1.v[e] * co;
-                    }
-                    if (head < a.nq) {
-                        const int g = a.nq / a.nkv, kvh = head / g, hl = head % g, rr = j * g + hl;
-                        const size_t qs = ((size_t)b * a.nkv + kvh) * a.q_rows_pad * a.d;
-                        u32x4 h0, l0, h1, l1;
-                        split8(y0, h0, l0);
-                        split8(y1, h1, l1);
-                        const size_t i_0 = qs + packed_index(rr, ch, a.d >> 5), i_1 = qs + packed_index(rr, ch + half, a.d >> 5);
-                        *reinterpret_cast<u32x4 *>(a.Qp + i_0) = h0; *reinterpret_cast<u32x4 *>(a.Qp_lo + i_0) = l0;
-                        *reinterpret_cast<u32x4 *>(a.Qp + i_1) = h1; *reinterpret_cast<u32x4 *>(a.Qp_lo + i_1) = l1;
-                    } else if (base >= 0) {
-                        head -= a.nq;
-                        uint16_t *kr = a.Kc + kcache_offset(a.kv, b, head, pos, 0);
-                        *reinterpret_cast<u32x4 *>(kr + ch) = round8(y0);
-                        *reinterpret_cast<u32x4 *>(kr + ch + half) = round8(y1);
-                    }
-                } else if (base >= 0) {
-                    head -= a.nq + a.nkv;
-                    uint16_t *vv = a.Vc + kv_block_offset(a.kv, kv_page(a.kv, b, pos >> 5), head);
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) {
-                        vv[vblock_index(pos & 31, ch + e, a.d)] = f32_to_bf16(v0.v[e]);
-                        vv[vblock_index(pos & 31, ch + half + e, a.d)] = f32_to_bf16(v1.v[e]);
-                    }
-                }
-            }
+            if (live) qkv8(a, m, cb / bph, col - (cb / bph) * a.d, rs, v0, v1);   // first-half channel of v0[0]
         } else if (EPI == FEPI_SWIGLU) {
-            if (live) {
-                Vec8 hv;
-#pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    const float gg = v0.v[e] * rs;
-                    hv.v[e] = gg / (1.f + __expf(-gg)) * (v1.v[e] * rs);
-                }
-                u32x4 hi, lo;
-                split8(hv, hi, lo);
-                const size_t idx = packed_index(m, col, a.KT_out);
-                *reinterpret_cast<u32x4 *>(a.out_hi + idx) = hi;
-                *reinterpret_cast<u32x4 *>(a.out_lo + idx) = lo;
-            }
+            if (live) swiglu8(a, m, col, rs, v0, v1);
         } else if (EPI == FEPI_STORE) {
             if (live) store8(a.out + (size_t)m * a.Ntot + col, v0);
         } else if (EPI == FEPI_RESID) {
-            resid_block<false>(a, m, col, live, kg, v0);
+            if (live) ss += resid8<false>(a, m, col, v0);
         } else {  // FEPI_LM
-            const int n0 = cb * 32 + kg * 8;
-            float bv = -INFINITY;
-            int bi = n0;
-            if (live) {
-#pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    const float logit = v0.v[e] * rs;
-                    v0.v[e] = logit;
-                    if (logit > bv) { bv = logit; bi = n0 + e; }   // ascending columns: the lowest index keeps a tie
-                }
-                if (a.logits) store8(a.logits + (size_t)m * a.vocab + n0, v0);
-            }
-            const float ov = __shfl_xor(bv, 16);
-            const int oi = __shfl_xor(bi, 16);
-            if (ov > bv || (ov == bv && oi < bi)) { bv = ov; bi = oi; }
-            if (live && !(kg & 1)) {
-                a.part_val[(size_t)m * a.NT + (n0 >> 4)] = bv;
-                a.part_idx[(size_t)m * a.NT + (n0 >> 4)] = bi;
-            }
+            lm8(a, m, cb * 32 + kg * 8, live, kg, rs, v0);
         }
         v0 = n0v;
         v1 = n1v;
     }
+    if (EPI == FEPI_RESID) {   // one sum of squares per row and workgroup
+        __shared__ float ss_s[4][16];
+        ss += __shfl_xor(ss, 16);
+        ss += __shfl_xor(ss, 32);
+        if (kg == 0) ss_s[wave][r] = ss;
+        __syncthreads();
+        if (threadIdx.x < 16 && row_ok)
+            a.ssq_out[(size_t)m * gridDim.x + blockIdx.x] = (ss_s[0][r] + ss_s[1][r]) + (ss_s[2][r] + ss_s[3][r]);
+    }
 }
 
-template <int EPI> hipError_t launch_epi(const FusedGemmArgs &a, hipStream_t s)
+template <int EPI> hipError_t launch_epi(FusedGemmArgs &a, hipStream_t s)
 {
     const int n_cu = a.n_cu > 0 ? a.n_cu : 256;
     const int row_tiles = (a.M + 15) / 16;
@@ -404,7 +342,9 @@ template <int EPI> hipError_t launch_epi(const FusedGemmArgs &a, hipStream_t s)
     const int groups_x = (4 * n_cu + row_tiles - 1) / row_tiles;
     int bpw = (n_cb + groups_x - 1) / groups_x;
     bpw = (bpw + 3) / 4 * 4;
-    hipLaunchKernelGGL((epi_kernel<EPI>), dim3((n_cb + bpw - 1) / bpw, row_tiles), dim3(256), 0, s, a, bpw);
+    const int nx = (n_cb + bpw - 1) / bpw;
+    if (EPI == FEPI_RESID) a.nss_out = nx;
+    hipLaunchKernelGGL((epi_kernel<EPI>), dim3(nx, row_tiles), dim3(256), 0, s, a, bpw);
     return hipGetLastError();
 }
 
@@ -426,7 +366,45 @@ __device__ __forceinline__ const u32x4 *tile_weights_seg(const FusedGemmArgs &a,
     return base + gt * stride;
 }
 
-// grid = row blocks * column groups * J workgroups of QW waves on MT16 row tiles of 16; writes partials[j][row][col].
+// Concatenated 16-column tile at place t of the order in which the waves take them: the two tiles of an epilogue unit (rotary
+// partners, gate and up) side by side, so that one wave holds both.
+__device__ __forceinline__ int q_tile(const FusedGemmArgs &a, int t)
+{
+    if (a.epi == FEPI_QKV) return unit_tile<FEPI_QKV>(a, t >> 1, t & 1);
+    if (a.epi == FEPI_SWIGLU) return unit_tile<FEPI_SWIGLU>(a, t >> 1, t & 1);
+    return t;
+}
+
+// rsqrt(mean(x^2) + eps) of rows m0 .. m0 + ROWS - 1 into LDS (published by the caller's barrier): 16 lanes a row, the rows of
+// a wave's turns fetched together.
+template <int ROWS, int QW> __device__ __forceinline__ void row_scales(const FusedGemmArgs &a, int m0, float *rstd_s)
+{
+    constexpr int TURNS = ROWS / (4 * QW) + (ROWS % (4 * QW) != 0);
+    const int first = (threadIdx.x >> 4), c = threadIdx.x & 15, n = a.nss_in;
+    float sum[TURNS];
+#pragma unroll
+    for (int i = 0; i < TURNS; ++i) sum[i] = 0.f;
+    for (int t = c; t < n; t += 16) {
+#pragma unroll
+        for (int i = 0; i < TURNS; ++i) {
+            const int r = first + i * 4 * QW;
+            if (r < ROWS && m0 + r < a.M) sum[i] += a.ssq_in[(size_t)(m0 + r) * n + t];
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < TURNS; ++i) {
+        const int r = first + i * 4 * QW;
+#pragma unroll
+        for (int off = 8; off >= 1; off >>= 1) sum[i] += __shfl_xor(sum[i], off, 16);
+        if (r < ROWS && c == 0) rstd_s[r] = rsqrtf(sum[i] / (float)a.h + a.eps);
+    }
+}
+
+// grid = row blocks * column groups * J workgroups of QW waves on MT16 row tiles of 16; J > 1: writes partials[j][row][col].
+// J = 1: applies the epilogue, through LDS, so that a lane holds eight columns of a row and stores whole operand records.  As
+// a launch of its own behind sums in memory it cost 70B gate/up at 144 rows 16.6 us, 8B gate/up at 512 rows 24 us, an LM head of
+// 128256 at 91 rows 27 us; whole steps with such a launch: 70B layer 625 -> 605 us, two 8B layers at 512 rows 1022 -> 984, 8B
+// layer and head at 91 rows 435 -> 415.  (Per element from the accumulators, in 2-byte stores, it had cost more than it saved.)
 // Both operands are the packed tiles as stored: lane l holds (row or column l%16, k-slots 8*(l/16)..+7) of a 16 x 32 tile.
 // One 32-column tile pair per wave, so two waves share a SIMD at QW = 8 (256 columns per workgroup, the large matrices);
 // QW = 4 for the small ones, whose K then splits half as often.
@@ -452,13 +430,16 @@ template <int MT16, int QW, bool BLOCKS> struct QShape {
     static constexpr int TILES = MT16 * 2;                      // activation tiles (hi and lo) of one k-tile
     static constexpr int APT = (TILES + QW - 1) / QW;           // tiles fetched per wave; surplus waves re-read the last one
     static constexpr int SLOT = TILES * 64;                     // records of a ring slot
+    static constexpr int RING = QDW * SLOT, STAGE = QW * 320;   // records of the ring, of the epilogue's staging area
+    static constexpr int LDS = RING > STAGE ? RING : STAGE;
 };
 
 // Rows 16 * tile0 .. 16 * (tile0 + MT16) - 1; gj: column group and slice.  ring: QDW slots.
 template <int MT16, int QW, bool BLOCKS>
-__device__ __forceinline__ void qgemm16_rows(const FusedGemmArgs a, int NT16, int tile0, int gj, u32x4 (*ring)[QShape<MT16, QW, BLOCKS>::SLOT])
+__device__ __forceinline__ void qgemm16_rows(const FusedGemmArgs a, int NT16, int tile0, int gj, u32x4 *lds, float *rstd_s)
 {
     using S = QShape<MT16, QW, BLOCKS>;
+    u32x4 (*ring)[S::SLOT] = reinterpret_cast<u32x4 (*)[S::SLOT]>(lds);
     constexpr int QDW = S::QDW, TILES = S::TILES, APT = S::APT;
     constexpr bool TWO = BLOCKS || MT16 <= 3;     // sums in two levels, where the registers allow it
     constexpr bool COMP = !BLOCKS && MT16 <= 2;   // ... the upper one compensated
@@ -480,14 +461,11 @@ __device__ __forceinline__ void qgemm16_rows(const FusedGemmArgs a, int NT16, in
     const int kt_begin = j * kps, kt_end = kt_begin + kps < KT ? kt_begin + kps : KT;
     const int n_iter = kt_end - kt_begin;
 
-    const int c16 = (grp * CW + cg) * NC;         // this wave's first 16-column tile
+    const int c16 = (grp * CW + cg) * NC;         // this wave's first 16-column tile, in the order of the epilogue units
     const u32x4 *wp[NC];
 #pragma unroll
-    for (int ct = 0; ct < NC; ++ct) {
-        int t16 = c16 + ct;
-        if (t16 >= NT16) t16 = NT16 - 1;          // columns past the matrix re-read the last tile, never stored
-        wp[ct] = tile_weights_seg(a, t16) + lane;
-    }
+    for (int ct = 0; ct < NC; ++ct)               // columns past the matrix re-read the last tile, never stored
+        wp[ct] = tile_weights_seg(a, q_tile(a, c16 + ct < NT16 ? c16 + ct : NT16 - 1)) + lane;
     const u32x4 *asrc[APT];
 #pragma unroll
     for (int i = 0; i < APT; ++i) {
@@ -524,6 +502,7 @@ __device__ __forceinline__ void qgemm16_rows(const FusedGemmArgs a, int NT16, in
         load_a(u, u);
         load_w(u, u);
     }
+    if (J == 1 && a.epi != FEPI_RESID && a.epi != FEPI_STORE) row_scales<16 * MT16, QW>(a, m_base, rstd_s);
     stage(0);
     __syncthreads();
     const int a_at = half * MTW * 128 + lane;
@@ -604,18 +583,70 @@ __device__ __forceinline__ void qgemm16_rows(const FusedGemmArgs a, int NT16, in
             }
     }
 
-    // acc[i][ct][v] of lane l: row 16 * (half * MTW + i) + 4*(l/16) + v, column 16 * (c16 + ct) + l%16
+    // acc[i][ct][v] of lane l: row 16 * (half * MTW + i) + 4*(l/16) + v, column l%16 of tile q_tile(c16 + ct)
+    const int row0 = m_base + 16 * half * MTW;
+    if (J > 1) {
 #pragma unroll
-    for (int ct = 0; ct < NC; ++ct) {
-        const int col = (c16 + ct) * 16 + (lane & 15);
-        if (col >= a.Ntot) continue;
+        for (int ct = 0; ct < NC; ++ct) {
+            if (c16 + ct >= NT16) continue;
+            const int col = q_tile(a, c16 + ct) * 16 + (lane & 15);
 #pragma unroll
-        for (int i = 0; i < MTW; ++i) {
+            for (int i = 0; i < MTW; ++i) {
 #pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int row = m_base + 16 * (half * MTW + i) + 4 * (lane >> 4) + v;
-                if (row < a.part_rows) a.partials[((size_t)j * a.part_rows + row) * a.Ntot + col] = acc[i][ct][v];
+                for (int v = 0; v < 4; ++v) {
+                    const int row = row0 + 16 * i + 4 * (lane >> 4) + v;
+                    if (row < a.part_rows) a.partials[((size_t)j * a.part_rows + row) * a.Ntot + col] = acc[i][ct][v];
+                }
             }
+        }
+        return;
+    }
+    __syncthreads();   // the ring has been read
+    float *mine = reinterpret_cast<float *>(lds + wave * 320);
+    const float *scale = rstd_s + 16 * half * MTW;
+    // One pair of tiles at a time through the wave's own LDS: 16 lanes of a tile hold a row's columns, the epilogues want
+    // eight columns of a row in a lane.  A row takes 20 floats: the four rows that a store writes together, and the sixteen that
+    // a read takes, lie in different banks.
+    const bool paired = a.epi == FEPI_QKV || a.epi == FEPI_SWIGLU;
+    const int r = lane & 15, kg = lane >> 4;
+#pragma unroll
+    for (int ct = 0; ct < NC; ct += 2) {
+        if (c16 + ct >= NT16) continue;
+#pragma unroll
+        for (int i = 0; i < MTW; i += 2) {   // two row tiles: lanes of kg 0 and 1 then take the first, those of 2 and 3 the second
+#pragma unroll
+            for (int ii = 0; ii < 2 && i + ii < MTW; ++ii)
+#pragma unroll
+                for (int part = 0; part < 2; ++part)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v)
+                        mine[((part * 2 + ii) * 16 + 4 * (lane >> 4) + v) * 20 + (lane & 15)] = acc[i + ii][ct + part][v];
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            if (paired) {
+                const int ii = kg >> 1, m = row0 + 16 * (i + ii) + r, unit = (c16 + ct) >> 1;
+                if (i + ii < MTW && m < a.M) {
+                    const Vec8 v0 = load8(mine + (ii * 16 + r) * 20 + 8 * (kg & 1)), v1 = load8(mine + ((2 + ii) * 16 + r) * 20 + 8 * (kg & 1));
+                    const float rs = scale[16 * (i + ii) + r];
+                    if (a.epi == FEPI_SWIGLU) {
+                        swiglu8(a, m, unit * 16 + 8 * (kg & 1), rs, v0, v1);
+                    } else {
+                        const int per_head = a.d >> 5;
+                        qkv8(a, m, unit / per_head, unit % per_head * 16 + 8 * (kg & 1), rs, v0, v1);
+                    }
+                }
+            } else {
+                const int col = (c16 + ct) * 16 + 8 * kg;
+#pragma unroll
+                for (int ii = 0; ii < 2 && i + ii < MTW; ++ii) {
+                    const int m = row0 + 16 * (i + ii) + r;
+                    const bool live = m < a.M && col < a.Ntot;
+                    const Vec8 v0 = load8(mine + ((kg >> 1) * 32 + ii * 16 + r) * 20 + 8 * (kg & 1));
+                    if (a.epi == FEPI_LM) lm8(a, m, col, live, kg, scale[16 * (i + ii) + r], v0);
+                    else if (a.epi == FEPI_RESID) resid_block<false>(a, m, col, live, kg, v0);
+                    else if (live) store8(a.out + (size_t)m * a.Ntot + col, v0);
+                }
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         }
     }
 }
@@ -630,19 +661,21 @@ __global__ __launch_bounds__(QW * 64) __attribute__((amdgpu_waves_per_eu(!BLOCKS
 {
     if constexpr (BLOCKS) {
         using S = QShape<MT16 ? MT16 : 8, QW, true>;
-        __shared__ u32x4 ring[S::QDW][S::SLOT];
+        __shared__ u32x4 lds[S::LDS];
+        __shared__ float rstd_s[16 * (MT16 ? MT16 : 8)];
         const int bid = blockIdx.x, whole = pairs & ~7;   // (column group, slice) pairs; those in full sets of 8
         const bool in_set = bid < whole * RB;
         const int x = in_set ? bid >> 3 : bid - whole * RB, by = in_set ? RB : pairs - whole;
         const int q = (int)((unsigned)x / (unsigned)by), r = x - q * by;
         const int rb = in_set ? r : q, gj = in_set ? q * 8 + (bid & 7) : whole + r;
-        if constexpr (MT16 != 0) qgemm16_rows<MT16, QW, true>(a, NT16, MT16 * rb, gj, ring);
-        else if (rb < n8) qgemm16_rows<8, QW, true>(a, NT16, 8 * rb, gj, ring);
-        else qgemm16_rows<6, QW, true>(a, NT16, 8 * n8 + 6 * (rb - n8), gj, reinterpret_cast<u32x4 (*)[QShape<6, QW, true>::SLOT]>(ring));
+        if constexpr (MT16 != 0) qgemm16_rows<MT16, QW, true>(a, NT16, MT16 * rb, gj, lds, rstd_s);
+        else if (rb < n8) qgemm16_rows<8, QW, true>(a, NT16, 8 * rb, gj, lds, rstd_s);
+        else qgemm16_rows<6, QW, true>(a, NT16, 8 * n8 + 6 * (rb - n8), gj, lds, rstd_s);
     } else {
         using S = QShape<MT16, QW, false>;
-        __shared__ u32x4 ring[S::QDW][S::SLOT];
-        qgemm16_rows<MT16, QW, false>(a, NT16, 0, blockIdx.x, ring);
+        __shared__ u32x4 lds[S::LDS];
+        __shared__ float rstd_s[16 * MT16];
+        qgemm16_rows<MT16, QW, false>(a, NT16, 0, blockIdx.x, lds, rstd_s);
     }
 }
 
@@ -745,12 +778,14 @@ __host__ bool is_small(int M, int Ntot, int K)
 
 template <int EPI> hipError_t launch_large(FusedGemmArgs &a, hipStream_t s, bool *needs_epilogue, hipEvent_t t0, hipEvent_t t1)
 {
-    *needs_epilogue = true;
     const int NT16 = a.Ntot / 16;
     const QPlan p = q_plan(a.Ntot, a.KT * 32, a.M);
     a.J = p.J;
     a.kps = p.kps;
     a.part_rows = round_up(a.M, 16);
+    a.epi = EPI;
+    a.nss_out = a.h >> 4;
+    *needs_epilogue = a.J > 1;   // an unsplit K: the kernel applies the epilogue itself
     if (EPI == FEPI_QKV) { a.seg0 = a.nq * (a.d >> 4); a.seg1 = a.nkv * (a.d >> 4); }
     else if (EPI == FEPI_SWIGLU) { a.seg0 = a.NT; a.seg1 = a.NT; }
     else { a.seg0 = NT16; a.seg1 = 0; }
@@ -817,6 +852,7 @@ template <int EPI> hipError_t launch_small(FusedGemmArgs &a, hipStream_t s, bool
     a.upw = sp.upw;
     a.groups = sp.groups;
     a.part_rows = 16 * sp.rh;
+    a.nss_out = a.h >> 4;
     if (a.J > 1 && (size_t)a.J * a.part_rows * a.Ntot * sizeof(float) > a.partial_bytes) return hipErrorInvalidValue;
     const dim3 grid(groups * a.J * sp.rh), block(PW * 64);
     if (groups * sp.rh > a.tail_slots) a.tail_count = nullptr;   // no counter for every group: epilogue launch
@@ -906,7 +942,7 @@ hipError_t launch_stream_gemm(FusedGemmArgs &a, int epilogue, hipStream_t s, boo
     }
 }
 
-hipError_t launch_stream_epilogue(const FusedGemmArgs &a, int epilogue, hipStream_t s)
+hipError_t launch_stream_epilogue(FusedGemmArgs &a, int epilogue, hipStream_t s)
 {
     switch (epilogue) {
     case FEPI_QKV: return launch_epi<FEPI_QKV>(a, s);
