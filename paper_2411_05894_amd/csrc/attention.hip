@@ -9,24 +9,34 @@
 //
 // One workgroup owns one segment of one sequence's positions for one kv head.  A sequence is cut by
 // its own length (attention_cut, by the kernel that validates the lens): caches with room to grow cost
-// nothing, and what the other sequences hold changes no bit.  (Segments of equal length throughout a
-// ragged batch would load the compute units better: 32 sequences of 1024..4096 at k = 4 65 us against
-// 70 in the step, a schedule of their own apart.)  All g*(k+1) query rows
-// that share the kv head are processed against the segment, one 16-row tile per wave,
-// so every cached byte is read from HBM once per step: the waves stage each block of
-// 32 positions through LDS together (double buffered, the next block's loads in flight
-// during the current block's arithmetic) and every wave reads its operands from there.
-// Per block and wave:
-//   S^T = K . Q^T        (A operand = 16 cached K rows; LDS rows are padded by 32 bytes, the
-//                         pitch at which this 16-rows-by-4-records read of a wave measured free
-//                         of bank conflicts -- 16 bytes of padding cost 1.5x the cycles)
-//   online softmax in registers; the row statistics need only two cross-lane xors
+// nothing, and what the other sequences hold changes no bit.  All g*(k+1) query rows that share the kv
+// head are processed against the segment, up to four 16-row tiles at once, so every cached byte is read
+// from HBM once per step (more tiles: the passes over the cache sit next to each other on a die and share
+// its L2).
+//
+// The four waves of a workgroup take every fourth block of 32 positions each and carry ALL query rows
+// through it: a block's K and V go from memory straight into the registers of the one wave that uses them
+// (both pools are stored in operand order, 1 KiB in a row per load), nothing is staged through LDS and no
+// wave waits for another until the segment is done.  As soon as a block's K (or V) has been used, the next
+// block's is requested into the same registers.  The query operands, the same for every block, are read
+// from LDS (one row tile: kept in registers).  Per block, wave and row tile:
+//   S^T = K . Q^T        (A operand = 16 cached K rows)
+//   online softmax in registers; the row statistics need only two cross-lane swaps
 //   O^T += V^T . P^T     (A operand = V in its block-transposed cache order,
 //                         B operand = the lane's own probabilities)
 // The transposed forms are chosen so that the lane that owns a query row's
 // statistics also owns that row's accumulator columns: no shuffles to rescale.
-// The segments of a sequence are merged by a second kernel in fixed order (deterministic); a
-// sequence that lies in one segment is finished by its workgroup itself.
+// At the end the waves bring their sums to one reference and add them up through LDS, each wave ending with a
+// quarter of the channels.  The segments of a sequence are merged by a second kernel in fixed order
+// (deterministic); a sequence that lies in one segment is finished by its workgroup itself.
+//
+// What bounds it: the cache stream from a few MB per compute unit on (a compute unit pulls 30-35 GB/s), below that the chain
+// from the launch to the first operands and the final sums.  Measured against one wave per row tile with K and V staged
+// through LDS behind two barriers per block, us of sssd_op_attention over cold caches (four small launches in it, 17 us):
+// 8B shape B = 2, k = 17, context 12345 51 -> 45; B = 16, k = 31, 4000 132 -> 105; B = 32, k = 4, 1024..4096 90 -> 80; B = 4, k = 8,
+// 32768 108 -> 105; 70B shape B = 16, k = 8, 2048 71 -> 60.  Two blocks ahead instead of one: 3-8 % slower at one and two row tiles (fewer
+// registers are left to the second workgroup of a compute unit).  K rows in plain order: every load took half of sixteen cache lines, and
+// streaming loads fetched some of them twice (B = 40, k = 3 69 us, 59 now).
 #include "kernels.h"
 
 namespace {
@@ -37,28 +47,60 @@ __device__ __forceinline__ f32x4 mfma(const u32x4 &a, const u32x4 &b, f32x4 c)
 }
 
 constexpr float NEG_BIG = -1.0e30f;
-constexpr int MAX_WAVES = 6;   // query-row tiles per launch
+constexpr int MAX_TILES = 4;   // query-row tiles of a pass
+constexpr int NWAVE = 4;       // waves of a workgroup, each on every fourth block of the segment
 
-// grid = (B * share * kv heads, passes over the row tiles); block = NW waves; wave w owns query-row tile pass * NW + w.
-// Workgroups 8 apart run on one die, where the heads of a segment follow each other: they read one page (64 KiB of K at
-// eight heads of 128) at about the same time (B = 4, context 32768: 101 us with the heads 64 workgroups apart, 96 us so).
-// The kernel is bound by bytes in flight, i.e. by resident workgroups: with three or more waves the
-// register allocator is held to three waves per SIMD (four workgroups per compute unit).
-template <int HD, int NW>
-__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW >= 3 ? 3 : NW, 3))) void attn_partial_kernel(Dims D, AttnArgs a, int q_rows_pad)
+// max / sum over the four lanes 16 apart that share a query row
+__device__ __forceinline__ float rows_max(float x)
+{
+    auto h = __builtin_amdgcn_permlane32_swap(f32_bits(x), f32_bits(x), false, false);
+    x = fmaxf(bits_f32(h[0]), bits_f32(h[1]));
+    h = __builtin_amdgcn_permlane16_swap(f32_bits(x), f32_bits(x), false, false);
+    return fmaxf(bits_f32(h[0]), bits_f32(h[1]));
+}
+__device__ __forceinline__ float rows_sum(float x)
+{
+    auto h = __builtin_amdgcn_permlane32_swap(f32_bits(x), f32_bits(x), false, false);
+    x = bits_f32(h[0]) + bits_f32(h[1]);
+    h = __builtin_amdgcn_permlane16_swap(f32_bits(x), f32_bits(x), false, false);
+    return bits_f32(h[0]) + bits_f32(h[1]);
+}
+
+__device__ __forceinline__ f32x4 pick(bool first, f32x4 x, f32x4 y)   // by value: selected by address, arrays would go to scratch memory
+{
+    return f32x4{first ? x[0] : y[0], first ? x[1] : y[1], first ? x[2] : y[2], first ? x[3] : y[3]};
+}
+
+// grid = B * share * kv heads * passes over the row tiles; block = four waves; RT row tiles per pass; ONCE: a single pass.
+// Workgroups 8 apart run on one die, where the passes and then the heads of a segment follow each other: they read one page
+// (64 KiB of K at eight heads of 128) at about the same time.  Two waves per SIMD: two workgroups fit a compute unit.
+template <int HD, int RT, bool ONCE>
+__global__ __launch_bounds__(NWAVE * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_partial_kernel(Dims D, AttnArgs a, int q_rows_pad, int passes)
 {
     constexpr int KS = HD / 32, DT = HD / 16;
-    constexpr int CPR = HD / 8;          // 16-byte records per cached K row
-    constexpr int KROW = CPR + 2;        // LDS row pitch in records (two records of padding)
-    constexpr int NREC = 32 * CPR;       // records of a 32-position block, K and V alike
-    constexpr int T = NW * 64;
-    constexpr int SPT = (NREC + T - 1) / T;   // records staged per thread and operand
-    __shared__ u32x4 Ks[2][32 * KROW];
-    __shared__ u32x4 Vs[2][NREC];
+    constexpr int NREC = 4 * HD;             // 16-byte records of a block of 32 positions, K and V alike
+    constexpr bool QREG = RT == 1;           // query operands in registers, else in LDS
+    constexpr int QREC = RT * KS * 2 * 64, RRED = NWAVE * RT * (DT / 2) * 64;   // records of the query tiles, of the final sums
+    __shared__ u32x4 lds[QREC > RRED ? QREC : RRED];
+    __shared__ float2 ml_s[NWAVE][RT * 16];
 
     int kvh, wg;   // kv head; (turn, segment)
+    int pass = 0;
     {
-        const int id = blockIdx.x, whole = (a.B * a.plan.share) & ~7;
+        int id = blockIdx.x;
+        if (passes > 1) {
+            const int n = a.B * a.plan.share * D.nkv, sets = n & ~7;
+            if (id < sets * passes) {
+                const int x = id / (8 * passes), r = id - x * 8 * passes;
+                pass = r >> 3;
+                id = x * 8 + (r & 7);
+            } else {
+                const int r = id - sets * passes;
+                pass = r / (n - sets);
+                id = sets + r % (n - sets);
+            }
+        }
+        const int whole = (a.B * a.plan.share) & ~7;
         if (id < whole * D.nkv) {
             wg = id / (8 * D.nkv) * 8 + (id & 7);
             kvh = (id >> 3) % D.nkv;
@@ -73,200 +115,239 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW >= 3
     const int b = me.b, len = me.len, total = len + a.k + 1;   // a rejected sequence is read as empty
     const AttnCut cut = me.cut;
     if (segment >= cut.n) return;
-    const int t_begin = segment * cut.each * 32;
-    const int t_end = min(total, t_begin + cut.each * 32);
+    const int first_blk = segment * cut.each, n_blk = min(cut.each, ((total + 31) >> 5) - first_blk);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int q = lane >> 4, c = lane & 15;
-    const int rt = min((int)blockIdx.y * NW + wave, (q_rows_pad >> 4) - 1);   // the last pass may have waves to spare: they repeat a tile
-    const bool row_tile_ok = (int)blockIdx.y * NW + wave < a.row_tiles;
+    const int rt0 = pass * RT, n_it = n_blk > wave ? (n_blk - wave + NWAVE - 1) / NWAVE : 0;
 
-    // Pages of the segment's blocks: lane l keeps the page of block first_blk + 64*group + l, so the
-    // page of any block of the current group of 64 is one cross-lane read away.
-    const u32x4 *Kpool = reinterpret_cast<const u32x4 *>(a.Kc), *Vpool = reinterpret_cast<const u32x4 *>(a.Vc);
-    const int first_blk = t_begin >> 5;
-    int pg_group = 0;
-    auto load_pages = [&](int group) {
-        const int blk = min(first_blk + 64 * group + lane, a.kv.blocks_per_seq - 1);
-        return kv_page(a.kv, b, blk);
-    };
-    int pg = load_pages(0);
-    // 16-byte record offset of block (t0 / 32) of this (sequence, kv head) in either pool
-    auto block_records = [&](int t0) -> size_t {
-        const int rel = (t0 >> 5) - first_blk;
-        if ((rel >> 6) != pg_group) {   // wave-uniform, once per 64 blocks
-            pg_group = rel >> 6;
-            pg = load_pages(pg_group);
-        }
-        const int page = __shfl(pg, rel & 63);
-        return (((size_t)page * D.nkv + kvh) * 32 * HD) >> 3;
-    };
-    const u32x4 *Qs = reinterpret_cast<const u32x4 *>(a.Qp + ((size_t)b * D.nkv + kvh) * q_rows_pad * HD) + (size_t)rt * KS * 64 + lane;
-    const u32x4 *Ql = reinterpret_cast<const u32x4 *>(a.Qp_lo + ((size_t)b * D.nkv + kvh) * q_rows_pad * HD) + (size_t)rt * KS * 64 + lane;
+    // Pages of this wave's blocks: lane l keeps the page of its block number 64 * chunk + l, one chunk ahead of the next.
+    auto load_pages = [&](int chunk) { return kv_page(a.kv, b, min(first_blk + wave + NWAVE * (64 * chunk + lane), a.kv.blocks_per_seq - 1)); };
+    int chunk = 0, pg = load_pages(0), pg_next = load_pages(1);
 
-    // staging: record i of a block; K rows are contiguous in the cache, so is a whole V block.
-    // Two register stages: while block i is processed out of LDS, block i+1 sits in one stage
-    // (loaded during the previous iteration, moved to LDS at the end of this one) and block i+2 is
-    // being fetched into the other, so two blocks (32 KiB with d = 128) are in flight per workgroup.
-    // Every load is issued unconditionally -- past the segment's end all lanes re-read one record of the
-    // last block (a single cache line of traffic), which is never stored -- because a load under a
-    // branch would make every later wait a full drain.
-    struct Stage {
-        u32x4 k[SPT], v[SPT];
+    // Query operands of tile t: hi and lo parts (q ~= hi + lo, so the scores carry fp32-level accuracy although K is bf16)
+    auto query = [&](int t, int ks, int part) {
+        const int rt = min(rt0 + t, (q_rows_pad >> 4) - 1);   // the last pass may have tiles to spare: they repeat one
+        const uint16_t *base = part ? a.Qp_lo : a.Qp;
+        return reinterpret_cast<const u32x4 *>(base + ((size_t)b * D.nkv + kvh) * q_rows_pad * HD) + ((size_t)rt * KS + ks) * 64;
     };
-    const int t_last = t_begin + ((t_end - t_begin - 1) & ~31);   // first position of the segment's last block
-    auto stage_load = [&](Stage &st, int t0) {
-        const bool past = t0 > t_last;   // nothing left to fetch: every lane reads one and the same record
-        if (past) t0 = t_last;
-        const size_t base = block_records(t0);
+    u32x4 qreg[QREG ? KS : 1][2];
+    constexpr int QPT = QREG ? 1 : RT * KS * 2 / NWAVE;   // operand tiles copied per wave
+    u32x4 qcopy[QPT];
+    if (QREG) {
 #pragma unroll
-        for (int i = 0; i < SPT; ++i) {
-            int rec = threadIdx.x + i * T;
-            if (NREC % T != 0 && rec >= NREC) rec = NREC - 1;
-            if (past) rec = 0;
-            st.k[i] = __builtin_nontemporal_load(Kpool + base + rec);
-            st.v[i] = __builtin_nontemporal_load(Vpool + base + rec);
+        for (int ks = 0; ks < KS; ++ks) {
+            qreg[QREG ? ks : 0][0] = query(0, ks, 0)[lane];
+            qreg[QREG ? ks : 0][1] = query(0, ks, 1)[lane];
         }
-    };
-    auto stage_store = [&](int buf, const Stage &st) {
+    } else {
 #pragma unroll
-        for (int i = 0; i < SPT; ++i) {
-            const int rec = threadIdx.x + i * T;
-            if (NREC % T == 0 || rec < NREC) {
-                Ks[buf][(rec / CPR) * KROW + rec % CPR] = st.k[i];
-                Vs[buf][rec] = st.v[i];
-            }
+        for (int i = 0; i < QPT; ++i) {
+            const int x = wave * QPT + i;   // [tile][ks][part]
+            qcopy[i] = query(x / (2 * KS), (x >> 1) % KS, x & 1)[lane];
         }
-    };
-    Stage sa, sb;
-    stage_load(sa, t_begin);
-
-    // q ~= hi + lo (two bf16), so the scores carry fp32-level accuracy although K is bf16.
-    u32x4 qreg[KS], qlo[KS];
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-        qreg[ks] = Qs[ks * 64];
-        qlo[ks] = Ql[ks * 64];
     }
-    f32x4 o[DT];
-#pragma unroll
-    for (int dt = 0; dt < DT; ++dt) o[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
-    float m_run = NEG_BIG, l_run = 0.f;
-    int j = (rt * 16 + c) / D.g;   // query row -> node of the chain or tree
-    if (j > a.k) j = a.k;
-    const uint32_t vis = a.anc[b * (a.k + 1) + j];   // visible new rows: bit i = cache row len + i
-    const float scale = 1.4426950408889634f * rsqrtf((float)HD);  // log2(e)/sqrt(d)
 
-    stage_store(0, sa);
-    stage_load(sa, t_begin + 32);
-    __syncthreads();
-
-    // one block of 32 positions out of LDS buffer `buf`
-    auto block = [&](int buf, int t0) {
-        f32x4 s[2];
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            s[u] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int ks = 0; ks < KS; ++ks) {
-                const u32x4 kk = Ks[buf][(16 * u + c) * KROW + ks * 4 + q];
-                s[u] = mfma(kk, qreg[ks], s[u]);
-                s[u] = mfma(kk, qlo[ks], s[u]);
-            }
-        }
-        // s[u][r] is the score of position t0 + 16u + 4q + r for query row rt*16 + c.
-        float v[8];
+    // A block's operands.  Every load is issued unconditionally -- past the end all lanes re-read records of the last block, for
+    // nothing -- because a load under a branch would make every later wait a full drain.  A single pass streams; several passes
+    // find K, and mostly V, in the die's L2.
+    u32x4 k[2][KS], v[DT];
+    auto block_base = [&](int i) -> size_t {   // first record of the wave's block i, past the end of its last one
+        i = i < n_it ? i : (n_it > 0 ? n_it - 1 : 0);
+        const int x = __builtin_amdgcn_readlane(i >> 6 == chunk ? pg : pg_next, i & 63);
+        return ((size_t)x * D.nkv + kvh) * NREC;
+    };
+    auto load_k = [&](int i) {
+        const u32x4 *p = reinterpret_cast<const u32x4 *>(a.Kc) + block_base(i) + (i < n_it ? lane : 0);
 #pragma unroll
         for (int u = 0; u < 2; ++u)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) v[u * 4 + r] = s[u][r] * scale;
-        if (t0 + 32 > len) {   // the block holds new rows: apply the node's visibility word
-#pragma unroll
-            for (int u = 0; u < 2; ++u)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int rel = t0 + 16 * u + 4 * q + r - len;   // < 0: old cache, always visible
-                    if (rel >= 0 && (rel > 31 || !((vis >> rel) & 1u))) v[u * 4 + r] = NEG_BIG;
-                }
-        }
-        float mx = fmaxf(fmaxf(fmaxf(v[0], v[1]), fmaxf(v[2], v[3])), fmaxf(fmaxf(v[4], v[5]), fmaxf(v[6], v[7])));
-        mx = fmaxf(mx, __shfl_xor(mx, 16));
-        mx = fmaxf(mx, __shfl_xor(mx, 32));
-        // The exponent's reference m_run follows the running maximum lazily: it moves (and the
-        // accumulators are rescaled) only when some row's maximum has outgrown it by more than 2^8,
-        // so most blocks skip the rescale.  Any reference gives the same softmax; probabilities stay
-        // below 2^8 and the partial (o, l, m_run) handed to the merge is consistent with it.
-        if (__any(mx > m_run + 8.f)) {
-            const float m_new = fmaxf(m_run, mx);
-            const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
-            m_run = m_new;
-            l_run *= alpha;
-#pragma unroll
-            for (int dt = 0; dt < DT; ++dt) o[dt] *= alpha;
-        }
-        float psum = 0.f;
-        uint32_t pk[4], pkl[4];
-#pragma unroll
-        for (int e = 0; e < 8; e += 2) {
-            const float p0 = __builtin_amdgcn_exp2f(v[e] - m_run), p1 = __builtin_amdgcn_exp2f(v[e + 1] - m_run);
-            split_bf16x2(p0, p1, pk[e >> 1], pkl[e >> 1]);   // p ~= hi + lo: the probabilities keep ~16 mantissa bits
-            psum += p0 + p1;
-        }
-        l_run += psum;
-        const u32x4 pb = u32x4{pk[0], pk[1], pk[2], pk[3]}, pl = u32x4{pkl[0], pkl[1], pkl[2], pkl[3]};
-#pragma unroll
-        for (int dt = 0; dt < DT; ++dt) {
-            const u32x4 vv = Vs[buf][dt * 64 + lane];
-            o[dt] = mfma(vv, pb, o[dt]);
-            o[dt] = mfma(vv, pl, o[dt]);
-        }
+            for (int ks = 0; ks < KS; ++ks) k[u][ks] = ONCE ? __builtin_nontemporal_load(p + (u * KS + ks) * 64) : p[(u * KS + ks) * 64];
     };
+    auto load_v = [&](int i) {
+        const u32x4 *p = reinterpret_cast<const u32x4 *>(a.Vc) + block_base(i) + (i < n_it ? lane : 0);
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt) v[dt] = __builtin_nontemporal_load(p + dt * 64);
+    };
+    uint32_t vis[RT];   // visible new rows of query row c of each tile: bit i = cache row len + i
+#pragma unroll
+    for (int t = 0; t < RT; ++t) vis[t] = 0;
+    if ((first_blk + n_blk) * 32 > len) {
+#pragma unroll
+        for (int t = 0; t < RT; ++t) {
+            const int j = min(((rt0 + t) * 16 + c) / D.g, a.k);   // query row -> node of the chain or tree
+            vis[t] = a.anc[b * (a.k + 1) + j];
+        }
+    }
+    load_k(0);
+    load_v(0);
 
-    // Entering an iteration at t0: LDS buffer 0 holds block t0, stage sa block t0+32.  The LDS buffer
-    // written at the end of a half-iteration was read in the previous one, which every wave left
-    // through a barrier before anyone got here.
-    for (int t0 = t_begin; t0 < t_end; t0 += 64) {
-        stage_load(sb, t0 + 64);
-        block(0, t0);
-        if (t0 + 32 >= t_end) break;
-        stage_store(1, sa);
-        __syncthreads();
-        stage_load(sa, t0 + 96);
-        block(1, t0 + 32);
-        if (t0 + 64 >= t_end) break;
-        stage_store(0, sb);
+    f32x4 o[RT][DT];
+    float m_run[RT], l_run[RT];
+#pragma unroll
+    for (int t = 0; t < RT; ++t) {
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt) o[t][dt] = f32x4{0.f, 0.f, 0.f, 0.f};
+        m_run[t] = NEG_BIG;
+        l_run[t] = 0.f;
+    }
+    if (!QREG) {
+#pragma unroll
+        for (int i = 0; i < QPT; ++i) lds[(wave * QPT + i) * 64 + lane] = qcopy[i];
         __syncthreads();
     }
+    const float scale = 1.4426950408889634f * rsqrtf((float)HD);  // log2(e)/sqrt(d)
 
-    // o[dt][r] of lane (q, c): channel dt*16 + 4q + r of query row rt*16 + c.
-    float l = l_run;
-    l += __shfl_xor(l, 16);
-    l += __shfl_xor(l, 32);
-    const int row = rt * 16 + c;
-    if (cut.n == 1) {   // the whole sequence: the packed operands of the O projection
-        const int jj = row / D.g, hl = row - jj * D.g;
-        if (row_tile_ok && jj <= a.k) {
-            const float inv = 1.f / l;
-            const int m = b * (a.k + 1) + jj, KTq = (D.qd + 31) >> 5;
-            const size_t idx = packed_index(m, (kvh * D.g + hl) * HD + 4 * q, KTq);
+    for (int i = 0; i < n_it; ++i) {
+        if (i >> 6 != chunk) {   // once per 64 blocks
+            chunk = i >> 6;
+            pg = pg_next;
+            pg_next = load_pages(chunk + 1);
+        }
+        int ql = lane;
+        asm volatile("" : "+v"(ql));   // the query operands are read again for every block: hoisted, they would not fit the registers
+        // s[t][u][r]: score of position t0 + 16u + 4q + r for query row c of tile t
+        f32x4 s[RT][2];
 #pragma unroll
-            for (int dt = 0; dt < DT; ++dt) {
-                uint32_t h0, l0, h1, l1;
-                split_bf16x2(o[dt][0] * inv, o[dt][1] * inv, h0, l0);
-                split_bf16x2(o[dt][2] * inv, o[dt][3] * inv, h1, l1);
-                // channels dt*16 + 4q ..+3: half of lane record 2*(dt%2) + q/2 of k-tile dt/2 of the head
-                const size_t at = idx + (size_t)(dt >> 1) * 512 + (size_t)(dt & 1) * 256;
-                *reinterpret_cast<uint2 *>(a.out_hi + at) = uint2{h0, h1};
-                *reinterpret_cast<uint2 *>(a.out_lo + at) = uint2{l0, l1};
+        for (int t = 0; t < RT; ++t) {
+            s[t][0] = s[t][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) {
+                const u32x4 hi = QREG ? qreg[QREG ? ks : 0][0] : lds[((t * KS + ks) * 2) * 64 + ql];
+                const u32x4 lo = QREG ? qreg[QREG ? ks : 0][1] : lds[((t * KS + ks) * 2 + 1) * 64 + ql];
+#pragma unroll
+                for (int u = 0; u < 2; ++u) s[t][u] = mfma(k[u][ks], hi, s[t][u]);
+#pragma unroll
+                for (int u = 0; u < 2; ++u) s[t][u] = mfma(k[u][ks], lo, s[t][u]);
             }
         }
-    } else if (row_tile_ok) {
-        const size_t at = (((size_t)kvh * a.B + b) * a.plan.share + segment) * q_rows_pad + row;
-        float *po = a.part_o + at * HD;
+        load_k(i + 1);
+        const int t0 = (first_blk + wave + NWAVE * i) * 32;
+        if (t0 + 32 > len) {   // the block holds new rows: apply the nodes' visibility words
 #pragma unroll
-        for (int dt = 0; dt < DT; ++dt) *reinterpret_cast<f32x4 *>(po + dt * 16 + 4 * q) = o[dt];
-        if (q == 0) {
-            a.part_ml[at * 2] = m_run;
-            a.part_ml[at * 2 + 1] = l;
+            for (int t = 0; t < RT; ++t)
+#pragma unroll
+                for (int u = 0; u < 2; ++u)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const int rel = t0 + 16 * u + 4 * q + r - len;   // < 0: old cache, always visible
+                        if (rel >= 0 && (rel > 31 || !((vis[t] >> rel) & 1u))) s[t][u][r] = -INFINITY;
+                    }
+        }
+        // The exponent's reference m_run follows the running maximum lazily: it moves (and the accumulators are rescaled)
+        // only when some row's maximum has outgrown it by more than 2^8, so most blocks skip the rescale.  Any reference gives
+        // the same softmax; probabilities stay below 2^8 and the partial (o, l, m_run) handed on is consistent with it.
+        float mx[RT];
+        bool grow = false;
+#pragma unroll
+        for (int t = 0; t < RT; ++t) {
+            mx[t] = fmaxf(fmaxf(fmaxf(s[t][0][0], s[t][0][1]), fmaxf(s[t][0][2], s[t][0][3])),
+                          fmaxf(fmaxf(s[t][1][0], s[t][1][1]), fmaxf(s[t][1][2], s[t][1][3])));
+            mx[t] = rows_max(mx[t]) * scale;
+            grow = grow || mx[t] > m_run[t] + 8.f;
+        }
+        if (__any(grow)) {
+#pragma unroll
+            for (int t = 0; t < RT; ++t) {
+                const float m_new = mx[t] > m_run[t] + 8.f ? mx[t] : m_run[t], alpha = __builtin_amdgcn_exp2f(m_run[t] - m_new);
+                m_run[t] = m_new;
+                l_run[t] *= alpha;
+#pragma unroll
+                for (int dt = 0; dt < DT; ++dt) o[t][dt] *= alpha;
+            }
+        }
+#pragma unroll
+        for (int t = 0; t < RT; ++t) {
+            uint32_t pk[4], pkl[4];
+            float psum = 0.f;
+#pragma unroll
+            for (int e = 0; e < 8; e += 2) {
+                const float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[t][e >> 2][e & 3], scale, -m_run[t]));
+                const float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[t][e >> 2][(e & 3) + 1], scale, -m_run[t]));
+                split_bf16x2(p0, p1, pk[e >> 1], pkl[e >> 1]);   // p ~= hi + lo: the probabilities keep ~16 mantissa bits
+                psum += p0 + p1;
+            }
+            l_run[t] += psum;
+            const u32x4 pb = u32x4{pk[0], pk[1], pk[2], pk[3]}, pl = u32x4{pkl[0], pkl[1], pkl[2], pkl[3]};
+#pragma unroll
+            for (int dt = 0; dt < DT; ++dt) o[t][dt] = mfma(v[dt], pb, o[t][dt]);
+#pragma unroll
+            for (int dt = 0; dt < DT; ++dt) o[t][dt] = mfma(v[dt], pl, o[t][dt]);
+        }
+        load_v(i + 1);
+    }
+
+    // The waves' sums on one reference per query row, then added up: every wave ends with a quarter of the channels of all rows.
+#pragma unroll
+    for (int t = 0; t < RT; ++t) {
+        l_run[t] = rows_sum(l_run[t]);
+        if (q == 0) ml_s[wave][t * 16 + c] = float2{m_run[t], l_run[t]};
+    }
+    __syncthreads();   // the query tiles have been read
+    float m_all[RT], l_all[RT];
+#pragma unroll
+    for (int t = 0; t < RT; ++t) {
+        float2 x[NWAVE];
+#pragma unroll
+        for (int w = 0; w < NWAVE; ++w) x[w] = ml_s[w][t * 16 + c];
+        m_all[t] = fmaxf(fmaxf(x[0].x, x[1].x), fmaxf(x[2].x, x[3].x));
+        l_all[t] = 0.f;
+#pragma unroll
+        for (int w = 0; w < NWAVE; ++w) l_all[t] += x[w].y * __builtin_amdgcn_exp2f(x[w].x - m_all[t]);
+        const float f = __builtin_amdgcn_exp2f(m_run[t] - m_all[t]);
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt) o[t][dt] *= f;
+    }
+    f32x4 *red = reinterpret_cast<f32x4 *>(lds);
+    constexpr int H = DT / 2, QT = DT / 4;
+    const bool up2 = wave >> 1, up1 = wave & 1;
+#pragma unroll
+    for (int t = 0; t < RT; ++t)
+#pragma unroll
+        for (int x = 0; x < H; ++x) red[((wave * RT + t) * H + x) * 64 + lane] = pick(up2, o[t][x], o[t][H + x]);
+    __syncthreads();
+    f32x4 oh[RT][H];
+#pragma unroll
+    for (int t = 0; t < RT; ++t)
+#pragma unroll
+        for (int x = 0; x < H; ++x) oh[t][x] = pick(up2, o[t][H + x], o[t][x]) + red[(((wave ^ 2) * RT + t) * H + x) * 64 + lane];
+    __syncthreads();
+#pragma unroll
+    for (int t = 0; t < RT; ++t)
+#pragma unroll
+        for (int x = 0; x < QT; ++x) red[((wave * RT + t) * QT + x) * 64 + lane] = pick(up1, oh[t][x], oh[t][QT + x]);
+    __syncthreads();
+    const int dt0 = (up2 ? H : 0) + (up1 ? QT : 0);
+#pragma unroll
+    for (int t = 0; t < RT; ++t) {
+        f32x4 y[QT];   // y[x][r]: channel (dt0 + x) * 16 + 4q + r of query row c of tile t
+#pragma unroll
+        for (int x = 0; x < QT; ++x) y[x] = pick(up1, oh[t][QT + x], oh[t][x]) + red[(((wave ^ 1) * RT + t) * QT + x) * 64 + lane];
+        const int row = (rt0 + t) * 16 + c;
+        if (rt0 + t >= a.row_tiles) continue;
+        if (cut.n == 1) {   // the whole sequence: the packed operands of the O projection
+            const int jj = row / D.g, hl = row - jj * D.g;
+            if (jj <= a.k) {
+                const float inv = 1.f / l_all[t];
+                const int m = b * (a.k + 1) + jj, KTq = (D.qd + 31) >> 5;
+                const size_t idx = packed_index(m, (kvh * D.g + hl) * HD + 4 * q, KTq);
+#pragma unroll
+                for (int x = 0; x < QT; ++x) {
+                    const int dt = dt0 + x;
+                    uint32_t h0, l0, h1, l1;
+                    split_bf16x2(y[x][0] * inv, y[x][1] * inv, h0, l0);
+                    split_bf16x2(y[x][2] * inv, y[x][3] * inv, h1, l1);
+                    // channels dt*16 + 4q ..+3: half of lane record 2*(dt%2) + q/2 of k-tile dt/2 of the head
+                    const size_t at = idx + (size_t)(dt >> 1) * 512 + (size_t)(dt & 1) * 256;
+                    *reinterpret_cast<uint2 *>(a.out_hi + at) = uint2{h0, h1};
+                    *reinterpret_cast<uint2 *>(a.out_lo + at) = uint2{l0, l1};
+                }
+            }
+        } else {
+            const size_t at = (((size_t)kvh * a.B + b) * a.plan.share + segment) * q_rows_pad + row;
+            float *po = a.part_o + at * HD;
+#pragma unroll
+            for (int x = 0; x < QT; ++x) *reinterpret_cast<f32x4 *>(po + (dt0 + x) * 16 + 4 * q) = y[x];
+            if (wave == 0 && q == 0) *reinterpret_cast<float2 *>(a.part_ml + at * 2) = float2{m_all[t], l_all[t]};
         }
     }
 }
@@ -351,17 +432,15 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(Dims D, AttnArgs a, i
 
 template <int HD> hipError_t launch_partial(const Dims &D, const AttnArgs &a, int q_rows_pad, hipStream_t s)
 {
-    // One wave per query-row tile; more than MAX_WAVES tiles are spread evenly over several passes over the cache.
-    const int passes = (a.row_tiles + MAX_WAVES - 1) / MAX_WAVES, nw = (a.row_tiles + passes - 1) / passes;
-    const dim3 grid(a.B * a.plan.share * D.nkv, passes);
-#define SSSD_ALAUNCH(NW) hipLaunchKernelGGL((attn_partial_kernel<HD, NW>), grid, dim3(NW * 64), 0, s, D, a, q_rows_pad)
-    switch (nw) {
-    case 1: SSSD_ALAUNCH(1); break;
-    case 2: SSSD_ALAUNCH(2); break;
-    case 3: SSSD_ALAUNCH(3); break;
-    case 4: SSSD_ALAUNCH(4); break;
-    case 5: SSSD_ALAUNCH(5); break;
-    default: SSSD_ALAUNCH(6); break;
+    // More than MAX_TILES tiles are spread evenly over several passes over the cache.
+    const int passes = (a.row_tiles + MAX_TILES - 1) / MAX_TILES, rt = (a.row_tiles + passes - 1) / passes;
+    const dim3 grid(a.B * a.plan.share * D.nkv * passes);
+#define SSSD_ALAUNCH(RT, ONCE) hipLaunchKernelGGL((attn_partial_kernel<HD, RT, ONCE>), grid, dim3(NWAVE * 64), 0, s, D, a, q_rows_pad, passes)
+    switch (rt) {
+    case 1: SSSD_ALAUNCH(1, true); break;
+    case 2: SSSD_ALAUNCH(2, true); break;
+    case 3: if (passes == 1) SSSD_ALAUNCH(3, true); else SSSD_ALAUNCH(3, false); break;
+    default: if (passes == 1) SSSD_ALAUNCH(4, true); else SSSD_ALAUNCH(4, false); break;
     }
 #undef SSSD_ALAUNCH
     return hipGetLastError();
@@ -369,42 +448,25 @@ template <int HD> hipError_t launch_partial(const Dims &D, const AttnArgs &a, in
 
 }  // namespace
 
-// Segments per sequence.  The device holds four workgroups per compute unit with up to three waves (row tiles) each, three
-// with four waves, two with five or six, i.e. 1024 / 768 / 512 at once, and a launch is kept to one such round.  Within it
-// fewer and longer segments are faster (every segment is a partial result of g*(k+1) rows to write and merge, and HBM
-// serves 512 concurrent streams better than 1024), until compute units stand idle or ragged batches load them unevenly.  Measured as sssd_op_attention over the
-// caches of enough layers (1 GB) that nothing stays in a cache, us, all sequences at 4000 / at 1333..4000, by segments per
-// sequence (workgroups):
-//   up to four waves, 512 workgroups, or 768 where more than a sixth of 512 would be missing.  8B shape:
-//     k = 8, B = 13: 2 (208) 83 / 83, 4 (416) 66 / 65, 7 (728) 67 / 62, 9 (936) 69 / 63
-//     k = 8, B = 24: 2 (384) 103 / 97, 3 (576) 102 / 83, 4 (768) 98 / 83, 5 (960) 106 / 88
-//     k = 4, B = 32: 1 (256) 122 / 120, 2 (512) 105 / 91, 3 (768) 111 / 90, 4 (1024) 112 / 91
-//     k = 4, B = 4: 8 (256) 35 / 35, 16 (512) 33 / 33, 24 (768) 36 / 34, 32 (1024) 38 / 36
-//   one wave and fewer than six segments by that, 768, or 1024 for three: it needs them to even out ragged batches:
-//     k = 0, B = 16: 2 (256) 79 / 79, 4 (512) 60 / 54, 6 (768) 60 / 50, 8 (1024) 62 / 50
-//     k = 0, B = 40, 2000 / 667..2000: 1 (320) 82 / 79, 2 (640) 70 / 60, 3 (960) 70 / 56
-//   five and six waves, 256, where that leaves at most a quarter of the compute units idle, else 512.  70B shape, k = 8:
-//     B = 4: 8 (256) 50 / 50, 12 (384) 57 / 56, 16 (512) 53 / 53; B = 16: 2 (256) 101 / 100, 3 (384) 123 / 105, 4 (512) 107 / 96
-//     B = 11: 2 (176) 97 / 96, 4 (352) 104 / 89, 5 (440) 94 / 81; B = 24: 1 (192) 155 / 153, 2 (384) 169 / 148
-// At least four blocks per segment: 2 / 4 / 8 blocks at B = 1, k = 8 8B context 2048 26.4 / 25.2 / 27.8, 70B B = 2 context
-// 1000 35.0 / 34.1 / 36.9, 8B context 300 22.0 / 23.0 / 24.2.  More than four row tiles make partial results dear: at least
-// 16 blocks as soon as segments of that length fill the compute units (B = 16, k = 31, context 479 58 -> 56).
+// Segments per sequence.  One workgroup per compute unit: what bounds a launch is the bytes that the busiest compute unit
+// pulls, and every segment is a partial result of g*(k+1) rows to write and merge.  Two workgroups fit a compute unit; they are
+// asked for where 256 leave a quarter of the device idle and the cache is passed over more than once.  sssd_op_attention over cold
+// caches, us, all sequences at 3000 / at 1000..3000, by workgroups:
+//   one pass, 8B: k = 8, B = 5: 240 35 / 33, 360 38 / 37, 480 38 / 37; B = 12: 192 50 / 47, 384 54 / 47, 480 53 / 48; B = 24: 192 68 / 62, 384 81 / 66;
+//     k = 4, B = 20: 160 57 / 52, 320 72 / 59, 480 66 / 56; 70B, k = 0, B = 20: 160 59 / 55, 480 64 / 53
+//   two passes: 70B, k = 8, B = 4: 256 42 / 41, 512 44 / 41; B = 9: 144 66 / 65, 432 61 / 55; B = 12: 192 67 / 66, 384 72 / 64; 8B, B = 10, k = 31:
+//     160 79 / 78, 480 71 / 63; B = 12, k = 24: 192 79 / 78, 384 79 / 68; B = 16, k = 31, context 1000: 256 55, 512 67
+// At least four blocks per segment, one for each wave; up to eight blocks are one segment, which needs no merge (tiny shape, one
+// sequence of 133 positions: step 73.5 -> 68.6 us).
 AttnPlan attention_plan(const Dims &D, int B, int k)
 {
     const int tiles = (D.g * (k + 1) + 15) / 16;
-    const int passes = (tiles + MAX_WAVES - 1) / MAX_WAVES, waves = (tiles + passes - 1) / passes;
+    const int passes = (tiles + MAX_TILES - 1) / MAX_TILES;
     const long units = (long)B * D.nkv * passes;   // workgroups for one segment of every sequence
-    long share;
-    if (waves >= 5) {
-        share = 256 / units * units >= 192 ? 256 / units : 512 / units;
-    } else {
-        share = 512 / units;
-        if (share * units < 426 || (waves == 1 && share < 6)) share = 768 / units;
-        if (waves == 1 && share < 3) share = 1024 / units;
-    }
+    long share = 256 / units;
+    if (passes > 1 && share * units <= 192) share = 512 / units;
     AttnPlan p;
     p.share = share < 1 ? 1 : (share > ATTN_MAX_SEGMENTS ? ATTN_MAX_SEGMENTS : (int)share);
-    p.long_blocks = tiles > 4 ? (int)((16 * 256 + units - 1) / units) : 0x7FFFFFFF;
     return p;
 }
 

@@ -55,12 +55,16 @@ __host__ __device__ __forceinline__ size_t packed_index(int r, int k, int KT)
 
 // ---- KV cache: pages of 32 positions ---------------------------------------------
 // The cache of one layer is a pool of pages; a page holds 32 consecutive positions of ONE sequence for
-// all kv heads: K as [kv head][32 rows][head_dim] (row-major), V as [kv head][head_dim/16 operand
+// all kv heads: K as [kv head][2 x head_dim/32 operand tiles of 1 KiB], V as [kv head][head_dim/16 operand
 // tiles of 1 KiB].  Block i of sequence b (positions 32i .. 32i+31) lives in page table[b][i], or in
 // page b * blocks_per_seq + i when no table is set (every sequence then owns a contiguous run of
 // pages).  A (sequence, kv head, block) is 32*head_dim contiguous bf16 in both caches: the unit the
 // attention kernel streams.
 //
+// Within a K block, tile u * head_dim/32 + ks holds rows 16u .. 16u+15 and channels 32ks .. 32ks+31 in the order of
+// packed_index: what a score MFMA reads is 1 KiB in a row.  bf16 index of (row r of the block, channel ch):
+__host__ __device__ __forceinline__ size_t kblock_index(int r, int ch, int head_dim) { return packed_index(r, ch, head_dim >> 5); }
+
 // Within a V block, lane l = 16*q + c of tile dt holds channel dt*16 + c at the 8 positions
 // {4q..4q+3} u {16+4q..16+4q+3} of the block: exactly the positions whose scores that lane owns
 // after the two 16-position score MFMAs, so probabilities feed the second MFMA without any
@@ -105,7 +109,7 @@ __device__ __forceinline__ size_t kv_block_offset(const KvGeom &g, int page, int
 // bf16 offsets of element (position t, channel ch) of (sequence b, kv head kvh)
 __device__ __forceinline__ size_t kcache_offset(const KvGeom &g, int b, int kvh, int t, int ch)
 {
-    return kv_block_offset(g, kv_page(g, b, t >> 5), kvh) + (size_t)(t & 31) * g.d + ch;
+    return kv_block_offset(g, kv_page(g, b, t >> 5), kvh) + kblock_index(t & 31, ch, g.d);
 }
 __device__ __forceinline__ size_t vcache_offset(const KvGeom &g, int b, int kvh, int t, int ch)
 {

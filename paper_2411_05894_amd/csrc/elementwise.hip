@@ -138,8 +138,8 @@ __global__ void rollback_kernel(int B, int32_t *lens, const int32_t *accepted_le
 }
 
 // grid = (blocks of 32 positions that the rows touch, nkv), 256 threads.  ext layout [nkv][n_rows][HD]; Kc/Vc: the
-// layer's pools.  One workgroup moves one (block, kv head): HD*64 bytes of K, contiguous on both sides, and as many of V,
-// whose block is stored transposed (8 positions of one channel per 16-byte record) and turns through LDS.  Everything in
+// layer's pools.  One workgroup moves one (block, kv head): HD*64 bytes of K, whose 16-byte records are stored in another
+// order, and as many of V, stored transposed (8 positions of one channel per record); both turn through LDS.  Everything in
 // memory is read and written 16 bytes at a time, all loads of a thread in flight together: the kernel is bound by the
 // copy rate (read + write) of the memory.  A pitch of HD + 8 elements keeps the 2-byte column accesses of a wave in
 // separate banks (four rows 4 apart, 16 channels each).  4001 rows x 8 heads x 128, in or out: 17.4 -> 8.0 us (4.1 TB/s of reads and writes).
@@ -150,7 +150,7 @@ __global__ __launch_bounds__(256) void kv_block_copy_kernel(KvGeom kv, uint16_t 
                                                             uint16_t *v_ext, int32_t *err_flag)
 {
     constexpr int CPR = HD / 8, NREC = 32 * CPR, N = NREC / 256, PITCH = HD + 8;
-    __shared__ __align__(16) uint16_t tile[32 * PITCH];
+    __shared__ __align__(16) uint16_t tile[32 * PITCH], ktile[32 * PITCH];
     const int blk = (t0 >> 5) + blockIdx.x, kvh = blockIdx.y;
     const int first = 32 * blk;                                   // position of the block's row 0
     if (!kv_pages_ok(kv, b, first, first)) {
@@ -163,20 +163,29 @@ __global__ __launch_bounds__(256) void kv_block_copy_kernel(KvGeom kv, uint16_t 
     // 16-byte records of the block's rows in the plain layout (row r, channels 8x..8x+7 at record r * CPR + x)
     const ptrdiff_t e0 = ((ptrdiff_t)kvh * n_rows + (first - t0)) * CPR;
     u32x4 *ke = reinterpret_cast<u32x4 *>(k_ext) + e0, *ve = reinterpret_cast<u32x4 *>(v_ext) + e0;
+    // record rec of a K block: row, and which eight channels
+    auto krow = [](int rec) { return rec / (CPR * 16) * 16 + (rec & 15); };
+    auto kcol = [](int rec) { return rec / 64 % (CPR / 4) * 4 + (rec >> 4) % 4; };
     u32x4 k[N], v[N];
 #pragma unroll
     for (int i = 0; i < N; ++i) {
         const int rec = threadIdx.x + 256 * i, row = rec / CPR;
         const bool in = row >= lo && row < hi;
         k[i] = v[i] = u32x4{0u, 0u, 0u, 0u};
-        if (in) k[i] = IMPORT ? ke[rec] : kc[rec];
-        if (IMPORT) { if (in) v[i] = ve[rec]; }
-        else v[i] = vc[rec];
+        if (IMPORT) {
+            if (in) {
+                k[i] = ke[rec];
+                v[i] = ve[rec];
+            }
+        } else {
+            k[i] = kc[rec];
+            v[i] = vc[rec];
+        }
     }
 #pragma unroll
     for (int i = 0; i < N; ++i) {
-        const int rec = threadIdx.x + 256 * i, row = rec / CPR;
-        if (row >= lo && row < hi) (IMPORT ? kc : ke)[rec] = k[i];
+        const int rec = threadIdx.x + 256 * i;
+        *reinterpret_cast<u32x4 *>(IMPORT ? &ktile[(rec / CPR) * PITCH + (rec % CPR) * 8] : &ktile[krow(rec) * PITCH + kcol(rec) * 8]) = k[i];
     }
     // record rec of a V block: channel (rec / 64) * 16 + rec % 16, positions 4q..4q+3 and 16+4q..16+4q+3, q = (rec / 16) % 4
 #pragma unroll
@@ -191,6 +200,11 @@ __global__ __launch_bounds__(256) void kv_block_copy_kernel(KvGeom kv, uint16_t 
         }
     }
     __syncthreads();
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        const int rec = threadIdx.x + 256 * i, row = IMPORT ? krow(rec) : rec / CPR, col = IMPORT ? kcol(rec) : rec % CPR;
+        if (row >= lo && row < hi) (IMPORT ? kc : ke)[rec] = *reinterpret_cast<const u32x4 *>(&ktile[row * PITCH + col * 8]);
+    }
 #pragma unroll
     for (int i = 0; i < N; ++i) {
         const int rec = threadIdx.x + 256 * i;

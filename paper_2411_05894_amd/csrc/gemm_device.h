@@ -105,9 +105,9 @@ __device__ __forceinline__ void epilogue(const FusedGemmArgs &a, int unit, int m
                 st<COH>(a.Qp + i_1, h1); st<COH>(a.Qp_lo + i_1, l1);
             } else if (base >= 0) {
                 head -= a.nq;
-                uint16_t *kr = a.Kc + kcache_offset(a.kv, b, head, pos, 0);
-                st<COH>(kr + ch, f32_to_bf16(y0));
-                st<COH>(kr + ch + half, f32_to_bf16(y1));
+                uint16_t *kk = a.Kc + kv_block_offset(a.kv, kv_page(a.kv, b, pos >> 5), head);
+                st<COH>(kk + kblock_index(pos & 31, ch, a.d), f32_to_bf16(y0));
+                st<COH>(kk + kblock_index(pos & 31, ch + half, a.d), f32_to_bf16(y1));
             }
         } else if (base >= 0) {
             head -= a.nq + a.nkv;
@@ -313,9 +313,9 @@ __device__ __forceinline__ void qkv8(const FusedGemmArgs &a, int m, int head, in
             *reinterpret_cast<u32x4 *>(a.Qp + i_1) = h1; *reinterpret_cast<u32x4 *>(a.Qp_lo + i_1) = l1;
         } else if (base >= 0) {
             head -= a.nq;
-            uint16_t *kr = a.Kc + kcache_offset(a.kv, b, head, pos, 0);
-            *reinterpret_cast<u32x4 *>(kr + ch) = round8(y0);
-            *reinterpret_cast<u32x4 *>(kr + ch + half) = round8(y1);
+            uint16_t *kk = a.Kc + kv_block_offset(a.kv, kv_page(a.kv, b, pos >> 5), head);
+            *reinterpret_cast<u32x4 *>(kk + kblock_index(pos & 31, ch, a.d)) = round8(y0);
+            *reinterpret_cast<u32x4 *>(kk + kblock_index(pos & 31, ch + half, a.d)) = round8(y1);
         }
     } else if (base >= 0) {
         head -= a.nq + a.nkv;

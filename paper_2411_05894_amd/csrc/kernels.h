@@ -8,7 +8,6 @@
 // rounding, on the sequences beside it.
 struct AttnPlan {
     int share;         // segments of a sequence at most
-    int long_blocks;   // a sequence of so many blocks of 32 positions or more has segments of at least 16 blocks, not 4
 };
 constexpr int ATTN_MAX_SEGMENTS = 64;   // per sequence: what the merge takes
 AttnPlan attention_plan(const Dims &D, int B, int k);
@@ -21,16 +20,14 @@ struct AttnSeq {
     int b, len;        // sequence, cached rows it is read with
     AttnCut cut;
 };
-// The sequence is shared out evenly.  Lengths of 16 blocks and more are made odd: an even one puts the segments' streams a
-// multiple of a large power of two apart, where they meet on the same memory channels (B = 4, context 32768, eight heads
-// of 128: 96 us of attention with segments of 65 blocks, 104 us with 64).
+// The sequence is shared out evenly; segments of 16 blocks and more are whole rounds of the four waves of a workgroup.
 __host__ __device__ __forceinline__ AttnCut attention_cut(const AttnPlan &p, int blocks)
 {
     auto ceil_div = [](int x, int y) { return (int)(((unsigned)x + (unsigned)y - 1u) / (unsigned)y); };
-    const int fair = ceil_div(blocks, p.share), least = blocks >= p.long_blocks ? 16 : 4;
+    const int fair = ceil_div(blocks, p.share), least = blocks <= 8 ? 8 : 4;
     AttnCut c;
     c.each = ceil_div(blocks, ceil_div(blocks, fair > least ? fair : least));
-    if (c.each >= 16) c.each |= 1;
+    if (c.each >= 16) c.each = (c.each + 3) & ~3;
     c.n = ceil_div(blocks, c.each);
     return c;
 }
