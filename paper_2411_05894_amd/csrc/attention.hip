@@ -490,6 +490,9 @@ hipError_t launch_attention(const Dims &D, const AttnArgs &a_in, hipStream_t s)
     a.plan = attention_plan(D, a.B, a.k);
     hipError_t e = D.d == 128 ? launch_partial<128>(D, a, q_rows_pad, s) : launch_partial<64>(D, a, q_rows_pad, s);
     if (e != hipSuccess) return e;
+    // No merge where no sequence can have two segments.  With every workgroup of the merge returning at once the launch still
+    // took 5 us (70B layer, B = 16, k = 8: 5 of 597; two layers of the tiny shape with room for 133 positions: 10 of 68).
+    if (a.plan.share == 1 || D.blocks_per_seq <= ATTN_WHOLE_BLOCKS) return hipSuccess;
     const int n_tasks = a.B * D.nkv * D.g * (a.k + 1);
     if (D.d == 128) hipLaunchKernelGGL(attn_combine_kernel<128>, dim3((n_tasks + 3) / 4), dim3(256), 0, s, D, a, q_rows_pad);
     else hipLaunchKernelGGL(attn_combine_kernel<64>, dim3((n_tasks + 3) / 4), dim3(256), 0, s, D, a, q_rows_pad);

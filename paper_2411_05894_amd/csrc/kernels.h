@@ -10,6 +10,7 @@ struct AttnPlan {
     int share;         // segments of a sequence at most
 };
 constexpr int ATTN_MAX_SEGMENTS = 64;   // per sequence: what the merge takes
+constexpr int ATTN_WHOLE_BLOCKS = 8;    // sequences of up to so many blocks of 32 positions are one segment
 AttnPlan attention_plan(const Dims &D, int B, int k);
 struct AttnCut {
     int each, n;       // blocks per segment (the last may be shorter), segments
@@ -24,7 +25,7 @@ struct AttnSeq {
 __host__ __device__ __forceinline__ AttnCut attention_cut(const AttnPlan &p, int blocks)
 {
     auto ceil_div = [](int x, int y) { return (int)(((unsigned)x + (unsigned)y - 1u) / (unsigned)y); };
-    const int fair = ceil_div(blocks, p.share), least = blocks <= 8 ? 8 : 4;
+    const int fair = ceil_div(blocks, p.share), least = blocks <= ATTN_WHOLE_BLOCKS ? ATTN_WHOLE_BLOCKS : 4;
     AttnCut c;
     c.each = ceil_div(blocks, ceil_div(blocks, fair > least ? fair : least));
     if (c.each >= 16) c.each = (c.each + 3) & ~3;
