@@ -555,10 +555,10 @@ int run_step(sssd_ctx *c, int32_t B, int32_t k, const int32_t *tokens, const int
         Prof p(c, s, SSSD_PROF_ACCEPT);
         HIP_TRY(launch_sample_rows(smp->logits, M, D.V, smp->temperature, smp->top_k, smp->top_p, smp->uniforms, W.that_dbg,
                                    W.sample_scratch, W.sample_scratch_bytes, true, c->n_cu, W.err_flag, s));
-        HIP_TRY(launch_accept(D, io, nullptr, nullptr, D.V / 16, W.that_dbg, s));
+        HIP_TRY(launch_accept(io, nullptr, nullptr, 0, W.that_dbg, s));
     } else {
         Prof p(c, s, SSSD_PROF_ACCEPT);
-        HIP_TRY(launch_accept(D, io, W.part_val, W.part_idx, D.V / 16, W.that_dbg, s));
+        HIP_TRY(launch_accept(io, W.part_val, W.part_idx, f.n_part, W.that_dbg, s));
     }
     if (c->dbg_that)
         HIP_TRY(hipMemcpyAsync(c->dbg_that, W.that_dbg, (size_t)M * 4, hipMemcpyDeviceToDevice, s));

@@ -124,24 +124,20 @@ __device__ __forceinline__ void epilogue(const FusedGemmArgs &a, int unit, int m
         const size_t idx = packed_index(m, unit * 16 + c, a.KT_out);
         st<COH>(a.out_hi + idx, hi);
         st<COH>(a.out_lo + idx, lo);
-    } else {  // FEPI_LM
-        const int n = unit * 16 + c;
-        const float logit = valid ? v0 * rs : -INFINITY;
-        if (valid && a.logits) a.logits[(size_t)m * a.vocab + n] = logit;
-        float bv = logit;
-        int bi = n;
-#pragma unroll
-        for (int off = 8; off >= 1; off >>= 1) {
-            const float ov = __shfl_xor(bv, off, 16);
-            const int oi = __shfl_xor(bi, off, 16);
-            if (ov > bv || (ov == bv && oi < bi)) { bv = ov; bi = oi; }
-        }
-        if (valid && c == 0) {
-            a.part_val[(size_t)m * a.NT + unit] = bv;
-            a.part_idx[(size_t)m * a.NT + unit] = bi;
-        }
     }
 }
+
+// Running arg-max of a row: the larger value, of equal ones the lower column.  A value that is no number never wins.
+struct Best {
+    float v;
+    int i;
+    __device__ __forceinline__ void take(float v2, int i2)
+    {
+        if (v2 > v || (v2 == v && i2 < i)) { v = v2; i = i2; }
+    }
+    static __device__ __forceinline__ Best none() { return Best{-INFINITY, 0x7FFFFFFF}; }
+    __device__ __forceinline__ void across(int off) { take(__shfl_xor(v, off), __shfl_xor(i, off)); }   // the lane `off` away
+};
 
 // rsqrt(mean(x^2) + eps) of row m from the producer's sums of squares; whole wave.
 template <bool COH = false> __device__ __forceinline__ float row_rstd(const FusedGemmArgs &a, int m, int lane)
@@ -344,27 +340,15 @@ __device__ __forceinline__ void swiglu8(const FusedGemmArgs &a, int m, int col, 
     *reinterpret_cast<u32x4 *>(a.out_lo + idx) = lo;
 }
 
-// LM: logits (if asked for) and the arg-max of each 16 columns; whole waves call it, lanes 16 apart share 16 columns.
-__device__ __forceinline__ void lm8(const FusedGemmArgs &a, int m, int n0, bool live, int kg, float rs, Vec8 v0)
+// LM: logits (if asked for), and columns n0..n0+7 of row m into the row's running arg-max.
+__device__ __forceinline__ void lm8(const FusedGemmArgs &a, int m, int n0, float rs, Vec8 v0, Best &best)
 {
-    float bv = -INFINITY;
-    int bi = n0;
-    if (live) {
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const float logit = v0.v[e] * rs;
-            v0.v[e] = logit;
-            if (logit > bv) { bv = logit; bi = n0 + e; }   // ascending columns: the lowest index keeps a tie
-        }
-        if (a.logits) store8(a.logits + (size_t)m * a.vocab + n0, v0);
+    for (int e = 0; e < 8; ++e) {
+        v0.v[e] *= rs;
+        best.take(v0.v[e], n0 + e);
     }
-    const float ov = __shfl_xor(bv, 16);
-    const int oi = __shfl_xor(bi, 16);
-    if (ov > bv || (ov == bv && oi < bi)) { bv = ov; bi = oi; }
-    if (live && !(kg & 1)) {
-        a.part_val[(size_t)m * a.NT + (n0 >> 4)] = bv;
-        a.part_idx[(size_t)m * a.NT + (n0 >> 4)] = bi;
-    }
+    if (a.logits) store8(a.logits + (size_t)m * a.vocab + n0, v0);
 }
 
 }  // namespace

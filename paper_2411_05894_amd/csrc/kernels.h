@@ -77,8 +77,8 @@ struct FusedGemmArgs {
     const int32_t *rope_pos;      // QKV: rotary position of row m
     uint16_t *Qp, *Qp_lo, *Kc, *Vc;  // Kc, Vc: this layer's cache pools
     KvGeom kv;                    // QKV: page geometry of the cache
-    float *logits, *part_val;     // LM
-    int *part_idx;
+    float *logits, *part_val;     // LM: [M][n_part] maxima of column ranges and the lowest columns that hold them
+    int *part_idx, n_part;        // n_part is filled in by the launch that writes them
     // weight streamer (stream_gemm.hip)
     int n_units;                  // epilogue units: rotary tile pairs (QKV), gate/up tile pairs (SWIGLU), tiles (RESID, LM)
     int Ntot;                     // columns of the concatenated output: (nq+2nkv)*d, 2*ffn, h, vocab
@@ -111,11 +111,10 @@ hipError_t launch_fused_embed(const Dims &D, const StepIO &io, const KvGeom &kv,
                               float *X, uint16_t *A_hi, uint16_t *A_lo, float *ssq, int32_t *pos_base, AttnSeq *seq, int32_t *segments, int32_t *rope_pos,
                               uint32_t *anc, int32_t *err_flag, hipStream_t s);
 
-// Merge per-tile arg-max partials, then greedy acceptance (longest matching prefix of a chain, or
+// Merge the n_part arg-max partials of every row, then greedy acceptance (longest matching prefix of a chain, or
 // the walk from the root of a draft tree when io.parents is set).
 // With part_val == nullptr `that` already holds the target's choice per row (sampled tokens) and only the walk runs.
-hipError_t launch_accept(const Dims &D, const StepIO &io, const float *part_val, const int *part_idx, int NT,
-                         int32_t *that, hipStream_t s);
+hipError_t launch_accept(const StepIO &io, const float *part_val, const int *part_idx, int n_part, int32_t *that, hipStream_t s);
 // One token per row drawn from softmax(logits / temperature) restricted by top_k (0: off) and top_p
 // (1: off), with the caller's uniform number per row; sampling.hip states the exact definition.
 // With scratch (sample_scratch_bytes(rows, n_cu) bytes) and few rows, a row is spread over a cluster of

@@ -25,7 +25,7 @@
 //   QKV     RMSNorm scale, rotary embedding, Q -> packed hi/lo operand, K/V -> cache (in place)
 //   RESID   X += acc; packed X*gamma_next hi/lo; sums of squares per 16 columns
 //   SWIGLU  RMSNorm scale, silu(gate)*up -> packed hi/lo operand
-//   LM      RMSNorm scale, per-tile arg-max (with an unsplit K logits are materialised only if asked for; else
+//   LM      RMSNorm scale, arg-max of a workgroup's columns (with an unsplit K logits are materialised only if asked for; else
 //           they pass through memory once as unscaled sums)
 // RMSNorm needs no pass of its own: the producer of the residual stream x writes x*gamma and
 // partial sums of squares, the consuming GEMM scales its fp32 results by rsqrt(mean(x^2)+eps),
@@ -128,6 +128,7 @@ __global__ __launch_bounds__(PW * 64) void pgemm_kernel(FusedGemmArgs a)
     if (EPI != FEPI_RESID && EPI != FEPI_STORE && !SPLIT) rstd_s[wave] = row_rstd(a, m_base + wave, lane);   // published by the first barrier
 
     float keep = 0.f;
+    Best best = Best::none();   // LM: of this thread's row and column within the tiles
     for (int s = 0; s < n_steps; ++s) {
         const int unit = u_begin + (s / TPU) * u_stride, part = s % TPU;
         f32x4 acc;
@@ -155,9 +156,23 @@ __global__ __launch_bounds__(PW * 64) void pgemm_kernel(FusedGemmArgs a)
                 keep = v;
             } else {
                 const float rs = (EPI == FEPI_RESID || EPI == FEPI_STORE) ? 1.f : rstd_s[ml];
-                if (TPU == 2) epilogue<EPI>(a, unit, m, c, m < a.M, keep, v, rs);
+                if (EPI == FEPI_LM) {
+                    const int n = unit * 16 + c;
+                    best.take(v * rs, n);
+                    if (m < a.M && a.logits) a.logits[(size_t)m * a.vocab + n] = v * rs;
+                } else if (TPU == 2) epilogue<EPI>(a, unit, m, c, m < a.M, keep, v, rs);
                 else epilogue<EPI>(a, unit, m, c, m < a.M, v, 0.f, rs);
             }
+        }
+    }
+
+    if (EPI == FEPI_LM && !SPLIT && wave < 4) {
+#pragma unroll
+        for (int off = 8; off >= 1; off >>= 1) best.across(off);
+        const int m = m_base + 4 * (lane >> 4) + wave;
+        if (m < a.M && (lane & 15) == 0) {
+            a.part_val[(size_t)m * a.n_part + grp] = best.v;
+            a.part_idx[(size_t)m * a.n_part + grp] = best.i;
         }
     }
 
@@ -207,7 +222,28 @@ __global__ __launch_bounds__(PW * 64) void pgemm_kernel(FusedGemmArgs a)
                     for (int jj = 1; jj < J; ++jj) sum += ld<true>(pp + jj * jstride);
                     v[part] = sum;
                 }
-                epilogue<EPI>(a, unit, m, c, m < a.M, v[0], TPU == 2 ? v[TPU - 1] : 0.f, SCALED ? rstd_s[ml] : 1.f);
+                if (EPI == FEPI_LM) {
+                    const float logit = v[0] * rstd_s[ml];
+                    best.take(logit, unit * 16 + c);
+                    if (m < a.M && a.logits) a.logits[(size_t)m * a.vocab + unit * 16 + c] = logit;
+                } else {
+                    epilogue<EPI>(a, unit, m, c, m < a.M, v[0], TPU == 2 ? v[TPU - 1] : 0.f, SCALED ? rstd_s[ml] : 1.f);
+                }
+            }
+            if (EPI == FEPI_LM) {   // every fourth tile of a row lies with the threads 256 on
+                __shared__ Best best_s[4][16];
+#pragma unroll
+                for (int off = 8; off >= 1; off >>= 1) best.across(off);
+                if ((threadIdx.x & 15) == 0) best_s[threadIdx.x >> 8][(threadIdx.x & 255) >> 4] = best;
+                __syncthreads();
+                const int m = m_base + threadIdx.x;
+                if (threadIdx.x < 16 && m < a.M) {
+                    Best all = best_s[0][threadIdx.x];
+#pragma unroll
+                    for (int x = 1; x < 4; ++x) all.take(best_s[x][threadIdx.x].v, best_s[x][threadIdx.x].i);
+                    a.part_val[(size_t)m * a.n_part + grp] = all.v;
+                    a.part_idx[(size_t)m * a.n_part + grp] = all.i;
+                }
             }
         }
     }
@@ -303,6 +339,7 @@ __global__ __launch_bounds__(256) void epi_kernel(FusedGemmArgs a, int blocks_pe
     const float rs = SCALED ? rstd_s[r] : 1.f;
 
     float ss = 0.f;   // RESID: of this row, over the thread's columns
+    Best best = Best::none();   // LM: likewise
     for (int cb = cb_begin + wave; cb < cb_end; cb += 4) {
         Vec8 n0v, n1v;
         fetch(cb + 4, n0v, n1v);
@@ -317,10 +354,23 @@ __global__ __launch_bounds__(256) void epi_kernel(FusedGemmArgs a, int blocks_pe
         } else if (EPI == FEPI_RESID) {
             if (live) ss += resid8<false>(a, m, col, v0);
         } else {  // FEPI_LM
-            lm8(a, m, cb * 32 + kg * 8, live, kg, rs, v0);
+            if (live) lm8(a, m, col, rs, v0, best);
         }
         v0 = n0v;
         v1 = n1v;
+    }
+    if (EPI == FEPI_LM) {   // one arg-max per row and workgroup
+        __shared__ Best best_s[4][16];
+        best.across(16);
+        best.across(32);
+        if (kg == 0) best_s[wave][r] = best;
+        __syncthreads();
+        if (threadIdx.x < 16 && row_ok) {
+#pragma unroll
+            for (int x = 1; x < 4; ++x) best.take(best_s[x][r].v, best_s[x][r].i);
+            a.part_val[(size_t)m * gridDim.x + blockIdx.x] = best.v;
+            a.part_idx[(size_t)m * gridDim.x + blockIdx.x] = best.i;
+        }
     }
     if (EPI == FEPI_RESID) {   // one sum of squares per row and workgroup
         __shared__ float ss_s[4][16];
@@ -344,6 +394,7 @@ template <int EPI> hipError_t launch_epi(FusedGemmArgs &a, hipStream_t s)
     bpw = (bpw + 3) / 4 * 4;
     const int nx = (n_cb + bpw - 1) / bpw;
     if (EPI == FEPI_RESID) a.nss_out = nx;
+    if (EPI == FEPI_LM) a.n_part = nx;
     hipLaunchKernelGGL((epi_kernel<EPI>), dim3(nx, row_tiles), dim3(256), 0, s, a, bpw);
     return hipGetLastError();
 }
@@ -609,6 +660,9 @@ __device__ __forceinline__ void qgemm16_rows(const FusedGemmArgs a, int NT16, in
     // a read takes, lie in different banks.
     const bool paired = a.epi == FEPI_QKV || a.epi == FEPI_SWIGLU;
     const int r = lane & 15, kg = lane >> 4;
+    Best best[MTW];
+#pragma unroll
+    for (int i = 0; i < MTW; ++i) best[i] = Best::none();
 #pragma unroll
     for (int ct = 0; ct < NC; ct += 2) {
         if (c16 + ct >= NT16) continue;
@@ -641,12 +695,32 @@ __device__ __forceinline__ void qgemm16_rows(const FusedGemmArgs a, int NT16, in
                     const int m = row0 + 16 * (i + ii) + r;
                     const bool live = m < a.M && col < a.Ntot;
                     const Vec8 v0 = load8(mine + ((kg >> 1) * 32 + ii * 16 + r) * 20 + 8 * (kg & 1));
-                    if (a.epi == FEPI_LM) lm8(a, m, col, live, kg, scale[16 * (i + ii) + r], v0);
-                    else if (a.epi == FEPI_RESID) resid_block<false>(a, m, col, live, kg, v0);
+                    if (a.epi == FEPI_LM) {
+                        if (live) lm8(a, m, col, scale[16 * (i + ii) + r], v0, best[i + ii]);
+                    } else if (a.epi == FEPI_RESID) resid_block<false>(a, m, col, live, kg, v0);
                     else if (live) store8(a.out + (size_t)m * a.Ntot + col, v0);
                 }
             }
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        }
+    }
+    if (a.epi == FEPI_LM) {   // one arg-max per row and workgroup
+        Best(*best_s)[16 * MT16] = reinterpret_cast<Best(*)[16 * MT16]>(lds);
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < MTW; ++i) {
+            best[i].across(16);
+            best[i].across(32);
+            if (kg == 0) best_s[cg][16 * (half * MTW + i) + r] = best[i];
+        }
+        __syncthreads();
+        for (int row = threadIdx.x; row < 16 * MT16; row += QW * 64) {
+            if (m_base + row >= a.M) continue;
+            Best all = best_s[0][row];
+#pragma unroll
+            for (int x = 1; x < CW; ++x) all.take(best_s[x][row].v, best_s[x][row].i);
+            a.part_val[(size_t)(m_base + row) * a.n_part + grp] = all.v;
+            a.part_idx[(size_t)(m_base + row) * a.n_part + grp] = all.i;
         }
     }
 }
@@ -785,6 +859,7 @@ template <int EPI> hipError_t launch_large(FusedGemmArgs &a, hipStream_t s, bool
     a.part_rows = round_up(a.M, 16);
     a.epi = EPI;
     a.nss_out = a.h >> 4;
+    a.n_part = p.groups;
     *needs_epilogue = a.J > 1;   // an unsplit K: the kernel applies the epilogue itself
     if (EPI == FEPI_QKV) { a.seg0 = a.nq * (a.d >> 4); a.seg1 = a.nkv * (a.d >> 4); }
     else if (EPI == FEPI_SWIGLU) { a.seg0 = a.NT; a.seg1 = a.NT; }
@@ -853,6 +928,7 @@ template <int EPI> hipError_t launch_small(FusedGemmArgs &a, hipStream_t s, bool
     a.groups = sp.groups;
     a.part_rows = 16 * sp.rh;
     a.nss_out = a.h >> 4;
+    a.n_part = sp.groups;
     if (a.J > 1 && (size_t)a.J * a.part_rows * a.Ntot * sizeof(float) > a.partial_bytes) return hipErrorInvalidValue;
     const dim3 grid(groups * a.J * sp.rh), block(PW * 64);
     if (groups * sp.rh > a.tail_slots) a.tail_count = nullptr;   // no counter for every group: epilogue launch
