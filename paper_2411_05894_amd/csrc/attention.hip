@@ -36,7 +36,9 @@
 // 8B shape B = 2, k = 17, context 12345 51 -> 45; B = 16, k = 31, 4000 132 -> 105; B = 32, k = 4, 1024..4096 90 -> 80; B = 4, k = 8,
 // 32768 108 -> 105; 70B shape B = 16, k = 8, 2048 71 -> 60.  Two blocks ahead instead of one: 3-8 % slower at one and two row tiles (fewer
 // registers are left to the second workgroup of a compute unit).  K rows in plain order: every load took half of sixteen cache lines, and
-// streaming loads fetched some of them twice (B = 40, k = 3 69 us, 59 now).
+// streaming loads fetched some of them twice (B = 40, k = 3 69 us, 59 now).  Matrix and vector instructions in turn against the
+// compiler's order, all probabilities first and then all products: B = 16, k = 31, 4000 104 -> 95, 70B shape B = 3, k = 15,
+// 4000..12000 72 -> 65, 8B B = 2, k = 17 44.7 -> 42.6, one and two row tiles the same.
 #include "kernels.h"
 
 namespace {
@@ -80,9 +82,11 @@ __global__ __launch_bounds__(NWAVE * 64) __attribute__((amdgpu_waves_per_eu(2, 2
     constexpr int KS = HD / 32, DT = HD / 16;
     constexpr int NREC = 4 * HD;             // 16-byte records of a block of 32 positions, K and V alike
     constexpr bool QREG = RT == 1;           // query operands in registers, else in LDS
+    constexpr int QAHEAD = RT == 4 ? 1 : 3;  // pairs of them fetched ahead: four tiles leave registers for one
     constexpr int QREC = RT * KS * 2 * 64, RRED = NWAVE * RT * (DT / 2) * 64;   // records of the query tiles, of the final sums
     __shared__ u32x4 lds[QREC > RRED ? QREC : RRED];
     __shared__ float2 ml_s[NWAVE][RT * 16];
+    __shared__ uint32_t vis_s[RT * 16];      // visible new rows of every query row: bit i = cache row len + i
 
     int kvh, wg;   // kv head; (turn, segment)
     int pass = 0;
@@ -168,14 +172,18 @@ __global__ __launch_bounds__(NWAVE * 64) __attribute__((amdgpu_waves_per_eu(2, 2
 #pragma unroll
         for (int dt = 0; dt < DT; ++dt) v[dt] = __builtin_nontemporal_load(p + dt * 64);
     };
-    uint32_t vis[RT];   // visible new rows of query row c of each tile: bit i = cache row len + i
+    const bool has_new = (first_blk + n_blk) * 32 > len;   // the segment holds new rows
+    auto visible = [&](int row) { return a.anc[b * (a.k + 1) + min((rt0 * 16 + row) / D.g, a.k)]; };   // query row -> node of the chain or tree
+    constexpr bool VREG = RT <= 3;   // in registers, else in LDS
+    uint32_t vis[VREG ? RT : 1];
 #pragma unroll
-    for (int t = 0; t < RT; ++t) vis[t] = 0;
-    if ((first_blk + n_blk) * 32 > len) {
+    for (int t = 0; t < (VREG ? RT : 1); ++t) vis[t] = 0;
+    if (has_new) {
+        if (VREG) {
 #pragma unroll
-        for (int t = 0; t < RT; ++t) {
-            const int j = min(((rt0 + t) * 16 + c) / D.g, a.k);   // query row -> node of the chain or tree
-            vis[t] = a.anc[b * (a.k + 1) + j];
+            for (int t = 0; t < (VREG ? RT : 1); ++t) vis[t] = visible(t * 16 + c);
+        } else if ((int)threadIdx.x < RT * 16) {
+            vis[0] = visible(threadIdx.x);
         }
     }
     load_k(0);
@@ -193,58 +201,79 @@ __global__ __launch_bounds__(NWAVE * 64) __attribute__((amdgpu_waves_per_eu(2, 2
     if (!QREG) {
 #pragma unroll
         for (int i = 0; i < QPT; ++i) lds[(wave * QPT + i) * 64 + lane] = qcopy[i];
-        __syncthreads();
     }
+    if (!VREG && threadIdx.x < RT * 16) vis_s[threadIdx.x] = vis[0];
+    if (!QREG) __syncthreads();
     const float scale = 1.4426950408889634f * rsqrtf((float)HD);  // log2(e)/sqrt(d)
 
+    // A block: scores of every tile, their maxima, then probabilities and results.  A wave issues in order, and alone on its SIMD it
+    // keeps matrix and vector units busy only if their instructions alternate: the maxima of a tile are taken between the score
+    // MFMAs of the next, the probabilities of a tile between the result MFMAs of the one before.
     for (int i = 0; i < n_it; ++i) {
         if (i >> 6 != chunk) {   // once per 64 blocks
             chunk = i >> 6;
             pg = pg_next;
             pg_next = load_pages(chunk + 1);
         }
+        const int t0 = (first_blk + wave + NWAVE * i) * 32;
         int ql = lane;
         asm volatile("" : "+v"(ql));   // the query operands are read again for every block: hoisted, they would not fit the registers
-        // s[t][u][r]: score of position t0 + 16u + 4q + r for query row c of tile t
-        f32x4 s[RT][2];
+        f32x4 s[RT][2];                // s[t][u][r]: score of position t0 + 16u + 4q + r for query row c of tile t
+        float mx[RT];
+        bool grow = false;
+        u32x4 qx[QREG ? 1 : QAHEAD][2];
+        auto fetch_q = [&](int x) {
+            qx[x % QAHEAD][0] = lds[x * 128 + ql];
+            qx[x % QAHEAD][1] = lds[x * 128 + 64 + ql];
+        };
+        auto maxima = [&](int t, int part) {   // in four parts
+            if (part == 0) mx[t] = fmaxf(fmaxf(fmaxf(s[t][0][0], s[t][0][1]), s[t][0][2]), s[t][0][3]);
+            if (part == 1) mx[t] = fmaxf(fmaxf(fmaxf(fmaxf(mx[t], s[t][1][0]), s[t][1][1]), s[t][1][2]), s[t][1][3]);
+            if (part == 2) mx[t] = rows_max(mx[t]);
+            if (part == 3) {
+                mx[t] *= scale;
+                grow = grow || mx[t] > m_run[t] + 8.f;
+            }
+        };
+        if (!QREG) {
+#pragma unroll
+            for (int x = 0; x < QAHEAD; ++x) fetch_q(x);
+        }
 #pragma unroll
         for (int t = 0; t < RT; ++t) {
             s[t][0] = s[t][1] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks) {
-                const u32x4 hi = QREG ? qreg[QREG ? ks : 0][0] : lds[((t * KS + ks) * 2) * 64 + ql];
-                const u32x4 lo = QREG ? qreg[QREG ? ks : 0][1] : lds[((t * KS + ks) * 2 + 1) * 64 + ql];
+                const int x = t * KS + ks;
+                const u32x4 hi = QREG ? qreg[QREG ? ks : 0][0] : qx[x % QAHEAD][0], lo = QREG ? qreg[QREG ? ks : 0][1] : qx[x % QAHEAD][1];
 #pragma unroll
                 for (int u = 0; u < 2; ++u) s[t][u] = mfma(k[u][ks], hi, s[t][u]);
 #pragma unroll
                 for (int u = 0; u < 2; ++u) s[t][u] = mfma(k[u][ks], lo, s[t][u]);
-            }
-        }
-        load_k(i + 1);
-        const int t0 = (first_blk + wave + NWAVE * i) * 32;
-        if (t0 + 32 > len) {   // the block holds new rows: apply the nodes' visibility words
+                if (!QREG && x + QAHEAD < RT * KS) fetch_q(x + QAHEAD);
+                if (t > 0) {
 #pragma unroll
-            for (int t = 0; t < RT; ++t)
+                    for (int part = ks * 4 / KS; part < (ks + 1) * 4 / KS; ++part) maxima(t - 1, part);
+                }
+                if (!QREG) __builtin_amdgcn_sched_barrier(0);
+            }
+            if (t0 + 32 > len) {   // the block holds new rows: apply the nodes' visibility words
+                const uint32_t seen = VREG ? vis[VREG ? t : 0] : vis_s[t * 16 + c];
 #pragma unroll
                 for (int u = 0; u < 2; ++u)
 #pragma unroll
                     for (int r = 0; r < 4; ++r) {
                         const int rel = t0 + 16 * u + 4 * q + r - len;   // < 0: old cache, always visible
-                        if (rel >= 0 && (rel > 31 || !((vis[t] >> rel) & 1u))) s[t][u][r] = -INFINITY;
+                        if (rel >= 0 && (rel > 31 || !((seen >> rel) & 1u))) s[t][u][r] = -INFINITY;
                     }
+            }
         }
+        load_k(i + 1);
+#pragma unroll
+        for (int part = 0; part < 4; ++part) maxima(RT - 1, part);
         // The exponent's reference m_run follows the running maximum lazily: it moves (and the accumulators are rescaled)
         // only when some row's maximum has outgrown it by more than 2^8, so most blocks skip the rescale.  Any reference gives
         // the same softmax; probabilities stay below 2^8 and the partial (o, l, m_run) handed on is consistent with it.
-        float mx[RT];
-        bool grow = false;
-#pragma unroll
-        for (int t = 0; t < RT; ++t) {
-            mx[t] = fmaxf(fmaxf(fmaxf(s[t][0][0], s[t][0][1]), fmaxf(s[t][0][2], s[t][0][3])),
-                          fmaxf(fmaxf(s[t][1][0], s[t][1][1]), fmaxf(s[t][1][2], s[t][1][3])));
-            mx[t] = rows_max(mx[t]) * scale;
-            grow = grow || mx[t] > m_run[t] + 8.f;
-        }
         if (__any(grow)) {
 #pragma unroll
             for (int t = 0; t < RT; ++t) {
@@ -255,23 +284,42 @@ __global__ __launch_bounds__(NWAVE * 64) __attribute__((amdgpu_waves_per_eu(2, 2
                 for (int dt = 0; dt < DT; ++dt) o[t][dt] *= alpha;
             }
         }
+        // p ~= hi + lo: the probabilities keep ~16 mantissa bits.  Two of a tile's eight per call, in four parts.
+        uint32_t pk[2][4], pkl[2][4];
+        float p0, p1;
+        auto probs = [&](int t, int e, int part) {
+            uint32_t &hi = pk[t & 1][e], &lo = pkl[t & 1][e];
+            if (part == 0) {
+                p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[t][e >> 1][2 * (e & 1)], scale, -m_run[t]));
+                p1 = __builtin_fmaf(s[t][e >> 1][2 * (e & 1) + 1], scale, -m_run[t]);
+            }
+            if (part == 1) {
+                p1 = __builtin_amdgcn_exp2f(p1);
+                l_run[t] += p0;
+            }
+            if (part == 2) {
+                hi = pack_bf16x2(p0, p1);
+                l_run[t] += p1;
+                p0 -= bits_f32(hi << 16);
+            }
+            if (part == 3) lo = pack_bf16x2(p0, p1 - bits_f32(hi & 0xFFFF0000u));
+        };
+#pragma unroll
+        for (int x = 0; x < 16; ++x) probs(0, x >> 2, x & 3);
+        if (RT > 1) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int t = 0; t < RT; ++t) {
-            uint32_t pk[4], pkl[4];
-            float psum = 0.f;
+            const u32x4 pb = u32x4{pk[t & 1][0], pk[t & 1][1], pk[t & 1][2], pk[t & 1][3]}, pl = u32x4{pkl[t & 1][0], pkl[t & 1][1], pkl[t & 1][2], pkl[t & 1][3]};
 #pragma unroll
-            for (int e = 0; e < 8; e += 2) {
-                const float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[t][e >> 2][e & 3], scale, -m_run[t]));
-                const float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[t][e >> 2][(e & 3) + 1], scale, -m_run[t]));
-                split_bf16x2(p0, p1, pk[e >> 1], pkl[e >> 1]);   // p ~= hi + lo: the probabilities keep ~16 mantissa bits
-                psum += p0 + p1;
+            for (int x = 0; x < 2 * DT; ++x) {   // hi and lo of two tiles of channels in turn
+                const int dt = x >> 2 << 1 | (x & 1);
+                o[t][dt] = mfma(v[dt], x & 2 ? pl : pb, o[t][dt]);
+                if (t + 1 < RT) {
+#pragma unroll
+                    for (int y = x * 16 / (2 * DT); y < (x + 1) * 16 / (2 * DT); ++y) probs(t + 1, y >> 2, y & 3);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
             }
-            l_run[t] += psum;
-            const u32x4 pb = u32x4{pk[0], pk[1], pk[2], pk[3]}, pl = u32x4{pkl[0], pkl[1], pkl[2], pkl[3]};
-#pragma unroll
-            for (int dt = 0; dt < DT; ++dt) o[t][dt] = mfma(v[dt], pb, o[t][dt]);
-#pragma unroll
-            for (int dt = 0; dt < DT; ++dt) o[t][dt] = mfma(v[dt], pl, o[t][dt]);
         }
         load_v(i + 1);
     }
