@@ -114,6 +114,7 @@ __global__ __launch_bounds__(PW * 64) void pgemm_kernel(FusedGemmArgs a)
 #pragma unroll
     for (int i = 0; i < KPW; ++i) koff[i] = (kt0 + i < KT ? kt0 + i : KT - 1) * 64;
 
+    constexpr bool SCALED = EPI != FEPI_RESID && EPI != FEPI_STORE;
     u32x4 w[KPW], ah[KPW], al[KPW];
     const u32x4 *wp = tile_weights<EPI>(a, unit_tile<EPI>(a, u_begin, 0)) + lane;
 #pragma unroll
@@ -125,7 +126,7 @@ __global__ __launch_bounds__(PW * 64) void pgemm_kernel(FusedGemmArgs a)
         ah[i] = live ? a.A_hi[at] : u32x4{0, 0, 0, 0};
         al[i] = live ? a.A_lo[at] : u32x4{0, 0, 0, 0};
     }
-    if (EPI != FEPI_RESID && EPI != FEPI_STORE && !SPLIT) rstd_s[wave] = row_rstd(a, m_base + wave, lane);   // published by the first barrier
+    if (SCALED && !SPLIT) rstd_s[wave] = row_rstd(a, m_base + wave, lane);   // published by the first barrier
 
     float keep = 0.f;
     Best best = Best::none();   // LM: of this thread's row and column within the tiles
@@ -193,7 +194,6 @@ __global__ __launch_bounds__(PW * 64) void pgemm_kernel(FusedGemmArgs a)
         }
         __syncthreads();
         if (!last_s) return;
-        constexpr bool SCALED = EPI != FEPI_RESID && EPI != FEPI_STORE;
         if (SCALED) {
             rstd_s[wave] = row_rstd(a, m_base + wave, lane);
             __syncthreads();
@@ -308,15 +308,13 @@ __global__ __launch_bounds__(256) void epi_kernel(FusedGemmArgs a, int blocks_pe
     constexpr int SV = 2;                     // sums of squares per lane and row held in registers: all that a launch of this kernel leaves
     const int NSS = a.nss_in;
     float sv[4][SV];
-    if (SCALED) {
+    if (SCALED) {   // no load under a branch: each would be waited for by itself
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             const int mm = m0 + wave + 4 * q;
+            const float *p = a.ssq_in + (size_t)(mm < a.M ? mm : a.M - 1) * NSS;
 #pragma unroll
-            for (int i = 0; i < SV; ++i) {
-                const int t = lane + 64 * i;
-                sv[q][i] = (mm < a.M && t < NSS) ? a.ssq_in[(size_t)mm * NSS + t] : 0.f;
-            }
+            for (int i = 0; i < SV; ++i) sv[q][i] = p[lane + 64 * i < NSS ? lane + 64 * i : 0];
         }
     }
     Vec8 v0, v1;
@@ -327,11 +325,10 @@ __global__ __launch_bounds__(256) void epi_kernel(FusedGemmArgs a, int blocks_pe
             const int mm = m0 + wave + 4 * q;
             float sum = 0.f;
 #pragma unroll
-            for (int i = 0; i < SV; ++i) sum += sv[q][i];
+            for (int i = 0; i < SV; ++i) sum += lane + 64 * i < NSS ? sv[q][i] : 0.f;
             if (mm < a.M)
                 for (int t = lane + 64 * SV; t < NSS; t += 64) sum += a.ssq_in[(size_t)mm * NSS + t];
-#pragma unroll
-            for (int off = 32; off >= 1; off >>= 1) sum += __shfl_xor(sum, off);
+            sum = wave_sum(sum);
             if (lane == 0) rstd_s[wave + 4 * q] = rsqrtf(sum / (float)a.h + a.eps);
         }
         __syncthreads();
@@ -426,30 +423,51 @@ __device__ __forceinline__ int q_tile(const FusedGemmArgs &a, int t)
     return t;
 }
 
-// rsqrt(mean(x^2) + eps) of rows m0 .. m0 + ROWS - 1 into LDS (published by the caller's barrier): 16 lanes a row, the rows of
-// a wave's turns fetched together.
-template <int ROWS, int QW> __device__ __forceinline__ void row_scales(const FusedGemmArgs &a, int m0, float *rstd_s)
-{
-    constexpr int TURNS = ROWS / (4 * QW) + (ROWS % (4 * QW) != 0);
-    const int first = (threadIdx.x >> 4), c = threadIdx.x & 15, n = a.nss_in;
-    float sum[TURNS];
-#pragma unroll
-    for (int i = 0; i < TURNS; ++i) sum[i] = 0.f;
-    for (int t = c; t < n; t += 16) {
+// rsqrt(mean(x^2) + eps) of ROWS rows from m0 on into LDS (published by the caller's barrier), 16 lanes a row: request() goes in
+// front of the launch's first operands, finish() behind them.
+template <int ROWS, int QW> struct RowScales {
+    static constexpr int TURNS = ROWS / (4 * QW) + (ROWS % (4 * QW) != 0);   // rows per lane
+    static constexpr int U = TURNS > 4 ? 4 : 16 / TURNS;                     // sums per lane and row in flight
+    float v[TURNS][U];
+    __device__ __forceinline__ void load(const FusedGemmArgs &a, int m0, int t0)
+    {
 #pragma unroll
         for (int i = 0; i < TURNS; ++i) {
-            const int r = first + i * 4 * QW;
-            if (r < ROWS && m0 + r < a.M) sum[i] += a.ssq_in[(size_t)(m0 + r) * n + t];
+            const int m = m0 + (threadIdx.x >> 4) + i * 4 * QW;
+            const float *p = a.ssq_in + (size_t)(m < a.M ? m : a.M - 1) * a.nss_in;
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int t = t0 + (threadIdx.x & 15) + 16 * u;
+                v[i][u] = p[t < a.nss_in ? t : 0];
+            }
         }
     }
+    __device__ __forceinline__ void add(const FusedGemmArgs &a, int t0, float (&sum)[TURNS])
+    {
 #pragma unroll
-    for (int i = 0; i < TURNS; ++i) {
-        const int r = first + i * 4 * QW;
+        for (int i = 0; i < TURNS; ++i)
 #pragma unroll
-        for (int off = 8; off >= 1; off >>= 1) sum[i] += __shfl_xor(sum[i], off, 16);
-        if (r < ROWS && c == 0) rstd_s[r] = rsqrtf(sum[i] / (float)a.h + a.eps);
+            for (int u = 0; u < U; ++u) sum[i] += t0 + (int)(threadIdx.x & 15) + 16 * u < a.nss_in ? v[i][u] : 0.f;
     }
-}
+    __device__ __forceinline__ void request(const FusedGemmArgs &a, int m0) { load(a, m0, 0); }
+    __device__ __forceinline__ void finish(const FusedGemmArgs &a, int m0, float *rstd_s)
+    {
+        float sum[TURNS];
+#pragma unroll
+        for (int i = 0; i < TURNS; ++i) sum[i] = 0.f;
+        add(a, 0, sum);
+        for (int t0 = 16 * U; t0 < a.nss_in; t0 += 16 * U) {
+            load(a, m0, t0);
+            add(a, t0, sum);
+        }
+#pragma unroll
+        for (int i = 0; i < TURNS; ++i) {
+            const int r = (threadIdx.x >> 4) + i * 4 * QW;
+            const float total = row16_sum(sum[i]);
+            if (r < ROWS && (threadIdx.x & 15) == 0) rstd_s[r] = rsqrtf(total / (float)a.h + a.eps);
+        }
+    }
+};
 
 // grid = row blocks * column groups * J workgroups of QW waves on MT16 row tiles of 16; J > 1: writes partials[j][row][col].
 // J = 1: applies the epilogue, through LDS, so that a lane holds eight columns of a row and stores whole operand records.  As
@@ -548,12 +566,15 @@ __device__ __forceinline__ void qgemm16_rows(const FusedGemmArgs a, int NT16, in
         for (int i = 0; i < APT; ++i)   // without the padding: at nine tiles and eight waves a quarter of the stores
             if (TILES % QW == 0 || i < APT - 1 || wave + i * QW < TILES) ring[u][(wave + i * QW) * 64 + lane] = apre[u][i];
     };
+    const bool scaled = J == 1 && a.epi != FEPI_RESID && a.epi != FEPI_STORE;
+    RowScales<16 * MT16, QW> scales;
+    if (scaled) scales.request(a, m_base);
 #pragma unroll
     for (int u = 0; u < QDW; ++u) {
         load_a(u, u);
         load_w(u, u);
     }
-    if (J == 1 && a.epi != FEPI_RESID && a.epi != FEPI_STORE) row_scales<16 * MT16, QW>(a, m_base, rstd_s);
+    if (scaled) scales.finish(a, m_base, rstd_s);
     stage(0);
     __syncthreads();
     const int a_at = half * MTW * 128 + lane;
