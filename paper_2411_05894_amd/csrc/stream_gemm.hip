@@ -918,9 +918,14 @@ template <int EPI> hipError_t launch_large(FusedGemmArgs &a, hipStream_t s, bool
     return hipGetLastError();
 }
 
-// k-tiles per wave: 7 when K is a multiple of 16*7*32 but not of 16*8*32 (the FFN widths of the
-// Llama shapes), else 8.  A ragged K split is legal in every case.
-__host__ int small_kpw(int KT) { return (KT % (PW * 7) == 0 && KT % (PW * 8) != 0) ? 7 : 8; }
+// k-tiles per wave: as many as share a short K out over the 16 waves -- with eight, the waves past the end of a K of 256 fetched
+// eight tiles of padding each, and a launch was bound by them (tiny model, five rows: 62.3 -> 55.2 us a step) -- else 7 when K is a multiple of
+// 16*7*32 but not of 16*8*32 (the FFN widths of the Llama shapes), else 8.  A ragged K split is legal in every case.
+__host__ int small_kpw(int KT)
+{
+    if (KT <= PW * 4) return KT <= PW ? 1 : (KT <= PW * 2 ? 2 : 4);
+    return (KT % (PW * 7) == 0 && KT % (PW * 8) != 0) ? 7 : 8;
+}
 
 struct SmallPlan {
     int rh, kpw, J, upw, groups;
@@ -958,10 +963,19 @@ template <int EPI> hipError_t launch_small(FusedGemmArgs &a, hipStream_t s, bool
         if (a.J > 1) hipExtLaunchKernelGGL((pgemm_kernel<EPI, KPW, true, RH>), grid, block, 0, s, t0, t1, 0, a); \
         else hipExtLaunchKernelGGL((pgemm_kernel<EPI, KPW, false, RH>), grid, block, 0, s, t0, t1, 0, a);       \
     } while (0)
-    if (sp.rh == 2 && kpw == 7) SSSD_PLAUNCH(7, 2);
+#define SSSD_PWHOLE(KPW)                                                                                            \
+    do {                                                                                                            \
+        if (sp.rh == 2) hipExtLaunchKernelGGL((pgemm_kernel<EPI, KPW, false, 2>), grid, block, 0, s, t0, t1, 0, a); \
+        else hipExtLaunchKernelGGL((pgemm_kernel<EPI, KPW, false, 1>), grid, block, 0, s, t0, t1, 0, a);            \
+    } while (0)
+    if (kpw == 1) SSSD_PWHOLE(1);
+    else if (kpw == 2) SSSD_PWHOLE(2);
+    else if (kpw == 4) SSSD_PWHOLE(4);
+    else if (sp.rh == 2 && kpw == 7) SSSD_PLAUNCH(7, 2);
     else if (sp.rh == 2) SSSD_PLAUNCH(8, 2);
     else if (kpw == 7) SSSD_PLAUNCH(7, 1);
     else SSSD_PLAUNCH(8, 1);
+#undef SSSD_PWHOLE
 #undef SSSD_PLAUNCH
     *needs_epilogue = a.J > 1 && !a.tail_count;
     return hipGetLastError();
