@@ -137,8 +137,10 @@ __device__ __forceinline__ void for_row(const float *z, int begin, int end, int 
 }
 
 // The whole row, any order: 16-byte loads (four tokens per thread and load) when the row allows it.  `more` (wave-uniform)
-// is asked before every round of loads and ends the walk.
-template <typename F, typename P> __device__ __forceinline__ void for_whole_row(const float *z, int V, bool vec4, int tid, F body, P more)
+// is asked before every round of loads and ends the walk.  BACK: the last round first; a pass after a forward one then starts with what
+// the die's L2 still holds, which has no room for the rows of all its compute units (160 rows of 128256, top-k 20 + top-p 0.8
+// 35.2 -> 34.3 us, 128 rows, top-k 50 40.0 -> 37.8, 96 rows, top-p 0.95 50.7 -> 49.4).
+template <bool BACK, typename F, typename P> __device__ __forceinline__ void for_whole_row(const float *z, int V, bool vec4, int tid, F body, P more)
 {
     if (!vec4) {
         for (int base = 0; base < V && more(); base += ST * SU) for_row(z, base, min(V, base + ST * SU), tid, ST, body);
@@ -146,7 +148,9 @@ template <typename F, typename P> __device__ __forceinline__ void for_whole_row(
     }
     const f32x4 *z4 = reinterpret_cast<const f32x4 *>(z);
     const int V4 = V >> 2;
-    for (int base = 0; base < V4 && more(); base += ST * SU) {
+    const int rounds = (V4 + ST * SU - 1) / (ST * SU);
+    for (int n = 0; n < rounds && more(); ++n) {
+        const int base = (BACK ? rounds - 1 - n : n) * (ST * SU);
         f32x4 zz[SU];
 #pragma unroll
         for (int u = 0; u < SU; ++u) {
@@ -161,9 +165,9 @@ template <typename F, typename P> __device__ __forceinline__ void for_whole_row(
         }
     }
 }
-template <typename F> __device__ __forceinline__ void for_whole_row(const float *z, int V, bool vec4, int tid, F body)
+template <bool BACK = false, typename F> __device__ __forceinline__ void for_whole_row(const float *z, int V, bool vec4, int tid, F body)
 {
-    for_whole_row(z, V, vec4, tid, body, [] { return true; });
+    for_whole_row<BACK>(z, V, vec4, tid, body, [] { return true; });
 }
 
 // ---- several workgroups per row ----
@@ -489,7 +493,7 @@ __device__ __forceinline__ int short_row(ShortLds &L, Cluster &cl, const float *
 
     if (use_k) {
         // ---- pass 2: the tokens at or above the bound; the first workgroup does the rest ----
-        for_whole_row(zs, Vs, vec4, tid, [&](int i, float x, bool ok) {
+        for_whole_row<true>(zs, Vs, vec4, tid, [&](int i, float x, bool ok) {
             const uint32_t key = order_key(x);
             list_push(L, ok && key >= bound, key, seg_lo + i, lane);
         }, [&] { return __builtin_amdgcn_readfirstlane(*(volatile uint32_t *)&L.n) <= LIST_K_MAX; });
@@ -552,7 +556,7 @@ __device__ __forceinline__ int short_row(ShortLds &L, Cluster &cl, const float *
         // are LIST_MAX in the middle of a normal distribution.
         if ((float)V > ((r.mx - key_logit(kmin)) * r.scale * 16.f + 1.f) * (LIST_MAX / 4)) return SHORT_GENERAL;
         uint64_t sum = 0;
-        for_whole_row(zs, Vs, vec4, tid, [&](int, float x, bool ok) {
+        for_whole_row<true>(zs, Vs, vec4, tid, [&](int, float x, bool ok) {
             const uint64_t m = ok ? fix_mass(r, x) : 0;
             if (m) atomicAdd((unsigned long long *)&L.fine[lane & (FINE_COPIES - 1)][fine_bin(r, x)], (unsigned long long)m);
             sum += m;
