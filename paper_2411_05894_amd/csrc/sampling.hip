@@ -139,7 +139,7 @@ __device__ __forceinline__ void for_row(const float *z, int begin, int end, int 
 // The whole row, any order: 16-byte loads (four tokens per thread and load) when the row allows it.  `more` (wave-uniform)
 // is asked before every round of loads and ends the walk.  BACK: the last round first; a pass after a forward one then starts with what
 // the die's L2 still holds, which has no room for the rows of all its compute units (160 rows of 128256, top-k 20 + top-p 0.8
-// 35.2 -> 34.3 us, 128 rows, top-k 50 40.0 -> 37.8, 96 rows, top-p 0.95 50.7 -> 49.4).
+// 35.2 -> 34.1 us, 128 rows, top-k 50 40.0 -> 37.8, 96 rows, top-p 0.95 50.7 -> 49.4).
 template <bool BACK, typename F, typename P> __device__ __forceinline__ void for_whole_row(const float *z, int V, bool vec4, int tid, F body, P more)
 {
     if (!vec4) {
@@ -148,9 +148,8 @@ template <bool BACK, typename F, typename P> __device__ __forceinline__ void for
     }
     const f32x4 *z4 = reinterpret_cast<const f32x4 *>(z);
     const int V4 = V >> 2;
-    const int rounds = (V4 + ST * SU - 1) / (ST * SU);
-    for (int n = 0; n < rounds && more(); ++n) {
-        const int base = (BACK ? rounds - 1 - n : n) * (ST * SU);
+    constexpr int STEP = ST * SU;
+    for (int base = BACK ? (V4 - 1) / STEP * STEP : 0; (BACK ? base >= 0 : base < V4) && more(); base += BACK ? -STEP : STEP) {
         f32x4 zz[SU];
 #pragma unroll
         for (int u = 0; u < SU; ++u) {
