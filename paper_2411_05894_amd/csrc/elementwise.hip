@@ -137,7 +137,9 @@ __global__ void rollback_kernel(int B, int32_t *lens, const int32_t *accepted_le
 // order, and as many of V, stored transposed (8 positions of one channel per record); both turn through LDS.  Everything in
 // memory is read and written 16 bytes at a time, all loads of a thread in flight together: the kernel is bound by the
 // copy rate (read + write) of the memory.  A pitch of HD + 8 elements keeps the 2-byte column accesses of a wave in
-// separate banks (four rows 4 apart, 16 channels each).  4001 rows x 8 heads x 128, in or out: 17.4 -> 8.0 us (4.1 TB/s of reads and writes).
+// separate banks (four rows 4 apart, 16 channels each).  4001 rows x 8 heads x 128, in or out: 17.4 -> 8.0 us (4.1 TB/s of reads and writes);
+// 8192 rows 11.7 us (5.7 TB/s).
+// The caller's rows are streamed (read or written once, here), the cache's are not: two layers of 8192 rows in and out 54.7 -> 47.0 us.
 // A block that the rows cover only in part keeps its other rows: K rows and V elements outside are not written.
 // Blocks that the table sends outside the pool are skipped (nothing written on either side) and raise the sticky flag.
 template <int HD, bool IMPORT>
@@ -169,8 +171,8 @@ __global__ __launch_bounds__(256) void kv_block_copy_kernel(KvGeom kv, uint16_t 
         k[i] = v[i] = u32x4{0u, 0u, 0u, 0u};
         if (IMPORT) {
             if (in) {
-                k[i] = ke[rec];
-                v[i] = ve[rec];
+                k[i] = __builtin_nontemporal_load(ke + rec);
+                v[i] = __builtin_nontemporal_load(ve + rec);
             }
         } else {
             k[i] = kc[rec];
@@ -198,14 +200,17 @@ __global__ __launch_bounds__(256) void kv_block_copy_kernel(KvGeom kv, uint16_t 
 #pragma unroll
     for (int i = 0; i < N; ++i) {
         const int rec = threadIdx.x + 256 * i, row = IMPORT ? krow(rec) : rec / CPR, col = IMPORT ? kcol(rec) : rec % CPR;
-        if (row >= lo && row < hi) (IMPORT ? kc : ke)[rec] = *reinterpret_cast<const u32x4 *>(&ktile[row * PITCH + col * 8]);
+        if (row < lo || row >= hi) continue;
+        const u32x4 r = *reinterpret_cast<const u32x4 *>(&ktile[row * PITCH + col * 8]);
+        if (IMPORT) kc[rec] = r;
+        else __builtin_nontemporal_store(r, ke + rec);
     }
 #pragma unroll
     for (int i = 0; i < N; ++i) {
         const int rec = threadIdx.x + 256 * i;
         if (!IMPORT) {
             const int row = rec / CPR;
-            if (row >= lo && row < hi) ve[rec] = *reinterpret_cast<const u32x4 *>(&tile[row * PITCH + (rec % CPR) * 8]);
+            if (row >= lo && row < hi) __builtin_nontemporal_store(*reinterpret_cast<const u32x4 *>(&tile[row * PITCH + (rec % CPR) * 8]), ve + rec);
             continue;
         }
         const int ch = (rec >> 6) * 16 + (rec & 15), q = (rec >> 4) & 3;
