@@ -463,8 +463,8 @@ int run_step(sssd_ctx *c, int32_t B, int32_t k, const int32_t *tokens, const int
     const int M = B * (k + 1);
     StepIO io{tokens, lens, accepted_len, next_token, B, k, parents, path};
 
-    // Six launches per layer (QKV, attention, merge, O, gate/up, down) plus an epilogue launch
-    // after every GEMM on the pipelined kernel.
+    // Per layer QKV, attention, the merge of its segments (where a sequence can have two), O, gate/up, down, and an
+    // epilogue launch after every GEMM on the pipelined kernel whose K is split.
     {
         Prof p(c, s, SSSD_PROF_ELEM);
         HIP_TRY(launch_fused_embed(D, io, kv_geom(c), c->embed, c->layers[0].attn_norm, W.X, W.Ah_hi, W.Ah_lo, W.ssq1, W.pos_base,

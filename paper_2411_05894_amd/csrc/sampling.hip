@@ -283,7 +283,7 @@ __device__ __forceinline__ bool merge_bins(Cluster &cl, int pass, uint32_t *chis
 // keys in question share, which need no pass.  They are told early, since a pass more is what it would cost them: by the
 // range of the logits (pass 1), by the mass of the last bin (pass 2), or when the top-k list is full.  top_k above
 // SHORT_K_MAX is a kernel of its own, without the lists' registers.
-// Measured at vocabulary 128256, us, without lists -> with: 160 rows top-k 20 + top-p 0.8 212 -> 36, top-p 0.9 on N(0, 2)
+// Measured at vocabulary 128256, us, without lists -> with: 160 rows top-k 20 + top-p 0.8 212 -> 34, top-p 0.9 on N(0, 2)
 // 192 -> 77, neither 65 -> 46; 9 rows top-p 0.95 46 -> 30, neither 24 -> 16.  On the general path, 160 rows: top-p 0.9 on
 // equal logits 224 -> 216, on N(0, 0.1) 186 -> 188, on logits rounded to quarters 245 -> 218, top-k 50 on equal logits
 // 164 -> 102, top-k 300 167 -> 159.
