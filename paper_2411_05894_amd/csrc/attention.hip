@@ -77,7 +77,7 @@ __device__ __forceinline__ f32x4 pick(bool first, f32x4 x, f32x4 y)   // by valu
 // Workgroups 8 apart run on one die, where the passes and then the heads of a segment follow each other: they read one page
 // (64 KiB of K at eight heads of 128) at about the same time.  Two waves per SIMD: two workgroups fit a compute unit.
 template <int HD, int RT, bool ONCE>
-__global__ __launch_bounds__(NWAVE * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_partial_kernel(Dims D, AttnArgs a, int q_rows_pad, int passes)
+__global__ __launch_bounds__(NWAVE * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_partial_kernel(Dims D, AttnArgs a, int q_rows_pad)
 {
     constexpr int KS = HD / 32, DT = HD / 16;
     constexpr int NREC = 4 * HD;             // 16-byte records of a block of 32 positions, K and V alike
@@ -90,6 +90,7 @@ __global__ __launch_bounds__(NWAVE * 64) __attribute__((amdgpu_waves_per_eu(2, 2
 
     int kvh, wg;   // kv head; (turn, segment)
     int pass = 0;
+    const int passes = a.plan.passes;
     {
         int id = blockIdx.x;
         if (passes > 1) {
@@ -480,13 +481,12 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(Dims D, AttnArgs a, i
 
 template <int HD> hipError_t launch_partial(const Dims &D, const AttnArgs &a, int q_rows_pad, hipStream_t s)
 {
-    // More than MAX_TILES tiles are spread evenly over several passes over the cache.
-    const int passes = (a.row_tiles + MAX_TILES - 1) / MAX_TILES, rt = (a.row_tiles + passes - 1) / passes;
+    const int passes = a.plan.passes, rt = (a.row_tiles + passes - 1) / passes;
     const dim3 grid(a.B * a.plan.share * D.nkv * passes);
-#define SSSD_ALAUNCH(RT, ONCE) hipLaunchKernelGGL((attn_partial_kernel<HD, RT, ONCE>), grid, dim3(NWAVE * 64), 0, s, D, a, q_rows_pad, passes)
+#define SSSD_ALAUNCH(RT, ONCE) hipLaunchKernelGGL((attn_partial_kernel<HD, RT, ONCE>), grid, dim3(NWAVE * 64), 0, s, D, a, q_rows_pad)
     switch (rt) {
     case 1: SSSD_ALAUNCH(1, true); break;
-    case 2: SSSD_ALAUNCH(2, true); break;
+    case 2: if (passes == 1) SSSD_ALAUNCH(2, true); else SSSD_ALAUNCH(2, false); break;
     case 3: if (passes == 1) SSSD_ALAUNCH(3, true); else SSSD_ALAUNCH(3, false); break;
     default: if (passes == 1) SSSD_ALAUNCH(4, true); else SSSD_ALAUNCH(4, false); break;
     }
@@ -495,6 +495,29 @@ template <int HD> hipError_t launch_partial(const Dims &D, const AttnArgs &a, in
 }
 
 }  // namespace
+
+// Passes over the cache for `tiles` row tiles, heads = sequences x kv heads: as few as MAX_TILES allows; for four tiles, and for ten to
+// fifteen, one more (two of two; passes of three) or two more (ten tiles: of two) where that gives one workgroup to every compute unit or
+// to at least three quarters of them, and one more where the fewest leave a second round to few workgroups.  A workgroup's query tiles,
+// first operands and final sums grow with its tiles, and are most of its time when a wave has only a block or two; the passes share the
+// cache's bytes in the die's L2.  More passes than that cost 2-7 % at 20000 positions.  sssd_op_attention over cold caches, us, fewest / more
+// (workgroups for one segment), contexts 150, 500, 2048, 8000:
+//   four tiles, 8B, k = 15: B = 1 (8 / 16) 23.6 / 19.4, 25.1 / 22.3, 26.9 / 24.4, 32.2 / 27.3; B = 8 (64 / 128) 29.7 / 24.0, 34.6 / 30.3, 40.1 / 37.1,
+//     69.8 / 70.0; B = 14 (112 / 224) 31.6 / 25.8, 38.7 / 27.6, 51.4 / 43.6, 99.6 / 92.7; not: B = 6 (48 / 96) 26.7 / 23.3, 33.4 / 31.1, 39.3 / 35.0,
+//     58.8 / 64.5; B = 12 (96 / 192) 31.1 / 28.6, 37.5 / 35.7, 47.9 / 53.7, 87.6 / 116; B = 20 (160 / 320) 31.9 / 29.7, 36.8 / 34.3, 55.9 / 64.6
+//   ten, 70B, k = 18: B = 6 (144 / 240) 38.1 / 33.0, 49.4 / 35.0, 59.3 / 44.3, 106 / 97
+//   twelve, 70B, k = 23: B = 1 (24 / 32) 31.2 / 28.7, 34.2 / 33.7, 37.2 / 34.9, 44.7 / 40.3; B = 8 (192 / 256) 43.6 / 35.6, 54.5 / 38.8, 72.2 / 53.7,
+//     140 / 122; B = 14 (336 / 448) 48.2 / 44.7, 54.5 / 50.4, 91.0 / 82.3; not: B = 10 (240 / 320) 39.7 / 40.2, 43.7 / 44.7, 64.7 / 73.2, 155 / 176;
+//     B = 20 (480 / 640) 57.2 / 60.3, 65.4 / 69.7, 109 / 115
+//   fourteen, 70B, k = 27: B = 6 (192 / 240) 41.3 / 34.7, 52.4 / 37.9, 69.2 / 51.5, 137 / 115
+static int attention_passes(int tiles, long heads)
+{
+    const int fewest = (tiles + MAX_TILES - 1) / MAX_TILES;
+    if (tiles != 4 && (tiles < 10 || tiles > 15)) return fewest;
+    auto one_round = [heads](int passes) { return heads * passes <= 256 && 256 / (heads * passes) * (heads * passes) > 192; };
+    if (one_round(fewest + 1) || (heads * fewest > 256 && heads * (fewest + 1) <= 512)) return fewest + 1;
+    return tiles == 10 && one_round(fewest + 2) ? fewest + 2 : fewest;
+}
 
 // Segments per sequence.  One workgroup per compute unit: what bounds a launch is the bytes that the busiest compute unit
 // pulls, and every segment is a partial result of g*(k+1) rows to write and merge.  Two workgroups fit a compute unit; they are
@@ -509,11 +532,11 @@ template <int HD> hipError_t launch_partial(const Dims &D, const AttnArgs &a, in
 AttnPlan attention_plan(const Dims &D, int B, int k)
 {
     const int tiles = (D.g * (k + 1) + 15) / 16;
-    const int passes = (tiles + MAX_TILES - 1) / MAX_TILES;
-    const long units = (long)B * D.nkv * passes;   // workgroups for one segment of every sequence
-    long share = 256 / units;
-    if (passes > 1 && share * units <= 192) share = 512 / units;
     AttnPlan p;
+    p.passes = attention_passes(tiles, (long)B * D.nkv);
+    const long units = (long)B * D.nkv * p.passes;   // workgroups for one segment of every sequence
+    long share = 256 / units;
+    if (p.passes > 1 && share * units <= 192) share = 512 / units;
     p.share = share < 1 ? 1 : (share > ATTN_MAX_SEGMENTS ? ATTN_MAX_SEGMENTS : (int)share);
     return p;
 }

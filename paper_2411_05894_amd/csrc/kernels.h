@@ -8,6 +8,7 @@
 // rounding, on the sequences beside it.
 struct AttnPlan {
     int share;         // segments of a sequence at most
+    int passes;        // over the cache, the 16-row tiles of query rows spread evenly
 };
 constexpr int ATTN_MAX_SEGMENTS = 64;   // per sequence: what the merge takes
 constexpr int ATTN_WHOLE_BLOCKS = 8;    // sequences of up to so many blocks of 32 positions are one segment
