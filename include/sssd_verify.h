@@ -117,7 +117,8 @@ int sssd_verify_init(const sssd_model_config *cfg, const sssd_weights *weights, 
  *                longest prefix with tokens[b][i+1] == argmax(logits[b][i])
  *   next_token   device int32 [B] out; argmax(logits[b][accepted_len[b]]), the
  *                bonus token, so accepted drafts + next_token is exactly what greedy
- *                decoding emits.  Ties in argmax go to the lowest token id.
+ *                decoding emits.  Ties in argmax go to the lowest token id; a logit that
+ *                is no number never wins (token 0 if none of a row is one).
  * Sequence b is cache slot b (0 <= b < B <= max_batch).  The step writes K/V
  * rows lens[b] .. lens[b]+k of every layer and does NOT change lens; rows of
  * rejected drafts stay behind as dead data and are overwritten by the next

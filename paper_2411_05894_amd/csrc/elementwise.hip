@@ -54,6 +54,7 @@ __global__ __launch_bounds__(1024) void accept_kernel(StepIO io, const float *pa
                 if (ov > bv || (ov == bv && oi < bi)) { bv = ov; bi = oi; }
             }
             if (lane == 0) {
+                if (bi == 0x7FFFFFFF) bi = 0;   // no logit of the row is a number
                 that_s[j] = bi;
                 that[b * sq + j] = bi;
             }
