@@ -264,10 +264,13 @@ template <int EPI> __device__ __host__ __forceinline__ int column_blocks(const F
 }
 
 // grid = (column-block groups, row tiles of 16), 256 threads; each wave takes column blocks
-// cb0 + wave, cb0 + wave + 4, ...  The partial sums of a block are fetched one block ahead (the
-// first block's before the row scales are reduced), all slices of a batch together, so the kernel's dependent memory round
-// trips overlap.  What is left is the traffic of the slices and the launch: RESID of 160 rows x 4096 in seven slices, 26 MB,
-// takes 10 us.  RESID leaves one sum of squares per row and workgroup: the launches that scale rows read few of them.
+// cb0 + wave, cb0 + wave + 4, ...  The partial sums of the first block are fetched before the row scales are reduced, all slices of
+// a batch together, so the kernel's dependent memory round trips overlap.  A wave has a second block only in wide outputs at many
+// rows, and it is not fetched ahead: that took 129-143 registers, room for three workgroups per compute unit under a grid made for
+// four, and a second, quarter-full round at 512 rows (RESID of 4096 columns 12.8 -> 11.9 us without; SWIGLU of 160 rows 11.8 -> 11.1; held to 128
+// registers it spilled, and steps were 0.2-1 % slower).  What is left is the traffic of the slices and the launch: RESID of 160 rows x
+// 4096 in seven slices, 26 MB, takes 11 us.  RESID leaves one sum of squares per row and workgroup: the launches that scale rows read
+// few of them.
 template <int EPI>
 __global__ __launch_bounds__(256) void epi_kernel(FusedGemmArgs a, int blocks_per_wg)
 {
@@ -338,8 +341,7 @@ __global__ __launch_bounds__(256) void epi_kernel(FusedGemmArgs a, int blocks_pe
     float ss = 0.f;   // RESID: of this row, over the thread's columns
     Best best = Best::none();   // LM: likewise
     for (int cb = cb_begin + wave; cb < cb_end; cb += 4) {
-        Vec8 n0v, n1v;
-        fetch(cb + 4, n0v, n1v);
+        if (cb != cb_begin + wave) fetch(cb, v0, v1);
         const int col = column(cb);
         const bool live = col >= 0;
         if (EPI == FEPI_QKV) {
@@ -353,8 +355,6 @@ __global__ __launch_bounds__(256) void epi_kernel(FusedGemmArgs a, int blocks_pe
         } else {  // FEPI_LM
             if (live) lm8(a, m, col, rs, v0, best);
         }
-        v0 = n0v;
-        v1 = n1v;
     }
     if (EPI == FEPI_LM) {   // one arg-max per row and workgroup
         __shared__ Best best_s[4][16];
