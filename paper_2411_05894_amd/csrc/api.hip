@@ -286,7 +286,7 @@ int sssd_verify_plan_check(const sssd_model_config *cfg, int32_t B, int32_t k)
     const size_t ntot[5] = {(size_t)D.qd + 2 * D.kd, (size_t)D.h, 2 * (size_t)D.f, (size_t)D.h, (size_t)D.V};
     const int kin[5] = {D.h, D.qd, D.h, D.f, D.h};
     for (int i = 0; i < 5; ++i)
-        if (stream_gemm_scratch_bytes(M, (int)ntot[i], kin[i]) > W.partial_bytes) return SSSD_ECAPACITY;
+        if (stream_gemm_launch_bytes(M, (int)ntot[i], kin[i]) > W.partial_bytes) return SSSD_ECAPACITY;
     // attention partial slots: [kv heads][B][segments] x q_rows_pad rows, laid out behind part_o / part_ml
     if ((size_t)D.nkv * B * attention_plan(D, B, k).share > W.attn_slots) return SSSD_ECAPACITY;
     return SSSD_OK;

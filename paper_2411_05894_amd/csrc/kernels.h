@@ -98,6 +98,7 @@ struct FusedGemmArgs {
 int stream_gemm_max_rows();
 const char *stream_gemm_kernel_name(int M, int N, int K);   // the kernel that serves a GEMM of M rows
 size_t stream_gemm_partial_bytes(const Dims &D, int M);
+size_t stream_gemm_launch_bytes(int M, int N, int K);    // one GEMM of them
 size_t stream_gemm_scratch_bytes(int M, int N, int K);   // one GEMM (kernel-level entry point)
 // Launches the weight-streaming kernel and records its plan (J, part_rows, ...) in `a`; when
 // *needs_epilogue comes back true the results are split-K partials and launch_stream_epilogue

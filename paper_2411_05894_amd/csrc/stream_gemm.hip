@@ -885,7 +885,7 @@ template <int EPI> hipError_t launch_large(FusedGemmArgs &a, hipStream_t s, bool
     if (EPI == FEPI_QKV) { a.seg0 = a.nq * (a.d >> 4); a.seg1 = a.nkv * (a.d >> 4); }
     else if (EPI == FEPI_SWIGLU) { a.seg0 = a.NT; a.seg1 = a.NT; }
     else { a.seg0 = NT16; a.seg1 = 0; }
-    if ((size_t)a.J * a.part_rows * a.Ntot * sizeof(float) > a.partial_bytes) return hipErrorInvalidValue;
+    if (a.J > 1 && (size_t)a.J * a.part_rows * a.Ntot * sizeof(float) > a.partial_bytes) return hipErrorInvalidValue;
     const int mt16 = (a.M + 15) / 16;
     const RowBlocks rows = row_blocks(mt16);
     const dim3 grid(p.groups * a.J * rows.RB), block(p.qw * 64);
@@ -990,46 +990,52 @@ const char *stream_gemm_kernel_name(int M, int N, int K)
     return is_small(M, N, (K + 31) / 32 * 32) ? "pgemm_kernel" : "qgemm16_kernel";
 }
 
-// Split-K scratch needed for M rows: the largest J * rows * Ntot over the model's GEMMs.
-size_t stream_gemm_partial_bytes(const Dims &D, int M)
-{
-    size_t best = 0;
-    const size_t rows_small = M > 16 ? 32 : 16;
-    auto consider = [&](int K, size_t ntot) {
-        const int KT = (K + 31) / 32, ks = PW * small_kpw(KT);
-        const size_t need = (size_t)((KT + ks - 1) / ks) * rows_small * ntot;
-        if (need > rows_small * ntot && need > best) best = need;   // only a split K needs scratch
-    };
-    consider(D.h, (size_t)D.qd + 2 * D.kd);
-    consider(D.qd, D.h);
-    consider(D.h, 2 * (size_t)D.f);
-    consider(D.f, D.h);
-    consider(D.h, D.V);
-    // larger steps: the K split depends on the number of row tiles, so take the worst case over every step size up to M
-    for (int rows_c = 16;; rows_c += 16) {
-        const int rows = rows_c < round_up(M, 16) ? rows_c : round_up(M, 16);
-        auto large = [&](int K, size_t ntot) {
-            if (is_small(rows, (int)ntot, round_up(K, 32))) return;
-            const size_t need = (size_t)q_plan((int)ntot, round_up(K, 32), rows).J * rows * ntot;
-            if (need > best) best = need;
-        };
-        large(D.h, (size_t)D.qd + 2 * D.kd);
-        large(D.qd, D.h);
-        large(D.h, 2 * (size_t)D.f);
-        large(D.f, D.h);
-        large(D.h, D.V);
-        if (rows_c >= M) break;
-    }
-    return best * sizeof(float);
-}
-
-size_t stream_gemm_scratch_bytes(int M, int N, int K)
+// K slices of a GEMM of M rows, and the rows that each of its slices has in the split-K scratch.
+static int gemm_slices(int M, int N, int K, int *rows)
 {
     const int KT = (K + 31) / 32;
-    if (!is_small(M, N, KT * 32)) return (size_t)q_plan(N, KT * 32, M).J * round_up(M, 16) * N * sizeof(float);
+    if (!is_small(M, N, KT * 32)) {
+        *rows = round_up(M, 16);
+        return q_plan(N, KT * 32, M).J;
+    }
+    *rows = M <= 16 ? 16 : 32;
     const int ks = PW * small_kpw(KT);
-    const size_t j = (size_t)((KT + ks - 1) / ks);
-    return j > 1 ? j * (M <= 16 ? 16 : 32) * N * sizeof(float) : 0;
+    return (KT + ks - 1) / ks;
+}
+
+// Split-K scratch that a launch of M rows uses: none where the K is whole.
+size_t stream_gemm_launch_bytes(int M, int N, int K)
+{
+    int rows;
+    const size_t J = (size_t)gemm_slices(M, N, K, &rows);
+    return J > 1 ? J * rows * N * sizeof(float) : 0;
+}
+
+// ... that any step of up to M rows uses: the K split depends on the number of row tiles, so the worst case over every size.
+size_t stream_gemm_partial_bytes(const Dims &D, int M)
+{
+    size_t most = 0;
+    auto consider = [&](int rows, int N, int K) {
+        const size_t need = stream_gemm_launch_bytes(rows, N, K);
+        if (need > most) most = need;
+    };
+    for (int rows = 16; rows <= round_up(M, 16); rows += 16) {
+        consider(rows, D.qd + 2 * D.kd, D.h);
+        consider(rows, D.h, D.qd);
+        consider(rows, 2 * D.f, D.h);
+        consider(rows, D.h, D.f);
+        consider(rows, D.V, D.h);
+    }
+    return most;
+}
+
+// What the kernel-level entry points ask for.  qgemm16_kernel applies the epilogue of a whole K itself and touches no scratch, but one
+// copy of the output is asked for all the same: callers hold these sizes, and the entry point with scratch of its own refuses by them.
+size_t stream_gemm_scratch_bytes(int M, int N, int K)
+{
+    int rows;
+    const size_t J = (size_t)gemm_slices(M, N, K, &rows);
+    return J > 1 || !is_small(M, N, (K + 31) / 32 * 32) ? J * rows * N * sizeof(float) : 0;
 }
 
 hipError_t launch_stream_gemm(FusedGemmArgs &a, int epilogue, hipStream_t s, bool *needs_epilogue, hipEvent_t t0,

@@ -85,3 +85,13 @@ def test_the_gemm_kernel_of_a_matrix_follows_from_its_size_without_gpu():
     assert of(0, 16, 32) == of(1, 8, 32) == of(1, 16, 0) == ""
     for M in (1, 16, 17, 32, 33, 160, 512):
         assert sv.sssd_op_gemm_kernel_name(M) == of(M, 28672, 4096)
+
+
+def test_workspace_holds_no_copy_of_logits_that_no_launch_splits_without_gpu():
+    """An LM head whose K is never split over workgroups adds its arg-max partials to the workspace (a value and an index per
+    16 columns and row, rows in whole blocks of 160), not the fp32 copy of its output that only split sums pass through."""
+    from types import SimpleNamespace
+    base = MODEL_SHAPES["8b"].__dict__
+    ws = [sv.sssd_verify_sizes(sv.make_config(SimpleNamespace(**{**base, "vocab": v}), 16, 31, 512))[1] for v in (1024, 128256)]
+    rows = 640                                    # 16 * 32 in blocks of 160
+    assert ws[1] - ws[0] <= 8 * rows * (128256 - 1024) // 16 + 1024
