@@ -16,12 +16,12 @@ from sssd_synth import MODEL_SHAPES, global_weight_specs, layer_weight_specs, no
 DEV = "cuda:0"
 CASES = [  # shape, k, lens, max_seq
     ("8b", 8, [5000, 17, 1200], 20000),            # three row tiles
-    ("8b", 4, [9000], 9100),                       # one sequence, segments of an odd number of blocks
+    ("8b", 4, [9000], 9100),                       # one sequence, segments of nine blocks: a partial round of the waves
     ("8b", 31, [479] * 16, 1024),                  # eight row tiles in two passes, one segment per sequence
     ("8b", 12, [0, 700, 31, 32, 1500], 4096),      # four row tiles
     ("70b", 8, [2048, 40], 8192),                  # five row tiles
     ("70b", 10, [700, 3000], 3100),                # six row tiles
-    ("70b", 12, [64, 640], 1000),                  # seven row tiles: two passes, the second with a wave to spare
+    ("70b", 12, [64, 640], 1000),                  # seven row tiles: two passes of four, one tile to spare
     ("8b", 0, [100 * i for i in range(40)], 4200),
     ("tiny", 1, [(37 * i) % 301 for i in range(130)], 400),   # more than 64 sequences, head size 64
 ]

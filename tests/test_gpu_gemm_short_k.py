@@ -1,11 +1,15 @@
 """Steps of up to 32 rows with a short K: one, two and four k-tiles per wave, on both sides of every line between them, K that ends
-inside a k-tile, and waves with nothing but padding."""
+inside a k-tile, and waves with nothing but padding; the plain store and the fused epilogues."""
+from types import SimpleNamespace
+
 import pytest
 import torch
 
 pytestmark = pytest.mark.gpu
 
+from harness import Pair, compare_step
 from paper_2411_05894_amd import binding as sv
+from sssd_synth import uniform_int
 from test_gpu_gemm_pipeline import check
 
 
@@ -14,3 +18,24 @@ from test_gpu_gemm_pipeline import check
 def test_short_k(N, K, M):
     assert sv.sssd_op_gemm_kernel_of(M, N, K) == "pgemm_kernel"
     check(N, K, M)
+
+
+# QKV and LM head, residual and SwiGLU with two k-tiles per wave (17, 20 and 17 k-tiles; the down projection's 33 take four) and with
+# four (33, 36, 33 and 47), one and two row tiles
+@pytest.mark.parametrize("hidden,nq,ffn", [(528, 10, 1040), (1040, 18, 1504)])
+@pytest.mark.parametrize("B,k", [(1, 4), (2, 7), (1, 16), (4, 7)])     # 5, 16, 17 and 32 rows
+def test_fused_short_k(hidden, nq, ffn, B, k):
+    print(f"fused short K h={hidden} ffn={ffn} B={B} k={k}", flush=True)
+    s = SimpleNamespace(name="edge", n_layers=2, hidden=hidden, n_q_heads=nq, n_kv_heads=2, head_dim=64, ffn=ffn, vocab=1040, rms_eps=1e-5,
+                        rope_base=10000.0)
+    p = Pair(s, seed=35, max_batch=B, max_k=k, max_seq=96, unit_gains=False)
+    lens = uniform_int(36, B * 64 + k, (B,), 0, 96 - k - 1)
+    for b in range(B):
+        p.prefill_random_kv(37, b, int(lens[b]), oracle_slot=b)
+    tokens = uniform_int(38, B * 64 + k, (B, k + 1), 0, s.vocab - 1)
+    ref = p.oracle.verify_step(tokens, lens.to(torch.int32), return_hidden=True)
+    gpu = p.step(tokens, lens.to(torch.int32))
+    compare_step(gpu, ref, tokens)
+    herr = (gpu["hidden"] - ref["hidden"]).abs().max().item() / ref["hidden"].abs().max().item()
+    assert herr < 5e-3      # a bf16 rounding of a new K or V element may fall the other way: 2^-9 of it
+    p.ctx.sssd_verify_destroy()
