@@ -30,7 +30,8 @@
 // quarter of the channels.  The segments of a sequence are merged by a second kernel in fixed order
 // (deterministic); a sequence that lies in one segment is finished by its workgroup itself.
 //
-// What bounds it: the cache stream from a few MB per compute unit on (a compute unit pulls 30-35 GB/s), below that the chain
+// What bounds it: the cache stream from a few MB per compute unit on (a compute unit pulls 24 GB/s with all of them at work, 537 MB in
+// 87 us, and 32 GB/s beside idle ones, the longest of 32 ragged sequences, 2.1 MB in 66 us), below that the chain
 // from the launch to the first operands and the final sums.  Measured against one wave per row tile with K and V staged
 // through LDS behind two barriers per block, us of sssd_op_attention over cold caches (four small launches in it, 17 us):
 // 8B shape B = 2, k = 17, context 12345 51 -> 45; B = 16, k = 31, 4000 132 -> 105; B = 32, k = 4, 1024..4096 90 -> 80; B = 4, k = 8,
@@ -527,8 +528,11 @@ static int attention_passes(int tiles, long heads)
 //     k = 4, B = 20: 160 57 / 52, 320 72 / 59, 480 66 / 56; 70B, k = 0, B = 20: 160 59 / 55, 480 64 / 53
 //   two passes: 70B, k = 8, B = 4: 256 42 / 41, 512 44 / 41; B = 9: 144 66 / 65, 432 61 / 55; B = 12: 192 67 / 66, 384 72 / 64; 8B, B = 10, k = 31:
 //     160 79 / 78, 480 71 / 63; B = 12, k = 24: 192 79 / 78, 384 79 / 68; B = 16, k = 31, context 1000: 256 55, 512 67
-// At least four blocks per segment, one for each wave; up to eight blocks are one segment, which needs no merge (tiny shape, one
-// sequence of 133 positions: step 73.5 -> 68.6 us).
+// At least four blocks per segment, one for each wave; up to eight blocks are one segment, which is finished by its workgroup: its partial
+// results and the merge's work cost more than the idle compute units, also where a cache with room has the merge launched.  One segment /
+// segments of four blocks, caches of 4096, contexts 130 / 230: 8B B = 1, k = 0 17.0 / 18.9, 17.1 / 18.8, k = 8 22.2 / 22.5, 22.2 / 22.9; B = 4, k = 8
+// 24.2 / 25.3, 24.5 / 25.9; B = 16, k = 4 24.6 / 27.1, 24.5 / 27.6; 70B B = 1, k = 8 29.0 / 29.3, 29.1 / 29.6; B = 4, k = 8 31.6 / 33.0, 31.8 / 33.6
+// (without a merge launch, tiny shape, one sequence of 133 positions: step 73.5 -> 68.6 us).
 AttnPlan attention_plan(const Dims &D, int B, int k)
 {
     const int tiles = (D.g * (k + 1) + 15) / 16;

@@ -58,7 +58,7 @@ template <bool COH, typename T> __device__ __forceinline__ T ld(const T *p)
 
 // One output element pair of a unit: row m, column c of the 16-column tile(s).  v0/v1 are the
 // fp32 results of the unit's first/second tile.  The 16 lanes c = 0..15 of a row are adjacent
-// lanes of one wave (RESID and LM reduce over them).
+// lanes of one wave (RESID reduces over them).  Not for LM, whose callers keep a running arg-max.
 template <int EPI, bool COH = false>
 __device__ __forceinline__ void epilogue(const FusedGemmArgs &a, int unit, int m, int c, bool valid, float v0, float v1, float rs)
 {

@@ -55,9 +55,9 @@ struct StepIO {
 // ------------------------------------------------------------ fused GEMMs ----
 enum FusedEpilogue {
     FEPI_QKV = 0,    // RMSNorm scale, rotary embedding, Q operand packing, KV append; units = rotary tile pairs
-    FEPI_RESID = 1,  // X += acc; packed X*gamma_next; sums of squares per 16 columns; units = single tiles
+    FEPI_RESID = 1,  // X += acc; packed X*gamma_next; nss_out sums of squares per row; units = single tiles
     FEPI_SWIGLU = 2, // RMSNorm scale, silu(gate)*up, operand packing; units = (gate tile, up tile)
-    FEPI_LM = 3,     // RMSNorm scale, per-tile arg-max, optional logits; units = single tiles
+    FEPI_LM = 3,     // RMSNorm scale, n_part arg-max partials per row, optional logits; units = single tiles
     FEPI_STORE = 4   // out[m][n] = acc (kernel-level entry point only)
 };
 

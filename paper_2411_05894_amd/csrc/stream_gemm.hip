@@ -23,7 +23,7 @@
 //
 // Epilogues (everything Table 2 leaves out is folded into them):
 //   QKV     RMSNorm scale, rotary embedding, Q -> packed hi/lo operand, K/V -> cache (in place)
-//   RESID   X += acc; packed X*gamma_next hi/lo; sums of squares per 16 columns
+//   RESID   X += acc; packed X*gamma_next hi/lo; sums of squares per 16 columns, or per workgroup of epi_kernel (nss_out says how many)
 //   SWIGLU  RMSNorm scale, silu(gate)*up -> packed hi/lo operand
 //   LM      RMSNorm scale, arg-max of a workgroup's columns (with an unsplit K logits are materialised only if asked for; else
 //           they pass through memory once as unscaled sums)
