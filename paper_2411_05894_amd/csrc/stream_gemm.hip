@@ -414,12 +414,13 @@ __device__ __forceinline__ const u32x4 *tile_weights_seg(const FusedGemmArgs &a,
     return base + gt * stride;
 }
 
-// Concatenated 16-column tile at place t of the order in which the waves take them: the two tiles of an epilogue unit (rotary
-// partners, gate and up) side by side, so that one wave holds both.
-__device__ __forceinline__ int q_tile(const FusedGemmArgs &a, int t)
+// Concatenated 16-column tile at place t of the order in which the waves take them.  WHOLE: the two tiles of an epilogue unit (rotary
+// partners, gate and up) side by side, so that one wave holds both.  Else any order serves; gate and up side by side measured
+// 14.5 against 16.7-17.4 us for 2 x 8192 columns of K = 2048 at 20 rows (8B gate/up at 65..80 rows 50 against 47, at 160 rows the same).
+template <bool WHOLE> __device__ __forceinline__ int q_tile(const FusedGemmArgs &a, int t)
 {
-    if (a.epi == FEPI_QKV) return unit_tile<FEPI_QKV>(a, t >> 1, t & 1);
     if (a.epi == FEPI_SWIGLU) return unit_tile<FEPI_SWIGLU>(a, t >> 1, t & 1);
+    if (WHOLE && a.epi == FEPI_QKV) return unit_tile<FEPI_QKV>(a, t >> 1, t & 1);
     return t;
 }
 
@@ -475,6 +476,9 @@ template <int ROWS, int QW> struct RowScales {
 // 128256 at 91 rows 27 us; whole steps with such a launch: 70B layer 625 -> 605 us, two 8B layers at 512 rows 1022 -> 984, 8B
 // layer and head at 91 rows 435 -> 415.  (Per element from the accumulators, in 2-byte stores, it had cost more than it saved.)
 // Both operands are the packed tiles as stored: lane l holds (row or column l%16, k-slots 8*(l/16)..+7) of a 16 x 32 tile.
+// Whole and split K have kernels of their own (WHOLE): the epilogue's row scales and tile order in front of the first loads, and its
+// staging area, cost the split GEMMs, which use none of it, 0.3-1 us each -- 4096 x 4096 at 36 rows 13.3 -> 12.4 us, 8B QKV at 36 rows
+// 14.6 -> 13.5, K = 1024 at 33 rows 7.7 -> 6.9; steps of 33..160 rows 0.5-4 %.
 // One 32-column tile pair per wave, so two waves share a SIMD at QW = 8 (256 columns per workgroup, the large matrices);
 // QW = 4 for the small ones, whose K then splits half as often.
 //
@@ -494,20 +498,20 @@ template <int ROWS, int QW> struct RowScales {
 // loads then, not streaming ones).  There the matrix pipes bound everything and two waves share 64 columns, each on half
 // of the rows: half the operand reads per MFMA for a second fetch of the weights from the die's L2 (8B gate/up at 512 rows
 // 235 -> 220 us, but 84 -> 100 us at 160 rows, which are still bound by what a compute unit can fetch).
-template <int MT16, int QW, bool BLOCKS> struct QShape {
+template <int MT16, int QW, bool BLOCKS, bool WHOLE> struct QShape {
     static constexpr int QDW = BLOCKS ? 3 : 4;                  // k-tiles in flight
     static constexpr int TILES = MT16 * 2;                      // activation tiles (hi and lo) of one k-tile
     static constexpr int APT = (TILES + QW - 1) / QW;           // tiles fetched per wave; surplus waves re-read the last one
     static constexpr int SLOT = TILES * 64;                     // records of a ring slot
-    static constexpr int RING = QDW * SLOT, STAGE = QW * 320;   // records of the ring, of the epilogue's staging area
+    static constexpr int RING = QDW * SLOT, STAGE = WHOLE ? QW * 320 : 0;   // records of the ring, of the epilogue's staging area
     static constexpr int LDS = RING > STAGE ? RING : STAGE;
 };
 
 // Rows 16 * tile0 .. 16 * (tile0 + MT16) - 1; gj: column group and slice.  ring: QDW slots.
-template <int MT16, int QW, bool BLOCKS>
+template <int MT16, int QW, bool BLOCKS, bool WHOLE>
 __device__ __forceinline__ void qgemm16_rows(const FusedGemmArgs a, int NT16, int tile0, int gj, u32x4 *lds, float *rstd_s)
 {
-    using S = QShape<MT16, QW, BLOCKS>;
+    using S = QShape<MT16, QW, BLOCKS, WHOLE>;
     u32x4 (*ring)[S::SLOT] = reinterpret_cast<u32x4 (*)[S::SLOT]>(lds);
     constexpr int QDW = S::QDW, TILES = S::TILES, APT = S::APT;
     constexpr bool TWO = BLOCKS || MT16 <= 3;     // sums in two levels, where the registers allow it
@@ -524,17 +528,19 @@ __device__ __forceinline__ void qgemm16_rows(const FusedGemmArgs a, int NT16, in
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int half = wave / CW, cg = wave % CW;
     const int m_base = tile0 * 16;
+    // WHOLE: J is 1, but a value of the launch all the same.  With a k-range known to begin at zero the addresses of the loads in
+    // flight take 8-24 registers more (17..32 rows: spills, 1.03 x the time).
     const int J = a.J, grp = (int)((unsigned)gj / (unsigned)J), j = gj - grp * J;
     const int KT = a.KT;
     const int kps = a.kps;
     const int kt_begin = j * kps, kt_end = kt_begin + kps < KT ? kt_begin + kps : KT;
     const int n_iter = kt_end - kt_begin;
 
-    const int c16 = (grp * CW + cg) * NC;         // this wave's first 16-column tile, in the order of the epilogue units
+    const int c16 = (grp * CW + cg) * NC;         // this wave's first 16-column tile, in the order of q_tile
     const u32x4 *wp[NC];
 #pragma unroll
     for (int ct = 0; ct < NC; ++ct)               // columns past the matrix re-read the last tile, never stored
-        wp[ct] = tile_weights_seg(a, q_tile(a, c16 + ct < NT16 ? c16 + ct : NT16 - 1)) + lane;
+        wp[ct] = tile_weights_seg(a, q_tile<WHOLE>(a, c16 + ct < NT16 ? c16 + ct : NT16 - 1)) + lane;
     const u32x4 *asrc[APT];
 #pragma unroll
     for (int i = 0; i < APT; ++i) {
@@ -566,7 +572,7 @@ __device__ __forceinline__ void qgemm16_rows(const FusedGemmArgs a, int NT16, in
         for (int i = 0; i < APT; ++i)   // without the padding: at nine tiles and eight waves a quarter of the stores
             if (TILES % QW == 0 || i < APT - 1 || wave + i * QW < TILES) ring[u][(wave + i * QW) * 64 + lane] = apre[u][i];
     };
-    const bool scaled = J == 1 && a.epi != FEPI_RESID && a.epi != FEPI_STORE;
+    const bool scaled = WHOLE && J == 1 && a.epi != FEPI_RESID && a.epi != FEPI_STORE;
     RowScales<16 * MT16, QW> scales;
     if (scaled) scales.request(a, m_base);
 #pragma unroll
@@ -657,11 +663,11 @@ __device__ __forceinline__ void qgemm16_rows(const FusedGemmArgs a, int NT16, in
 
     // acc[i][ct][v] of lane l: row 16 * (half * MTW + i) + 4*(l/16) + v, column l%16 of tile q_tile(c16 + ct)
     const int row0 = m_base + 16 * half * MTW;
-    if (J > 1) {
+    if constexpr (!WHOLE) {
 #pragma unroll
         for (int ct = 0; ct < NC; ++ct) {
             if (c16 + ct >= NT16) continue;
-            const int col = q_tile(a, c16 + ct) * 16 + (lane & 15);
+            const int col = q_tile<false>(a, c16 + ct) * 16 + (lane & 15);
 #pragma unroll
             for (int i = 0; i < MTW; ++i) {
 #pragma unroll
@@ -748,29 +754,29 @@ __device__ __forceinline__ void qgemm16_rows(const FusedGemmArgs a, int NT16, in
 
 // BLOCKS: RB blocks of rows, of MT16 tiles, or (MT16 = 0) the first n8 of eight tiles and the others of six.  Blocks of one
 // size have kernels of their own: in the mixed one they are 2 % slower.
-template <int MT16, int QW, bool BLOCKS>
+template <int MT16, int QW, bool BLOCKS, bool WHOLE>
 // Registers: two workgroups of four waves per compute unit up to nine tiles (tiny shape with a vocabulary of 128256, 144 rows:
 // 276 registers and one workgroup 69 us, 256 and two 66), which at three tiles costs more than it gives (8B gate/up at 33 rows
 // 44.4 -> 45.2); four waves per SIMD up to two tiles.
 __global__ __launch_bounds__(QW * 64) __attribute__((amdgpu_waves_per_eu(!BLOCKS && MT16 <= 2 ? 4 : (QW == 4 && MT16 >= 4 && MT16 <= 9 ? 2 : 1)))) void qgemm16_kernel(FusedGemmArgs a, int RB, int n8, int NT16, int pairs)
 {
     if constexpr (BLOCKS) {
-        using S = QShape<MT16 ? MT16 : 8, QW, true>;
+        using S = QShape<MT16 ? MT16 : 8, QW, true, WHOLE>;
         __shared__ u32x4 lds[S::LDS];
-        __shared__ float rstd_s[16 * (MT16 ? MT16 : 8)];
+        __shared__ float rstd_s[WHOLE ? 16 * (MT16 ? MT16 : 8) : 1];
         const int bid = blockIdx.x, whole = pairs & ~7;   // (column group, slice) pairs; those in full sets of 8
         const bool in_set = bid < whole * RB;
         const int x = in_set ? bid >> 3 : bid - whole * RB, by = in_set ? RB : pairs - whole;
         const int q = (int)((unsigned)x / (unsigned)by), r = x - q * by;
         const int rb = in_set ? r : q, gj = in_set ? q * 8 + (bid & 7) : whole + r;
-        if constexpr (MT16 != 0) qgemm16_rows<MT16, QW, true>(a, NT16, MT16 * rb, gj, lds, rstd_s);
-        else if (rb < n8) qgemm16_rows<8, QW, true>(a, NT16, 8 * rb, gj, lds, rstd_s);
-        else qgemm16_rows<6, QW, true>(a, NT16, 8 * n8 + 6 * (rb - n8), gj, lds, rstd_s);
+        if constexpr (MT16 != 0) qgemm16_rows<MT16, QW, true, WHOLE>(a, NT16, MT16 * rb, gj, lds, rstd_s);
+        else if (rb < n8) qgemm16_rows<8, QW, true, WHOLE>(a, NT16, 8 * rb, gj, lds, rstd_s);
+        else qgemm16_rows<6, QW, true, WHOLE>(a, NT16, 8 * n8 + 6 * (rb - n8), gj, lds, rstd_s);
     } else {
-        using S = QShape<MT16, QW, false>;
+        using S = QShape<MT16, QW, false, WHOLE>;
         __shared__ u32x4 lds[S::LDS];
-        __shared__ float rstd_s[16 * MT16];
-        qgemm16_rows<MT16, QW, false>(a, NT16, 0, blockIdx.x, lds, rstd_s);
+        __shared__ float rstd_s[WHOLE ? 16 * MT16 : 1];
+        qgemm16_rows<MT16, QW, false, WHOLE>(a, NT16, 0, blockIdx.x, lds, rstd_s);
     }
 }
 
@@ -889,7 +895,11 @@ template <int EPI> hipError_t launch_large(FusedGemmArgs &a, hipStream_t s, bool
     const int mt16 = (a.M + 15) / 16;
     const RowBlocks rows = row_blocks(mt16);
     const dim3 grid(p.groups * a.J * rows.RB), block(p.qw * 64);
-#define SSSD_Q16LAUNCH(MT, QW, BLOCKS) hipExtLaunchKernelGGL((qgemm16_kernel<MT, QW, BLOCKS>), grid, block, 0, s, t0, t1, 0, a, rows.RB, rows.n8, NT16, p.groups * a.J)
+#define SSSD_Q16LAUNCH(MT, QW, BLOCKS)                                                                                                          \
+    do {                                                                                                                                        \
+        if (a.J == 1) hipExtLaunchKernelGGL((qgemm16_kernel<MT, QW, BLOCKS, true>), grid, block, 0, s, t0, t1, 0, a, rows.RB, rows.n8, NT16, p.groups); \
+        else hipExtLaunchKernelGGL((qgemm16_kernel<MT, QW, BLOCKS, false>), grid, block, 0, s, t0, t1, 0, a, rows.RB, rows.n8, NT16, p.groups * a.J);   \
+    } while (0)
 #define SSSD_Q16ROWS(MT)                                  \
     do {                                                  \
         if (p.qw == 8) SSSD_Q16LAUNCH(MT, 8, false);      \
