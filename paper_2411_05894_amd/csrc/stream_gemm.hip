@@ -264,13 +264,13 @@ template <int EPI> __device__ __host__ __forceinline__ int column_blocks(const F
 }
 
 // grid = (column-block groups, row tiles of 16), 256 threads; each wave takes column blocks
-// cb0 + wave, cb0 + wave + 4, ...  The partial sums of the first block are fetched before the row scales are reduced, all slices of
-// a batch together, so the kernel's dependent memory round trips overlap.  A wave has a second block only in wide outputs at many
-// rows, and it is not fetched ahead: that took 129-143 registers, room for three workgroups per compute unit under a grid made for
-// four, and a second, quarter-full round at 512 rows (RESID of 4096 columns 12.8 -> 11.9 us without; SWIGLU of 160 rows 11.8 -> 11.1; held to 128
-// registers it spilled, and steps were 0.2-1 % slower).  What is left is the traffic of the slices and the launch: RESID of 160 rows x
-// 4096 in seven slices, 26 MB, takes 11 us.  RESID leaves one sum of squares per row and workgroup: the launches that scale rows read
-// few of them.
+// cb0 + wave, cb0 + wave + 4, ...  The partial sums of the first block are fetched before the row scales are reduced, two slices at
+// a time: the waves of a compute unit hide the round trips better than a wave's own loads do.  Eight slices at a time (four, of two
+// columns) took 118-127 registers and four workgroups per compute unit, two take 42-85 and five to eight fit: RESID of 160 rows x 4096 in
+// four slices 11.8 -> 10.4 us, in seven 8.0 -> 7.3, of 144 rows x 8192 11.5 -> 10.5, QKV of 160 rows 11.3 -> 10.4, of 36 rows 8.1 -> 7.7, of 512
+// rows 15.7 -> 14.6; one at a time the same or up to 5 % slower.  A second block of a wave, in wide outputs at many rows, is
+// not fetched ahead: with eight slices that had taken 129-143 registers and a second, quarter-full round of workgroups at 512 rows (RESID
+// 12.8 -> 11.9 us without).  RESID leaves one sum of squares per row and workgroup: the launches that scale rows read few of them.
 template <int EPI>
 __global__ __launch_bounds__(256) void epi_kernel(FusedGemmArgs a, int blocks_per_wg)
 {
@@ -299,7 +299,7 @@ __global__ __launch_bounds__(256) void epi_kernel(FusedGemmArgs a, int blocks_pe
     auto fetch = [&](int cb, Vec8 &v0, Vec8 &v1) {
         const int col = cb < cb_end ? column(cb) : -1;
         if (col >= 0) {
-            sum_slices<PAIRED ? 4 : 8, PAIRED>(a, m, col, col + (EPI == FEPI_QKV ? half : a.Ntot >> 1), v0, v1);
+            sum_slices<2, PAIRED>(a, m, col, col + (EPI == FEPI_QKV ? half : a.Ntot >> 1), v0, v1);
         } else {
 #pragma unroll
             for (int e = 0; e < 8; ++e) v0.v[e] = v1.v[e] = 0.f;
