@@ -164,10 +164,12 @@ __global__ void rollback_kernel(int B, int32_t *lens, const int32_t *accepted_le
 // copy rate (read + write) of the memory.  A pitch of HD + 8 elements keeps the 2-byte column accesses of a wave in
 // separate banks (four rows 4 apart, 16 channels each).  4001 rows x 8 heads x 128, in or out: 17.4 -> 8.0 us (4.1 TB/s of reads and writes);
 // 8192 rows 11.7 us (5.7 TB/s).
-// The caller's rows are streamed (read or written once, here), the cache's are not: two layers of 8192 rows in and out 54.7 -> 47.0 us.
+// The caller's rows are streamed (read or written once, here), the cache's are not: two layers of 8192 rows in and out 54.7 -> 47.0 us,
+// eight of 4001 rows 121.5 -> 119.4 (sixteen calls of 7.3 from the host).  Rows that are not 16-byte aligned are read and written two bytes at
+// a time on the caller's side only: 4001 rows x 8 heads x 128 in / out 17.5 / 19.1 us element by element, 7.2 / 7.4 so.
 // A block that the rows cover only in part keeps its other rows: K rows and V elements outside are not written.
 // Blocks that the table sends outside the pool are skipped (nothing written on either side) and raise the sticky flag.
-template <int HD, bool IMPORT>
+template <int HD, bool IMPORT, bool ALIGNED>
 __global__ __launch_bounds__(256) void kv_block_copy_kernel(KvGeom kv, uint16_t *Kc, uint16_t *Vc, int b, int t0, int n_rows, uint16_t *k_ext,
                                                             uint16_t *v_ext, int32_t *err_flag)
 {
@@ -184,7 +186,22 @@ __global__ __launch_bounds__(256) void kv_block_copy_kernel(KvGeom kv, uint16_t 
     u32x4 *kc = reinterpret_cast<u32x4 *>(Kc + base), *vc = reinterpret_cast<u32x4 *>(Vc + base);
     // 16-byte records of the block's rows in the plain layout (row r, channels 8x..8x+7 at record r * CPR + x)
     const ptrdiff_t e0 = ((ptrdiff_t)kvh * n_rows + (first - t0)) * CPR;
-    u32x4 *ke = reinterpret_cast<u32x4 *>(k_ext) + e0, *ve = reinterpret_cast<u32x4 *>(v_ext) + e0;
+    uint16_t *ke = k_ext + e0 * 8, *ve = v_ext + e0 * 8;
+    auto get = [](const uint16_t *p) {
+        if (ALIGNED) return __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(p));
+        u32x4 r;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) r[e] = (uint32_t)p[2 * e] | ((uint32_t)p[2 * e + 1] << 16);
+        return r;
+    };
+    auto put = [](uint16_t *p, const u32x4 &r) {
+        if (ALIGNED) {
+            __builtin_nontemporal_store(r, reinterpret_cast<u32x4 *>(p));
+        } else {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) p[e] = (uint16_t)(r[e >> 1] >> (16 * (e & 1)));
+        }
+    };
     // record rec of a K block: row, and which eight channels
     auto krow = [](int rec) { return rec / (CPR * 16) * 16 + (rec & 15); };
     auto kcol = [](int rec) { return rec / 64 % (CPR / 4) * 4 + (rec >> 4) % 4; };
@@ -196,8 +213,8 @@ __global__ __launch_bounds__(256) void kv_block_copy_kernel(KvGeom kv, uint16_t 
         k[i] = v[i] = u32x4{0u, 0u, 0u, 0u};
         if (IMPORT) {
             if (in) {
-                k[i] = __builtin_nontemporal_load(ke + rec);
-                v[i] = __builtin_nontemporal_load(ve + rec);
+                k[i] = get(ke + rec * 8);
+                v[i] = get(ve + rec * 8);
             }
         } else {
             k[i] = kc[rec];
@@ -228,14 +245,14 @@ __global__ __launch_bounds__(256) void kv_block_copy_kernel(KvGeom kv, uint16_t 
         if (row < lo || row >= hi) continue;
         const u32x4 r = *reinterpret_cast<const u32x4 *>(&ktile[row * PITCH + col * 8]);
         if (IMPORT) kc[rec] = r;
-        else __builtin_nontemporal_store(r, ke + rec);
+        else put(ke + rec * 8, r);
     }
 #pragma unroll
     for (int i = 0; i < N; ++i) {
         const int rec = threadIdx.x + 256 * i;
         if (!IMPORT) {
             const int row = rec / CPR;
-            if (row >= lo && row < hi) __builtin_nontemporal_store(*reinterpret_cast<const u32x4 *>(&tile[row * PITCH + (rec % CPR) * 8]), ve + rec);
+            if (row >= lo && row < hi) put(ve + rec * 8, *reinterpret_cast<const u32x4 *>(&tile[row * PITCH + (rec % CPR) * 8]));
             continue;
         }
         const int ch = (rec >> 6) * 16 + (rec & 15), q = (rec >> 4) & 3;
@@ -256,31 +273,6 @@ __global__ __launch_bounds__(256) void kv_block_copy_kernel(KvGeom kv, uint16_t 
         }
     }
 }
-
-// The same copy element by element, for caller arrays that are not 16-byte aligned: grid = (n_rows, nkv), block = d.
-// A row whose block the table sends outside the pool is skipped (nothing written on either side) and
-// raises the sticky flag.
-__global__ void kv_copy_kernel(Dims D, KvGeom kv, uint16_t *Kc, uint16_t *Vc, int b, int t0, int n_rows, uint16_t *k_ext,
-                               uint16_t *v_ext, bool import, int32_t *err_flag)
-{
-    (void)D;
-    const int t = blockIdx.x, kvh = blockIdx.y, i = threadIdx.x;
-    if (!kv_pages_ok(kv, b, t0 + t, t0 + t)) {
-        if (i == 0 && kvh == 0) *err_flag = 1;
-        return;
-    }
-    uint16_t *kc = Kc + kcache_offset(kv, b, kvh, t0 + t, i);
-    uint16_t *vc = Vc + vcache_offset(kv, b, kvh, t0 + t, i);
-    const size_t e = ((size_t)kvh * n_rows + t) * kv.d + i;
-    if (import) {
-        *kc = k_ext[e];
-        *vc = v_ext[e];
-    } else {
-        k_ext[e] = *kc;
-        v_ext[e] = *vc;
-    }
-}
-
 
 // grid = M rows.  Plain fp32 -> packed bf16 hi/lo (no normalisation).
 __global__ __launch_bounds__(256) void pack_act_kernel(const float *X, int K, int KT, uint16_t *A_hi, uint16_t *A_lo)
@@ -558,16 +550,21 @@ hipError_t launch_kv_copy(const Dims &D, const KvGeom &kv, uint16_t *Kc_layer, u
                           uint16_t *k_ext, uint16_t *v_ext, bool import, int32_t *err_flag, hipStream_t s)
 {
     if (n_rows <= 0) return hipSuccess;
-    if (((uintptr_t)k_ext | (uintptr_t)v_ext) % 16 == 0) {   // rows are 128 or 256 bytes: every row is aligned then
-        const dim3 grid(((t0 + n_rows - 1) >> 5) - (t0 >> 5) + 1, D.nkv);
-#define SSSD_KVLAUNCH(HD, IN) hipLaunchKernelGGL((kv_block_copy_kernel<HD, IN>), grid, dim3(256), 0, s, kv, Kc_layer, Vc_layer, b, t0, n_rows, k_ext, v_ext, err_flag)
-        if (D.d == 128) { if (import) SSSD_KVLAUNCH(128, true); else SSSD_KVLAUNCH(128, false); }
-        else { if (import) SSSD_KVLAUNCH(64, true); else SSSD_KVLAUNCH(64, false); }
-#undef SSSD_KVLAUNCH
-        return hipGetLastError();
+    const bool aligned = ((uintptr_t)k_ext | (uintptr_t)v_ext) % 16 == 0;   // rows are 128 or 256 bytes: every row is aligned then
+    const dim3 grid(((t0 + n_rows - 1) >> 5) - (t0 >> 5) + 1, D.nkv);
+#define SSSD_KVLAUNCH(HD, IN)                                                                                                              \
+    do {                                                                                                                                   \
+        if (aligned) hipLaunchKernelGGL((kv_block_copy_kernel<HD, IN, true>), grid, dim3(256), 0, s, kv, Kc_layer, Vc_layer, b, t0, n_rows, k_ext, v_ext, err_flag); \
+        else hipLaunchKernelGGL((kv_block_copy_kernel<HD, IN, false>), grid, dim3(256), 0, s, kv, Kc_layer, Vc_layer, b, t0, n_rows, k_ext, v_ext, err_flag);        \
+    } while (0)
+    if (D.d == 128) {
+        if (import) SSSD_KVLAUNCH(128, true);
+        else SSSD_KVLAUNCH(128, false);
+    } else {
+        if (import) SSSD_KVLAUNCH(64, true);
+        else SSSD_KVLAUNCH(64, false);
     }
-    hipLaunchKernelGGL(kv_copy_kernel, dim3(n_rows, D.nkv), dim3(D.d), 0, s, D, kv, Kc_layer, Vc_layer, b, t0, n_rows, k_ext,
-                       v_ext, import, err_flag);
+#undef SSSD_KVLAUNCH
     return hipGetLastError();
 }
 

@@ -1,5 +1,5 @@
 """Cache import / export against a plain tensor: ranges that start and end inside blocks of 32 positions, both head
-sizes, a shuffled block table, and caller arrays that are 16-byte aligned or not (each has its own kernel)."""
+sizes, a shuffled block table, and caller arrays that are 16-byte aligned or not (each has its own form of the kernel)."""
 import pytest
 import torch
 
