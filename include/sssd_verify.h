@@ -74,6 +74,10 @@ typedef struct {
                                  (needs hidden, n_q*d and ffn to be multiples of 32);
                                  the caller's matrices are then in the library's private
                                  tile order until the process frees them                  */
+#define SSSD_NO_WAIT 2u       /* workgroups that add up each other's partial results never
+                                 wait for one another: the last one of them does all of it
+                                 (the same results, slower; what they do in any case when
+                                 others do not arrive in time)                            */
 
 /* Bytes the caller must provide for a configuration (host computation only): the KV cache of Table 2's
  * caption (2 bytes per element, b x n_kv x s_kv x d per layer for K and for V), the workspace of one pass of

@@ -15,6 +15,7 @@ LIB_PATH = os.path.join(HERE, "libsssd_verify.so")
 
 SSSD_OK, SSSD_EINVAL, SSSD_ECAPACITY, SSSD_ENOSPACE, SSSD_EHIP = 0, -1, -2, -3, -4
 SSSD_PACK_IN_PLACE = 1
+SSSD_NO_WAIT = 2
 SSSD_PROF_CLASSES = 8
 PROF_NAMES = ("gemm", "attention", "elementwise", "accept")
 
@@ -147,7 +148,7 @@ class VerifyContext:
     """Owns the device buffers (as torch tensors) and the sssd_ctx handle."""
 
     def __init__(self, cfg: ModelConfig, layers: Sequence[Dict[str, torch.Tensor]], globals_: Dict[str, torch.Tensor],
-                 in_place: bool = False, device: str = "cuda:0"):
+                 in_place: bool = False, device: str = "cuda:0", no_wait: bool = False):
         self.cfg = cfg
         self.device = torch.device(device)
         kv_b, ws_b, pk_b = sssd_verify_sizes(cfg)
@@ -170,7 +171,7 @@ class VerifyContext:
         with torch.cuda.device(self.device):
             _check(lib().sssd_verify_init(C.byref(cfg), C.byref(w), _ptr(self.kv_cache), kv_b, _ptr(self.workspace),
                                           ws_b, _ptr(self.packed), pk_b if self.packed is not None else 0,
-                                          SSSD_PACK_IN_PLACE if in_place else 0, C.byref(h)), "sssd_verify_init")
+                                          (SSSD_PACK_IN_PLACE if in_place else 0) | (SSSD_NO_WAIT if no_wait else 0), C.byref(h)), "sssd_verify_init")
         self.handle = h
 
     # -- the C ABI, one method per entry point --

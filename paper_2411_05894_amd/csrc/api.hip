@@ -30,7 +30,7 @@ struct Buffers {
     int32_t *segments;
     uint32_t *anc;
     float *rope_cs, *ssq1;
-    uint8_t *staging;
+    uint8_t *staging;   // of in-place packing; from the end of sssd_verify_init on, its first bytes are the words of Hand
     size_t staging_bytes;
     float *partials;
     size_t partial_bytes;
@@ -69,6 +69,7 @@ struct sssd_ctx {
     double prof_ms[SSSD_PROF_CLASSES];
     int64_t prof_n[SSSD_PROF_CLASSES];
     int device, n_cu;
+    Hand hand;
 };
 
 namespace {
@@ -399,6 +400,18 @@ int sssd_verify_init(const sssd_model_config *cfg, const sssd_weights *w, void *
         INIT_TRY(hipGetDeviceProperties(&prop, c->device));
         c->n_cu = prop.multiProcessorCount;
     }
+    // Workgroups hand results over within a die where all of a device's eight are there and take the workgroups in turn.
+    c->hand = Hand{nullptr, flags & SSSD_NO_WAIT ? 0 : HAND_POLLS};
+    {
+        static_assert(HAND_GROUPS * HAND_STRIDE * sizeof(uint32_t) <= (size_t)1 << 20, "staging holds the words");
+        uint32_t *words = (uint32_t *)c->W.staging, strays = 0;
+        INIT_TRY(hipMemsetAsync(words, 0, HAND_GROUPS * HAND_STRIDE * sizeof(uint32_t), s));
+        INIT_TRY(launch_die_check(words, s));
+        INIT_TRY(hipMemcpyAsync(&strays, words, sizeof(strays), hipMemcpyDeviceToHost, s));
+        INIT_TRY(hipMemsetAsync(words, 0, sizeof(uint32_t), s));
+        INIT_TRY(hipStreamSynchronize(s));
+        if (c->n_cu == 256 && strays == 0) c->hand.words = words;
+    }
     INIT_TRY(hipStreamSynchronize(s));
     c->magic = MAGIC;
     *out = c;
@@ -536,7 +549,7 @@ int run_step(sssd_ctx *c, int32_t B, int32_t k, const int32_t *tokens, const int
     for (int l = 0; l < D.L; ++l) {
         uint16_t *Kl = c->Kc + (size_t)l * c->S.kv_layer_elems, *Vl = c->Vc + (size_t)l * c->S.kv_layer_elems;
         {
-            AttnArgs a{W.Qp, W.Qp_lo, Kl, Vl, kv_geom(c), W.seq, W.segments, W.anc, W.part_o, W.part_ml, W.Aq_hi, W.Aq_lo, B, k, {}, 0};
+            AttnArgs a{W.Qp, W.Qp_lo, Kl, Vl, kv_geom(c), W.seq, W.segments, W.anc, W.part_o, W.part_ml, W.Aq_hi, W.Aq_lo, B, k, {}, 0, c->hand};
             Prof p(c, s, SSSD_PROF_ATTN);
             HIP_TRY(launch_attention(D, a, s));
         }
@@ -869,7 +882,7 @@ int sssd_op_attention(sssd_ctx *c, int32_t layer, int32_t B, int32_t k, const fl
     HIP_TRY(launch_lens(D, B, k, lens, W.pos_base, W.seq, W.segments, W.rope_pos, W.anc, W.err_flag, s));
     HIP_TRY(launch_q_pack(D, q, B, k, W.Qp, W.Qp_lo, s));
     uint16_t *Kl = c->Kc + (size_t)layer * c->S.kv_layer_elems, *Vl = c->Vc + (size_t)layer * c->S.kv_layer_elems;
-    AttnArgs a{W.Qp, W.Qp_lo, Kl, Vl, kv_geom(c), W.seq, W.segments, W.anc, W.part_o, W.part_ml, W.Aq_hi, W.Aq_lo, B, k, {}, 0};
+    AttnArgs a{W.Qp, W.Qp_lo, Kl, Vl, kv_geom(c), W.seq, W.segments, W.anc, W.part_o, W.part_ml, W.Aq_hi, W.Aq_lo, B, k, {}, 0, c->hand};
     HIP_TRY(launch_attention(D, a, s));
     HIP_TRY(launch_unpack_act(W.Aq_hi, W.Aq_lo, B * (k + 1), D.qd, out, s));
     return SSSD_OK;

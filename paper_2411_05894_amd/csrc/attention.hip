@@ -27,8 +27,11 @@
 // The transposed forms are chosen so that the lane that owns a query row's
 // statistics also owns that row's accumulator columns: no shuffles to rescale.
 // At the end the waves bring their sums to one reference and add them up through LDS, each wave ending with a
-// quarter of the channels.  The segments of a sequence are merged by a second kernel in fixed order
-// (deterministic); a sequence that lies in one segment is finished by its workgroup itself.
+// quarter of the channels.  A sequence that lies in one segment is finished by its workgroup itself; else the segments are merged in
+// fixed order (deterministic): inside the launch where all segments of a (sequence, kv head) can run on one die (attention_in_die), by a
+// second launch otherwise.  The second launch took 5.0-7.6 us and the gap in front of it; the workgroups of a die pass their sums on
+// through its L2 and share the rows out: whole 8B step, one sequence of 2048 3421 -> 3357 us, four sequences of 32768, k = 8 2.6 us less a
+// layer, sssd_op_attention of two sequences of 12345, k = 17 40.1 -> 38.1.
 //
 // What bounds it: the cache stream from a few MB per compute unit on (a compute unit pulls 24 GB/s with all of them at work, 537 MB in
 // 87 us, and 32 GB/s beside idle ones, the longest of 32 ragged sequences, 2.1 MB in 66 us), below that the chain
@@ -74,6 +77,100 @@ __device__ __forceinline__ f32x4 pick(bool first, f32x4 x, f32x4 y)   // by valu
     return f32x4{first ? x[0] : y[0], first ? x[1] : y[1], first ? x[2] : y[2], first ? x[3] : y[3]};
 }
 
+// Over the whole wave, in every lane, without LDS.
+__device__ __forceinline__ float wave_max(float x)
+{
+    x = fmaxf(x, bits_f32((uint32_t)__builtin_amdgcn_mov_dpp((int)f32_bits(x), 0x128, 0xF, 0xF, true)));   // rotated by 8, 4, 2, 1 lanes of 16
+    x = fmaxf(x, bits_f32((uint32_t)__builtin_amdgcn_mov_dpp((int)f32_bits(x), 0x124, 0xF, 0xF, true)));
+    x = fmaxf(x, bits_f32((uint32_t)__builtin_amdgcn_mov_dpp((int)f32_bits(x), 0x122, 0xF, 0xF, true)));
+    x = fmaxf(x, bits_f32((uint32_t)__builtin_amdgcn_mov_dpp((int)f32_bits(x), 0x121, 0xF, 0xF, true)));
+    return rows_max(x);
+}
+__device__ __forceinline__ float wave_sum(float x)
+{
+    x += bits_f32((uint32_t)__builtin_amdgcn_mov_dpp((int)f32_bits(x), 0x128, 0xF, 0xF, true));
+    x += bits_f32((uint32_t)__builtin_amdgcn_mov_dpp((int)f32_bits(x), 0x124, 0xF, 0xF, true));
+    x += bits_f32((uint32_t)__builtin_amdgcn_mov_dpp((int)f32_bits(x), 0x122, 0xF, 0xF, true));
+    x += bits_f32((uint32_t)__builtin_amdgcn_mov_dpp((int)f32_bits(x), 0x121, 0xF, 0xF, true));
+    return rows_sum(x);
+}
+
+// The segments of ROWS query rows r0, r0 + step, ... (below r_end) of (sequence b, kv head kvh) merged by one wave, in fixed order.  The
+// wave reads the rows' partial outputs of 4*U segments in one round of independent loads: lanes 16s..16s+15 take segment s, s+4, ...
+// with 8 channels each, and the four lane groups are summed at the end.  DIE: workgroups of this launch, on this die, stored them.
+template <int HD, int ROWS, int U, bool DIE>
+__device__ __forceinline__ void merge_rows(const Dims &D, const AttnArgs &a, int q_rows_pad, int b, int kvh, int r0, int step, int r_end, int n_splits, int lane)
+{
+    constexpr int LPR = HD / 8;   // lanes that cover a row of HD channels, 8 each
+    const int KTq = (D.qd + 31) >> 5;
+    const int sg = lane >> 4, cl = lane & 15;
+    const size_t slot0 = ((size_t)kvh * a.B + b) * a.plan.share;
+    const float *part_o = a.part_o + slot0 * q_rows_pad * HD, *part_ml = a.part_ml + slot0 * q_rows_pad * 2;
+    const DieBuffer die_o(part_o, (size_t)n_splits * q_rows_pad * HD * sizeof(float)), die_ml(part_ml, (size_t)n_splits * q_rows_pad * sizeof(float2));
+
+    float2 ml[ROWS];
+    float num[ROWS][8], w_lane[ROWS];
+#pragma unroll
+    for (int i = 0; i < ROWS; ++i) {
+        const int r = min(r0 + i * step, r_end - 1), at = min(lane, n_splits - 1) * q_rows_pad + r;
+        ml[i] = DIE ? die_ml.load2(at * 8) : *reinterpret_cast<const float2 *>(part_ml + (size_t)at * 2);
+        w_lane[i] = 0.f;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) num[i][e] = 0.f;
+    }
+    for (int base = 0; base < n_splits; base += 4 * U) {
+        f32x4 pv[ROWS][U][2];
+#pragma unroll
+        for (int i = 0; i < ROWS; ++i)
+#pragma unroll
+            for (int u = 0; u < U; ++u) {   // past the last segment: that one again, not added
+                const int r = min(r0 + i * step, r_end - 1), at = (min(base + 4 * u + sg, n_splits - 1) * q_rows_pad + r) * HD + min(cl, LPR - 1) * 8;
+                if (DIE) {
+                    pv[i][u][0] = die_o.load4(at * 4);
+                    pv[i][u][1] = die_o.load4(at * 4, 16);
+                } else {
+                    pv[i][u][0] = *reinterpret_cast<const f32x4 *>(part_o + at);
+                    pv[i][u][1] = *reinterpret_cast<const f32x4 *>(part_o + at + 4);
+                }
+            }
+        if (base == 0) {
+#pragma unroll
+            for (int i = 0; i < ROWS; ++i) {
+                const float w = __builtin_amdgcn_exp2f(ml[i].x - wave_max(ml[i].x));   // all lanes: the maximum crosses them
+                w_lane[i] = lane < n_splits ? w : 0.f;
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < ROWS; ++i)
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int s = base + 4 * u + sg;
+                const float w = __shfl(w_lane[i], s < 64 ? s : 63);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    num[i][e] += s < n_splits ? w * pv[i][u][0][e] : 0.f;
+                    num[i][4 + e] += s < n_splits ? w * pv[i][u][1][e] : 0.f;
+                }
+            }
+    }
+#pragma unroll
+    for (int i = 0; i < ROWS; ++i) {
+        const int r = r0 + i * step;
+        const float den = wave_sum(w_lane[i] * ml[i].y);
+        uint32_t hi[4], lo[4];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) num[i][e] = rows_sum(num[i][e]);
+#pragma unroll
+        for (int e = 0; e < 8; e += 2) split_bf16x2(num[i][e] / den, num[i][e + 1] / den, hi[e >> 1], lo[e >> 1]);
+        if (r < r_end && sg == 0 && cl < LPR) {
+            const int j = r / D.g, hl = r % D.g, m = b * (a.k + 1) + j;
+            const size_t idx = packed_index(m, (kvh * D.g + hl) * HD + cl * 8, KTq);   // whole lane records
+            *reinterpret_cast<u32x4 *>(a.out_hi + idx) = u32x4{hi[0], hi[1], hi[2], hi[3]};
+            *reinterpret_cast<u32x4 *>(a.out_lo + idx) = u32x4{lo[0], lo[1], lo[2], lo[3]};
+        }
+    }
+}
+
 // grid = B * share * kv heads * passes over the row tiles; block = four waves; RT row tiles per pass; ONCE: a single pass.
 // Workgroups 8 apart run on one die, where the passes and then the heads of a segment follow each other: they read one page
 // (64 KiB of K at eight heads of 128) at about the same time.  Two waves per SIMD: two workgroups fit a compute unit.
@@ -87,6 +184,7 @@ __global__ __launch_bounds__(NWAVE * 64) __attribute__((amdgpu_waves_per_eu(2, 2
     constexpr int QREC = RT * KS * 2 * 64, RRED = NWAVE * RT * (DT / 2) * 64;   // records of the query tiles, of the final sums
     __shared__ u32x4 lds[QREC > RRED ? QREC : RRED];
     __shared__ float2 ml_s[NWAVE][RT * 16];
+    __shared__ int way_s;
     __shared__ uint32_t vis_s[RT * 16];      // visible new rows of every query row: bit i = cache row len + i
 
     int kvh, wg;   // kv head; (turn, segment)
@@ -94,26 +192,35 @@ __global__ __launch_bounds__(NWAVE * 64) __attribute__((amdgpu_waves_per_eu(2, 2
     const int passes = a.plan.passes;
     {
         int id = blockIdx.x;
-        if (passes > 1) {
-            const int n = a.B * a.plan.share * D.nkv, sets = n & ~7;
-            if (id < sets * passes) {
-                const int x = id / (8 * passes), r = id - x * 8 * passes;
-                pass = r >> 3;
-                id = x * 8 + (r & 7);
-            } else {
-                const int r = id - sets * passes;
-                pass = r / (n - sets);
-                id = sets + r % (n - sets);
-            }
-        }
-        const int whole = (a.B * a.plan.share) & ~7;
-        if (id < whole * D.nkv) {
-            wg = id / (8 * D.nkv) * 8 + (id & 7);
-            kvh = (id >> 3) % D.nkv;
+        if (a.hand.words) {   // all segments of a (sequence, kv head) on one die, its passes next to each other
+            // Heads of one sequence and, by turn, of different sequences on a die: with one head per die each die would read the same
+            // eighth of every page.
+            const int slot = id >> 3, x = slot / passes, row = x / a.plan.share, u = row * 8 + ((id - row) & 7);
+            pass = slot - x * passes;
+            wg = u / D.nkv * a.plan.share + x % a.plan.share;
+            kvh = u % D.nkv;
         } else {
-            const int r = id - whole * D.nkv;
-            wg = whole + r / D.nkv;
-            kvh = r % D.nkv;
+            if (passes > 1) {
+                const int n = a.B * a.plan.share * D.nkv, sets = n & ~7;
+                if (id < sets * passes) {
+                    const int x = id / (8 * passes), r = id - x * 8 * passes;
+                    pass = r >> 3;
+                    id = x * 8 + (r & 7);
+                } else {
+                    const int r = id - sets * passes;
+                    pass = r / (n - sets);
+                    id = sets + r % (n - sets);
+                }
+            }
+            const int whole = (a.B * a.plan.share) & ~7;
+            if (id < whole * D.nkv) {
+                wg = id / (8 * D.nkv) * 8 + (id & 7);
+                kvh = (id >> 3) % D.nkv;
+            } else {
+                const int r = id - whole * D.nkv;
+                wg = whole + r / D.nkv;
+                kvh = r % D.nkv;
+            }
         }
     }
     const int segment = wg % a.plan.share;
@@ -400,84 +507,34 @@ __global__ __launch_bounds__(NWAVE * 64) __attribute__((amdgpu_waves_per_eu(2, 2
             if (wave == 0 && q == 0) *reinterpret_cast<float2 *>(a.part_ml + at * 2) = float2{m_all[t], l_all[t]};
         }
     }
+    if (cut.n == 1 || !a.hand.words) return;
+    const int group = (wg / a.plan.share * D.nkv + kvh) * passes + pass;   // by turn, not by sequence: both count to B
+    HandWay way = hand_over(a.hand, group, cut.n, &way_s);
+    if (way == HAND_TURN_IN) way = hand_turn_in(a.hand, group, cut.n, &way_s);
+    uint32_t left = way == HAND_SHARE ? hand_leave(a.hand, group) : 0;   // under way while the shares are done
+    if (way != HAND_NOTHING) {   // the rows of this pass shared out over the waves of all segments
+        const int r_end = min(D.g * (a.k + 1), (rt0 + RT) * 16), step = (way == HAND_ALL ? 1 : cut.n) * NWAVE;
+        int r = rt0 * 16 + (way == HAND_ALL ? wave : wave * cut.n + segment);
+        if (cut.n <= 4) for (; r < r_end; r += 4 * step) merge_rows<HD, 4, 1, true>(D, a, q_rows_pad, b, kvh, r, step, r_end, cut.n, lane);
+        else if (cut.n <= 8) for (; r < r_end; r += 2 * step) merge_rows<HD, 2, 2, true>(D, a, q_rows_pad, b, kvh, r, step, r_end, cut.n, lane);
+        else for (; r < r_end; r += step) merge_rows<HD, 1, 5, true>(D, a, q_rows_pad, b, kvh, r, step, r_end, cut.n, lane);
+    }
+    if (way != HAND_SHARE) left = hand_leave(a.hand, group);
+    hand_clear(a.hand, group, cut.n, left);
 }
 
-// One wave per (sequence, kv head, query row); 4 waves per block.  The wave reads the row's
-// partial outputs of up to 4*BATCH chunks in one round of independent loads: lanes 16s..16s+15
-// take chunk s, s+4, ... with 8 channels each, and the four lane groups are summed at the end
-// in fixed order.
+// The merge as a launch of its own: one wave per (sequence, kv head, query row), 4 waves per block.
 template <int HD>
 __global__ __launch_bounds__(256) void attn_combine_kernel(Dims D, AttnArgs a, int q_rows_pad)
 {
-    constexpr int BATCH = 5;      // nine cost registers: B = 12, k = 31, context 900..2700 81 us of attention, five 78
-    constexpr int LPR = HD / 8;   // lanes that cover a row of HD channels, 8 each
-    const int lane = threadIdx.x & 63, k = a.k;
-    const int R = D.g * (k + 1);
-    const int n_tasks = a.B * D.nkv * R;
+    const int R = D.g * (a.k + 1);
     const int task = blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (task >= n_tasks) return;
-    const int KTq = (D.qd + 31) >> 5;
-    const int sg = lane >> 4, cl = lane & 15;
+    if (task >= a.B * D.nkv * R) return;
     const int r = task % R, kvh = (task / R) % D.nkv, b = task / (R * D.nkv);
     const int n_splits = a.segments[b];    // at most ATTN_MAX_SEGMENTS
     if (n_splits == 1) return;             // finished by its workgroup
-    const size_t slot0 = ((size_t)kvh * a.B + b) * a.plan.share;
-
-    float2 ml = float2{NEG_BIG, 0.f};
-    if (lane < n_splits) ml = *reinterpret_cast<const float2 *>(a.part_ml + ((slot0 + lane) * q_rows_pad + r) * 2);
-    float num[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    float m_star = 0.f, w_lane = 0.f;
-    for (int base = 0; base < n_splits; base += 4 * BATCH) {
-        f32x4 pv[BATCH][2];
-#pragma unroll
-        for (int u = 0; u < BATCH; ++u) {
-            const int s = base + 4 * u + sg;
-            const bool live = s < n_splits && cl < LPR;
-            const f32x4 *p = reinterpret_cast<const f32x4 *>(a.part_o + ((slot0 + (live ? s : 0)) * q_rows_pad + r) * HD + (cl < LPR ? cl : 0) * 8);
-            pv[u][0] = live ? p[0] : f32x4{0.f, 0.f, 0.f, 0.f};
-            pv[u][1] = live ? p[1] : f32x4{0.f, 0.f, 0.f, 0.f};
-        }
-        if (base == 0) {
-            m_star = ml.x;
-#pragma unroll
-            for (int off = 32; off >= 1; off >>= 1) m_star = fmaxf(m_star, __shfl_xor(m_star, off));
-            w_lane = lane < n_splits ? exp2f(ml.x - m_star) : 0.f;
-        }
-#pragma unroll
-        for (int u = 0; u < BATCH; ++u) {
-            const int s = base + 4 * u + sg;
-            const float w = __shfl(w_lane, s < 64 ? s : 0);   // chunks past n_splits carry weight 0
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                num[e] += w * pv[u][0][e];
-                num[4 + e] += w * pv[u][1][e];
-            }
-        }
-    }
-    float den = w_lane * ml.y;
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) den += __shfl_xor(den, off);
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        num[e] += __shfl_xor(num[e], 16);
-        num[e] += __shfl_xor(num[e], 32);
-    }
-    if (sg == 0 && cl < LPR) {
-        const int j = r / D.g, hl = r % D.g, m = b * (k + 1) + j;
-        const int col = (kvh * D.g + hl) * HD + cl * 8;
-        uint32_t hi[4], lo[4];
-#pragma unroll
-        for (int e = 0; e < 8; e += 2) {
-            uint16_t h0, l0, h1, l1;
-            split_bf16(num[e] / den, h0, l0);
-            split_bf16(num[e + 1] / den, h1, l1);
-            hi[e >> 1] = (uint32_t)h0 | ((uint32_t)h1 << 16);
-            lo[e >> 1] = (uint32_t)l0 | ((uint32_t)l1 << 16);
-        }
-        const size_t idx = packed_index(m, col, KTq);   // col % 8 == 0: one whole lane record
-        *reinterpret_cast<u32x4 *>(a.out_hi + idx) = u32x4{hi[0], hi[1], hi[2], hi[3]};
-        *reinterpret_cast<u32x4 *>(a.out_lo + idx) = u32x4{lo[0], lo[1], lo[2], lo[3]};
-    }
+    // nine at a time cost registers: B = 12, k = 31, context 900..2700 81 us of attention, five 78
+    merge_rows<HD, 1, 5, false>(D, a, q_rows_pad, b, kvh, r, 1, r + 1, n_splits, threadIdx.x & 63);
 }
 
 template <int HD> hipError_t launch_partial(const Dims &D, const AttnArgs &a, int q_rows_pad, hipStream_t s)
@@ -545,6 +602,16 @@ AttnPlan attention_plan(const Dims &D, int B, int k)
     return p;
 }
 
+// The segments of a (sequence, kv head) are merged inside the launch where the groups are the same number on every die and no
+// compute unit gets a second workgroup while others wait (two fit where the plan asks for two).
+static bool attention_in_die(const Dims &D, const AttnPlan &p, int B)
+{
+    const long groups = (long)B * D.nkv * p.passes;
+    const size_t slot_bytes = (size_t)round_up(D.g * (D.max_k + 1), 16) * D.d * sizeof(float);
+    if (slot_bytes * p.share >= (size_t)1 << 31) return false;   // DieBuffer's offsets
+    return B * D.nkv % 8 == 0 && groups <= HAND_GROUPS && groups * p.share <= 512;
+}
+
 // Most partial results that any step of up to B sequences leaves, all kv heads.
 size_t attention_slots(const Dims &D, int B)
 {
@@ -563,11 +630,13 @@ hipError_t launch_attention(const Dims &D, const AttnArgs &a_in, hipStream_t s)
     const int q_rows_pad = round_up(D.g * (D.max_k + 1), 16);
     a.row_tiles = (D.g * (a.k + 1) + 15) / 16;
     a.plan = attention_plan(D, a.B, a.k);
+    const bool merge = a.plan.share > 1 && D.blocks_per_seq > ATTN_WHOLE_BLOCKS;
+    if (!merge || !attention_in_die(D, a.plan, a.B)) a.hand.words = nullptr;
     hipError_t e = D.d == 128 ? launch_partial<128>(D, a, q_rows_pad, s) : launch_partial<64>(D, a, q_rows_pad, s);
     if (e != hipSuccess) return e;
     // No merge where no sequence can have two segments.  With every workgroup of the merge returning at once the launch still
     // took 5 us (70B layer, B = 16, k = 8: 5 of 597; two layers of the tiny shape with room for 133 positions: 10 of 68).
-    if (a.plan.share == 1 || D.blocks_per_seq <= ATTN_WHOLE_BLOCKS) return hipSuccess;
+    if (!merge || a.hand.words) return hipSuccess;
     const int n_tasks = a.B * D.nkv * D.g * (a.k + 1);
     if (D.d == 128) hipLaunchKernelGGL(attn_combine_kernel<128>, dim3((n_tasks + 3) / 4), dim3(256), 0, s, D, a, q_rows_pad);
     else hipLaunchKernelGGL(attn_combine_kernel<64>, dim3((n_tasks + 3) / 4), dim3(256), 0, s, D, a, q_rows_pad);

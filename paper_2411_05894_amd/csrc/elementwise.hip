@@ -512,7 +512,18 @@ __global__ __launch_bounds__(256) void stream_read_kernel(const u32x4 *src, size
     if (threadIdx.x == 0) sink[blockIdx.x] = part[0] ^ part[1] ^ part[2] ^ part[3];
 }
 
+__global__ __launch_bounds__(64) void die_check_kernel(uint32_t *strays)
+{
+    if (threadIdx.x == 0 && !on_own_die()) atomicAdd(strays, 1u);
+}
+
 }  // namespace
+
+hipError_t launch_die_check(uint32_t *strays, hipStream_t s)
+{
+    hipLaunchKernelGGL(die_check_kernel, dim3(512), dim3(64), 0, s, strays);
+    return hipGetLastError();
+}
 
 hipError_t launch_stream_read(const void *src, size_t bytes, uint32_t *sink, int n_cu, hipStream_t s)
 {

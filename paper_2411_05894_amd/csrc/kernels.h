@@ -1,6 +1,7 @@
 // Private launcher interface between the C-ABI layer (api.hip) and the kernel files.
 #pragma once
 #include "common.h"
+#include "handover.h"
 
 // -------------------------------------------------- attention segments ----
 // How a sequence's positions are cut into segments, one workgroup per segment and kv head.  The cut follows from the
@@ -137,6 +138,9 @@ hipError_t launch_kv_compact(const Dims &D, const KvGeom &kv, uint16_t *Kc, uint
 hipError_t launch_kv_copy(const Dims &D, const KvGeom &kv, uint16_t *Kc_layer, uint16_t *Vc_layer, int b, int t0, int n_rows,
                           uint16_t *k_ext, uint16_t *v_ext, bool import, int32_t *err_flag, hipStream_t s);
 
+// Counts workgroups that do not run on the die their block index names into *strays.
+hipError_t launch_die_check(uint32_t *strays, hipStream_t s);
+
 // Kernel-level entry points only (parity tests, micro-benchmarks).
 hipError_t launch_pack_act(const float *X, int M, int K, uint16_t *A_hi, uint16_t *A_lo, hipStream_t s);
 hipError_t launch_unpack_act(const uint16_t *A_hi, const uint16_t *A_lo, int M, int K, float *X, hipStream_t s);
@@ -163,6 +167,7 @@ struct AttnArgs {
     int B, k;
     AttnPlan plan;             // filled in by launch_attention
     int row_tiles;             // ... 16-row tiles of query rows
+    Hand hand;                 // words for segments merged inside the launch, or none: a second launch merges them
 };
 // Partial slots of a step of B sequences, all kv heads (sizes the buffers).
 size_t attention_slots(const Dims &D, int B);

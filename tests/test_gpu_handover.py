@@ -1,0 +1,43 @@
+"""Partial results handed over between the workgroups of one launch (one die's workgroups share its L2).  A context created with
+SSSD_NO_WAIT never waits for the others, so its last workgroups do whole groups' work: the way taken when workgroups do not arrive in
+time.  Both ways must give the reference and the same bits, launch after launch (the words between them are zero again)."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+from paper_2411_05894_amd import binding as sv
+from sssd_synth import normal_bf16
+from test_gpu_attention_segments import attention_context, reference
+
+DEV = "cuda:0"
+
+
+@pytest.mark.parametrize("shape_name,k,lens,max_seq", [
+    ("8b", 8, [2048], 2057),               # 8 heads, 17 segments of one sequence
+    ("8b", 0, [5000], 5001),               # four rows for 32 segments: most have nothing to merge
+    ("8b", 17, [700, 12345], 12400),       # five row tiles, two passes
+    ("8b", 31, [1500, 40, 3000], 3100),    # a sequence of one segment beside merged ones
+    ("8b", 12, [900 + 100 * i for i in range(14)], 4000),   # passes of two tiles, two workgroups per compute unit
+    ("tiny", 4, [300, 2000, 5, 1000], 2100)])               # two kv heads, head size 64
+def test_attention_merged_inside_the_launch(shape_name, k, lens, max_seq):
+    B, sq = len(lens), k + 1
+    outs = []
+    for no_wait in (False, True):
+        s, ctx = attention_context(shape_name, B, k, max_seq, no_wait=no_wait)
+        q = (normal_bf16(51, 1, (B, sq, s.n_q_heads, s.head_dim), 1.0, device=DEV).float() * 1.28).contiguous()
+        kv = [[normal_bf16(52, 2 * b + i, (s.n_kv_heads, n + sq, s.head_dim), 1.0, device=DEV) for i in range(2)] for b, n in enumerate(lens)]
+        for b in range(B):
+            ctx.sssd_kv_import(0, b, 0, *kv[b])
+        out = torch.empty(B, sq, s.n_q_heads * s.head_dim, dtype=torch.float32, device=DEV)
+        print(f"hand-over attention {shape_name} k={k} B={B} no_wait={no_wait}", flush=True)
+        for i in range(12):
+            out.fill_(-1.0)
+            ctx.sssd_op_attention(0, q, torch.tensor(lens, dtype=torch.int32, device=DEV), out)
+            assert ctx.sssd_verify_sync() == 0
+            outs.append(out.clone())
+    got = outs[0].view(B, sq, s.n_q_heads, s.head_dim)
+    for b in range(B):   # as test_gpu_attention_segments: operands in bf16 pairs, ~2^-17 relative
+        assert (got[b] - reference(q[b], *kv[b], lens[b], s.n_q_heads // s.n_kv_heads)).abs().max().item() <= 1e-4, b
+    for o in outs[1:]:
+        assert torch.equal(o, outs[0])
