@@ -549,7 +549,7 @@ int run_step(sssd_ctx *c, int32_t B, int32_t k, const int32_t *tokens, const int
     for (int l = 0; l < D.L; ++l) {
         uint16_t *Kl = c->Kc + (size_t)l * c->S.kv_layer_elems, *Vl = c->Vc + (size_t)l * c->S.kv_layer_elems;
         {
-            AttnArgs a{W.Qp, W.Qp_lo, Kl, Vl, kv_geom(c), W.seq, W.segments, W.anc, W.part_o, W.part_ml, W.Aq_hi, W.Aq_lo, B, k, {}, 0, c->hand};
+            AttnArgs a{W.Qp, W.Qp_lo, Kl, Vl, kv_geom(c), W.seq, W.segments, W.anc, W.part_o, W.part_ml, W.Aq_hi, W.Aq_lo, B, k, {}, 0, {}, {}, {}, {}, c->hand};
             Prof p(c, s, SSSD_PROF_ATTN);
             HIP_TRY(launch_attention(D, a, s));
         }
@@ -882,7 +882,7 @@ int sssd_op_attention(sssd_ctx *c, int32_t layer, int32_t B, int32_t k, const fl
     HIP_TRY(launch_lens(D, B, k, lens, W.pos_base, W.seq, W.segments, W.rope_pos, W.anc, W.err_flag, s));
     HIP_TRY(launch_q_pack(D, q, B, k, W.Qp, W.Qp_lo, s));
     uint16_t *Kl = c->Kc + (size_t)layer * c->S.kv_layer_elems, *Vl = c->Vc + (size_t)layer * c->S.kv_layer_elems;
-    AttnArgs a{W.Qp, W.Qp_lo, Kl, Vl, kv_geom(c), W.seq, W.segments, W.anc, W.part_o, W.part_ml, W.Aq_hi, W.Aq_lo, B, k, {}, 0, c->hand};
+    AttnArgs a{W.Qp, W.Qp_lo, Kl, Vl, kv_geom(c), W.seq, W.segments, W.anc, W.part_o, W.part_ml, W.Aq_hi, W.Aq_lo, B, k, {}, 0, {}, {}, {}, {}, c->hand};
     HIP_TRY(launch_attention(D, a, s));
     HIP_TRY(launch_unpack_act(W.Aq_hi, W.Aq_lo, B * (k + 1), D.qd, out, s));
     return SSSD_OK;

@@ -72,13 +72,7 @@ __device__ __forceinline__ float rows_sum(float x)
     return bits_f32(h[0]) + bits_f32(h[1]);
 }
 
-__device__ __forceinline__ f32x4 pick(bool first, f32x4 x, f32x4 y)   // by value: selected by address, arrays would go to scratch memory
-{
-    return f32x4{first ? x[0] : y[0], first ? x[1] : y[1], first ? x[2] : y[2], first ? x[3] : y[3]};
-}
-
-// Over the whole wave, in every lane, without LDS.
-__device__ __forceinline__ float wave_max(float x)
+__device__ __forceinline__ float wave_max(float x)   // in every lane, without LDS
 {
     x = fmaxf(x, bits_f32((uint32_t)__builtin_amdgcn_mov_dpp((int)f32_bits(x), 0x128, 0xF, 0xF, true)));   // rotated by 8, 4, 2, 1 lanes of 16
     x = fmaxf(x, bits_f32((uint32_t)__builtin_amdgcn_mov_dpp((int)f32_bits(x), 0x124, 0xF, 0xF, true)));
@@ -86,45 +80,44 @@ __device__ __forceinline__ float wave_max(float x)
     x = fmaxf(x, bits_f32((uint32_t)__builtin_amdgcn_mov_dpp((int)f32_bits(x), 0x121, 0xF, 0xF, true)));
     return rows_max(x);
 }
-__device__ __forceinline__ float wave_sum(float x)
-{
-    x += bits_f32((uint32_t)__builtin_amdgcn_mov_dpp((int)f32_bits(x), 0x128, 0xF, 0xF, true));
-    x += bits_f32((uint32_t)__builtin_amdgcn_mov_dpp((int)f32_bits(x), 0x124, 0xF, 0xF, true));
-    x += bits_f32((uint32_t)__builtin_amdgcn_mov_dpp((int)f32_bits(x), 0x122, 0xF, 0xF, true));
-    x += bits_f32((uint32_t)__builtin_amdgcn_mov_dpp((int)f32_bits(x), 0x121, 0xF, 0xF, true));
-    return rows_sum(x);
-}
 
 // The segments of ROWS query rows r0, r0 + step, ... (below r_end) of (sequence b, kv head kvh) merged by one wave, in fixed order.  The
 // wave reads the rows' partial outputs of 4*U segments in one round of independent loads: lanes 16s..16s+15 take segment s, s+4, ...
-// with 8 channels each, and the four lane groups are summed at the end.  DIE: workgroups of this launch, on this die, stored them.
-template <int HD, int ROWS, int U, bool DIE>
+// with 8 channels each; then the four lane groups are summed, each ending with two of the eight.  MANY: more than 4*U segments, in
+// rounds.  DIE: workgroups of this launch, on this die, stored them.
+template <int HD, int ROWS, int U, bool MANY, bool DIE>
 __device__ __forceinline__ void merge_rows(const Dims &D, const AttnArgs &a, int q_rows_pad, int b, int kvh, int r0, int step, int r_end, int n_splits, int lane)
 {
+#pragma clang fp contract(off)   // a row's bits must not depend on how many are merged at once: fused where it says so
     constexpr int LPR = HD / 8;   // lanes that cover a row of HD channels, 8 each
     const int KTq = (D.qd + 31) >> 5;
     const int sg = lane >> 4, cl = lane & 15;
     const size_t slot0 = ((size_t)kvh * a.B + b) * a.plan.share;
     const float *part_o = a.part_o + slot0 * q_rows_pad * HD, *part_ml = a.part_ml + slot0 * q_rows_pad * 2;
     const DieBuffer die_o(part_o, (size_t)n_splits * q_rows_pad * HD * sizeof(float)), die_ml(part_ml, (size_t)n_splits * q_rows_pad * sizeof(float2));
+    auto stats = [&](int segment, int r) {
+        const int at = segment * q_rows_pad + r;
+        return DIE ? die_ml.load2(at * 8) : *reinterpret_cast<const float2 *>(part_ml + (size_t)at * 2);
+    };
+    auto row = [&](int i) { return min(r0 + i * step, r_end - 1); };
 
-    float2 ml[ROWS];
-    float num[ROWS][8], w_lane[ROWS];
+    float num[ROWS][8], den[ROWS], m_star[ROWS];
 #pragma unroll
     for (int i = 0; i < ROWS; ++i) {
-        const int r = min(r0 + i * step, r_end - 1), at = min(lane, n_splits - 1) * q_rows_pad + r;
-        ml[i] = DIE ? die_ml.load2(at * 8) : *reinterpret_cast<const float2 *>(part_ml + (size_t)at * 2);
-        w_lane[i] = 0.f;
+        m_star[i] = MANY ? stats(min(lane, n_splits - 1), row(i)).x : 0.f;   // at most ATTN_MAX_SEGMENTS, a lane each
+        den[i] = 0.f;
 #pragma unroll
         for (int e = 0; e < 8; ++e) num[i][e] = 0.f;
     }
-    for (int base = 0; base < n_splits; base += 4 * U) {
+    for (int base = 0; base < (MANY ? n_splits : 1); base += 4 * U) {
         f32x4 pv[ROWS][U][2];
+        float2 ml[ROWS][U];
 #pragma unroll
         for (int i = 0; i < ROWS; ++i)
 #pragma unroll
             for (int u = 0; u < U; ++u) {   // past the last segment: that one again, not added
-                const int r = min(r0 + i * step, r_end - 1), at = (min(base + 4 * u + sg, n_splits - 1) * q_rows_pad + r) * HD + min(cl, LPR - 1) * 8;
+                const int s = min(base + 4 * u + sg, n_splits - 1), at = (s * q_rows_pad + row(i)) * HD + min(cl, LPR - 1) * 8;
+                ml[i][u] = stats(s, row(i));
                 if (DIE) {
                     pv[i][u][0] = die_o.load4(at * 4);
                     pv[i][u][1] = die_o.load4(at * 4, 16);
@@ -136,37 +129,52 @@ __device__ __forceinline__ void merge_rows(const Dims &D, const AttnArgs &a, int
         if (base == 0) {
 #pragma unroll
             for (int i = 0; i < ROWS; ++i) {
-                const float w = __builtin_amdgcn_exp2f(ml[i].x - wave_max(ml[i].x));   // all lanes: the maximum crosses them
-                w_lane[i] = lane < n_splits ? w : 0.f;
+                if (MANY) {
+                    m_star[i] = wave_max(m_star[i]);
+                } else {
+                    float m = ml[i][0].x;
+#pragma unroll
+                    for (int u = 1; u < U; ++u) m = fmaxf(m, ml[i][u].x);
+                    m_star[i] = rows_max(m);
+                }
             }
         }
 #pragma unroll
         for (int i = 0; i < ROWS; ++i)
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                const int s = base + 4 * u + sg;
-                const float w = __shfl(w_lane[i], s < 64 ? s : 63);
+                const bool on = base + 4 * u + sg < n_splits;
+                const float w = __builtin_amdgcn_exp2f(ml[i][u].x - m_star[i]);
+                den[i] = on ? __builtin_fmaf(w, ml[i][u].y, den[i]) : den[i];
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    num[i][e] += s < n_splits ? w * pv[i][u][0][e] : 0.f;
-                    num[i][4 + e] += s < n_splits ? w * pv[i][u][1][e] : 0.f;
+                    num[i][e] = on ? __builtin_fmaf(w, pv[i][u][0][e], num[i][e]) : num[i][e];
+                    num[i][4 + e] = on ? __builtin_fmaf(w, pv[i][u][1][e], num[i][4 + e]) : num[i][4 + e];
                 }
             }
     }
 #pragma unroll
     for (int i = 0; i < ROWS; ++i) {
+        const float inv = 1.f / rows_sum(den[i]);
+        float half[4], two[2];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {   // lane groups 0 and 1 keep channels 0..3, 2 and 3 channels 4..7
+            const auto h = __builtin_amdgcn_permlane32_swap(f32_bits(num[i][e]), f32_bits(num[i][4 + e]), false, false);
+            half[e] = bits_f32(h[0]) + bits_f32(h[1]);
+        }
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {   // groups 0 and 2 the first two of them
+            const auto h = __builtin_amdgcn_permlane16_swap(f32_bits(half[e]), f32_bits(half[2 + e]), false, false);
+            two[e] = bits_f32(h[0]) + bits_f32(h[1]);
+        }
         const int r = r0 + i * step;
-        const float den = wave_sum(w_lane[i] * ml[i].y);
-        uint32_t hi[4], lo[4];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) num[i][e] = rows_sum(num[i][e]);
-#pragma unroll
-        for (int e = 0; e < 8; e += 2) split_bf16x2(num[i][e] / den, num[i][e + 1] / den, hi[e >> 1], lo[e >> 1]);
-        if (r < r_end && sg == 0 && cl < LPR) {
-            const int j = r / D.g, hl = r % D.g, m = b * (a.k + 1) + j;
-            const size_t idx = packed_index(m, (kvh * D.g + hl) * HD + cl * 8, KTq);   // whole lane records
-            *reinterpret_cast<u32x4 *>(a.out_hi + idx) = u32x4{hi[0], hi[1], hi[2], hi[3]};
-            *reinterpret_cast<u32x4 *>(a.out_lo + idx) = u32x4{lo[0], lo[1], lo[2], lo[3]};
+        if (r < r_end && cl < LPR) {
+            uint32_t hi, lo;
+            split_bf16x2(two[0] * inv, two[1] * inv, hi, lo);
+            const int j = a.by_g(r), hl = r - j * D.g, m = b * (a.k + 1) + j;
+            const size_t idx = packed_index(m, (kvh * D.g + hl) * HD + cl * 8 + (sg >> 1) * 4 + (sg & 1) * 2, KTq);
+            *reinterpret_cast<uint32_t *>(a.out_hi + idx) = hi;
+            *reinterpret_cast<uint32_t *>(a.out_lo + idx) = lo;
         }
     }
 }
@@ -181,50 +189,53 @@ __global__ __launch_bounds__(NWAVE * 64) __attribute__((amdgpu_waves_per_eu(2, 2
     constexpr int NREC = 4 * HD;             // 16-byte records of a block of 32 positions, K and V alike
     constexpr bool QREG = RT == 1;           // query operands in registers, else in LDS
     constexpr int QAHEAD = RT == 4 ? 1 : 3;  // pairs of them fetched ahead: four tiles leave registers for one
-    constexpr int QREC = RT * KS * 2 * 64, RRED = NWAVE * RT * (DT / 2) * 64;   // records of the query tiles, of the final sums
+    constexpr int QREC = QREG ? 0 : RT * KS * 2 * 64, RRED = NWAVE * (NWAVE - 1) * (RT <= 3 ? RT : 2) * (DT / 4) * 64;   // records of the query tiles, of the final sums
     __shared__ u32x4 lds[QREC > RRED ? QREC : RRED];
     __shared__ float2 ml_s[NWAVE][RT * 16];
     __shared__ int way_s;
     __shared__ uint32_t vis_s[RT * 16];      // visible new rows of every query row: bit i = cache row len + i
 
-    int kvh, wg;   // kv head; (turn, segment)
-    int pass = 0;
-    const int passes = a.plan.passes;
+    int pass = 0, turn, kvh, segment;
+    const int passes = a.plan.passes, share = a.plan.share;
     {
         int id = blockIdx.x;
         if (a.hand.words) {   // all segments of a (sequence, kv head) on one die, its passes next to each other
             // Heads of one sequence and, by turn, of different sequences on a die: with one head per die each die would read the same
             // eighth of every page.
-            const int slot = id >> 3, x = slot / passes, row = x / a.plan.share, u = row * 8 + ((id - row) & 7);
+            const int slot = id >> 3, x = a.by_passes(slot), row = a.by_share(x), u = row * 8 + ((id - row) & 7);
             pass = slot - x * passes;
-            wg = u / D.nkv * a.plan.share + x % a.plan.share;
-            kvh = u % D.nkv;
+            segment = x - row * share;
+            turn = a.by_nkv(u);
+            kvh = u - turn * D.nkv;
         } else {
             if (passes > 1) {
-                const int n = a.B * a.plan.share * D.nkv, sets = n & ~7;
+                const int n = a.B * share * D.nkv, sets = n & ~7;
                 if (id < sets * passes) {
-                    const int x = id / (8 * passes), r = id - x * 8 * passes;
-                    pass = r >> 3;
-                    id = x * 8 + (r & 7);
+                    const int x = a.by_passes(id >> 3);
+                    pass = (id >> 3) - x * passes;
+                    id = x * 8 + (id & 7);
                 } else {
                     const int r = id - sets * passes;
                     pass = r / (n - sets);
                     id = sets + r % (n - sets);
                 }
             }
-            const int whole = (a.B * a.plan.share) & ~7;
+            const int whole = (a.B * share) & ~7;
+            int wg;   // (turn, segment)
             if (id < whole * D.nkv) {
-                wg = id / (8 * D.nkv) * 8 + (id & 7);
-                kvh = (id >> 3) % D.nkv;
+                const int x = a.by_nkv(id >> 3);
+                wg = x * 8 + (id & 7);
+                kvh = (id >> 3) - x * D.nkv;
             } else {
-                const int r = id - whole * D.nkv;
-                wg = whole + r / D.nkv;
-                kvh = r % D.nkv;
+                const int r = id - whole * D.nkv, x = a.by_nkv(r);
+                wg = whole + x;
+                kvh = r - x * D.nkv;
             }
+            turn = a.by_share(wg);
+            segment = wg - turn * share;
         }
     }
-    const int segment = wg % a.plan.share;
-    const AttnSeq me = a.seq[wg / a.plan.share];
+    const AttnSeq me = a.seq[turn];
     const int b = me.b, len = me.len, total = len + a.k + 1;   // a rejected sequence is read as empty
     const AttnCut cut = me.cut;
     if (segment >= cut.n) return;
@@ -260,29 +271,33 @@ __global__ __launch_bounds__(NWAVE * 64) __attribute__((amdgpu_waves_per_eu(2, 2
         }
     }
 
-    // A block's operands.  Every load is issued unconditionally -- past the end all lanes re-read records of the last block, for
-    // nothing -- because a load under a branch would make every later wait a full drain.  A single pass streams; several passes
-    // find K, and mostly V, in the die's L2.
+    // A block's operands.  Every load is issued unconditionally, because a load under a branch would make every later wait a full drain;
+    // past the wave's last block the buffer they read has no records and the loads return at once without one.  (Reading the last block
+    // again instead kept the final sums waiting for memory: 2 us of a segment's time.)  A single pass streams; several passes find K, and
+    // mostly V, in the die's L2.
     u32x4 k[2][KS], v[DT];
-    auto block_base = [&](int i) -> size_t {   // first record of the wave's block i, past the end of its last one
-        i = i < n_it ? i : (n_it > 0 ? n_it - 1 : 0);
-        const int x = __builtin_amdgcn_readlane(i >> 6 == chunk ? pg : pg_next, i & 63);
-        return ((size_t)x * D.nkv + kvh) * NREC;
+    auto block = [&](const uint16_t *pool, int i) {   // the wave's block i
+        const int at = i < n_it ? i : 0;
+        const int x = __builtin_amdgcn_readlane(at >> 6 == chunk ? pg : pg_next, at & 63);
+        return __builtin_amdgcn_make_buffer_rsrc(const_cast<u32x4 *>(reinterpret_cast<const u32x4 *>(pool) + ((size_t)x * D.nkv + kvh) * NREC), 0,
+                                                 i < n_it ? NREC * 16 : 0, 0x00027000);
     };
+    constexpr int STREAM = 2;   // non-temporal
     auto load_k = [&](int i) {
-        const u32x4 *p = reinterpret_cast<const u32x4 *>(a.Kc) + block_base(i) + (i < n_it ? lane : 0);
+        const auto p = block(a.Kc, i);
 #pragma unroll
         for (int u = 0; u < 2; ++u)
 #pragma unroll
-            for (int ks = 0; ks < KS; ++ks) k[u][ks] = ONCE ? __builtin_nontemporal_load(p + (u * KS + ks) * 64) : p[(u * KS + ks) * 64];
+            for (int ks = 0; ks < KS; ++ks)
+                k[u][ks] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(p, lane * 16, (u * KS + ks) * 1024, ONCE ? STREAM : 0));
     };
     auto load_v = [&](int i) {
-        const u32x4 *p = reinterpret_cast<const u32x4 *>(a.Vc) + block_base(i) + (i < n_it ? lane : 0);
+        const auto p = block(a.Vc, i);
 #pragma unroll
-        for (int dt = 0; dt < DT; ++dt) v[dt] = __builtin_nontemporal_load(p + dt * 64);
+        for (int dt = 0; dt < DT; ++dt) v[dt] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(p, lane * 16, dt * 1024, STREAM));
     };
     const bool has_new = (first_blk + n_blk) * 32 > len;   // the segment holds new rows
-    auto visible = [&](int row) { return a.anc[b * (a.k + 1) + min((rt0 * 16 + row) / D.g, a.k)]; };   // query row -> node of the chain or tree
+    auto visible = [&](int row) { return a.anc[b * (a.k + 1) + min(a.by_g(rt0 * 16 + row), a.k)]; };   // query row -> node of the chain or tree
     constexpr bool VREG = RT <= 3;   // in registers, else in LDS
     uint32_t vis[VREG ? RT : 1];
 #pragma unroll
@@ -368,13 +383,13 @@ __global__ __launch_bounds__(NWAVE * 64) __attribute__((amdgpu_waves_per_eu(2, 2
             }
             if (t0 + 32 > len) {   // the block holds new rows: apply the nodes' visibility words
                 const uint32_t seen = VREG ? vis[VREG ? t : 0] : vis_s[t * 16 + c];
+                const int at = t0 - len;   // bit p of `in`: position p of the block is visible; old cache always is
+                const uint32_t in = at > 31 ? 0u : (at >= 0 ? seen >> at : seen << -at | ((1u << -at) - 1u)), mine = in >> (4 * q);
 #pragma unroll
                 for (int u = 0; u < 2; ++u)
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        const int rel = t0 + 16 * u + 4 * q + r - len;   // < 0: old cache, always visible
-                        if (rel >= 0 && (rel > 31 || !((seen >> rel) & 1u))) s[t][u][r] = -INFINITY;
-                    }
+                    for (int r = 0; r < 4; ++r)
+                        if (!(mine & (1u << (16 * u + r)))) s[t][u][r] = -INFINITY;
             }
         }
         load_k(i + 1);
@@ -388,6 +403,7 @@ __global__ __launch_bounds__(NWAVE * 64) __attribute__((amdgpu_waves_per_eu(2, 2
             for (int t = 0; t < RT; ++t) {
                 const float m_new = mx[t] > m_run[t] + 8.f ? mx[t] : m_run[t], alpha = __builtin_amdgcn_exp2f(m_run[t] - m_new);
                 m_run[t] = m_new;
+                if (i == 0) continue;   // nothing to rescale yet
                 l_run[t] *= alpha;
 #pragma unroll
                 for (int dt = 0; dt < DT; ++dt) o[t][dt] *= alpha;
@@ -433,58 +449,83 @@ __global__ __launch_bounds__(NWAVE * 64) __attribute__((amdgpu_waves_per_eu(2, 2
         load_v(i + 1);
     }
 
-    // The waves' sums on one reference per query row, then added up: every wave ends with a quarter of the channels of all rows.
+    // The waves' sums added up, on one reference per query row: every wave ends with a quarter of the channels of all rows.  It stores
+    // the other three quarters as they are; who takes them has all four references and weighs them while adding.  One wave per SIMD
+    // issues an instruction every four cycles: in two halving steps, selected by wave and scaled first, three tiles took 3.0 us of
+    // which these take 1.9.
+    constexpr int QT = DT / 4, TR = RT <= 3 ? RT : 2;   // channel tiles of a quarter; row tiles exchanged at a time
+    f32x4 *red = reinterpret_cast<f32x4 *>(lds);
+    const int dt0 = wave * QT;
+    f32x4 own[RT][QT];
+    if (RT > 1) __syncthreads();   // the query tiles have been read
 #pragma unroll
     for (int t = 0; t < RT; ++t) {
         l_run[t] = rows_sum(l_run[t]);
         if (q == 0) ml_s[wave][t * 16 + c] = float2{m_run[t], l_run[t]};
     }
-    __syncthreads();   // the query tiles have been read
-    float m_all[RT], l_all[RT];
+#pragma unroll
+    for (int w = 0; w < NWAVE; ++w)
+        if (w == wave)
+#pragma unroll
+            for (int t = 0; t < RT; ++t)
+#pragma unroll
+                for (int x = 0; x < QT; ++x) own[t][x] = o[t][w * QT + x];
+    auto part = [&](int quarter, int from, int t, int x) -> f32x4 & {   // of wave `from`, for the wave of `quarter`
+        return red[(((quarter * (NWAVE - 1) + from - (from > quarter ? 1 : 0)) * TR + t % TR) * QT + x) * 64 + lane];
+    };
+    auto give = [&](int t0) {
+#pragma unroll
+        for (int w = 0; w < NWAVE; ++w)
+            if (w != wave)
+#pragma unroll
+                for (int t = t0; t < t0 + TR; ++t)
+#pragma unroll
+                    for (int x = 0; x < QT; ++x) part(w, wave, t, x) = o[t][w * QT + x];
+    };
+    // What the others left for this wave, all of it requested before any is used; index i: wave + i, so in an order that the quarter fixes.
+    f32x4 taken[TR][NWAVE][QT];
+    float2 st[TR][NWAVE];
+    auto take = [&](int t0) {
+#pragma unroll
+        for (int i = 0; i < NWAVE; ++i) {
+            const int w = (wave + i) & (NWAVE - 1);
+#pragma unroll
+            for (int t = 0; t < TR; ++t) {
+                st[t][i] = ml_s[w][(t0 + t) * 16 + c];
+                if (i > 0)
+#pragma unroll
+                    for (int x = 0; x < QT; ++x) taken[t][i][x] = part(wave, w, t0 + t, x);
+            }
+        }
+    };
+    give(0);
+    __syncthreads();
+    take(0);
 #pragma unroll
     for (int t = 0; t < RT; ++t) {
-        float2 x[NWAVE];
-#pragma unroll
-        for (int w = 0; w < NWAVE; ++w) x[w] = ml_s[w][t * 16 + c];
-        m_all[t] = fmaxf(fmaxf(x[0].x, x[1].x), fmaxf(x[2].x, x[3].x));
-        l_all[t] = 0.f;
-#pragma unroll
-        for (int w = 0; w < NWAVE; ++w) l_all[t] += x[w].y * __builtin_amdgcn_exp2f(x[w].x - m_all[t]);
-        const float f = __builtin_amdgcn_exp2f(m_run[t] - m_all[t]);
-#pragma unroll
-        for (int dt = 0; dt < DT; ++dt) o[t][dt] *= f;
-    }
-    f32x4 *red = reinterpret_cast<f32x4 *>(lds);
-    constexpr int H = DT / 2, QT = DT / 4;
-    const bool up2 = wave >> 1, up1 = wave & 1;
-#pragma unroll
-    for (int t = 0; t < RT; ++t)
-#pragma unroll
-        for (int x = 0; x < H; ++x) red[((wave * RT + t) * H + x) * 64 + lane] = pick(up2, o[t][x], o[t][H + x]);
-    __syncthreads();
-    f32x4 oh[RT][H];
-#pragma unroll
-    for (int t = 0; t < RT; ++t)
-#pragma unroll
-        for (int x = 0; x < H; ++x) oh[t][x] = pick(up2, o[t][H + x], o[t][x]) + red[(((wave ^ 2) * RT + t) * H + x) * 64 + lane];
-    __syncthreads();
-#pragma unroll
-    for (int t = 0; t < RT; ++t)
-#pragma unroll
-        for (int x = 0; x < QT; ++x) red[((wave * RT + t) * QT + x) * 64 + lane] = pick(up1, oh[t][x], oh[t][QT + x]);
-    __syncthreads();
-    const int dt0 = (up2 ? H : 0) + (up1 ? QT : 0);
-#pragma unroll
-    for (int t = 0; t < RT; ++t) {
+        if (t > 0 && t % TR == 0) {
+            __syncthreads();
+            give(t);
+            __syncthreads();
+            take(t);
+        }
+        const float2 (&s4)[NWAVE] = st[t % TR];
+        const float m_all = fmaxf(fmaxf(s4[0].x, s4[1].x), fmaxf(s4[2].x, s4[3].x));
+        float l_all = 0.f;
         f32x4 y[QT];   // y[x][r]: channel (dt0 + x) * 16 + 4q + r of query row c of tile t
 #pragma unroll
-        for (int x = 0; x < QT; ++x) y[x] = pick(up1, oh[t][QT + x], oh[t][x]) + red[(((wave ^ 1) * RT + t) * QT + x) * 64 + lane];
+        for (int i = 0; i < NWAVE; ++i) {
+            const float f = __builtin_amdgcn_exp2f(s4[i].x - m_all);
+            l_all += s4[i].y * f;
+#pragma unroll
+            for (int x = 0; x < QT; ++x) y[x] = i ? y[x] + taken[t % TR][i][x] * f : own[t][x] * f;
+        }
         const int row = (rt0 + t) * 16 + c;
         if (rt0 + t >= a.row_tiles) continue;
         if (cut.n == 1) {   // the whole sequence: the packed operands of the O projection
-            const int jj = row / D.g, hl = row - jj * D.g;
+            const int jj = a.by_g(row), hl = row - jj * D.g;
             if (jj <= a.k) {
-                const float inv = 1.f / l_all[t];
+                const float inv = 1.f / l_all;
                 const int m = b * (a.k + 1) + jj, KTq = (D.qd + 31) >> 5;
                 const size_t idx = packed_index(m, (kvh * D.g + hl) * HD + 4 * q, KTq);
 #pragma unroll
@@ -504,20 +545,29 @@ __global__ __launch_bounds__(NWAVE * 64) __attribute__((amdgpu_waves_per_eu(2, 2
             float *po = a.part_o + at * HD;
 #pragma unroll
             for (int x = 0; x < QT; ++x) *reinterpret_cast<f32x4 *>(po + (dt0 + x) * 16 + 4 * q) = y[x];
-            if (wave == 0 && q == 0) *reinterpret_cast<float2 *>(a.part_ml + at * 2) = float2{m_all[t], l_all[t]};
+            if (wave == 0 && q == 0) *reinterpret_cast<float2 *>(a.part_ml + at * 2) = float2{m_all, l_all};
         }
     }
     if (cut.n == 1 || !a.hand.words) return;
-    const int group = (wg / a.plan.share * D.nkv + kvh) * passes + pass;   // by turn, not by sequence: both count to B
+    const int group = (turn * D.nkv + kvh) * passes + pass;   // by turn, not by sequence: both count to B
     HandWay way = hand_over(a.hand, group, cut.n, &way_s);
     if (way == HAND_TURN_IN) way = hand_turn_in(a.hand, group, cut.n, &way_s);
     uint32_t left = way == HAND_SHARE ? hand_leave(a.hand, group) : 0;   // under way while the shares are done
     if (way != HAND_NOTHING) {   // the rows of this pass shared out over the waves of all segments
         const int r_end = min(D.g * (a.k + 1), (rt0 + RT) * 16), step = (way == HAND_ALL ? 1 : cut.n) * NWAVE;
         int r = rt0 * 16 + (way == HAND_ALL ? wave : wave * cut.n + segment);
-        if (cut.n <= 4) for (; r < r_end; r += 4 * step) merge_rows<HD, 4, 1, true>(D, a, q_rows_pad, b, kvh, r, step, r_end, cut.n, lane);
-        else if (cut.n <= 8) for (; r < r_end; r += 2 * step) merge_rows<HD, 2, 2, true>(D, a, q_rows_pad, b, kvh, r, step, r_end, cut.n, lane);
-        else for (; r < r_end; r += step) merge_rows<HD, 1, 5, true>(D, a, q_rows_pad, b, kvh, r, step, r_end, cut.n, lane);
+        // as many rows at once as the wave has, up to four, when they have few segments
+#define SSSD_MERGE(ROWS, U, MANY) for (; r < r_end; r += ROWS * step) merge_rows<HD, ROWS, U, MANY, true>(D, a, q_rows_pad, b, kvh, r, step, r_end, cut.n, lane)
+        if (cut.n > 8) SSSD_MERGE(1, 5, true);
+        else if (cut.n > 4) {
+            if (r + step < r_end) SSSD_MERGE(2, 2, false);
+            else SSSD_MERGE(1, 2, false);
+        } else {
+            if (r + 2 * step < r_end) SSSD_MERGE(4, 1, false);
+            else if (r + step < r_end) SSSD_MERGE(2, 1, false);
+            else SSSD_MERGE(1, 1, false);
+        }
+#undef SSSD_MERGE
     }
     if (way != HAND_SHARE) left = hand_leave(a.hand, group);
     hand_clear(a.hand, group, cut.n, left);
@@ -534,7 +584,7 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(Dims D, AttnArgs a, i
     const int n_splits = a.segments[b];    // at most ATTN_MAX_SEGMENTS
     if (n_splits == 1) return;             // finished by its workgroup
     // nine at a time cost registers: B = 12, k = 31, context 900..2700 81 us of attention, five 78
-    merge_rows<HD, 1, 5, false>(D, a, q_rows_pad, b, kvh, r, 1, r + 1, n_splits, threadIdx.x & 63);
+    merge_rows<HD, 1, 5, true, false>(D, a, q_rows_pad, b, kvh, r, 1, r + 1, n_splits, threadIdx.x & 63);
 }
 
 template <int HD> hipError_t launch_partial(const Dims &D, const AttnArgs &a, int q_rows_pad, hipStream_t s)
@@ -630,6 +680,10 @@ hipError_t launch_attention(const Dims &D, const AttnArgs &a_in, hipStream_t s)
     const int q_rows_pad = round_up(D.g * (D.max_k + 1), 16);
     a.row_tiles = (D.g * (a.k + 1) + 15) / 16;
     a.plan = attention_plan(D, a.B, a.k);
+    a.by_passes = Div(a.plan.passes);
+    a.by_share = Div(a.plan.share);
+    a.by_nkv = Div(D.nkv);
+    a.by_g = Div(D.g);
     const bool merge = a.plan.share > 1 && D.blocks_per_seq > ATTN_WHOLE_BLOCKS;
     if (!merge || !attention_in_die(D, a.plan, a.B)) a.hand.words = nullptr;
     hipError_t e = D.d == 128 ? launch_partial<128>(D, a, q_rows_pad, s) : launch_partial<64>(D, a, q_rows_pad, s);

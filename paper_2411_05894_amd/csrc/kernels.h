@@ -167,6 +167,7 @@ struct AttnArgs {
     int B, k;
     AttnPlan plan;             // filled in by launch_attention
     int row_tiles;             // ... 16-row tiles of query rows
+    Div by_passes, by_share, by_nkv, by_g;   // ... divisors of the plan and the model
     Hand hand;                 // words for segments merged inside the launch, or none: a second launch merges them
 };
 // Partial slots of a step of B sequences, all kv heads (sizes the buffers).

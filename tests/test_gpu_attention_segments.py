@@ -37,13 +37,13 @@ def reference(q, K, V, n_old, g):
     return out
 
 
-def attention_context(shape_name, B, k, max_seq, no_wait=False):
+def attention_context(shape_name, B, k, max_seq):
     """A context of which only the cache matters: the matrices are small and zero."""
     s = MODEL_SHAPES[shape_name]
     s = type(s)(**{**s.__dict__, "n_layers": 1, "vocab": 1024, "hidden": 64, "ffn": 64})
     layers = [{n: torch.zeros(shp, dtype=torch.bfloat16, device=DEV) for n, _, shp in layer_weight_specs(s)}]
     g = {n: torch.zeros(shp, dtype=torch.bfloat16, device=DEV) for n, _, shp in global_weight_specs(s)}
-    return s, sv.VerifyContext(sv.make_config(s, B, k, max_seq), layers, g, no_wait=no_wait)
+    return s, sv.VerifyContext(sv.make_config(s, B, k, max_seq), layers, g)
 
 
 @pytest.mark.parametrize("shape_name,k,lens,max_seq", CASES)

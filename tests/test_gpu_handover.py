@@ -7,10 +7,19 @@ import torch
 pytestmark = pytest.mark.gpu
 
 from paper_2411_05894_amd import binding as sv
-from sssd_synth import normal_bf16
-from test_gpu_attention_segments import attention_context, reference
+from sssd_synth import MODEL_SHAPES, global_weight_specs, layer_weight_specs, normal_bf16
+from test_gpu_attention_segments import reference
 
 DEV = "cuda:0"
+
+
+def attention_context(shape_name, B, k, max_seq, no_wait):
+    """A context of which only the cache matters: the matrices are small and zero."""
+    s = MODEL_SHAPES[shape_name]
+    s = type(s)(**{**s.__dict__, "n_layers": 1, "vocab": 1024, "hidden": 64, "ffn": 64})
+    layers = [{n: torch.zeros(shp, dtype=torch.bfloat16, device=DEV) for n, _, shp in layer_weight_specs(s)}]
+    g = {n: torch.zeros(shp, dtype=torch.bfloat16, device=DEV) for n, _, shp in global_weight_specs(s)}
+    return s, sv.VerifyContext(sv.make_config(s, B, k, max_seq), layers, g, no_wait=no_wait)
 
 
 @pytest.mark.parametrize("shape_name,k,lens,max_seq", [
