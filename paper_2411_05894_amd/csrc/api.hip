@@ -30,7 +30,7 @@ struct Buffers {
     int32_t *segments;
     uint32_t *anc;
     float *rope_cs, *ssq1;
-    uint8_t *staging;   // of in-place packing; from the end of sssd_verify_init on, its first bytes are the words of Hand
+    uint8_t *staging;   // of in-place packing; from the end of sssd_verify_init on, Hand's words and parts
     size_t staging_bytes;
     float *partials;
     size_t partial_bytes;
@@ -401,9 +401,10 @@ int sssd_verify_init(const sssd_model_config *cfg, const sssd_weights *w, void *
         c->n_cu = prop.multiProcessorCount;
     }
     // Workgroups hand results over within a die where all of a device's eight are there and take the workgroups in turn.
-    c->hand = Hand{nullptr, flags & SSSD_NO_WAIT ? 0 : HAND_POLLS};
+    c->hand = Hand{nullptr, (float *)(c->W.staging + ((size_t)1 << 20)), flags & SSSD_NO_WAIT ? 0 : HAND_POLLS};
     {
-        static_assert(HAND_GROUPS * HAND_STRIDE * sizeof(uint32_t) <= (size_t)1 << 20, "staging holds the words");
+        static_assert(HAND_GROUPS * HAND_STRIDE * sizeof(uint32_t) <= (size_t)1 << 20, "the words lie in front of the parts");
+        if (c->W.staging_bytes < HAND_PARTS + ((size_t)1 << 20)) INIT_RC(SSSD_ECAPACITY);
         uint32_t *words = (uint32_t *)c->W.staging, strays = 0;
         INIT_TRY(hipMemsetAsync(words, 0, HAND_GROUPS * HAND_STRIDE * sizeof(uint32_t), s));
         INIT_TRY(launch_die_check(words, s));
@@ -489,7 +490,7 @@ int run_step(sssd_ctx *c, int32_t B, int32_t k, const int32_t *tokens, const int
     f.X = W.X; f.rope_cs = W.rope_cs; f.pos_base = W.pos_base; f.rope_pos = W.rope_pos; f.Qp = W.Qp; f.Qp_lo = W.Qp_lo;
     f.logits = smp ? smp->logits : c->dbg_logits; f.part_val = W.part_val; f.part_idx = W.part_idx;
     const int KTh = (D.h + 31) / 32, KTq = (D.qd + 31) / 32, KTf = (D.f + 31) / 32;
-    f.n_cu = c->n_cu; f.partials = W.partials; f.partial_bytes = W.partial_bytes;
+    f.n_cu = c->n_cu; f.partials = W.partials; f.partial_bytes = W.partial_bytes; f.hand = c->hand;
     int nss = embed_row_sums(D.h);   // sums of squares per row of the residual stream, as its last writer left them
     auto fgemm = [&](int epi) -> hipError_t {
         bool more = false;

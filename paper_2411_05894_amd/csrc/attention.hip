@@ -550,7 +550,7 @@ __global__ __launch_bounds__(NWAVE * 64) __attribute__((amdgpu_waves_per_eu(2, 2
     }
     if (cut.n == 1 || !a.hand.words) return;
     const int group = (turn * D.nkv + kvh) * passes + pass;   // by turn, not by sequence: both count to B
-    HandWay way = hand_over(a.hand, group, cut.n, &way_s);
+    HandWay way = hand_wait(a.hand, group, cut.n, hand_arrive(a.hand, group), &way_s);
     if (way == HAND_TURN_IN) way = hand_turn_in(a.hand, group, cut.n, &way_s);
     uint32_t left = way == HAND_SHARE ? hand_leave(a.hand, group) : 0;   // under way while the shares are done
     if (way != HAND_NOTHING) {   // the rows of this pass shared out over the waves of all segments

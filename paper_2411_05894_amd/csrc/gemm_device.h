@@ -87,7 +87,7 @@ __device__ __forceinline__ void epilogue(const FusedGemmArgs &a, int unit, int m
         const int pair = unit % per_head;
         v0 *= rs;
         v1 *= rs;
-        const int b = m / (a.k + 1), j = m % (a.k + 1);
+        const int b = a.by_k1(m), j = m - b * (a.k + 1);
         const int base = a.pos_base[b];                 // < 0: a rejected sequence, which must not touch the cache
         const int pos = base + j;                       // cache row of node j
         const int half = a.d >> 1, ch = pair * 16 + c;  // channel of v0; v1 is ch + half
@@ -95,7 +95,7 @@ __device__ __forceinline__ void epilogue(const FusedGemmArgs &a, int unit, int m
             const float2 cs = *reinterpret_cast<const float2 *>(a.rope_cs + ((size_t)a.rope_pos[m] * half + ch) * 2);
             const float y0 = v0 * cs.x - v1 * cs.y, y1 = v0 * cs.y + v1 * cs.x;
             if (head < a.nq) {
-                const int g = a.nq / a.nkv, kvh = head / g, hl = head % g, rr = j * g + hl;
+                const int g = (int)a.by_g.d, kvh = a.by_g(head), hl = head - kvh * g, rr = j * g + hl;
                 const size_t qs = ((size_t)b * a.nkv + kvh) * a.q_rows_pad * a.d;
                 uint16_t h0, l0, h1, l1;
                 split_bf16(y0, h0, l0);
@@ -219,23 +219,14 @@ __device__ __forceinline__ void split8(const Vec8 &x, u32x4 &hi, u32x4 &lo)
 {
     uint32_t h[4], l[4];
 #pragma unroll
-    for (int e = 0; e < 8; e += 2) {
-        uint16_t h0, l0, h1, l1;
-        split_bf16(x.v[e], h0, l0);
-        split_bf16(x.v[e + 1], h1, l1);
-        h[e >> 1] = (uint32_t)h0 | ((uint32_t)h1 << 16);
-        l[e >> 1] = (uint32_t)l0 | ((uint32_t)l1 << 16);
-    }
+    for (int e = 0; e < 4; ++e) split_bf16x2(x.v[2 * e], x.v[2 * e + 1], h[e], l[e]);
     hi = u32x4{h[0], h[1], h[2], h[3]};
     lo = u32x4{l[0], l[1], l[2], l[3]};
 }
 
 __device__ __forceinline__ u32x4 round8(const Vec8 &x)
 {
-    uint32_t h[4];
-#pragma unroll
-    for (int e = 0; e < 8; e += 2) h[e >> 1] = (uint32_t)f32_to_bf16(x.v[e]) | ((uint32_t)f32_to_bf16(x.v[e + 1]) << 16);
-    return u32x4{h[0], h[1], h[2], h[3]};
+    return u32x4{pack_bf16x2(x.v[0], x.v[1]), pack_bf16x2(x.v[2], x.v[3]), pack_bf16x2(x.v[4], x.v[5]), pack_bf16x2(x.v[6], x.v[7])};
 }
 
 // Sums of the J slices of 8 columns each at `col` (and at `col1`, with TWO) of row m, slices in order.  BATCH slices are
@@ -268,16 +259,26 @@ __device__ __forceinline__ void sum_slices(const FusedGemmArgs &a, int m, int co
 // Epilogues on 8 consecutive columns per thread, which are one 16-byte lane record of a packed operand.
 
 // RESID: X += v0, packed X * gamma.  v0 = the projection's result at columns col..col+7 of row m.  Returns the sum of squares
-// of the updated columns.
-template <bool COH> __device__ __forceinline__ float resid8(const FusedGemmArgs &a, int m, int col, const Vec8 &v0)
+// of the updated columns.  What it reads can be requested ahead.
+struct ResidIn {
+    Vec8 x;
+    u32x4 gamma;
+};
+template <bool COH> __device__ __forceinline__ ResidIn resid_in(const FusedGemmArgs &a, int m, int col)
+{
+    ResidIn in;
+    in.x = load8<COH>(a.X + (size_t)m * a.h + col);
+    __builtin_memcpy(&in.gamma, a.gamma_next + col, 16);   // caller's array: no alignment assumed
+    return in;
+}
+template <bool COH> __device__ __forceinline__ float resid8(const FusedGemmArgs &a, int m, int col, const Vec8 &v0, const ResidIn &in)
 {
     float ss = 0.f;
-    const Vec8 x = load8<COH>(a.X + (size_t)m * a.h + col);
     Vec8 xn, xg;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-        xn.v[e] = x.v[e] + v0.v[e];
-        xg.v[e] = xn.v[e] * bf16_to_f32(a.gamma_next[col + e]);   // caller's array: no alignment assumed
+        xn.v[e] = in.x.v[e] + v0.v[e];
+        xg.v[e] = xn.v[e] * bits_f32(e & 1 ? in.gamma[e >> 1] & 0xFFFF0000u : in.gamma[e >> 1] << 16);
         ss += xn.v[e] * xn.v[e];
     }
     store8<COH>(a.X + (size_t)m * a.h + col, xn);
@@ -287,6 +288,10 @@ template <bool COH> __device__ __forceinline__ float resid8(const FusedGemmArgs 
     st_record<COH>(a.out_hi + idx, hi);
     st_record<COH>(a.out_lo + idx, lo);
     return ss;
+}
+template <bool COH> __device__ __forceinline__ float resid8(const FusedGemmArgs &a, int m, int col, const Vec8 &v0)
+{
+    return resid8<COH>(a, m, col, v0, resid_in<COH>(a, m, col));
 }
 
 // RESID with one sum of squares per 16 columns; whole waves call it.  kg: which 8-column group of its 32-column block the
@@ -298,27 +303,40 @@ template <bool COH> __device__ __forceinline__ void resid_block(const FusedGemmA
     if (live && !(kg & 1)) st<COH>(a.ssq_out + (size_t)m * (a.h >> 4) + (col >> 4), ss);
 }
 
-// QKV: v0 at channels ch..ch+7 of the first half of a head, v1 at the same channels of the second half.
-__device__ __forceinline__ void qkv8(const FusedGemmArgs &a, int m, int head, int ch, float rs, Vec8 v0, Vec8 v1)
+// QKV: v0 at channels ch..ch+7 of the first half of a head, v1 at the same channels of the second half.  What it reads can be
+// requested ahead.
+struct QkvIn {
+    int base;        // cache row of the sequence's first node; < 0: a rejected sequence, which must not touch the cache
+    Vec8 cs0, cs1;   // (cos, sin) of channels ch..ch+3, ch+4..ch+7 (Q and K heads)
+};
+__device__ __forceinline__ QkvIn qkv_in(const FusedGemmArgs &a, int m, int head, int ch)
+{
+    QkvIn in;
+    in.base = a.pos_base[a.by_k1(m)];
+    if (head < a.nq + a.nkv) {
+        const float *cs = a.rope_cs + ((size_t)a.rope_pos[m] * (a.d >> 1) + ch) * 2;
+        in.cs0 = load8(cs);
+        in.cs1 = load8(cs + 8);
+    }
+    return in;
+}
+__device__ __forceinline__ void qkv8(const FusedGemmArgs &a, int m, int head, int ch, float rs, Vec8 v0, Vec8 v1, const QkvIn &in)
 {
     const int half = a.d >> 1;
-    const int b = m / (a.k + 1), j = m % (a.k + 1);
-    const int base = a.pos_base[b];               // < 0: a rejected sequence, which must not touch the cache
-    const int pos = base + j;                     // cache row of node j
+    const int b = a.by_k1(m), j = m - b * (a.k + 1);
+    const int pos = in.base + j;                  // cache row of node j
 #pragma unroll
     for (int e = 0; e < 8; ++e) { v0.v[e] *= rs; v1.v[e] *= rs; }
     if (head < a.nq + a.nkv) {
-        const float *cs = a.rope_cs + ((size_t)a.rope_pos[m] * half + ch) * 2;
-        const Vec8 cs0 = load8(cs), cs1 = load8(cs + 8);   // (cos, sin) of channels ch..ch+3, ch+4..ch+7
         Vec8 y0, y1;
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-            const float co = e < 4 ? cs0.v[2 * e] : cs1.v[2 * (e - 4)], si = e < 4 ? cs0.v[2 * e + 1] : cs1.v[2 * (e - 4) + 1];
+            const float co = e < 4 ? in.cs0.v[2 * e] : in.cs1.v[2 * (e - 4)], si = e < 4 ? in.cs0.v[2 * e + 1] : in.cs1.v[2 * (e - 4) + 1];
             y0.v[e] = v0.v[e] * co - v1.v[e] * si;
             y1.v[e] = v0.v[e] * si + v1.v[e] * co;
         }
         if (head < a.nq) {
-            const int g = a.nq / a.nkv, kvh = head / g, hl = head % g, rr = j * g + hl;
+            const int g = (int)a.by_g.d, kvh = a.by_g(head), hl = head - kvh * g, rr = j * g + hl;
             const size_t qs = ((size_t)b * a.nkv + kvh) * a.q_rows_pad * a.d;
             u32x4 h0, l0, h1, l1;
             split8(y0, h0, l0);
@@ -326,21 +344,26 @@ __device__ __forceinline__ void qkv8(const FusedGemmArgs &a, int m, int head, in
             const size_t i_0 = qs + packed_index(rr, ch, a.d >> 5), i_1 = qs + packed_index(rr, ch + half, a.d >> 5);
             *reinterpret_cast<u32x4 *>(a.Qp + i_0) = h0; *reinterpret_cast<u32x4 *>(a.Qp_lo + i_0) = l0;
             *reinterpret_cast<u32x4 *>(a.Qp + i_1) = h1; *reinterpret_cast<u32x4 *>(a.Qp_lo + i_1) = l1;
-        } else if (base >= 0) {
+        } else if (in.base >= 0) {
             head -= a.nq;
             uint16_t *kk = a.Kc + kv_block_offset(a.kv, kv_page(a.kv, b, pos >> 5), head);
             *reinterpret_cast<u32x4 *>(kk + kblock_index(pos & 31, ch, a.d)) = round8(y0);
             *reinterpret_cast<u32x4 *>(kk + kblock_index(pos & 31, ch + half, a.d)) = round8(y1);
         }
-    } else if (base >= 0) {
+    } else if (in.base >= 0) {
         head -= a.nq + a.nkv;
         uint16_t *vv = a.Vc + kv_block_offset(a.kv, kv_page(a.kv, b, pos >> 5), head);
+        const u32x4 r0 = round8(v0), r1 = round8(v1);
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-            vv[vblock_index(pos & 31, ch + e, a.d)] = f32_to_bf16(v0.v[e]);
-            vv[vblock_index(pos & 31, ch + half + e, a.d)] = f32_to_bf16(v1.v[e]);
+            vv[vblock_index(pos & 31, ch + e, a.d)] = (uint16_t)(r0[e >> 1] >> (e & 1) * 16);
+            vv[vblock_index(pos & 31, ch + half + e, a.d)] = (uint16_t)(r1[e >> 1] >> (e & 1) * 16);
         }
     }
+}
+__device__ __forceinline__ void qkv8(const FusedGemmArgs &a, int m, int head, int ch, float rs, const Vec8 &v0, const Vec8 &v1)
+{
+    qkv8(a, m, head, ch, rs, v0, v1, qkv_in(a, m, head, ch));
 }
 
 // SWIGLU: gate v0, up v1 at columns col..col+7 of the FFN.

@@ -22,8 +22,11 @@ constexpr int HAND_STRIDE = 32, HAND_GROUPS = 256;   // ... groups of a launch a
 constexpr uint32_t HAND_ARRIVE = 1u, HAND_LEAVE = 1u << 8, HAND_SLOW = 1u << 16, HAND_GONE = 1u << 24;
 constexpr int HAND_POLLS = 400;   // 0.6 us each: past every difference between workgroups that start together
 
+constexpr size_t HAND_PARTS = (size_t)40 << 20;
+
 struct Hand {            // of a launch
     uint32_t *words;     // HAND_GROUPS * HAND_STRIDE, or null: no hand-over
+    float *parts;        // HAND_PARTS bytes for what GEMMs hand over: 256 workgroups of ten units of 2 KiB in each of eight waves
     int polls;           // HAND_POLLS, or 0: nobody waits, and most groups go the slow way
 };
 
@@ -39,27 +42,31 @@ __device__ __forceinline__ bool on_own_die()
     return __builtin_amdgcn_s_getreg(20 | 3 << 11) == (blockIdx.x & 7u);   // XCC_ID, 4 bits
 }
 
-// The workgroup's stores so far are part of its group's results; n workgroups form the group.  All threads call it, with an LDS word.
-// Stores count down vmcnt when the die's L2 has them.
-__device__ __forceinline__ HandWay hand_over(const Hand &h, int group, int n, int *way_s)
+// The workgroup's stores so far are part of its group's results; n workgroups form the group.  All threads call both, in turn; what
+// stands between them needs no other workgroup.  Stores count down vmcnt when the die's L2 has them.
+__device__ __forceinline__ uint32_t hand_arrive(const Hand &h, int group)
 {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
+    if (threadIdx.x != 0) return 0;
+    uint32_t *word = h.words + (size_t)group * HAND_STRIDE;
+    if (on_own_die()) return __hip_atomic_fetch_add(word, HAND_ARRIVE, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + HAND_ARRIVE;
+    // not counted in: the others cannot all arrive
+    return __hip_atomic_fetch_or(word, HAND_GONE, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) | HAND_GONE;
+}
+
+__device__ __forceinline__ HandWay hand_wait(const Hand &h, int group, int n, uint32_t seen, int *way_s)
+{
     if (threadIdx.x == 0) {
-        uint32_t *word = h.words + (size_t)group * HAND_STRIDE, seen;
-        if (on_own_die()) {
-            seen = __hip_atomic_fetch_add(word, HAND_ARRIVE, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + HAND_ARRIVE;
-            auto open = [&]() { return (int)(seen & 0xFFu) < n && !(seen & HAND_GONE); };
-            for (int i = 0; i < h.polls && open(); ++i) {
-                __builtin_amdgcn_s_sleep(1);
-                seen = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
-            while (open())   // at most as often as others count themselves in
-                if (__hip_atomic_compare_exchange_strong(word, &seen, seen | HAND_GONE, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
-                    seen |= HAND_GONE;
-        } else {             // not counted: the others cannot all arrive
-            seen = __hip_atomic_fetch_or(word, HAND_GONE, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) | HAND_GONE;
+        uint32_t *word = h.words + (size_t)group * HAND_STRIDE;
+        auto open = [&]() { return (int)(seen & 0xFFu) < n && !(seen & HAND_GONE); };
+        for (int i = 0; i < h.polls && open(); ++i) {
+            __builtin_amdgcn_s_sleep(1);
+            seen = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
+        while (open())   // at most as often as others count themselves in
+            if (__hip_atomic_compare_exchange_strong(word, &seen, seen | HAND_GONE, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+                seen |= HAND_GONE;
         *way_s = seen & HAND_GONE ? HAND_TURN_IN : HAND_SHARE;
     }
     __syncthreads();

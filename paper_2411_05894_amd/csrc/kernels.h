@@ -93,6 +93,9 @@ struct FusedGemmArgs {
     int seg0, seg1;               // tiles of W0 and of W1 in the concatenated output (qgemm16_kernel)
     int upw, J, part_rows, kps;   // filled in by the launcher: units per workgroup, K slices, rows per slice, k-tiles per slice
     int epi;                      // ... epilogue (qgemm16_kernel)
+    Div by_J, by_RB;              // ... K slices, row blocks
+    Div by_k1, by_g;              // QKV, ... rows per sequence, query heads per kv head
+    Hand hand;                    // words and room for slices summed inside the launch, or none (qgemm16_kernel)
     int groups;                   // ... and column groups (M <= 32: the grid is groups * J workgroups)
 };
 // Up to stream_gemm_max_rows() rows some matrices take the persistent weight streamer; NT must be the tile count of W0.

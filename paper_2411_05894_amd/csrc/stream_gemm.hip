@@ -34,6 +34,8 @@
 
 #include <hip/hip_ext.h>
 
+#include <type_traits>
+
 #include "gemm_device.h"
 
 namespace {
@@ -498,20 +500,24 @@ template <int ROWS, int QW> struct RowScales {
 // loads then, not streaming ones).  There the matrix pipes bound everything and two waves share 64 columns, each on half
 // of the rows: half the operand reads per MFMA for a second fetch of the weights from the die's L2 (8B gate/up at 512 rows
 // 235 -> 220 us, but 84 -> 100 us at 160 rows, which are still bound by what a compute unit can fetch).
-template <int MT16, int QW, bool BLOCKS, bool WHOLE> struct QShape {
+// What becomes of a workgroup's sums: they are stored for epi_kernel, they are whole and go through the epilogue here, or they are
+// handed over to the workgroups of the same columns and rows, which share the units of the epilogue out.
+enum QForm { PARTS, WHOLE, DIE };
+template <int MT16, int QW, bool BLOCKS, int FORM> struct QShape {
     static constexpr int QDW = BLOCKS ? 3 : 4;                  // k-tiles in flight
     static constexpr int TILES = MT16 * 2;                      // activation tiles (hi and lo) of one k-tile
     static constexpr int APT = (TILES + QW - 1) / QW;           // tiles fetched per wave; surplus waves re-read the last one
     static constexpr int SLOT = TILES * 64;                     // records of a ring slot
-    static constexpr int RING = QDW * SLOT, STAGE = WHOLE ? QW * 320 : 0;   // records of the ring, of the epilogue's staging area
+    static constexpr int RING = QDW * SLOT, STAGE = FORM == WHOLE ? QW * 320 : (FORM == DIE ? QW * 336 : 0);   // records of the ring, of the epilogue's staging area
     static constexpr int LDS = RING > STAGE ? RING : STAGE;
 };
 
-// Rows 16 * tile0 .. 16 * (tile0 + MT16) - 1; gj: column group and slice.  ring: QDW slots.
-template <int MT16, int QW, bool BLOCKS, bool WHOLE>
-__device__ __forceinline__ void qgemm16_rows(const FusedGemmArgs a, int NT16, int tile0, int gj, u32x4 *lds, float *rstd_s)
+// Rows 16 * tile0 .. 16 * (tile0 + MT16) - 1, column group grp, slice j; set: the group of workgroups that hand over to each other (DIE).
+template <int MT16, int QW, bool BLOCKS, int FORM>
+__device__ __forceinline__ void qgemm16_rows(const FusedGemmArgs a, int NT16, int tile0, int grp, int j, int set, u32x4 *lds, float *rstd_s)
 {
-    using S = QShape<MT16, QW, BLOCKS, WHOLE>;
+    using S = QShape<MT16, QW, BLOCKS, FORM>;
+    constexpr bool PAIRS = FORM != PARTS;    // a wave holds both tiles of an epilogue unit
     u32x4 (*ring)[S::SLOT] = reinterpret_cast<u32x4 (*)[S::SLOT]>(lds);
     constexpr int QDW = S::QDW, TILES = S::TILES, APT = S::APT;
     constexpr bool TWO = BLOCKS || MT16 <= 3;     // sums in two levels, where the registers allow it
@@ -528,9 +534,6 @@ __device__ __forceinline__ void qgemm16_rows(const FusedGemmArgs a, int NT16, in
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int half = wave / CW, cg = wave % CW;
     const int m_base = tile0 * 16;
-    // WHOLE: J is 1, but a value of the launch all the same.  With a k-range known to begin at zero the addresses of the loads in
-    // flight take 8-24 registers more (17..32 rows: spills, 1.03 x the time).
-    const int J = a.J, grp = (int)((unsigned)gj / (unsigned)J), j = gj - grp * J;
     const int KT = a.KT;
     const int kps = a.kps;
     const int kt_begin = j * kps, kt_end = kt_begin + kps < KT ? kt_begin + kps : KT;
@@ -540,7 +543,7 @@ __device__ __forceinline__ void qgemm16_rows(const FusedGemmArgs a, int NT16, in
     const u32x4 *wp[NC];
 #pragma unroll
     for (int ct = 0; ct < NC; ++ct)               // columns past the matrix re-read the last tile, never stored
-        wp[ct] = tile_weights_seg(a, q_tile<WHOLE>(a, c16 + ct < NT16 ? c16 + ct : NT16 - 1)) + lane;
+        wp[ct] = tile_weights_seg(a, q_tile<PAIRS>(a, c16 + ct < NT16 ? c16 + ct : NT16 - 1)) + lane;
     const u32x4 *asrc[APT];
 #pragma unroll
     for (int i = 0; i < APT; ++i) {
@@ -572,15 +575,15 @@ __device__ __forceinline__ void qgemm16_rows(const FusedGemmArgs a, int NT16, in
         for (int i = 0; i < APT; ++i)   // without the padding: at nine tiles and eight waves a quarter of the stores
             if (TILES % QW == 0 || i < APT - 1 || wave + i * QW < TILES) ring[u][(wave + i * QW) * 64 + lane] = apre[u][i];
     };
-    const bool scaled = WHOLE && J == 1 && a.epi != FEPI_RESID && a.epi != FEPI_STORE;
+    const bool scaled = FORM != PARTS && a.epi != FEPI_RESID && a.epi != FEPI_STORE;
     RowScales<16 * MT16, QW> scales;
-    if (scaled) scales.request(a, m_base);
+    if (FORM == WHOLE && scaled) scales.request(a, m_base);
 #pragma unroll
     for (int u = 0; u < QDW; ++u) {
         load_a(u, u);
         load_w(u, u);
     }
-    if (scaled) scales.finish(a, m_base, rstd_s);
+    if (FORM == WHOLE && scaled) scales.finish(a, m_base, rstd_s);
     stage(0);
     __syncthreads();
     const int a_at = half * MTW * 128 + lane;
@@ -663,7 +666,7 @@ __device__ __forceinline__ void qgemm16_rows(const FusedGemmArgs a, int NT16, in
 
     // acc[i][ct][v] of lane l: row 16 * (half * MTW + i) + 4*(l/16) + v, column l%16 of tile q_tile(c16 + ct)
     const int row0 = m_base + 16 * half * MTW;
-    if constexpr (!WHOLE) {
+    if constexpr (FORM == PARTS) {
 #pragma unroll
         for (int ct = 0; ct < NC; ++ct) {
             if (c16 + ct >= NT16) continue;
@@ -677,6 +680,191 @@ __device__ __forceinline__ void qgemm16_rows(const FusedGemmArgs a, int NT16, in
                 }
             }
         }
+        return;
+    }
+    // Epilogue of two units of a wave through its own LDS: 16 lanes of a tile hold a row's columns, the epilogues want eight columns of a row
+    // in a lane.  A row takes 20 floats: the four rows that a store writes together, and the sixteen that a read takes, lie in different
+    // banks.  One sum of squares or maximum per row, group and pair of column tiles.
+    ResidIn rin[2];
+    QkvIn qin;
+    const int qkv_bits = a.d == 128 ? 2 : 1;   // rotary pairs of tiles per head: 4 or 2
+    auto inputs = [&](int i0, int p0, int i1, int p1) {   // requested before the sums are there
+        const int r = lane & 15, kg = lane >> 4;
+        if (a.epi == FEPI_RESID) {
+#pragma unroll
+            for (int ii = 0; ii < 2; ++ii) {
+                const int m = row0 + 16 * (ii ? i1 : i0) + r, col = (c16 + 2 * (ii ? p1 : p0)) * 16 + 8 * kg;
+                rin[ii] = resid_in<false>(a, m < a.M ? m : a.M - 1, col < a.Ntot ? col : 0);
+            }
+        } else if (a.epi == FEPI_QKV) {
+            const int ii = kg >> 1, m = row0 + 16 * (ii ? i1 : i0) + r, unit = (c16 >> 1) + (ii ? p1 : p0);
+            const bool live = m < a.M && 2 * unit < NT16;
+            qin = qkv_in(a, live ? m : 0, live ? unit >> qkv_bits : 0, live ? (unit & ((1 << qkv_bits) - 1)) * 16 + 8 * (kg & 1) : 0);
+        }
+    };
+    auto finish = [&](int i0, int p0, int i1, int p1, bool both, const f32x4 (&sum)[2][2]) {
+        float *mine = reinterpret_cast<float *>(lds + wave * 320);
+        const float *scale = rstd_s + 16 * half * MTW;
+        const int r = lane & 15, kg = lane >> 4;
+#pragma unroll
+        for (int ii = 0; ii < 2; ++ii)
+#pragma unroll
+            for (int part = 0; part < 2; ++part)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) mine[((part * 2 + ii) * 16 + 4 * kg + v) * 20 + r] = sum[ii][part][v];
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        if (a.epi == FEPI_QKV || a.epi == FEPI_SWIGLU) {   // two tiles make one of 16 columns: lanes of kg 0 and 1 take the first unit
+            const int ii = kg >> 1, i = ii ? i1 : i0, p = ii ? p1 : p0, m = row0 + 16 * i + r, unit = (c16 >> 1) + p;
+            if (m < a.M && 2 * unit < NT16 && (both || !ii)) {
+                const Vec8 v0 = load8(mine + (ii * 16 + r) * 20 + 8 * (kg & 1)), v1 = load8(mine + ((2 + ii) * 16 + r) * 20 + 8 * (kg & 1));
+                const float rs = scale[16 * i + r];
+                if (a.epi == FEPI_SWIGLU) {
+                    swiglu8(a, m, unit * 16 + 8 * (kg & 1), rs, v0, v1);
+                } else {
+                    qkv8(a, m, unit >> qkv_bits, (unit & ((1 << qkv_bits) - 1)) * 16 + 8 * (kg & 1), rs, v0, v1, qin);
+                }
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            return;
+        }
+        float ss[2] = {0.f, 0.f};
+        Best best[2] = {Best::none(), Best::none()};
+#pragma unroll
+        for (int ii = 0; ii < 2; ++ii) {
+            const int i = ii ? i1 : i0, p = ii ? p1 : p0, m = row0 + 16 * i + r, col = (c16 + 2 * p) * 16 + 8 * kg;
+            if (m >= a.M || col >= a.Ntot || (ii && !both)) continue;
+            const Vec8 v0 = load8(mine + ((kg >> 1) * 32 + ii * 16 + r) * 20 + 8 * (kg & 1));
+            if (a.epi == FEPI_RESID) ss[ii] = resid8<false>(a, m, col, v0, rin[ii]);
+            else if (a.epi == FEPI_LM) lm8(a, m, col, scale[16 * i + r], v0, best[ii]);
+            else store8(a.out + (size_t)m * a.Ntot + col, v0);
+        }
+        if (a.epi != FEPI_RESID && a.epi != FEPI_LM) {
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            return;
+        }
+        float2 (*const row_s)[32] = reinterpret_cast<float2 (*)[32]>(lds + QW * 320);   // [wave][unit, row]
+        const bool lm = a.epi == FEPI_LM;
+#pragma unroll
+        for (int ii = 0; ii < 2; ++ii) {
+            if (lm) {
+                best[ii].across(16);
+                best[ii].across(32);
+            } else {
+                ss[ii] += __shfl_xor(ss[ii], 16);
+                ss[ii] += __shfl_xor(ss[ii], 32);
+            }
+            if (kg == 0) row_s[wave][ii * 16 + r] = lm ? float2{best[ii].v, __int_as_float(best[ii].i)} : float2{ss[ii], 0.f};
+        }
+        __syncthreads();
+        if (threadIdx.x < 32 * RH) {
+            const int h = threadIdx.x >> 5, ii = threadIdx.x >> 4 & 1, i = ii ? i1 : i0, p = ii ? p1 : p0;
+            const int m = m_base + 16 * (h * MTW + i) + (threadIdx.x & 15);
+            const size_t at = (size_t)m * (lm ? a.n_part : a.nss_out) + grp * (NC / 2) + p;
+            if (m < a.M && (both || !ii)) {
+                if (lm) {
+                    Best all = Best::none();
+#pragma unroll
+                    for (int x = 0; x < CW; ++x) {
+                        const float2 y = row_s[h * CW + x][threadIdx.x & 31];
+                        all.take(y.x, __float_as_int(y.y));
+                    }
+                    a.part_val[at] = all.v;
+                    a.part_idx[at] = all.i;
+                } else {
+                    float all = 0.f;
+#pragma unroll
+                    for (int x = 0; x < CW; ++x) all += row_s[h * CW + x][threadIdx.x & 31].x;
+                    a.ssq_out[at] = all;
+                }
+            }
+        }
+        __syncthreads();
+    };
+    if constexpr (FORM == DIE) {
+        // A unit is a wave's pair of column tiles on one row tile, v = row tile * NP + pair; unit v belongs to slice v modulo J.  The
+        // others' units are stored as the lanes hold them, its own stay in registers until the other slices of them have arrived.
+        constexpr int NP = NC / 2, UW = MTW * NP, ROOM = BLOCKS ? 8 : UW;   // units, room for them (blocks of eight and six tiles mix)
+        const int J = a.J;
+        float *const slot = a.hand.parts + ((size_t)set * J + j) * (QW * ROOM * 512) + wave * (ROOM * 512) + lane * 4;
+        auto put = [&](bool own) {
+            int o = 0;
+#pragma unroll
+            for (int v = 0; v < UW; ++v) {
+                if ((o == j) == own) {
+                    *reinterpret_cast<f32x4 *>(slot + v * 512) = acc[v / NP][v % NP * 2];
+                    *reinterpret_cast<f32x4 *>(slot + v * 512 + 256) = acc[v / NP][v % NP * 2 + 1];
+                }
+                if (++o == J) o = 0;
+            }
+        };
+        put(false);
+        const uint32_t seen = hand_arrive(a.hand, set);
+        if (scaled) {
+            scales.request(a, m_base);
+            scales.finish(a, m_base, rstd_s);   // published by the barrier of hand_wait
+        }
+        if (j < UW) inputs(j / NP, j % NP, (j + J < UW ? j + J : j) / NP, (j + J < UW ? j + J : j) % NP);   // of the first two units of its share
+        int *way_s = reinterpret_cast<int *>(rstd_s + 16 * MT16);
+        HandWay way = hand_wait(a.hand, set, J, seen, way_s);
+        uint32_t left = way == HAND_SHARE ? hand_leave(a.hand, set) : 0;
+        if (way == HAND_TURN_IN) {
+            put(true);
+            way = hand_turn_in(a.hand, set, J, way_s);
+        }
+        if (way != HAND_NOTHING) {
+            const DieBuffer parts(a.hand.parts + (size_t)set * J * (QW * ROOM * 512), (size_t)J * (QW * ROOM * 2048));
+            constexpr int SLICE = QW * ROOM * 2048;   // bytes
+            const int at = wave * (ROOM * 2048) + lane * 16, step = way == HAND_ALL ? 1 : J;
+            // Two units at a time, v0 and v0 + step, with up to NB slices of each in flight, or one with twice as many.
+            constexpr int NB = MT16 >= 10 && QW == 8 ? 3 : 4;
+            auto add_slices = [&](auto units, int v0, int v1, int o0, int o1, f32x4 (&sum)[2][2]) {
+                constexpr int U = decltype(units)::value, N = NB * 2 / U;
+                for (int n0 = 0; n0 < J - 1; n0 += N) {
+                    f32x4 t[N][U][2];
+#pragma unroll
+                    for (int n = 0; n < N; ++n)
+                        if (n0 + n < J - 1)
+#pragma unroll
+                            for (int part = 0; part < 2; ++part) {
+                                t[n][0][part] = parts.load4(at, (n0 + n + (n0 + n >= o0)) * SLICE + v0 * 2048 + part * 1024);
+                                if (U == 2) t[n][U - 1][part] = parts.load4(at, (n0 + n + (n0 + n >= o1)) * SLICE + v1 * 2048 + part * 1024);
+                            }
+#pragma unroll
+                    for (int n = 0; n < N; ++n)
+                        if (n0 + n < J - 1)
+#pragma unroll
+                            for (int ii = 0; ii < U; ++ii)
+#pragma unroll
+                                for (int part = 0; part < 2; ++part) sum[ii][part] += t[n][ii][part];
+                }
+            };
+            for (int v0 = way == HAND_ALL ? 0 : j; v0 < UW; v0 += 2 * step) {
+                const int v1 = v0 + step < UW ? v0 + step : v0;
+                f32x4 sum[2][2];
+                if (way == HAND_ALL || v0 != j) inputs(v0 / NP, v0 % NP, v1 / NP, v1 % NP);
+                if (way == HAND_ALL) {   // from memory, in the order in which the owner would have added
+#pragma unroll
+                    for (int ii = 0; ii < 2; ++ii)
+#pragma unroll
+                        for (int part = 0; part < 2; ++part) {
+                            const int v = ii ? v1 : v0;
+                            sum[ii][part] = parts.load4(at + v % J * SLICE + v * 2048 + part * 1024);
+                        }
+                } else {
+#pragma unroll
+                    for (int v = 0; v < UW; ++v) {
+                        if (v == v0) { sum[0][0] = acc[v / NP][v % NP * 2]; sum[0][1] = acc[v / NP][v % NP * 2 + 1]; }
+                        if (v == v1) { sum[1][0] = acc[v / NP][v % NP * 2]; sum[1][1] = acc[v / NP][v % NP * 2 + 1]; }
+                    }
+                }
+                const int o0 = way == HAND_ALL ? v0 % J : j, o1 = way == HAND_ALL ? v1 % J : j;
+                if (v1 != v0) add_slices(std::integral_constant<int, 2>{}, v0, v1, o0, o1, sum);
+                else add_slices(std::integral_constant<int, 1>{}, v0, v1, o0, o1, sum);
+                finish(v0 / NP, v0 % NP, v1 / NP, v1 % NP, v1 != v0, sum);
+            }
+        }
+        if (way != HAND_SHARE) left = hand_leave(a.hand, set);
+        hand_clear(a.hand, set, J, left);
         return;
     }
     __syncthreads();   // the ring has been read
@@ -754,30 +942,43 @@ __device__ __forceinline__ void qgemm16_rows(const FusedGemmArgs a, int NT16, in
 
 // BLOCKS: RB blocks of rows, of MT16 tiles, or (MT16 = 0) the first n8 of eight tiles and the others of six.  Blocks of one
 // size have kernels of their own: in the mixed one they are 2 % slower.
-template <int MT16, int QW, bool BLOCKS, bool WHOLE>
+template <int MT16, int QW, bool BLOCKS, int FORM>
 // Registers: two workgroups of four waves per compute unit up to nine tiles (tiny shape with a vocabulary of 128256, 144 rows:
 // 276 registers and one workgroup 69 us, 256 and two 66), which at three tiles costs more than it gives (8B gate/up at 33 rows
 // 44.4 -> 45.2); four waves per SIMD up to two tiles.
-__global__ __launch_bounds__(QW * 64) __attribute__((amdgpu_waves_per_eu(!BLOCKS && MT16 <= 2 ? 4 : (QW == 4 && MT16 >= 4 && MT16 <= 9 ? 2 : 1)))) void qgemm16_kernel(FusedGemmArgs a, int RB, int n8, int NT16, int pairs)
+__global__ __launch_bounds__(QW * 64) __attribute__((amdgpu_waves_per_eu(FORM == DIE ? 1 : (!BLOCKS && MT16 <= 2 ? 4 : (QW == 4 && MT16 >= 4 && MT16 <= 9 ? 2 : 1))))) void qgemm16_kernel(FusedGemmArgs a, int RB, int n8, int NT16, int pairs)
 {
-    if constexpr (BLOCKS) {
-        using S = QShape<MT16 ? MT16 : 8, QW, true, WHOLE>;
-        __shared__ u32x4 lds[S::LDS];
-        __shared__ float rstd_s[WHOLE ? 16 * (MT16 ? MT16 : 8) : 1];
-        const int bid = blockIdx.x, whole = pairs & ~7;   // (column group, slice) pairs; those in full sets of 8
-        const bool in_set = bid < whole * RB;
-        const int x = in_set ? bid >> 3 : bid - whole * RB, by = in_set ? RB : pairs - whole;
-        const int q = (int)((unsigned)x / (unsigned)by), r = x - q * by;
-        const int rb = in_set ? r : q, gj = in_set ? q * 8 + (bid & 7) : whole + r;
-        if constexpr (MT16 != 0) qgemm16_rows<MT16, QW, true, WHOLE>(a, NT16, MT16 * rb, gj, lds, rstd_s);
-        else if (rb < n8) qgemm16_rows<8, QW, true, WHOLE>(a, NT16, 8 * rb, gj, lds, rstd_s);
-        else qgemm16_rows<6, QW, true, WHOLE>(a, NT16, 8 * n8 + 6 * (rb - n8), gj, lds, rstd_s);
+    constexpr int MOST = MT16 ? MT16 : 8;   // row tiles of a workgroup at most
+    __shared__ u32x4 lds[QShape<MOST, QW, BLOCKS, FORM>::LDS];
+    __shared__ float rstd_s[FORM == PARTS ? 1 : 16 * MOST + 1];   // ... and a word for the hand-over
+    const int bid = blockIdx.x;
+    int rb = 0, grp, j, set = 0;
+    if constexpr (FORM == DIE) {   // `pairs` column groups; on each die every eighth of them, with its slices and their row blocks side by side
+        const int slot = bid >> 3, x = BLOCKS ? a.by_RB(slot) : slot, local = a.by_J(x);
+        rb = slot - x * (BLOCKS ? RB : 1);
+        j = x - local * a.J;
+        grp = local * 8 + (bid & 7);
+        if (grp >= pairs) return;
+        set = grp * (BLOCKS ? RB : 1) + rb;
     } else {
-        using S = QShape<MT16, QW, false, WHOLE>;
-        __shared__ u32x4 lds[S::LDS];
-        __shared__ float rstd_s[WHOLE ? 16 * MT16 : 1];
-        qgemm16_rows<MT16, QW, false, WHOLE>(a, NT16, 0, blockIdx.x, lds, rstd_s);
+        int gj = bid;
+        if constexpr (BLOCKS) {
+            const int whole = pairs & ~7;   // (column group, slice) pairs; those in full sets of 8
+            const bool in_set = bid < whole * RB;
+            const int x = in_set ? bid >> 3 : bid - whole * RB, by = in_set ? RB : pairs - whole;
+            const int q = (int)((unsigned)x / (unsigned)by), r = x - q * by;
+            rb = in_set ? r : q;
+            gj = in_set ? q * 8 + (bid & 7) : whole + r;
+        }
+        // WHOLE: J is 1, but a value of the launch all the same.  With a k-range known to begin at zero the addresses of the loads in
+        // flight take 8-24 registers more (17..32 rows: spills, 1.03 x the time).
+        grp = (int)((unsigned)gj / (unsigned)a.J);
+        j = gj - grp * a.J;
     }
+    if constexpr (!BLOCKS) qgemm16_rows<MT16, QW, false, FORM>(a, NT16, 0, grp, j, set, lds, rstd_s);
+    else if constexpr (MT16 != 0) qgemm16_rows<MT16, QW, true, FORM>(a, NT16, MT16 * rb, grp, j, set, lds, rstd_s);
+    else if (rb < n8) qgemm16_rows<8, QW, true, FORM>(a, NT16, 8 * rb, grp, j, set, lds, rstd_s);
+    else qgemm16_rows<6, QW, true, FORM>(a, NT16, 8 * n8 + 6 * (rb - n8), grp, j, set, lds, rstd_s);
 }
 
 // Row blocks of a launch: one of up to ten tiles, more of eight (the sums in two levels leave no registers for more), as many
@@ -877,28 +1078,49 @@ __host__ bool is_small(int M, int Ntot, int K)
     return (size_t)q_plan(Ntot, K, M).J * round_up(M, 16) * Ntot * sizeof(float) > SMALL_SCRATCH;
 }
 
+// The same split for slices that are summed inside the launch: one workgroup per compute unit (they wait for each other), the slices of
+// a column group on one die.  False, and the plan as it was, where that leaves no split.
+__host__ bool die_plan(QPlan &p, int KT, int RB, const Hand &hand)
+{
+    if (!hand.words) return false;
+    const int per_die = (p.groups + 7) / 8 * RB;   // workgroups of a die for one slice
+    int J = 32 / per_die;
+    if (J > KT / 8) J = KT / 8;
+    if (J > 16) J = 16;
+    if (RB > 1 && J > p.J) J = p.J;
+    if (J < 2 || round_up(p.groups, 8) * RB > HAND_GROUPS) return false;
+    p.kps = (KT + J - 1) / J;
+    p.J = (KT + p.kps - 1) / p.kps;
+    return true;
+}
+
 template <int EPI> hipError_t launch_large(FusedGemmArgs &a, hipStream_t s, bool *needs_epilogue, hipEvent_t t0, hipEvent_t t1)
 {
     const int NT16 = a.Ntot / 16;
-    const QPlan p = q_plan(a.Ntot, a.KT * 32, a.M);
+    QPlan p = q_plan(a.Ntot, a.KT * 32, a.M);
+    const int mt16 = (a.M + 15) / 16;
+    const RowBlocks rows = row_blocks(mt16);
+    const bool die = p.J > 1 && die_plan(p, a.KT, rows.RB, a.hand);
     a.J = p.J;
     a.kps = p.kps;
+    a.by_J = Div(p.J);
+    a.by_RB = Div(rows.RB);
     a.part_rows = round_up(a.M, 16);
     a.epi = EPI;
-    a.nss_out = a.h >> 4;
-    a.n_part = p.groups;
-    *needs_epilogue = a.J > 1;   // an unsplit K: the kernel applies the epilogue itself
+    const int halves = rows.RB > 1 ? 2 : 1;   // pairs of column tiles per wave
+    a.nss_out = die ? p.groups * halves : a.h >> 4;
+    a.n_part = die ? p.groups * halves : p.groups;
+    *needs_epilogue = a.J > 1 && !die;   // an unsplit K: the kernel applies the epilogue itself
     if (EPI == FEPI_QKV) { a.seg0 = a.nq * (a.d >> 4); a.seg1 = a.nkv * (a.d >> 4); }
     else if (EPI == FEPI_SWIGLU) { a.seg0 = a.NT; a.seg1 = a.NT; }
     else { a.seg0 = NT16; a.seg1 = 0; }
-    if (a.J > 1 && (size_t)a.J * a.part_rows * a.Ntot * sizeof(float) > a.partial_bytes) return hipErrorInvalidValue;
-    const int mt16 = (a.M + 15) / 16;
-    const RowBlocks rows = row_blocks(mt16);
-    const dim3 grid(p.groups * a.J * rows.RB), block(p.qw * 64);
+    if (*needs_epilogue && (size_t)a.J * a.part_rows * a.Ntot * sizeof(float) > a.partial_bytes) return hipErrorInvalidValue;
+    const dim3 grid((die ? round_up(p.groups, 8) : p.groups) * a.J * rows.RB), block(p.qw * 64);
 #define SSSD_Q16LAUNCH(MT, QW, BLOCKS)                                                                                                          \
     do {                                                                                                                                        \
-        if (a.J == 1) hipExtLaunchKernelGGL((qgemm16_kernel<MT, QW, BLOCKS, true>), grid, block, 0, s, t0, t1, 0, a, rows.RB, rows.n8, NT16, p.groups); \
-        else hipExtLaunchKernelGGL((qgemm16_kernel<MT, QW, BLOCKS, false>), grid, block, 0, s, t0, t1, 0, a, rows.RB, rows.n8, NT16, p.groups * a.J);   \
+        if (die) hipExtLaunchKernelGGL((qgemm16_kernel<MT, QW, BLOCKS, DIE>), grid, block, 0, s, t0, t1, 0, a, rows.RB, rows.n8, NT16, p.groups); \
+        else if (a.J == 1) hipExtLaunchKernelGGL((qgemm16_kernel<MT, QW, BLOCKS, WHOLE>), grid, block, 0, s, t0, t1, 0, a, rows.RB, rows.n8, NT16, p.groups); \
+        else hipExtLaunchKernelGGL((qgemm16_kernel<MT, QW, BLOCKS, PARTS>), grid, block, 0, s, t0, t1, 0, a, rows.RB, rows.n8, NT16, p.groups * a.J);   \
     } while (0)
 #define SSSD_Q16ROWS(MT)                                  \
     do {                                                  \
@@ -1051,6 +1273,10 @@ size_t stream_gemm_scratch_bytes(int M, int N, int K)
 hipError_t launch_stream_gemm(FusedGemmArgs &a, int epilogue, hipStream_t s, bool *needs_epilogue, hipEvent_t t0,
                               hipEvent_t t1)
 {
+    if (epilogue == FEPI_QKV) {
+        a.by_k1 = Div(a.k + 1);
+        a.by_g = Div(a.nq / a.nkv);
+    }
     if (!is_small(a.M, a.Ntot, a.KT * 32)) {
         switch (epilogue) {
         case FEPI_QKV: return launch_large<FEPI_QKV>(a, s, needs_epilogue, t0, t1);

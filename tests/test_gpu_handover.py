@@ -1,13 +1,16 @@
 """Partial results handed over between the workgroups of one launch (one die's workgroups share its L2).  A context created with
 SSSD_NO_WAIT never waits for the others, so its last workgroups do whole groups' work: the way taken when workgroups do not arrive in
 time.  Both ways must give the reference and the same bits, launch after launch (the words between them are zero again)."""
+from types import SimpleNamespace
+
 import pytest
 import torch
 
 pytestmark = pytest.mark.gpu
 
+from harness import Pair, compare_step, gen_weights
 from paper_2411_05894_amd import binding as sv
-from sssd_synth import MODEL_SHAPES, global_weight_specs, layer_weight_specs, normal_bf16
+from sssd_synth import MODEL_SHAPES, global_weight_specs, layer_weight_specs, normal_bf16, uniform_int
 from test_gpu_attention_segments import reference
 
 DEV = "cuda:0"
@@ -50,3 +53,40 @@ def test_attention_merged_inside_the_launch(shape_name, k, lens, max_seq):
         assert (got[b] - reference(q[b], *kv[b], lens[b], s.n_q_heads // s.n_kv_heads)).abs().max().item() <= 1e-4, b
     for o in outs[1:]:
         assert torch.equal(o, outs[0])
+
+
+# K in two slices and more everywhere but in the QKV and gate/up projections of the smaller model: 24 and 65 k-tiles (slices of unequal
+# length), units of one to ten row tiles shared out over as few as two and as many as eight slices, blocks of eight and six row tiles, column groups
+# that end inside the matrix, more slices than units; an LM head of few columns
+@pytest.mark.parametrize("hidden,nq,nkv,d,ffn,vocab", [(768, 6, 2, 128, 2064, 1040), (528, 4, 4, 64, 1120, 4112)])
+@pytest.mark.parametrize("B,k", [(3, 10), (6, 7), (5, 12), (7, 13), (9, 12), (9, 15), (5, 31), (7, 25), (11, 28), (16, 31)])   # 33 .. 512 rows
+def test_split_gemms_summed_inside_the_launch(hidden, nq, nkv, d, ffn, vocab, B, k):
+    s = SimpleNamespace(name="edge", n_layers=2, hidden=hidden, n_q_heads=nq, n_kv_heads=nkv, head_dim=d, ffn=ffn, vocab=vocab, rms_eps=1e-5,
+                        rope_base=10000.0)
+    p = Pair(s, seed=61, max_batch=B, max_k=k, max_seq=96, unit_gains=False)
+    late = Pair(s, seed=61, max_batch=B, max_k=k, max_seq=96, unit_gains=False, oracle_batch=1)
+    late.ctx.sssd_verify_destroy()
+    layers, g = gen_weights(s, 61, late.dev, False)
+    late.ctx = sv.VerifyContext(late.cfg, layers, g, no_wait=True)
+    late.ctx.sssd_debug_outputs(late.logits, late.hidden)
+    late.ctx.sssd_debug_argmax(late.that)
+    lens = uniform_int(62, B * 64 + k, (B,), 0, 96 - k - 1).to(torch.int32)
+    for b in range(B):
+        p.prefill_random_kv(63, b, int(lens[b]), oracle_slot=b)
+        late.prefill_random_kv(63, b, int(lens[b]))
+    tokens = uniform_int(64, B * 64 + k, (B, k + 1), 0, s.vocab - 1)
+    ref = p.oracle.verify_step(tokens, lens, return_hidden=True)
+    first = None
+    for pair in (p, late):
+        print(f"hand-over step h={hidden} ffn={ffn} B={B} k={k} no_wait={pair is late}", flush=True)
+        for i in range(4):
+            pair.logits.fill_(-1.0)
+            got = pair.step(tokens, lens)
+            if first is None:
+                first = got
+                compare_step(got, ref, tokens)
+                herr = (got["hidden"] - ref["hidden"]).abs().max().item() / ref["hidden"].abs().max().item()
+                assert herr < 5e-3   # a bf16 rounding of a new K or V element may fall the other way: 2^-9 of it
+            for name in ("logits", "hidden", "that", "accepted_len", "next_token"):
+                assert torch.equal(got[name], first[name]), (name, i, pair is late)
+        pair.ctx.sssd_verify_destroy()
