@@ -393,4 +393,113 @@ __device__ __forceinline__ void lm8(const FusedGemmArgs &a, int m, int n0, float
     if (a.logits) store8(a.logits + (size_t)m * a.vocab + n0, v0);
 }
 
+// ---- four columns per lane ----
+// qgemm16_kernel multiplies weights x activations, so a lane holds columns 4*(l/16)..+3 of row l%16 of every 16 x 16 tile: the
+// epilogues below work on the accumulators as they are.  What they read from memory can be requested ahead.
+struct QuadIn {
+    f32x4 x0, x1;       // RESID: residual of both tiles; QKV: (cos, sin) of channels 0, 1 and of 2, 3
+    uint2 g0, g1;       // RESID: gains of both tiles
+    int base;           // QKV: cache row of the sequence's first node; < 0: a rejected sequence, which must not touch the cache
+};
+
+__device__ __forceinline__ f32x4 load4(const float *p) { return *reinterpret_cast<const f32x4 *>(p); }
+__device__ __forceinline__ void split4(const f32x4 &x, uint2 &hi, uint2 &lo)
+{
+    split_bf16x2(x[0], x[1], hi.x, lo.x);
+    split_bf16x2(x[2], x[3], hi.y, lo.y);
+}
+__device__ __forceinline__ uint2 round4(const f32x4 &x) { return uint2{pack_bf16x2(x[0], x[1]), pack_bf16x2(x[2], x[3])}; }
+
+// Lanes kg and kg + 1 (16 apart, kg even) hold columns 0..3 and 4..7 of one 16-byte record: returns, to the first, the record of x,
+// to the second that of y, and stores them at p and q.  Stored by halves, every line would be written twice.
+__device__ __forceinline__ void store_records(uint16_t *p, uint16_t *q, const uint2 &x, const uint2 &y, bool first)
+{
+    const auto a = __builtin_amdgcn_permlane16_swap(x.x, y.x, false, false), b = __builtin_amdgcn_permlane16_swap(x.y, y.y, false, false);
+    *reinterpret_cast<u32x4 *>(first ? p : q) = u32x4{a[0], b[0], a[1], b[1]};
+}
+
+// Sum over the four lanes 16 apart that share a row, in each of them.
+__device__ __forceinline__ float row_sum4(float x)
+{
+    auto h = __builtin_amdgcn_permlane16_swap(f32_bits(x), f32_bits(x), false, false);
+    x = bits_f32(h[0]) + bits_f32(h[1]);
+    h = __builtin_amdgcn_permlane32_swap(f32_bits(x), f32_bits(x), false, false);
+    return bits_f32(h[0]) + bits_f32(h[1]);
+}
+
+// RESID: X += v, packed X * gamma at columns col..col+3 of row m.  Returns the sum of squares of the updated columns.
+// (m, col / 8) are the same in the two lanes of a pair, and both call it: so with all below.
+__device__ __forceinline__ float resid4(const FusedGemmArgs &a, int m, int col, const f32x4 &v, const f32x4 &x, const uint2 &gamma)
+{
+    const f32x4 xn = x + v;
+    const f32x4 g = {bits_f32(gamma.x << 16), bits_f32(gamma.x & 0xFFFF0000u), bits_f32(gamma.y << 16), bits_f32(gamma.y & 0xFFFF0000u)};
+    *reinterpret_cast<f32x4 *>(a.X + (size_t)m * a.h + col) = xn;
+    uint2 hi, lo;
+    split4(xn * g, hi, lo);
+    const size_t idx = packed_index(m, col & ~7, (a.h + 31) >> 5);
+    store_records(a.out_hi + idx, a.out_lo + idx, hi, lo, !(col & 4));
+    return (xn[0] * xn[0] + xn[1] * xn[1]) + (xn[2] * xn[2] + xn[3] * xn[3]);
+}
+
+// QKV: v0 at channels ch..ch+3 of the first half of a head, v1 at the same channels of the second half.
+__device__ __forceinline__ void qkv4(const FusedGemmArgs &a, int m, int head, int ch, float rs, f32x4 v0, f32x4 v1, const QuadIn &in)
+{
+    const int half = a.d >> 1;
+    const int b = a.by_k1(m), j = m - b * (a.k + 1);
+    const int pos = in.base + j;                  // cache row of node j
+    v0 *= rs;
+    v1 *= rs;
+    if (head < a.nq + a.nkv) {
+        const f32x4 co = {in.x0[0], in.x0[2], in.x1[0], in.x1[2]}, si = {in.x0[1], in.x0[3], in.x1[1], in.x1[3]};
+        const f32x4 y0 = v0 * co - v1 * si, y1 = v0 * si + v1 * co;
+        if (head < a.nq) {
+            const int g = (int)a.by_g.d, kvh = a.by_g(head), hl = head - kvh * g, rr = j * g + hl;
+            const size_t qs = ((size_t)b * a.nkv + kvh) * a.q_rows_pad * a.d;
+            uint2 h0, l0, h1, l1;
+            split4(y0, h0, l0);
+            split4(y1, h1, l1);
+            const size_t i_0 = qs + packed_index(rr, ch & ~7, a.d >> 5), i_1 = qs + packed_index(rr, (ch & ~7) + half, a.d >> 5);
+            store_records(a.Qp + i_0, a.Qp_lo + i_0, h0, l0, !(ch & 4));
+            store_records(a.Qp + i_1, a.Qp_lo + i_1, h1, l1, !(ch & 4));
+        } else if (in.base >= 0) {
+            head -= a.nq;
+            uint16_t *kk = a.Kc + kv_block_offset(a.kv, kv_page(a.kv, b, pos >> 5), head);
+            store_records(kk + kblock_index(pos & 31, ch & ~7, a.d), kk + kblock_index(pos & 31, (ch & ~7) + half, a.d), round4(y0), round4(y1), !(ch & 4));
+        }
+    } else if (in.base >= 0) {
+        head -= a.nq + a.nkv;
+        uint16_t *vv = a.Vc + kv_block_offset(a.kv, kv_page(a.kv, b, pos >> 5), head);
+        const uint2 r0 = round4(v0), r1 = round4(v1);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            vv[vblock_index(pos & 31, ch + e, a.d)] = (uint16_t)((e < 2 ? r0.x : r0.y) >> (e & 1) * 16);
+            vv[vblock_index(pos & 31, ch + half + e, a.d)] = (uint16_t)((e < 2 ? r1.x : r1.y) >> (e & 1) * 16);
+        }
+    }
+}
+
+// SWIGLU: gate v0, up v1 at columns col..col+3 of the FFN.
+__device__ __forceinline__ void swiglu4(const FusedGemmArgs &a, int m, int col, float rs, const f32x4 &v0, const f32x4 &v1)
+{
+    f32x4 hv;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const float gg = v0[e] * rs;
+        hv[e] = gg * __builtin_amdgcn_rcpf(1.f + __expf(-gg)) * (v1[e] * rs);   // the reciprocal to one unit in the last place, as the exponential
+    }
+    uint2 hi, lo;
+    split4(hv, hi, lo);
+    const size_t idx = packed_index(m, col & ~7, a.KT_out);
+    store_records(a.out_hi + idx, a.out_lo + idx, hi, lo, !(col & 4));
+}
+
+// LM: logits (if asked for), and columns n0..n0+3 of row m into the row's running arg-max.
+__device__ __forceinline__ void lm4(const FusedGemmArgs &a, int m, int n0, float rs, f32x4 v, Best &best)
+{
+    v *= rs;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) best.take(v[e], n0 + e);
+    if (a.logits) *reinterpret_cast<f32x4 *>(a.logits + (size_t)m * a.vocab + n0) = v;
+}
+
 }  // namespace

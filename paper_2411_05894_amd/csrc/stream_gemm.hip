@@ -432,16 +432,16 @@ template <int ROWS, int QW> struct RowScales {
     static constexpr int TURNS = ROWS / (4 * QW) + (ROWS % (4 * QW) != 0);   // rows per lane
     static constexpr int U = TURNS > 4 ? 4 : 16 / TURNS;                     // sums per lane and row in flight
     float v[TURNS][U];
-    __device__ __forceinline__ void load(const FusedGemmArgs &a, int m0, int t0)
+    __device__ __forceinline__ void load(const float *sums, int n, int M, int m0, int t0)
     {
 #pragma unroll
         for (int i = 0; i < TURNS; ++i) {
             const int m = m0 + (threadIdx.x >> 4) + i * 4 * QW;
-            const float *p = a.ssq_in + (size_t)(m < a.M ? m : a.M - 1) * a.nss_in;
+            const float *p = sums + (size_t)(m < M ? m : M - 1) * n;
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 const int t = t0 + (threadIdx.x & 15) + 16 * u;
-                v[i][u] = p[t < a.nss_in ? t : 0];
+                v[i][u] = p[t < n ? t : 0];
             }
         }
     }
@@ -452,7 +452,12 @@ template <int ROWS, int QW> struct RowScales {
 #pragma unroll
             for (int u = 0; u < U; ++u) sum[i] += t0 + (int)(threadIdx.x & 15) + 16 * u < a.nss_in ? v[i][u] : 0.f;
     }
-    __device__ __forceinline__ void request(const FusedGemmArgs &a, int m0) { load(a, m0, 0); }
+    // Without `scaled` (no sums to read) it loads activations for nothing: under a branch the first sum, and so the wait for it, comes
+    // before the first operands are requested (1 us of 1B..70B gate/up launches).
+    __device__ __forceinline__ void request(const FusedGemmArgs &a, int m0, bool scaled)
+    {
+        load(scaled ? a.ssq_in : reinterpret_cast<const float *>(a.A_hi), scaled ? a.nss_in : 1, a.M, m0, 0);
+    }
     __device__ __forceinline__ void finish(const FusedGemmArgs &a, int m0, float *rstd_s)
     {
         float sum[TURNS];
@@ -460,7 +465,7 @@ template <int ROWS, int QW> struct RowScales {
         for (int i = 0; i < TURNS; ++i) sum[i] = 0.f;
         add(a, 0, sum);
         for (int t0 = 16 * U; t0 < a.nss_in; t0 += 16 * U) {
-            load(a, m0, t0);
+            load(a.ssq_in, a.nss_in, a.M, m0, t0);
             add(a, t0, sum);
         }
 #pragma unroll
@@ -508,9 +513,37 @@ template <int MT16, int QW, bool BLOCKS, int FORM> struct QShape {
     static constexpr int TILES = MT16 * 2;                      // activation tiles (hi and lo) of one k-tile
     static constexpr int APT = (TILES + QW - 1) / QW;           // tiles fetched per wave; surplus waves re-read the last one
     static constexpr int SLOT = TILES * 64;                     // records of a ring slot
-    static constexpr int RING = QDW * SLOT, STAGE = FORM == WHOLE ? QW * 320 : (FORM == DIE ? QW * 336 : 0);   // records of the ring, of the epilogue's staging area
+    static constexpr int RING = QDW * SLOT, STAGE = FORM == PARTS ? 0 : QW * 8 * (FORM == DIE ? MT16 : MT16 / (BLOCKS ? 2 : 1));   // records of the ring, of the waves' row sums or maxima
     static constexpr int LDS = RING > STAGE ? RING : STAGE;
 };
+
+// What the epilogues read of the launch's first argument, loaded where it is called: loaded in front of the main loop, as the compiler does
+// by itself, these sixty scalars are moved into vector registers and back (130 instructions in front of the first load).
+__device__ __forceinline__ FusedGemmArgs epilogue_arguments()
+{
+    using Constant = const __attribute__((address_space(4))) FusedGemmArgs;
+    Constant *p = (Constant *)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));   // not before
+    FusedGemmArgs e{};
+#define SSSD_VALUE(f) e.f = p->f
+#define SSSD_POINTER(f) e.f = (decltype(e.f))(__attribute__((address_space(1))) void *)(void *)p->f
+    SSSD_VALUE(M); SSSD_VALUE(h); SSSD_VALUE(d); SSSD_VALUE(nq); SSSD_VALUE(nkv); SSSD_VALUE(k); SSSD_VALUE(q_rows_pad); SSSD_VALUE(vocab);
+    SSSD_VALUE(eps); SSSD_VALUE(nss_in); SSSD_VALUE(nss_out); SSSD_VALUE(KT_out); SSSD_VALUE(n_part); SSSD_VALUE(Ntot); SSSD_VALUE(J); SSSD_VALUE(epi);
+    SSSD_VALUE(by_J.d); SSSD_VALUE(by_J.m); SSSD_VALUE(by_k1.d); SSSD_VALUE(by_k1.m); SSSD_VALUE(by_g.d); SSSD_VALUE(by_g.m);
+    SSSD_VALUE(kv.blocks_per_seq); SSSD_VALUE(kv.n_pages); SSSD_VALUE(kv.nkv); SSSD_VALUE(kv.d); SSSD_VALUE(hand.polls);
+    SSSD_POINTER(X); SSSD_POINTER(ssq_out); SSSD_POINTER(out_hi); SSSD_POINTER(out_lo); SSSD_POINTER(Qp); SSSD_POINTER(Qp_lo);
+    SSSD_POINTER(Kc); SSSD_POINTER(Vc); SSSD_POINTER(logits); SSSD_POINTER(part_val); SSSD_POINTER(part_idx); SSSD_POINTER(out);
+    SSSD_POINTER(hand.words); SSSD_POINTER(hand.parts);
+    e.ssq_in = (const float *)(__attribute__((address_space(1))) const void *)(const void *)p->ssq_in;
+    e.gamma_next = (const uint16_t *)(__attribute__((address_space(1))) const void *)(const void *)p->gamma_next;
+    e.rope_cs = (const float *)(__attribute__((address_space(1))) const void *)(const void *)p->rope_cs;
+    e.pos_base = (const int32_t *)(__attribute__((address_space(1))) const void *)(const void *)p->pos_base;
+    e.rope_pos = (const int32_t *)(__attribute__((address_space(1))) const void *)(const void *)p->rope_pos;
+    e.kv.table = (const int32_t *)(__attribute__((address_space(1))) const void *)(const void *)p->kv.table;
+#undef SSSD_VALUE
+#undef SSSD_POINTER
+    return e;
+}
 
 // Rows 16 * tile0 .. 16 * (tile0 + MT16) - 1, column group grp, slice j; set: the group of workgroups that hand over to each other (DIE).
 template <int MT16, int QW, bool BLOCKS, int FORM>
@@ -577,13 +610,15 @@ __device__ __forceinline__ void qgemm16_rows(const FusedGemmArgs a, int NT16, in
     };
     const bool scaled = FORM != PARTS && a.epi != FEPI_RESID && a.epi != FEPI_STORE;
     RowScales<16 * MT16, QW> scales;
-    if (FORM == WHOLE && scaled) scales.request(a, m_base);
+    if (FORM == WHOLE) scales.request(a, m_base, scaled);
 #pragma unroll
     for (int u = 0; u < QDW; ++u) {
         load_a(u, u);
         load_w(u, u);
+        __builtin_amdgcn_sched_barrier(0);   // in the order of the loop: what the first turn may leave in flight, every turn may
     }
     if (FORM == WHOLE && scaled) scales.finish(a, m_base, rstd_s);
+    __builtin_amdgcn_sched_barrier(0);
     stage(0);
     __syncthreads();
     const int a_at = half * MTW * 128 + lane;
@@ -605,7 +640,7 @@ __device__ __forceinline__ void qgemm16_rows(const FusedGemmArgs a, int NT16, in
             x[r + AHEAD] = r < BAR ? ring[u][a_at + (r + AHEAD) * 64] : ring[un][a_at + (r + AHEAD - RECS) * 64];
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int ct = 0; ct < NC; ++ct) acc[r >> 1][ct] = mfma(x[r], w[u][ct], acc[r >> 1][ct]);
+            for (int ct = 0; ct < NC; ++ct) acc[r >> 1][ct] = mfma(w[u][ct], x[r], acc[r >> 1][ct]);
             __builtin_amdgcn_sched_barrier(0);
             if (r == PUT) {
                 stage(un);
@@ -664,279 +699,273 @@ __device__ __forceinline__ void qgemm16_rows(const FusedGemmArgs a, int NT16, in
             }
     }
 
-    // acc[i][ct][v] of lane l: row 16 * (half * MTW + i) + 4*(l/16) + v, column l%16 of tile q_tile(c16 + ct)
-    const int row0 = m_base + 16 * half * MTW;
+    // acc[i][ct][v] of lane l: row 16 * (half * MTW + i) + l%16, column 4*(l/16) + v of tile q_tile(c16 + ct)
+    const int row0 = m_base + 16 * half * MTW, r = lane & 15, kg = lane >> 4;
     if constexpr (FORM == PARTS) {
 #pragma unroll
         for (int ct = 0; ct < NC; ++ct) {
             if (c16 + ct >= NT16) continue;
-            const int col = q_tile<false>(a, c16 + ct) * 16 + (lane & 15);
+            const int col = q_tile<false>(a, c16 + ct) * 16 + 4 * kg;
 #pragma unroll
             for (int i = 0; i < MTW; ++i) {
-#pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    const int row = row0 + 16 * i + 4 * (lane >> 4) + v;
-                    if (row < a.part_rows) a.partials[((size_t)j * a.part_rows + row) * a.Ntot + col] = acc[i][ct][v];
-                }
+                const int row = row0 + 16 * i + r;
+                if (row < a.part_rows) *reinterpret_cast<f32x4 *>(a.partials + ((size_t)j * a.part_rows + row) * a.Ntot + col) = acc[i][ct];
             }
         }
         return;
     }
-    // Epilogue of two units of a wave through its own LDS: 16 lanes of a tile hold a row's columns, the epilogues want eight columns of a row
-    // in a lane.  A row takes 20 floats: the four rows that a store writes together, and the sixteen that a read takes, lie in different
-    // banks.  One sum of squares or maximum per row, group and pair of column tiles.
-    ResidIn rin[2];
-    QkvIn qin;
-    const int qkv_bits = a.d == 128 ? 2 : 1;   // rotary pairs of tiles per head: 4 or 2
-    auto inputs = [&](int i0, int p0, int i1, int p1) {   // requested before the sums are there
-        const int r = lane & 15, kg = lane >> 4;
-        if (a.epi == FEPI_RESID) {
-#pragma unroll
-            for (int ii = 0; ii < 2; ++ii) {
-                const int m = row0 + 16 * (ii ? i1 : i0) + r, col = (c16 + 2 * (ii ? p1 : p0)) * 16 + 8 * kg;
-                rin[ii] = resid_in<false>(a, m < a.M ? m : a.M - 1, col < a.Ntot ? col : 0);
-            }
-        } else if (a.epi == FEPI_QKV) {
-            const int ii = kg >> 1, m = row0 + 16 * (ii ? i1 : i0) + r, unit = (c16 >> 1) + (ii ? p1 : p0);
-            const bool live = m < a.M && 2 * unit < NT16;
-            qin = qkv_in(a, live ? m : 0, live ? unit >> qkv_bits : 0, live ? (unit & ((1 << qkv_bits) - 1)) * 16 + 8 * (kg & 1) : 0);
-        }
-    };
-    auto finish = [&](int i0, int p0, int i1, int p1, bool both, const f32x4 (&sum)[2][2]) {
-        float *mine = reinterpret_cast<float *>(lds + wave * 320);
-        const float *scale = rstd_s + 16 * half * MTW;
-        const int r = lane & 15, kg = lane >> 4;
-#pragma unroll
-        for (int ii = 0; ii < 2; ++ii)
-#pragma unroll
-            for (int part = 0; part < 2; ++part)
-#pragma unroll
-                for (int v = 0; v < 4; ++v) mine[((part * 2 + ii) * 16 + 4 * kg + v) * 20 + r] = sum[ii][part][v];
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        if (a.epi == FEPI_QKV || a.epi == FEPI_SWIGLU) {   // two tiles make one of 16 columns: lanes of kg 0 and 1 take the first unit
-            const int ii = kg >> 1, i = ii ? i1 : i0, p = ii ? p1 : p0, m = row0 + 16 * i + r, unit = (c16 >> 1) + p;
-            if (m < a.M && 2 * unit < NT16 && (both || !ii)) {
-                const Vec8 v0 = load8(mine + (ii * 16 + r) * 20 + 8 * (kg & 1)), v1 = load8(mine + ((2 + ii) * 16 + r) * 20 + 8 * (kg & 1));
-                const float rs = scale[16 * i + r];
-                if (a.epi == FEPI_SWIGLU) {
-                    swiglu8(a, m, unit * 16 + 8 * (kg & 1), rs, v0, v1);
-                } else {
-                    qkv8(a, m, unit >> qkv_bits, (unit & ((1 << qkv_bits) - 1)) * 16 + 8 * (kg & 1), rs, v0, v1, qin);
+    const FusedGemmArgs e = epilogue_arguments();
+    // A unit is a wave's pair p of column tiles on row tile i: an epilogue unit (rotary partners, gate and up) or 32 columns.
+    constexpr int NP = NC / 2, UW = MTW * NP;
+    const int qkv_bits = e.d == 128 ? 2 : 1;   // QKV: rotary pairs of tiles per head, 4 or 2
+    auto epilogue = [&](auto which) {   // one of them for all units, so that units overlap
+        constexpr int EPI = decltype(which)::value;
+        constexpr bool SCALED = EPI != FEPI_RESID && EPI != FEPI_STORE;
+        auto inputs = [&](int i, int p) -> QuadIn {
+            QuadIn in{};
+            const int m = min(row0 + 16 * i + r, e.M - 1), t0 = c16 + 2 * p, unit = (c16 >> 1) + p;
+            if (t0 >= NT16) return in;
+            if (EPI == FEPI_RESID) {
+                const int c0 = t0 * 16 + 4 * kg, c1 = t0 + 1 < NT16 ? c0 + 16 : c0;
+                in.x0 = load4(e.X + (size_t)m * e.h + c0);
+                in.x1 = load4(e.X + (size_t)m * e.h + c1);
+                __builtin_memcpy(&in.g0, e.gamma_next + c0, 8);   // caller's array: no alignment assumed
+                __builtin_memcpy(&in.g1, e.gamma_next + c1, 8);
+            } else if (EPI == FEPI_QKV) {
+                in.base = e.pos_base[e.by_k1(m)];
+                if (unit >> qkv_bits < e.nq + e.nkv) {
+                    const float *cs = e.rope_cs + ((size_t)e.rope_pos[m] * (e.d >> 1) + (unit & ((1 << qkv_bits) - 1)) * 16 + 4 * kg) * 2;
+                    in.x0 = load4(cs);
+                    in.x1 = load4(cs + 4);
                 }
             }
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-            return;
-        }
-        float ss[2] = {0.f, 0.f};
-        Best best[2] = {Best::none(), Best::none()};
-#pragma unroll
-        for (int ii = 0; ii < 2; ++ii) {
-            const int i = ii ? i1 : i0, p = ii ? p1 : p0, m = row0 + 16 * i + r, col = (c16 + 2 * p) * 16 + 8 * kg;
-            if (m >= a.M || col >= a.Ntot || (ii && !both)) continue;
-            const Vec8 v0 = load8(mine + ((kg >> 1) * 32 + ii * 16 + r) * 20 + 8 * (kg & 1));
-            if (a.epi == FEPI_RESID) ss[ii] = resid8<false>(a, m, col, v0, rin[ii]);
-            else if (a.epi == FEPI_LM) lm8(a, m, col, scale[16 * i + r], v0, best[ii]);
-            else store8(a.out + (size_t)m * a.Ntot + col, v0);
-        }
-        if (a.epi != FEPI_RESID && a.epi != FEPI_LM) {
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-            return;
-        }
-        float2 (*const row_s)[32] = reinterpret_cast<float2 (*)[32]>(lds + QW * 320);   // [wave][unit, row]
-        const bool lm = a.epi == FEPI_LM;
-#pragma unroll
-        for (int ii = 0; ii < 2; ++ii) {
-            if (lm) {
-                best[ii].across(16);
-                best[ii].across(32);
+            return in;
+        };
+        auto finish = [&](int i, int p, const f32x4 &v0, const f32x4 &v1, const QuadIn &in, float &ss, Best &best) {
+            const int ml = 16 * (half * MTW + i) + r, m = m_base + ml, t0 = c16 + 2 * p, unit = (c16 >> 1) + p;
+            if (m >= e.M || t0 >= NT16) return;
+            const int c0 = t0 * 16 + 4 * kg;
+            const bool two = t0 + 1 < NT16;
+            if (EPI == FEPI_SWIGLU) {
+                swiglu4(e, m, unit * 16 + 4 * kg, rstd_s[ml], v0, v1);
+            } else if (EPI == FEPI_QKV) {
+                qkv4(e, m, unit >> qkv_bits, (unit & ((1 << qkv_bits) - 1)) * 16 + 4 * kg, rstd_s[ml], v0, v1, in);
+            } else if (EPI == FEPI_RESID) {
+                ss += resid4(e, m, c0, v0, in.x0, in.g0);
+                if (two) ss += resid4(e, m, c0 + 16, v1, in.x1, in.g1);
+            } else if (EPI == FEPI_LM) {
+                lm4(e, m, c0, rstd_s[ml], v0, best);
+                if (two) lm4(e, m, c0 + 16, rstd_s[ml], v1, best);
             } else {
-                ss[ii] += __shfl_xor(ss[ii], 16);
-                ss[ii] += __shfl_xor(ss[ii], 32);
-            }
-            if (kg == 0) row_s[wave][ii * 16 + r] = lm ? float2{best[ii].v, __int_as_float(best[ii].i)} : float2{ss[ii], 0.f};
-        }
-        __syncthreads();
-        if (threadIdx.x < 32 * RH) {
-            const int h = threadIdx.x >> 5, ii = threadIdx.x >> 4 & 1, i = ii ? i1 : i0, p = ii ? p1 : p0;
-            const int m = m_base + 16 * (h * MTW + i) + (threadIdx.x & 15);
-            const size_t at = (size_t)m * (lm ? a.n_part : a.nss_out) + grp * (NC / 2) + p;
-            if (m < a.M && (both || !ii)) {
-                if (lm) {
-                    Best all = Best::none();
-#pragma unroll
-                    for (int x = 0; x < CW; ++x) {
-                        const float2 y = row_s[h * CW + x][threadIdx.x & 31];
-                        all.take(y.x, __float_as_int(y.y));
-                    }
-                    a.part_val[at] = all.v;
-                    a.part_idx[at] = all.i;
-                } else {
-                    float all = 0.f;
-#pragma unroll
-                    for (int x = 0; x < CW; ++x) all += row_s[h * CW + x][threadIdx.x & 31].x;
-                    a.ssq_out[at] = all;
-                }
-            }
-        }
-        __syncthreads();
-    };
-    if constexpr (FORM == DIE) {
-        // A unit is a wave's pair of column tiles on one row tile, v = row tile * NP + pair; unit v belongs to slice v modulo J.  The
-        // others' units are stored as the lanes hold them, its own stay in registers until the other slices of them have arrived.
-        constexpr int NP = NC / 2, UW = MTW * NP, ROOM = BLOCKS ? 8 : UW;   // units, room for them (blocks of eight and six tiles mix)
-        const int J = a.J;
-        float *const slot = a.hand.parts + ((size_t)set * J + j) * (QW * ROOM * 512) + wave * (ROOM * 512) + lane * 4;
-        auto put = [&](bool own) {
-            int o = 0;
-#pragma unroll
-            for (int v = 0; v < UW; ++v) {
-                if ((o == j) == own) {
-                    *reinterpret_cast<f32x4 *>(slot + v * 512) = acc[v / NP][v % NP * 2];
-                    *reinterpret_cast<f32x4 *>(slot + v * 512 + 256) = acc[v / NP][v % NP * 2 + 1];
-                }
-                if (++o == J) o = 0;
+                *reinterpret_cast<f32x4 *>(e.out + (size_t)m * e.Ntot + c0) = v0;
+                if (two) *reinterpret_cast<f32x4 *>(e.out + (size_t)m * e.Ntot + c0 + 16) = v1;
             }
         };
-        put(false);
-        const uint32_t seen = hand_arrive(a.hand, set);
-        if (scaled) {
-            scales.request(a, m_base);
-            scales.finish(a, m_base, rstd_s);   // published by the barrier of hand_wait
+        if constexpr (FORM == WHOLE) {
+            Best best[MTW];
+#pragma unroll
+            for (int i = 0; i < MTW; ++i) best[i] = Best::none();
+#pragma unroll
+            for (int p = 0; p < NP; ++p)
+#pragma unroll
+                for (int i = 0; i < MTW; ++i) {
+                    float ss = 0.f;
+                    finish(i, p, acc[i][2 * p], acc[i][2 * p + 1], inputs(i, p), ss, best[i]);
+                    if (EPI == FEPI_RESID) {   // one sum of squares per row and pair
+                        ss = row_sum4(ss);
+                        const int m = row0 + 16 * i + r;
+                        if (kg == 0 && m < e.M && c16 + 2 * p < NT16) e.ssq_out[(size_t)m * e.nss_out + (c16 >> 1) + p] = ss;
+                    }
+                }
+            if (EPI == FEPI_LM) {   // one arg-max per row and workgroup
+                __syncthreads();      // the ring has been read
+                Best(*best_s)[16 * MT16] = reinterpret_cast<Best(*)[16 * MT16]>(lds);
+#pragma unroll
+                for (int i = 0; i < MTW; ++i) {
+                    best[i].across(16);
+                    best[i].across(32);
+                    if (kg == 0) best_s[cg][16 * (half * MTW + i) + r] = best[i];
+                }
+                __syncthreads();
+                for (int row = threadIdx.x; row < 16 * MT16; row += QW * 64) {
+                    if (m_base + row >= e.M) continue;
+                    Best all = best_s[0][row];
+#pragma unroll
+                    for (int x = 1; x < CW; ++x) all.take(best_s[x][row].v, best_s[x][row].i);
+                    e.part_val[(size_t)(m_base + row) * e.n_part + grp] = all.v;
+                    e.part_idx[(size_t)(m_base + row) * e.n_part + grp] = all.i;
+                }
+            }
+            return;
         }
-        if (j < UW) inputs(j / NP, j % NP, (j + J < UW ? j + J : j) / NP, (j + J < UW ? j + J : j) % NP);   // of the first two units of its share
-        int *way_s = reinterpret_cast<int *>(rstd_s + 16 * MT16);
-        HandWay way = hand_wait(a.hand, set, J, seen, way_s);
-        uint32_t left = way == HAND_SHARE ? hand_leave(a.hand, set) : 0;
-        if (way == HAND_TURN_IN) {
-            put(true);
-            way = hand_turn_in(a.hand, set, J, way_s);
-        }
-        if (way != HAND_NOTHING) {
-            const DieBuffer parts(a.hand.parts + (size_t)set * J * (QW * ROOM * 512), (size_t)J * (QW * ROOM * 2048));
-            constexpr int SLICE = QW * ROOM * 2048;   // bytes
-            const int at = wave * (ROOM * 2048) + lane * 16, step = way == HAND_ALL ? 1 : J;
-            // Two units at a time, v0 and v0 + step, with up to NB slices of each in flight, or one with twice as many.
-            constexpr int NB = MT16 >= 10 && QW == 8 ? 3 : 4;
-            auto add_slices = [&](auto units, int v0, int v1, int o0, int o1, f32x4 (&sum)[2][2]) {
-                constexpr int U = decltype(units)::value, N = NB * 2 / U;
-                for (int n0 = 0; n0 < J - 1; n0 += N) {
-                    f32x4 t[N][U][2];
+        if constexpr (FORM == DIE) {
+            // Unit v = i * NP + p belongs to slice v modulo J.  The others' units are stored as the lanes hold them, its own stay in registers
+            // until the other slices of them have arrived.
+            constexpr int ROOM = BLOCKS ? 8 : UW;   // units a wave has room for (blocks of eight and six tiles mix)
+            constexpr int SLICE = QW * ROOM * 2048; // bytes
+            const int J = e.J;
+            float *const slot = e.hand.parts + ((size_t)set * J + j) * (SLICE / 4) + wave * (ROOM * 512) + lane * 4;
+            auto put = [&](bool own) {
+                int o = 0;
 #pragma unroll
-                    for (int n = 0; n < N; ++n)
-                        if (n0 + n < J - 1)
-#pragma unroll
-                            for (int part = 0; part < 2; ++part) {
-                                t[n][0][part] = parts.load4(at, (n0 + n + (n0 + n >= o0)) * SLICE + v0 * 2048 + part * 1024);
-                                if (U == 2) t[n][U - 1][part] = parts.load4(at, (n0 + n + (n0 + n >= o1)) * SLICE + v1 * 2048 + part * 1024);
-                            }
-#pragma unroll
-                    for (int n = 0; n < N; ++n)
-                        if (n0 + n < J - 1)
-#pragma unroll
-                            for (int ii = 0; ii < U; ++ii)
-#pragma unroll
-                                for (int part = 0; part < 2; ++part) sum[ii][part] += t[n][ii][part];
+                for (int v = 0; v < UW; ++v) {
+                    if ((o == j) == own) {
+                        *reinterpret_cast<f32x4 *>(slot + v * 512) = acc[v / NP][v % NP * 2];
+                        *reinterpret_cast<f32x4 *>(slot + v * 512 + 256) = acc[v / NP][v % NP * 2 + 1];
+                    }
+                    if (++o == J) o = 0;
                 }
             };
-            for (int v0 = way == HAND_ALL ? 0 : j; v0 < UW; v0 += 2 * step) {
-                const int v1 = v0 + step < UW ? v0 + step : v0;
-                f32x4 sum[2][2];
-                if (way == HAND_ALL || v0 != j) inputs(v0 / NP, v0 % NP, v1 / NP, v1 % NP);
-                if (way == HAND_ALL) {   // from memory, in the order in which the owner would have added
+            put(false);
+            const uint32_t seen = hand_arrive(e.hand, set);
+            QuadIn in[2];
+            in[0] = inputs(min(j, UW - 1) / NP, min(j, UW - 1) % NP);   // of the first two units of its share
+            in[1] = inputs(min(j + J, UW - 1) / NP, min(j + J, UW - 1) % NP);
+            if (SCALED) {
+                scales.request(e, m_base, true);
+                scales.finish(e, m_base, rstd_s);   // published by the barrier of hand_wait
+            }
+            int *way_s = reinterpret_cast<int *>(rstd_s + 16 * MT16);
+            HandWay way = hand_wait(e.hand, set, J, seen, way_s);
+            uint32_t left = way == HAND_SHARE ? hand_leave(e.hand, set) : 0;
+            if (way == HAND_TURN_IN) {
+                put(true);
+                way = hand_turn_in(e.hand, set, J, way_s);
+            }
+            if (way != HAND_NOTHING) {
+                const DieBuffer parts(e.hand.parts + (size_t)set * J * (SLICE / 4), (size_t)J * SLICE);
+                const int at = wave * (ROOM * 2048) + lane * 16, first = way == HAND_ALL ? 0 : j, step = way == HAND_ALL ? 1 : J;
+                float2 (*const row_s)[QW][16] = reinterpret_cast<float2 (*)[QW][16]>(lds);   // [unit of the share][wave][row]
+                auto done = [&](int v, const f32x4 &v0, const f32x4 &v1, const QuadIn &u) {
+                    float ss = 0.f;
+                    Best best = Best::none();
+                    finish(v / NP, v % NP, v0, v1, u, ss, best);
+                    const int k = way == HAND_ALL ? v : e.by_J(v);
+                    if (EPI == FEPI_RESID) {
+                        ss = row_sum4(ss);
+                        if (kg == 0) row_s[k][wave][r] = float2{ss, 0.f};
+                    } else if (EPI == FEPI_LM) {
+                        best.across(16);
+                        best.across(32);
+                        if (kg == 0) row_s[k][wave][r] = float2{best.v, __int_as_float(best.i)};
+                    }
+                };
+                // U units of the share from v0 on, up to N other slices of each in flight, added in the order of the slices (equal columns keep equal sums).
+                auto share = [&](auto units, auto slices, int v0) {
+                    constexpr int U = decltype(units)::value, N = decltype(slices)::value;
+                    f32x4 own[U][2], sum[U][2], t[U][N][2];
+                    auto unit = [&](int k) { return min(v0 + k * step, UW - 1); };   // past the last: not used
+                    auto request = [&](int n0) {
 #pragma unroll
-                    for (int ii = 0; ii < 2; ++ii)
+                        for (int k = 0; k < U; ++k)
+                            if (k == 0 || v0 + k * step < UW)
 #pragma unroll
-                        for (int part = 0; part < 2; ++part) {
-                            const int v = ii ? v1 : v0;
-                            sum[ii][part] = parts.load4(at + v % J * SLICE + v * 2048 + part * 1024);
+                                for (int n = 0; n < N; ++n)
+                                    if (n0 + n < J - 1) {
+                                        const int v = unit(k), o = way == HAND_ALL ? v - e.by_J(v) * J : j, q = n0 + n + (n0 + n >= o);
+                                        t[k][n][0] = parts.load4(at, q * SLICE + v * 2048);
+                                        t[k][n][1] = parts.load4(at, q * SLICE + v * 2048 + 1024);
+                                    }
+                    };
+                    request(0);
+#pragma unroll
+                    for (int k = 0; k < U; ++k) {
+                        const int mine = unit(k);
+                        sum[k][0] = sum[k][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+                        if (way == HAND_ALL) {
+                            const int o = mine - e.by_J(mine) * J;
+                            own[k][0] = parts.load4(at, o * SLICE + mine * 2048);
+                            own[k][1] = parts.load4(at, o * SLICE + mine * 2048 + 1024);
+                        } else {
+#pragma unroll
+                            for (int v = 0; v < UW; ++v)
+                                if (v == mine) {
+                                    own[k][0] = acc[v / NP][v % NP * 2];
+                                    own[k][1] = acc[v / NP][v % NP * 2 + 1];
+                                }
                         }
-                } else {
-#pragma unroll
-                    for (int v = 0; v < UW; ++v) {
-                        if (v == v0) { sum[0][0] = acc[v / NP][v % NP * 2]; sum[0][1] = acc[v / NP][v % NP * 2 + 1]; }
-                        if (v == v1) { sum[1][0] = acc[v / NP][v % NP * 2]; sum[1][1] = acc[v / NP][v % NP * 2 + 1]; }
                     }
-                }
-                const int o0 = way == HAND_ALL ? v0 % J : j, o1 = way == HAND_ALL ? v1 % J : j;
-                if (v1 != v0) add_slices(std::integral_constant<int, 2>{}, v0, v1, o0, o1, sum);
-                else add_slices(std::integral_constant<int, 1>{}, v0, v1, o0, o1, sum);
-                finish(v0 / NP, v0 % NP, v1 / NP, v1 % NP, v1 != v0, sum);
-            }
-        }
-        if (way != HAND_SHARE) left = hand_leave(a.hand, set);
-        hand_clear(a.hand, set, J, left);
-        return;
-    }
-    __syncthreads();   // the ring has been read
-    float *mine = reinterpret_cast<float *>(lds + wave * 320);
-    const float *scale = rstd_s + 16 * half * MTW;
-    // One pair of tiles at a time through the wave's own LDS: 16 lanes of a tile hold a row's columns, the epilogues want
-    // eight columns of a row in a lane.  A row takes 20 floats: the four rows that a store writes together, and the sixteen that
-    // a read takes, lie in different banks.
-    const bool paired = a.epi == FEPI_QKV || a.epi == FEPI_SWIGLU;
-    const int r = lane & 15, kg = lane >> 4;
-    Best best[MTW];
+                    for (int n0 = 0; n0 < J - 1; n0 += N) {
+                        if (n0 > 0) request(n0);
 #pragma unroll
-    for (int i = 0; i < MTW; ++i) best[i] = Best::none();
+                        for (int k = 0; k < U; ++k)
 #pragma unroll
-    for (int ct = 0; ct < NC; ct += 2) {
-        if (c16 + ct >= NT16) continue;
+                            for (int n = 0; n < N; ++n) {
+                                const int v = unit(k), o = way == HAND_ALL ? v - e.by_J(v) * J : j;
+                                if (n0 + n < J - 1) {
+                                    if (n0 + n == o) {
+                                        sum[k][0] += own[k][0];
+                                        sum[k][1] += own[k][1];
+                                    }
+                                    sum[k][0] += t[k][n][0];
+                                    sum[k][1] += t[k][n][1];
+                                }
+                            }
+                    }
 #pragma unroll
-        for (int i = 0; i < MTW; i += 2) {   // two row tiles: lanes of kg 0 and 1 then take the first, those of 2 and 3 the second
+                    for (int k = 0; k < U; ++k)
+                        if ((way == HAND_ALL ? unit(k) - e.by_J(unit(k)) * J : j) == J - 1) {
+                            sum[k][0] += own[k][0];
+                            sum[k][1] += own[k][1];
+                        }
+                    if constexpr (U <= 2) {
 #pragma unroll
-            for (int ii = 0; ii < 2 && i + ii < MTW; ++ii)
-#pragma unroll
-                for (int part = 0; part < 2; ++part)
-#pragma unroll
-                    for (int v = 0; v < 4; ++v)
-                        mine[((part * 2 + ii) * 16 + 4 * (lane >> 4) + v) * 20 + (lane & 15)] = acc[i + ii][ct + part][v];
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-            if (paired) {
-                const int ii = kg >> 1, m = row0 + 16 * (i + ii) + r, unit = (c16 + ct) >> 1;
-                if (i + ii < MTW && m < a.M) {
-                    const Vec8 v0 = load8(mine + (ii * 16 + r) * 20 + 8 * (kg & 1)), v1 = load8(mine + ((2 + ii) * 16 + r) * 20 + 8 * (kg & 1));
-                    const float rs = scale[16 * (i + ii) + r];
-                    if (a.epi == FEPI_SWIGLU) {
-                        swiglu8(a, m, unit * 16 + 8 * (kg & 1), rs, v0, v1);
+                        for (int k = 0; k < U; ++k)
+                            if (v0 + k * step < UW) {
+                                if (way == HAND_ALL || v0 != j) in[k] = inputs(unit(k) / NP, unit(k) % NP);
+                                done(unit(k), sum[k][0], sum[k][1], in[k]);
+                            }
                     } else {
-                        const int per_head = a.d >> 5;
-                        qkv8(a, m, unit / per_head, unit % per_head * 16 + 8 * (kg & 1), rs, v0, v1);
+                        for (int k = 0; k < U && v0 + k * step < UW; ++k) {
+                            f32x4 s0 = sum[0][0], s1 = sum[0][1];
+#pragma unroll
+                            for (int x = 1; x < U; ++x)
+                                if (x == k) { s0 = sum[x][0]; s1 = sum[x][1]; }
+                            done(unit(k), s0, s1, inputs(unit(k) / NP, unit(k) % NP));
+                        }
+                    }
+                };
+                constexpr int N = QW == 8 ? 4 : 8;
+                if (J == 2) {
+                    constexpr int U = (UW + 1) / 2 > 2 ? (UW + 1) / 2 : 2;
+                    for (int v0 = first; v0 < UW; v0 += U * step) share(std::integral_constant<int, U>{}, std::integral_constant<int, 1>{}, v0);
+                } else {
+                    for (int v0 = first; v0 < UW; v0 += 2 * step) share(std::integral_constant<int, 2>{}, std::integral_constant<int, N>{}, v0);
+                }
+                if (EPI == FEPI_RESID || EPI == FEPI_LM) {   // one sum of squares or maximum per row, group and pair of column tiles
+                    __syncthreads();
+                    const int n_units = first < UW ? e.by_J(UW - 1 - first) + 1 : 0, count = way == HAND_ALL ? UW : n_units;
+                    for (int x = threadIdx.x; x < count * 16 * RH; x += QW * 64) {
+                        const int k = x / (16 * RH), h = x / 16 % RH, v = first + k * step, m = m_base + 16 * (h * MTW + v / NP) + (x & 15);
+                        const size_t to = (size_t)m * (EPI == FEPI_LM ? e.n_part : e.nss_out) + grp * NP + v % NP;
+                        if (m >= e.M) continue;
+                        float2 all = row_s[k][h * CW][x & 15];
+                        if (EPI == FEPI_LM) {
+                            Best best{all.x, __float_as_int(all.y)};
+#pragma unroll
+                            for (int w2 = 1; w2 < CW; ++w2) best.take(row_s[k][h * CW + w2][x & 15].x, __float_as_int(row_s[k][h * CW + w2][x & 15].y));
+                            e.part_val[to] = best.v;
+                            e.part_idx[to] = best.i;
+                        } else {
+#pragma unroll
+                            for (int w2 = 1; w2 < CW; ++w2) all.x += row_s[k][h * CW + w2][x & 15].x;
+                            e.ssq_out[to] = all.x;
+                        }
                     }
                 }
-            } else {
-                const int col = (c16 + ct) * 16 + 8 * kg;
-#pragma unroll
-                for (int ii = 0; ii < 2 && i + ii < MTW; ++ii) {
-                    const int m = row0 + 16 * (i + ii) + r;
-                    const bool live = m < a.M && col < a.Ntot;
-                    const Vec8 v0 = load8(mine + ((kg >> 1) * 32 + ii * 16 + r) * 20 + 8 * (kg & 1));
-                    if (a.epi == FEPI_LM) {
-                        if (live) lm8(a, m, col, scale[16 * (i + ii) + r], v0, best[i + ii]);
-                    } else if (a.epi == FEPI_RESID) resid_block<false>(a, m, col, live, kg, v0);
-                    else if (live) store8(a.out + (size_t)m * a.Ntot + col, v0);
-                }
             }
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            if (way != HAND_SHARE) left = hand_leave(e.hand, set);
+            hand_clear(e.hand, set, J, left);
         }
-    }
-    if (a.epi == FEPI_LM) {   // one arg-max per row and workgroup
-        Best(*best_s)[16 * MT16] = reinterpret_cast<Best(*)[16 * MT16]>(lds);
-        __syncthreads();
-#pragma unroll
-        for (int i = 0; i < MTW; ++i) {
-            best[i].across(16);
-            best[i].across(32);
-            if (kg == 0) best_s[cg][16 * (half * MTW + i) + r] = best[i];
-        }
-        __syncthreads();
-        for (int row = threadIdx.x; row < 16 * MT16; row += QW * 64) {
-            if (m_base + row >= a.M) continue;
-            Best all = best_s[0][row];
-#pragma unroll
-            for (int x = 1; x < CW; ++x) all.take(best_s[x][row].v, best_s[x][row].i);
-            a.part_val[(size_t)(m_base + row) * a.n_part + grp] = all.v;
-            a.part_idx[(size_t)(m_base + row) * a.n_part + grp] = all.i;
-        }
+    };
+    switch (e.epi) {
+    case FEPI_QKV: epilogue(std::integral_constant<int, FEPI_QKV>{}); break;
+    case FEPI_RESID: epilogue(std::integral_constant<int, FEPI_RESID>{}); break;
+    case FEPI_SWIGLU: epilogue(std::integral_constant<int, FEPI_SWIGLU>{}); break;
+    case FEPI_LM: epilogue(std::integral_constant<int, FEPI_LM>{}); break;
+    default:
+        if constexpr (FORM == WHOLE) epilogue(std::integral_constant<int, FEPI_STORE>{});   // kernel-level GEMMs do not hand over
+        break;
     }
 }
 
@@ -946,7 +975,7 @@ template <int MT16, int QW, bool BLOCKS, int FORM>
 // Registers: two workgroups of four waves per compute unit up to nine tiles (tiny shape with a vocabulary of 128256, 144 rows:
 // 276 registers and one workgroup 69 us, 256 and two 66), which at three tiles costs more than it gives (8B gate/up at 33 rows
 // 44.4 -> 45.2); four waves per SIMD up to two tiles.
-__global__ __launch_bounds__(QW * 64) __attribute__((amdgpu_waves_per_eu(FORM == DIE ? 1 : (!BLOCKS && MT16 <= 2 ? 4 : (QW == 4 && MT16 >= 4 && MT16 <= 9 ? 2 : 1))))) void qgemm16_kernel(FusedGemmArgs a, int RB, int n8, int NT16, int pairs)
+__global__ __launch_bounds__(QW * 64) __attribute__((amdgpu_waves_per_eu(FORM == DIE ? 1 : (!BLOCKS && MT16 <= 2 ? 4 : (QW == 4 && MT16 >= 4 && MT16 <= (FORM == WHOLE ? 8 : 9) ? 2 : 1))))) void qgemm16_kernel(FusedGemmArgs a, int RB, int n8, int NT16, int pairs)
 {
     constexpr int MOST = MT16 ? MT16 : 8;   // row tiles of a workgroup at most
     __shared__ u32x4 lds[QShape<MOST, QW, BLOCKS, FORM>::LDS];
@@ -1108,7 +1137,7 @@ template <int EPI> hipError_t launch_large(FusedGemmArgs &a, hipStream_t s, bool
     a.part_rows = round_up(a.M, 16);
     a.epi = EPI;
     const int halves = rows.RB > 1 ? 2 : 1;   // pairs of column tiles per wave
-    a.nss_out = die ? p.groups * halves : a.h >> 4;
+    a.nss_out = die ? p.groups * halves : (NT16 + 1) / 2;   // read where this launch leaves them (RESID)
     a.n_part = die ? p.groups * halves : p.groups;
     *needs_epilogue = a.J > 1 && !die;   // an unsplit K: the kernel applies the epilogue itself
     if (EPI == FEPI_QKV) { a.seg0 = a.nq * (a.d >> 4); a.seg1 = a.nkv * (a.d >> 4); }
