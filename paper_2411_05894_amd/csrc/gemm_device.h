@@ -56,6 +56,28 @@ template <bool COH, typename T> __device__ __forceinline__ T ld(const T *p)
     return *p;
 }
 
+// RESID, one element: row m, column n = unit * 16 + c, with what was read of the residual stream and the gains.  The 16 lanes of a row
+// are adjacent.
+template <bool COH>
+__device__ __forceinline__ void resid1(const FusedGemmArgs &a, int unit, int m, int c, bool valid, float v0, float x, uint16_t gamma)
+{
+    const int n = unit * 16 + c;
+    float xn = 0.f;
+    if (valid) {
+        xn = x + v0;
+        st<COH>(a.X + (size_t)m * a.h + n, xn);
+        uint16_t hi, lo;
+        split_bf16(xn * bf16_to_f32(gamma), hi, lo);
+        const size_t idx = packed_index(m, n, (a.h + 31) >> 5);
+        st<COH>(a.out_hi + idx, hi);
+        st<COH>(a.out_lo + idx, lo);
+    }
+    float ss = xn * xn;
+#pragma unroll
+    for (int off = 8; off >= 1; off >>= 1) ss += __shfl_xor(ss, off, 16);
+    if (valid && c == 0) st<COH>(a.ssq_out + (size_t)m * (a.h >> 4) + unit, ss);
+}
+
 // One output element pair of a unit: row m, column c of the 16-column tile(s).  v0/v1 are the
 // fp32 results of the unit's first/second tile.  The 16 lanes c = 0..15 of a row are adjacent
 // lanes of one wave (RESID reduces over them).  Not for LM, whose callers keep a running arg-max.
@@ -66,20 +88,7 @@ __device__ __forceinline__ void epilogue(const FusedGemmArgs &a, int unit, int m
         if (valid) a.out[(size_t)m * a.Ntot + unit * 16 + c] = v0;
     } else if (EPI == FEPI_RESID) {
         const int n = unit * 16 + c;
-        float xn = 0.f;
-        if (valid) {
-            xn = ld<COH>(a.X + (size_t)m * a.h + n) + v0;
-            st<COH>(a.X + (size_t)m * a.h + n, xn);
-            uint16_t hi, lo;
-            split_bf16(xn * bf16_to_f32(a.gamma_next[n]), hi, lo);
-            const size_t idx = packed_index(m, n, (a.h + 31) >> 5);
-            st<COH>(a.out_hi + idx, hi);
-            st<COH>(a.out_lo + idx, lo);
-        }
-        float ss = xn * xn;
-#pragma unroll
-        for (int off = 8; off >= 1; off >>= 1) ss += __shfl_xor(ss, off, 16);
-        if (valid && c == 0) st<COH>(a.ssq_out + (size_t)m * (a.h >> 4) + unit, ss);
+        resid1<COH>(a, unit, m, c, valid, v0, valid ? ld<COH>(a.X + (size_t)m * a.h + n) : 0.f, valid ? a.gamma_next[n] : (uint16_t)0);
     } else if (EPI == FEPI_QKV) {
         if (!valid) return;
         const int TH = a.d >> 4, per_head = TH >> 1;

@@ -43,24 +43,34 @@ namespace {
 // ------------------------------------------------------------------ M <= 32 ----
 constexpr int PW = 16;  // waves per workgroup
 
+// A row of operand tiles as a buffer: the tile's place in it is a scalar, the lane's record the only vector part of the address.  With
+// 64-bit vector addresses the first loads of a wave held forty registers.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t tile_row(const void *p, int KT)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, KT * 1024, 0x00027000);
+}
 // Weight tile load.  One reader per byte (RH == 1): streaming, the line is not worth keeping.  Two
 // workgroups of a die reading the same tiles (RH == 2): an ordinary load, so that the line is still in
 // the die's L2 when the second request comes.
-template <int RH> __device__ __forceinline__ u32x4 wload(const u32x4 *p)
+template <int AUX> __device__ __forceinline__ u32x4 load_tile(__amdgpu_buffer_rsrc_t row, int at, int lane)
 {
-    return RH == 1 ? __builtin_nontemporal_load(p) : *p;
+    return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(row, lane * 16, at, AUX));
 }
+template <int RH> __device__ __forceinline__ u32x4 wload(__amdgpu_buffer_rsrc_t row, int at, int lane) { return load_tile<RH == 1 ? 2 : 0>(row, at, lane); }
 
 template <int KPW, bool PREFETCH, int RH>
-__device__ __forceinline__ f32x4 stream_tile(const u32x4 (&ah)[KPW], const u32x4 (&al)[KPW], u32x4 (&w)[KPW], const u32x4 *wn,
-                                             const int (&koff)[KPW])
+__device__ __forceinline__ f32x4 stream_tile(const u32x4 (&ah)[KPW], const u32x4 (&al)[KPW], u32x4 (&w)[KPW], __amdgpu_buffer_rsrc_t wn,
+                                             const int (&koff)[KPW], int lane)
 {
     f32x4 s0 = f32x4{0.f, 0.f, 0.f, 0.f}, s1 = s0;
 #pragma unroll
     for (int i = 0; i < KPW; ++i) {
         s0 = mfma(ah[i], w[i], s0);
         s1 = mfma(al[i], w[i], s1);
-        if (PREFETCH) w[i] = wload<RH>(wn + koff[i]);
+        if (PREFETCH) {
+            w[i] = wload<RH>(wn, koff[i], lane);
+            __builtin_amdgcn_sched_barrier(0);   // here, not behind the last product: the compiler gathers them there, with one load left in flight
+        }
     }
     return s0 + s1;
 }
@@ -76,7 +86,7 @@ __device__ __forceinline__ f32x4 stream_tile(const u32x4 (&ah)[KPW], const u32x4
 // sit 8 apart in the grid, i.e. on the same die, where they start together and ask for the same weight
 // tiles: one of the two requests is served by the die's L2 (or merged with the other in flight), so
 // HBM still sees each weight byte once (measured: 1.02 x the matrix bytes fetched per launch).
-template <int EPI, int KPW, bool SPLIT, int RH>
+template <int EPI, int KPW, bool SPLIT, int RH, bool ONE>
 __global__ __launch_bounds__(PW * 64) void pgemm_kernel(FusedGemmArgs a)
 {
     constexpr int TPU = Unit<EPI>::TILES;
@@ -114,33 +124,66 @@ __global__ __launch_bounds__(PW * 64) void pgemm_kernel(FusedGemmArgs a)
     // k-tiles past the matrix (ragged K split) contribute zero activations and re-read the last tile.
     int koff[KPW];
 #pragma unroll
-    for (int i = 0; i < KPW; ++i) koff[i] = (kt0 + i < KT ? kt0 + i : KT - 1) * 64;
+    for (int i = 0; i < KPW; ++i) koff[i] = (kt0 + i < KT ? kt0 + i : KT - 1) * 1024;
 
     constexpr bool SCALED = EPI != FEPI_RESID && EPI != FEPI_STORE;
     u32x4 w[KPW], ah[KPW], al[KPW];
-    const u32x4 *wp = tile_weights<EPI>(a, unit_tile<EPI>(a, u_begin, 0)) + lane;
-#pragma unroll
-    for (int i = 0; i < KPW; ++i) w[i] = wload<RH>(wp + koff[i]);
+    const auto wp = tile_row(tile_weights<EPI>(a, unit_tile<EPI>(a, u_begin, 0)), KT);
+    const auto hi = tile_row(a.A_hi + (size_t)rt * KT * 64, KT), lo = tile_row(a.A_lo + (size_t)rt * KT * 64, KT);
+    // Weights and activations of a k-tile together, in the order of their use: its products, and with them the request for the next
+    // tile's weights, need not wait for the others.  No activation load under a branch: every wait would cover all of them.
 #pragma unroll
     for (int i = 0; i < KPW; ++i) {
-        const bool live = kt0 + i < KT;
-        const size_t at = (size_t)rt * KT * 64 + koff[i] + lane;
-        ah[i] = live ? a.A_hi[at] : u32x4{0, 0, 0, 0};
-        al[i] = live ? a.A_lo[at] : u32x4{0, 0, 0, 0};
+        w[i] = wload<RH>(wp, koff[i], lane);
+        ah[i] = load_tile<0>(hi, koff[i], lane);
+        al[i] = load_tile<0>(lo, koff[i], lane);
+        __builtin_amdgcn_sched_barrier(0);
     }
-    if (SCALED && !SPLIT) rstd_s[wave] = row_rstd(a, m_base + wave, lane);   // published by the first barrier
+    // The row scales are needed by the first epilogue only: their sums (wave w: of row w) are requested behind the operands and added up
+    // behind the first tile's products, so no load of the first tiles waits for them.
+    constexpr int SV = PW * KPW * 2 / 64 > 0 ? PW * KPW * 2 / 64 : 1;   // sums per lane: a whole K of h is at most PW * KPW k-tiles, with two sums each at most
+    float sv[SV];
+    const int ms = m_base + wave < a.M ? m_base + wave : a.M - 1;
+    if (SCALED && !SPLIT) {
+        const float *p = a.ssq_in + (size_t)ms * a.nss_in;
+#pragma unroll
+        for (int i = 0; i < SV; ++i) sv[i] = p[lane + 64 * i < a.nss_in ? lane + 64 * i : 0];
+        __builtin_amdgcn_sched_barrier(0);
+    }
+
+    // ... and what the only epilogue of a workgroup adds to
+    constexpr bool AHEAD = ONE && EPI == FEPI_RESID && !SPLIT;
+    float x_ahead = 0.f;
+    uint16_t g_ahead = 0;
+    if (AHEAD) {
+        const int m = m_base + 4 * (lane >> 4) + (wave & 3), n = u_begin * 16 + (lane & 15);
+        x_ahead = a.X[(size_t)(m < a.M ? m : a.M - 1) * a.h + n];
+        g_ahead = a.gamma_next[n];
+        __builtin_amdgcn_sched_barrier(0);
+    }
+
+    if (kt0 + KPW > KT) {
+#pragma unroll
+        for (int i = 0; i < KPW; ++i)
+            if (kt0 + i >= KT) ah[i] = al[i] = u32x4{0, 0, 0, 0};
+    }
 
     float keep = 0.f;
     Best best = Best::none();   // LM: of this thread's row and column within the tiles
-    for (int s = 0; s < n_steps; ++s) {
+    auto scales = [&]() {
+        float sum = 0.f;
+#pragma unroll
+        for (int i = 0; i < SV; ++i) sum += lane + 64 * i < a.nss_in ? sv[i] : 0.f;
+        sum = wave_sum(sum);
+        if (lane == 0) rstd_s[wave] = rsqrtf(sum / (float)a.h + a.eps);
+    };
+    auto step = [&](int s, auto first, auto more) {
+        constexpr bool SCALES = decltype(first)::value && SCALED && !SPLIT, MORE = decltype(more)::value;
         const int unit = u_begin + (s / TPU) * u_stride, part = s % TPU;
-        f32x4 acc;
-        if (s + 1 < n_steps) {
-            const u32x4 *wn = tile_weights<EPI>(a, unit_tile<EPI>(a, u_begin + ((s + 1) / TPU) * u_stride, (s + 1) % TPU)) + lane;
-            acc = stream_tile<KPW, true, RH>(ah, al, w, wn, koff);
-        } else {
-            acc = stream_tile<KPW, false, RH>(ah, al, w, nullptr, koff);
-        }
+        const int next = MORE && s + 1 < n_steps ? s + 1 : s;
+        const auto wn = tile_row(tile_weights<EPI>(a, unit_tile<EPI>(a, u_begin + (next / TPU) * u_stride, next % TPU)), KT);
+        const f32x4 acc = stream_tile<KPW, MORE, RH>(ah, al, w, wn, koff, lane);
+        if (SCALES) scales();
         float *rb = &red[s & 1][0][0];
 #pragma unroll
         for (int r = 0; r < 4; ++r) rb[wave * 256 + r * 64 + lane] = acc[r];
@@ -163,10 +206,18 @@ __global__ __launch_bounds__(PW * 64) void pgemm_kernel(FusedGemmArgs a)
                     const int n = unit * 16 + c;
                     best.take(v * rs, n);
                     if (m < a.M && a.logits) a.logits[(size_t)m * a.vocab + n] = v * rs;
-                } else if (TPU == 2) epilogue<EPI>(a, unit, m, c, m < a.M, keep, v, rs);
+                } else if (AHEAD) resid1<false>(a, unit, m, c, m < a.M, v, x_ahead, g_ahead);
+                else if (TPU == 2) epilogue<EPI>(a, unit, m, c, m < a.M, keep, v, rs);
                 else epilogue<EPI>(a, unit, m, c, m < a.M, v, 0.f, rs);
             }
         }
+    };
+    // Steps with and without a next tile apart: where both meet, a wait covers the next tile's loads.  A workgroup with fewer tiles than
+    // the others (ONE: all have one) may fetch its only one twice.
+    step(0, std::true_type{}, std::integral_constant<bool, !ONE>{});
+    if (!ONE) {
+        for (int s = 1; s + 1 < n_steps; ++s) step(s, std::false_type{}, std::true_type{});
+        if (n_steps > 1) step(n_steps - 1, std::false_type{}, std::false_type{});
     }
 
     if (EPI == FEPI_LM && !SPLIT && wave < 4) {
@@ -1219,15 +1270,21 @@ template <int EPI> hipError_t launch_small(FusedGemmArgs &a, hipStream_t s, bool
     if (a.J > 1 && (size_t)a.J * a.part_rows * a.Ntot * sizeof(float) > a.partial_bytes) return hipErrorInvalidValue;
     const dim3 grid(groups * a.J * sp.rh), block(PW * 64);
     if (groups * sp.rh > a.tail_slots) a.tail_count = nullptr;   // no counter for every group: epilogue launch
-#define SSSD_PLAUNCH(KPW, RH)                                                                                   \
-    do {                                                                                                        \
-        if (a.J > 1) hipExtLaunchKernelGGL((pgemm_kernel<EPI, KPW, true, RH>), grid, block, 0, s, t0, t1, 0, a); \
-        else hipExtLaunchKernelGGL((pgemm_kernel<EPI, KPW, false, RH>), grid, block, 0, s, t0, t1, 0, a);       \
+    const bool one = Unit<EPI>::TILES == 1 && a.upw == 1;   // one tile per workgroup
+#define SSSD_PKERNEL(KPW, SPLIT, RH)                                                                                                       \
+    do {                                                                                                                                   \
+        if (one) hipExtLaunchKernelGGL((pgemm_kernel<EPI, KPW, SPLIT, RH, Unit<EPI>::TILES == 1>), grid, block, 0, s, t0, t1, 0, a);       \
+        else hipExtLaunchKernelGGL((pgemm_kernel<EPI, KPW, SPLIT, RH, false>), grid, block, 0, s, t0, t1, 0, a);                           \
     } while (0)
-#define SSSD_PWHOLE(KPW)                                                                                            \
-    do {                                                                                                            \
-        if (sp.rh == 2) hipExtLaunchKernelGGL((pgemm_kernel<EPI, KPW, false, 2>), grid, block, 0, s, t0, t1, 0, a); \
-        else hipExtLaunchKernelGGL((pgemm_kernel<EPI, KPW, false, 1>), grid, block, 0, s, t0, t1, 0, a);            \
+#define SSSD_PLAUNCH(KPW, RH)                         \
+    do {                                              \
+        if (a.J > 1) SSSD_PKERNEL(KPW, true, RH);     \
+        else SSSD_PKERNEL(KPW, false, RH);            \
+    } while (0)
+#define SSSD_PWHOLE(KPW)                              \
+    do {                                              \
+        if (sp.rh == 2) SSSD_PKERNEL(KPW, false, 2);  \
+        else SSSD_PKERNEL(KPW, false, 1);             \
     } while (0)
     if (kpw == 1) SSSD_PWHOLE(1);
     else if (kpw == 2) SSSD_PWHOLE(2);
@@ -1238,6 +1295,7 @@ template <int EPI> hipError_t launch_small(FusedGemmArgs &a, hipStream_t s, bool
     else SSSD_PLAUNCH(8, 1);
 #undef SSSD_PWHOLE
 #undef SSSD_PLAUNCH
+#undef SSSD_PKERNEL
     *needs_epilogue = a.J > 1 && !a.tail_count;
     return hipGetLastError();
 }
