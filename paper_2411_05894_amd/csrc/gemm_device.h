@@ -166,8 +166,7 @@ __device__ __forceinline__ float wave_sum(float x)
     return bits_f32(h[0]) + bits_f32(h[1]);
 }
 
-// rsqrt(mean(x^2) + eps) of row m from the producer's sums of squares; whole wave.  (pgemm_kernel's, behind its first operands: with
-// the sums requested in front of them, all at once, an 8B step of nine rows takes 3433 us instead of 3429.)
+// rsqrt(mean(x^2) + eps) of row m from the producer's sums of squares; whole wave.  (The last workgroup of pgemm_kernel's split.)
 template <bool COH = false> __device__ __forceinline__ float row_rstd(const FusedGemmArgs &a, int m, int lane)
 {
     const int NSS = a.nss_in;
@@ -268,26 +267,18 @@ __device__ __forceinline__ void sum_slices(const FusedGemmArgs &a, int m, int co
 // Epilogues on 8 consecutive columns per thread, which are one 16-byte lane record of a packed operand.
 
 // RESID: X += v0, packed X * gamma.  v0 = the projection's result at columns col..col+7 of row m.  Returns the sum of squares
-// of the updated columns.  What it reads can be requested ahead.
-struct ResidIn {
-    Vec8 x;
+// of the updated columns.
+template <bool COH> __device__ __forceinline__ float resid8(const FusedGemmArgs &a, int m, int col, const Vec8 &v0)
+{
+    const Vec8 x = load8<COH>(a.X + (size_t)m * a.h + col);
     u32x4 gamma;
-};
-template <bool COH> __device__ __forceinline__ ResidIn resid_in(const FusedGemmArgs &a, int m, int col)
-{
-    ResidIn in;
-    in.x = load8<COH>(a.X + (size_t)m * a.h + col);
-    __builtin_memcpy(&in.gamma, a.gamma_next + col, 16);   // caller's array: no alignment assumed
-    return in;
-}
-template <bool COH> __device__ __forceinline__ float resid8(const FusedGemmArgs &a, int m, int col, const Vec8 &v0, const ResidIn &in)
-{
+    __builtin_memcpy(&gamma, a.gamma_next + col, 16);   // caller's array: no alignment assumed
     float ss = 0.f;
     Vec8 xn, xg;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-        xn.v[e] = in.x.v[e] + v0.v[e];
-        xg.v[e] = xn.v[e] * bits_f32(e & 1 ? in.gamma[e >> 1] & 0xFFFF0000u : in.gamma[e >> 1] << 16);
+        xn.v[e] = x.v[e] + v0.v[e];
+        xg.v[e] = xn.v[e] * bits_f32(e & 1 ? gamma[e >> 1] & 0xFFFF0000u : gamma[e >> 1] << 16);
         ss += xn.v[e] * xn.v[e];
     }
     store8<COH>(a.X + (size_t)m * a.h + col, xn);
@@ -297,10 +288,6 @@ template <bool COH> __device__ __forceinline__ float resid8(const FusedGemmArgs 
     st_record<COH>(a.out_hi + idx, hi);
     st_record<COH>(a.out_lo + idx, lo);
     return ss;
-}
-template <bool COH> __device__ __forceinline__ float resid8(const FusedGemmArgs &a, int m, int col, const Vec8 &v0)
-{
-    return resid8<COH>(a, m, col, v0, resid_in<COH>(a, m, col));
 }
 
 // RESID with one sum of squares per 16 columns; whole waves call it.  kg: which 8-column group of its 32-column block the
@@ -312,35 +299,22 @@ template <bool COH> __device__ __forceinline__ void resid_block(const FusedGemmA
     if (live && !(kg & 1)) st<COH>(a.ssq_out + (size_t)m * (a.h >> 4) + (col >> 4), ss);
 }
 
-// QKV: v0 at channels ch..ch+7 of the first half of a head, v1 at the same channels of the second half.  What it reads can be
-// requested ahead.
-struct QkvIn {
-    int base;        // cache row of the sequence's first node; < 0: a rejected sequence, which must not touch the cache
-    Vec8 cs0, cs1;   // (cos, sin) of channels ch..ch+3, ch+4..ch+7 (Q and K heads)
-};
-__device__ __forceinline__ QkvIn qkv_in(const FusedGemmArgs &a, int m, int head, int ch)
-{
-    QkvIn in;
-    in.base = a.pos_base[a.by_k1(m)];
-    if (head < a.nq + a.nkv) {
-        const float *cs = a.rope_cs + ((size_t)a.rope_pos[m] * (a.d >> 1) + ch) * 2;
-        in.cs0 = load8(cs);
-        in.cs1 = load8(cs + 8);
-    }
-    return in;
-}
-__device__ __forceinline__ void qkv8(const FusedGemmArgs &a, int m, int head, int ch, float rs, Vec8 v0, Vec8 v1, const QkvIn &in)
+// QKV: v0 at channels ch..ch+7 of the first half of a head, v1 at the same channels of the second half.
+__device__ __forceinline__ void qkv8(const FusedGemmArgs &a, int m, int head, int ch, float rs, Vec8 v0, Vec8 v1)
 {
     const int half = a.d >> 1;
     const int b = a.by_k1(m), j = m - b * (a.k + 1);
-    const int pos = in.base + j;                  // cache row of node j
+    const int base = a.pos_base[b];               // cache row of the sequence's first node; < 0: a rejected sequence, which must not touch the cache
+    const int pos = base + j;                     // cache row of node j
 #pragma unroll
     for (int e = 0; e < 8; ++e) { v0.v[e] *= rs; v1.v[e] *= rs; }
     if (head < a.nq + a.nkv) {
+        const float *cs = a.rope_cs + ((size_t)a.rope_pos[m] * half + ch) * 2;
+        const Vec8 cs0 = load8(cs), cs1 = load8(cs + 8);   // (cos, sin) of channels ch..ch+3, ch+4..ch+7
         Vec8 y0, y1;
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-            const float co = e < 4 ? in.cs0.v[2 * e] : in.cs1.v[2 * (e - 4)], si = e < 4 ? in.cs0.v[2 * e + 1] : in.cs1.v[2 * (e - 4) + 1];
+            const float co = e < 4 ? cs0.v[2 * e] : cs1.v[2 * (e - 4)], si = e < 4 ? cs0.v[2 * e + 1] : cs1.v[2 * (e - 4) + 1];
             y0.v[e] = v0.v[e] * co - v1.v[e] * si;
             y1.v[e] = v0.v[e] * si + v1.v[e] * co;
         }
@@ -353,13 +327,13 @@ __device__ __forceinline__ void qkv8(const FusedGemmArgs &a, int m, int head, in
             const size_t i_0 = qs + packed_index(rr, ch, a.d >> 5), i_1 = qs + packed_index(rr, ch + half, a.d >> 5);
             *reinterpret_cast<u32x4 *>(a.Qp + i_0) = h0; *reinterpret_cast<u32x4 *>(a.Qp_lo + i_0) = l0;
             *reinterpret_cast<u32x4 *>(a.Qp + i_1) = h1; *reinterpret_cast<u32x4 *>(a.Qp_lo + i_1) = l1;
-        } else if (in.base >= 0) {
+        } else if (base >= 0) {
             head -= a.nq;
             uint16_t *kk = a.Kc + kv_block_offset(a.kv, kv_page(a.kv, b, pos >> 5), head);
             *reinterpret_cast<u32x4 *>(kk + kblock_index(pos & 31, ch, a.d)) = round8(y0);
             *reinterpret_cast<u32x4 *>(kk + kblock_index(pos & 31, ch + half, a.d)) = round8(y1);
         }
-    } else if (in.base >= 0) {
+    } else if (base >= 0) {
         head -= a.nq + a.nkv;
         uint16_t *vv = a.Vc + kv_block_offset(a.kv, kv_page(a.kv, b, pos >> 5), head);
         const u32x4 r0 = round8(v0), r1 = round8(v1);
@@ -369,10 +343,6 @@ __device__ __forceinline__ void qkv8(const FusedGemmArgs &a, int m, int head, in
             vv[vblock_index(pos & 31, ch + half + e, a.d)] = (uint16_t)(r1[e >> 1] >> (e & 1) * 16);
         }
     }
-}
-__device__ __forceinline__ void qkv8(const FusedGemmArgs &a, int m, int head, int ch, float rs, const Vec8 &v0, const Vec8 &v1)
-{
-    qkv8(a, m, head, ch, rs, v0, v1, qkv_in(a, m, head, ch));
 }
 
 // SWIGLU: gate v0, up v1 at columns col..col+7 of the FFN.

@@ -17,13 +17,14 @@
 //                  matrices) owns 32 output columns and streams their weights HBM -> registers (rolling prefetch,
 //                  every weight byte read once), while the activation k-tiles of the workgroup's k-slice, which all
 //                  its waves need, are staged through a register ring and an LDS ring.  With the whole K in one
-//                  workgroup it applies the epilogue itself; else its results go to split-K partials for epi_kernel.
-//   epi_kernel     Sums split-K partial results (when K is split over workgroups) in fixed order
-//                  and applies the epilogue.
+//                  workgroup it applies the epilogue itself; the slices of a split K are summed inside the launch, by
+//                  workgroups of one die through its L2, or go to split-K partials for epi_kernel.
+//   epi_kernel     Sums split-K partial results in fixed order and applies the epilogue, where they are not summed
+//                  inside the launch: callers without a context, more workgroups than compute units.
 //
 // Epilogues (everything Table 2 leaves out is folded into them):
 //   QKV     RMSNorm scale, rotary embedding, Q -> packed hi/lo operand, K/V -> cache (in place)
-//   RESID   X += acc; packed X*gamma_next hi/lo; sums of squares per 16 columns, or per workgroup of epi_kernel (nss_out says how many)
+//   RESID   X += acc; packed X*gamma_next hi/lo; sums of squares per 16 or 32 columns, or per workgroup (nss_out says how many)
 //   SWIGLU  RMSNorm scale, silu(gate)*up -> packed hi/lo operand
 //   LM      RMSNorm scale, arg-max of a workgroup's columns (with an unsplit K logits are materialised only if asked for; else
 //           they pass through memory once as unscaled sums)
@@ -139,6 +140,9 @@ __global__ __launch_bounds__(PW * 64) void pgemm_kernel(FusedGemmArgs a)
         al[i] = load_tile<0>(lo, koff[i], lane);
         __builtin_amdgcn_sched_barrier(0);
     }
+    // What bounds it: the weight stream, 8 TB/s once it runs (8B gate/up, 235 MB), and in front of it the chain from the launch to the
+    // first products, 7-10 us of a 9-25 us launch.  The operands of a k-tile are therefore requested together and in the order of use, none
+    // under a branch, and nothing else in front of them: 8B step of nine rows 3295 -> 3261 us.
     // The row scales are needed by the first epilogue only: their sums (wave w: of row w) are requested behind the operands and added up
     // behind the first tile's products, so no load of the first tiles waits for them.
     constexpr int SV = PW * KPW * 2 / 64 > 0 ? PW * KPW * 2 / 64 : 1;   // sums per lane: a whole K of h is at most PW * KPW k-tiles, with two sums each at most
@@ -528,15 +532,20 @@ template <int ROWS, int QW> struct RowScales {
     }
 };
 
-// grid = row blocks * column groups * J workgroups of QW waves on MT16 row tiles of 16; J > 1: writes partials[j][row][col].
-// J = 1: applies the epilogue, through LDS, so that a lane holds eight columns of a row and stores whole operand records.  As
-// a launch of its own behind sums in memory it cost 70B gate/up at 144 rows 16.6 us, 8B gate/up at 512 rows 24 us, an LM head of
-// 128256 at 91 rows 27 us; whole steps with such a launch: 70B layer 625 -> 605 us, two 8B layers at 512 rows 1022 -> 984, 8B
-// layer and head at 91 rows 435 -> 415.  (Per element from the accumulators, in 2-byte stores, it had cost more than it saved.)
+// grid = row blocks * column groups * J workgroups of QW waves on MT16 row tiles of 16.
+// Weights are the first operand of the products and activations the second, so a lane ends with four consecutive columns of one row: the
+// epilogues work on the accumulators as they are, store quads, and two lanes swap halves where a whole operand record is wanted (stored by
+// halves every line is written twice, 2 us of a launch).  Through LDS, with eight columns per lane, the epilogues cost 2-4 us more:
+// 70B layer at 144 rows 570 -> 561 us a step, two 8B layers at 512 rows 950 -> 939, at 160 rows 544 -> 527.
+// A whole K (J = 1) is finished by its workgroup.  As a launch of its own behind sums in memory the epilogue cost 70B gate/up at 144 rows
+// 16.6 us, 8B gate/up at 512 rows 24 us, an LM head of 128256 at 91 rows 27 us.
 // Both operands are the packed tiles as stored: lane l holds (row or column l%16, k-slots 8*(l/16)..+7) of a 16 x 32 tile.
-// Whole and split K have kernels of their own (WHOLE): the epilogue's row scales and tile order in front of the first loads, and its
-// staging area, cost the split GEMMs, which use none of it, 0.3-1 us each -- 4096 x 4096 at 36 rows 13.3 -> 12.4 us, 8B QKV at 36 rows
+// The three forms (QForm) have kernels of their own: the epilogue's row scales and tile order in front of the first loads, and its
+// staging area, cost the split GEMMs that use none of it 0.3-1 us each -- 4096 x 4096 at 36 rows 13.3 -> 12.4 us, 8B QKV at 36 rows
 // 14.6 -> 13.5, K = 1024 at 33 rows 7.7 -> 6.9; steps of 33..160 rows 0.5-4 %.
+// The first loads go out in the order of the loop (sched_barrier): reordered by the compiler they make the wait at the top of some loops
+// drain what is in flight once every QDW k-tiles (8B gate/up at 36 rows: loop 49.8 -> 42 us).  QDW = 4: with 3 / 6 / 8 weight k-tiles in
+// flight two 8B layers at 36 rows and 32768 positions take 426 / 425 / 428 us instead of 422, at 25 rows 237 instead of 232 with 3.
 // One 32-column tile pair per wave, so two waves share a SIMD at QW = 8 (256 columns per workgroup, the large matrices);
 // QW = 4 for the small ones, whose K then splits half as often.
 //
@@ -1160,6 +1169,10 @@ __host__ bool is_small(int M, int Ntot, int K)
 
 // The same split for slices that are summed inside the launch: one workgroup per compute unit (they wait for each other), the slices of
 // a column group on one die.  False, and the plan as it was, where that leaves no split.
+// As many slices as a die has compute units for (one row block): what a slice costs here is a share of one die's L2, not a copy of the
+// output in memory.  With row blocks no more than the plan above: they fill the device already.
+// Against partial sums and an epilogue launch, us a step: 70B layer at 144 rows 588 -> 570; two 8B layers at 36 rows 443 -> 428, 160 rows
+// 558 -> 544, 512 rows 968 -> 950; layer and head at 91 rows 402 -> 394.
 __host__ bool die_plan(QPlan &p, int KT, int RB, const Hand &hand)
 {
     if (!hand.words) return false;

@@ -39,3 +39,12 @@ def test_fused_short_k(hidden, nq, ffn, B, k):
     herr = (gpu["hidden"] - ref["hidden"]).abs().max().item() / ref["hidden"].abs().max().item()
     assert herr < 5e-3      # a bf16 rounding of a new K or V element may fall the other way: 2^-9 of it
     p.ctx.sssd_verify_destroy()
+
+
+# Workgroups with two tiles beside those with one, three beside two, one each and none to spare; whole and split K, one and two row tiles
+@pytest.mark.parametrize("tiles,K", [(256, 64), (257, 1024), (259, 1000), (515, 2048), (129, 4128), (131, 2056)])
+@pytest.mark.parametrize("M", [5, 16, 20])
+def test_uneven_tiles(tiles, K, M):
+    N = 16 * tiles
+    assert sv.sssd_op_gemm_kernel_of(M, N, K) == "pgemm_kernel"
+    check(N, K, M)
