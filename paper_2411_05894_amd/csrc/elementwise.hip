@@ -406,81 +406,108 @@ __device__ __forceinline__ void step_sequence(const Dims &D, const StepIO &io, c
     if (reject) *err_flag = 1;
 }
 
-// grid = M rows and a workgroup for every eight sequences (a wave each, beside the rows: in the rows' own waves the launch took
-// 1 us longer), 512 threads.  Validates lens/tokens/parents; row geometry (depth and visible new
-// rows of the node, from the draft tree or the chain); x = E[token]; packed x*gamma; sums of squares, one per wave.
+// Geometry of row m of a step, by one wave: its depth and visible new rows, from the draft tree or the chain.
+__device__ __forceinline__ void step_row(const Dims &D, const StepIO &io, int m, int lane, int32_t *rope_pos, uint32_t *anc, int32_t *err_flag)
+{
+    const int b = m / (io.k + 1), j = m % (io.k + 1), len = length_or_zero(D, io.k, io.lens[b]);
+    int depth = j;
+    uint32_t vis = 0xFFFFFFFFu >> (31 - j);
+    if (io.parents) {
+        // walk to the root over the parents that the lanes hold (through memory every node was a round trip); a parent outside
+        // [0, node) is treated as node-1 and flagged
+        const int mine = lane <= io.k ? io.parents[b * (io.k + 1) + lane] : 0;
+        depth = 0;
+        vis = 1u << j;
+        for (int i = j; i > 0;) {
+            int p = __builtin_amdgcn_readlane(mine, i);
+            if (p < 0 || p >= i) {
+                if (lane == 0) *err_flag = 1;
+                p = i - 1;
+            }
+            i = p;
+            vis |= 1u << i;
+            ++depth;
+        }
+    }
+    if (lane == 0) {
+        rope_pos[m] = len + depth;
+        anc[m] = vis;
+    }
+}
+
+// grid = (row tiles of 16) * (chunks of EMBED_CHUNK channels) workgroups of 512 threads, and a wave for every row's geometry and every
+// sequence beside them (in the rows' own waves the launch took 1 us longer).  Validates lens/tokens/parents; x = E[token]; packed
+// x*gamma; sums of squares, one per row and chunk.
+// What bounds it: the chain launch -> token -> row, and for many rows its stores (21 MB read and written at 512 x 4096 in 8.4 us).
+// A wave takes a whole operand tile, so its records are 1 KiB in a row; with a row per workgroup each went to a line of its own, 16 bytes
+// of 128.  Row per workgroup / chunks of 512 / of 256 channels, us: 512 rows of 4096 13.0 / 9.0 / 8.4, 160 rows 7.2 / 7.1 / 6.1, tree of
+// 91 rows 7.8 / 6.9 / 6.7, 144 rows of 8192 8.7 / 8.0 / 8.0, 36 rows of 4096 5.4 / 5.2 / 5.2, five rows of 256 3.1 / 2.2 / 2.1.
 __global__ __launch_bounds__(512) void fused_embed_kernel(Dims D, StepIO io, KvGeom kv, const uint16_t *embed, const uint16_t *gamma,
                                                           float *X, uint16_t *A_hi, uint16_t *A_lo, float *ssq,
                                                           int32_t *pos_base, AttnSeq *seq, int32_t *segments, int32_t *rope_pos,
                                                           uint32_t *anc, int32_t *err_flag, AttnPlan plan)
 {
-    const int n_rows = io.B * (io.k + 1);
-    if ((int)blockIdx.x >= n_rows) {
-        const int of = ((int)blockIdx.x - n_rows) * 8 + (threadIdx.x >> 6);
-        if (of < io.B) step_sequence(D, io, kv, plan, of, threadIdx.x & 63, pos_base, seq, segments, err_flag);
+    constexpr int TILES = EMBED_CHUNK / 32 / 8;   // operand tiles per wave
+    const int n_rows = io.B * (io.k + 1), chunks = embed_row_sums(D.h), tiles = (n_rows + 15) >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    if ((int)blockIdx.x >= tiles * chunks) {
+        const int of = ((int)blockIdx.x - tiles * chunks) * 8 + wave;
+        if (of < io.B) step_sequence(D, io, kv, plan, of, lane, pos_base, seq, segments, err_flag);
+        else if (of < io.B + n_rows) step_row(D, io, of - io.B, lane, rope_pos, anc, err_flag);
         return;
     }
-    const int m = blockIdx.x, b = m / (io.k + 1), j = m % (io.k + 1);
-    int tok = io.tokens[m];
+    __shared__ float ss_s[8][16];
+    const int tile = blockIdx.x / chunks, chunk = blockIdx.x % chunks, r = lane & 15, kg = lane >> 4;
+    const int m = tile * 16 + r, KT = (D.h + 31) >> 5, kt0 = (chunk * 8 + wave) * TILES;
+    const bool live = m < n_rows;
+    int tok = io.tokens[live ? m : n_rows - 1];
+    u32x4 g[TILES], e[TILES];   // the caller's arrays are only 2-byte aligned
+#pragma unroll
+    for (int t = 0; t < TILES; ++t) __builtin_memcpy(&g[t], gamma + min((kt0 + t) * 32 + kg * 8, D.h - 8), 16);
     if (tok < 0 || tok >= D.V) {
-        if (threadIdx.x == 0) *err_flag = 1;
+        if (live) *err_flag = 1;
         tok = 0;
     }
-    if (threadIdx.x < 64) {
-        const int lane = threadIdx.x, len = length_or_zero(D, io.k, io.lens[b]);
-        int depth = j;
-        uint32_t vis = 0xFFFFFFFFu >> (31 - j);
-        if (io.parents) {
-            // walk to the root over the parents that the lanes hold (through memory every node was a round trip); a parent outside
-            // [0, node) is treated as node-1 and flagged
-            const int mine = lane <= io.k ? io.parents[b * (io.k + 1) + lane] : 0;
-            depth = 0;
-            vis = 1u << j;
-            for (int i = j; i > 0;) {
-                int p = __builtin_amdgcn_readlane(mine, i);
-                if (p < 0 || p >= i) {
-                    if (lane == 0) *err_flag = 1;
-                    p = i - 1;
-                }
-                i = p;
-                vis |= 1u << i;
-                ++depth;
+#pragma unroll
+    for (int t = 0; t < TILES; ++t) __builtin_memcpy(&e[t], embed + (size_t)tok * D.h + min((kt0 + t) * 32 + kg * 8, D.h - 8), 16);
+    float ss = 0.f;
+#pragma unroll
+    for (int t = 0; t < TILES; ++t) {
+        const int col = (kt0 + t) * 32 + kg * 8;   // h is a multiple of 16
+        f32x4 x[2];
+        u32x4 hi, lo;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const float x0 = __uint_as_float(e[t][c] << 16), x1 = __uint_as_float(e[t][c] & 0xFFFF0000u);
+            uint32_t h2, l2;
+            split_bf16x2(x0 * __uint_as_float(g[t][c] << 16), x1 * __uint_as_float(g[t][c] & 0xFFFF0000u), h2, l2);
+            hi[c] = h2;
+            lo[c] = l2;
+            x[c >> 1][(c & 1) * 2] = x0;
+            x[c >> 1][(c & 1) * 2 + 1] = x1;
+            if (col < D.h) {
+                ss += x0 * x0;
+                ss += x1 * x1;
             }
         }
-        if (lane == 0) {
-            rope_pos[m] = len + depth;
-            anc[m] = vis;
+        if (live && col < D.h) {
+            *reinterpret_cast<f32x4 *>(X + (size_t)m * D.h + col) = x[0];
+            *reinterpret_cast<f32x4 *>(X + (size_t)m * D.h + col + 4) = x[1];
+            const size_t idx = packed_index(m, col, KT);
+            *reinterpret_cast<u32x4 *>(A_hi + idx) = hi;
+            *reinterpret_cast<u32x4 *>(A_lo + idx) = lo;
         }
     }
-    // Eight channels per thread: one 16-byte record of the packed operands (element by element the launch took 15.7 us at 512 rows of
-    // 4096).  The caller's arrays are only 2-byte aligned.
-    const uint16_t *row = embed + (size_t)tok * D.h;
-    const int KT = (D.h + 31) >> 5, NSS = embed_row_sums(D.h), wave = threadIdx.x >> 6;
-    float ss = 0.f;
-    for (int i = threadIdx.x * 8; i < D.h; i += 512 * 8) {   // h is a multiple of 16
-        uint16_t e[8], g[8];
+    ss += __shfl_xor(ss, 16);
+    ss += __shfl_xor(ss, 32);
+    if (kg == 0) ss_s[wave][r] = ss;
+    __syncthreads();
+    if (threadIdx.x < 16 && live) {
+        float all = 0.f;
 #pragma unroll
-        for (int c = 0; c < 8; ++c) { e[c] = row[i + c]; g[c] = gamma[i + c]; }
-        f32x4 x[2];
-        uint32_t hi[4], lo[4];
-#pragma unroll
-        for (int c = 0; c < 8; c += 2) {
-            const float x0 = bf16_to_f32(e[c]), x1 = bf16_to_f32(e[c + 1]);
-            x[c >> 2][c & 3] = x0;
-            x[c >> 2][(c & 3) + 1] = x1;
-            split_bf16x2(x0 * bf16_to_f32(g[c]), x1 * bf16_to_f32(g[c + 1]), hi[c >> 1], lo[c >> 1]);
-            ss += x0 * x0;
-            ss += x1 * x1;
-        }
-        *reinterpret_cast<f32x4 *>(X + (size_t)m * D.h + i) = x[0];
-        *reinterpret_cast<f32x4 *>(X + (size_t)m * D.h + i + 4) = x[1];
-        const size_t idx = packed_index(m, i, KT);
-        *reinterpret_cast<u32x4 *>(A_hi + idx) = u32x4{hi[0], hi[1], hi[2], hi[3]};
-        *reinterpret_cast<u32x4 *>(A_lo + idx) = u32x4{lo[0], lo[1], lo[2], lo[3]};
+        for (int w = 0; w < 8; ++w) all += ss_s[w][threadIdx.x];
+        ssq[(size_t)m * chunks + chunk] = all;
     }
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) ss += __shfl_xor(ss, off);
-    if ((threadIdx.x & 63) == 0 && wave < NSS) ssq[(size_t)m * NSS + wave] = ss;
 }
 
 // Plain read-only stream over a buffer: workgroup b reads the 16 KiB pieces b, b + grid, b + 2 grid, ...,
@@ -620,7 +647,8 @@ hipError_t launch_fused_embed(const Dims &D, const StepIO &io, const KvGeom &kv,
                               float *X, uint16_t *A_hi, uint16_t *A_lo, float *ssq, int32_t *pos_base, AttnSeq *seq, int32_t *segments, int32_t *rope_pos,
                               uint32_t *anc, int32_t *err_flag, hipStream_t s)
 {
-    hipLaunchKernelGGL(fused_embed_kernel, dim3(io.B * (io.k + 1) + (io.B + 7) / 8), dim3(512), 0, s, D, io, kv, embed, gamma, X, A_hi, A_lo, ssq,
+    const int n_rows = io.B * (io.k + 1), tiles = (n_rows + 15) / 16;
+    hipLaunchKernelGGL(fused_embed_kernel, dim3(tiles * embed_row_sums(D.h) + (n_rows + io.B + 7) / 8), dim3(512), 0, s, D, io, kv, embed, gamma, X, A_hi, A_lo, ssq,
                        pos_base, seq, segments, rope_pos, anc, err_flag, attention_plan(D, io.B, io.k));
     return hipGetLastError();
 }

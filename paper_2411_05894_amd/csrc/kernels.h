@@ -111,8 +111,9 @@ size_t stream_gemm_scratch_bytes(int M, int N, int K);   // one GEMM (kernel-lev
 hipError_t launch_stream_gemm(FusedGemmArgs &a, int epilogue, hipStream_t s, bool *needs_epilogue, hipEvent_t t0,
                               hipEvent_t t1);
 hipError_t launch_stream_epilogue(FusedGemmArgs &a, int epilogue, hipStream_t s);
-// Sums of squares per row that the embedding launch leaves: one per wave that has columns, 512 of them each (at most h/16).
-__host__ __device__ __forceinline__ int embed_row_sums(int h) { return h > 3584 ? 8 : (h + 511) / 512; }
+// Sums of squares per row that the embedding launch leaves: one per workgroup, of EMBED_CHUNK channels each (at most h/16).
+constexpr int EMBED_CHUNK = 256;
+__host__ __device__ __forceinline__ int embed_row_sums(int h) { return (h + EMBED_CHUNK - 1) / EMBED_CHUNK; }
 hipError_t launch_fused_embed(const Dims &D, const StepIO &io, const KvGeom &kv, const uint16_t *embed, const uint16_t *gamma,
                               float *X, uint16_t *A_hi, uint16_t *A_lo, float *ssq, int32_t *pos_base, AttnSeq *seq, int32_t *segments, int32_t *rope_pos,
                               uint32_t *anc, int32_t *err_flag, hipStream_t s);
