@@ -464,7 +464,7 @@ __device__ __forceinline__ void swiglu4(const FusedGemmArgs &a, int m, int col, 
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
         const float gg = v0[e] * rs;
-        hv[e] = gg * __builtin_amdgcn_rcpf(1.f + __expf(-gg)) * (v1[e] * rs);   // the reciprocal to one unit in the last place, as the exponential
+        hv[e] = gg / (1.f + __expf(-gg)) * (v1[e] * rs);
     }
     uint2 hi, lo;
     split4(hv, hi, lo);
