@@ -44,6 +44,10 @@ namespace {
 // ------------------------------------------------------------------ M <= 32 ----
 constexpr int PW = 16;  // waves per workgroup
 
+// Sums of squares of a row that an unsplit pgemm_kernel of KPW k-tiles per wave has room for, a whole number per lane: at most two for
+// each of its PW * KPW k-tiles (seven per wave: 224, so four per lane and not three).
+constexpr __host__ __device__ int small_row_sums(int kpw) { return (PW * kpw * 2 + 63) / 64 * 64; }
+
 // A row of operand tiles as a buffer: the tile's place in it is a scalar, the lane's record the only vector part of the address.  With
 // 64-bit vector addresses the first loads of a wave held forty registers.
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t tile_row(const void *p, int KT)
@@ -145,7 +149,7 @@ __global__ __launch_bounds__(PW * 64) void pgemm_kernel(FusedGemmArgs a)
     // under a branch, and nothing else in front of them: 8B step of nine rows 3295 -> 3261 us.
     // The row scales are needed by the first epilogue only: their sums (wave w: of row w) are requested behind the operands and added up
     // behind the first tile's products, so no load of the first tiles waits for them.
-    constexpr int SV = PW * KPW * 2 / 64 > 0 ? PW * KPW * 2 / 64 : 1;   // sums per lane: a whole K of h is at most PW * KPW k-tiles, with two sums each at most
+    constexpr int SV = small_row_sums(KPW) / 64;   // per lane
     float sv[SV];
     const int ms = m_base + wave < a.M ? m_base + wave : a.M - 1;
     if (SCALED && !SPLIT) {
@@ -1281,6 +1285,7 @@ template <int EPI> hipError_t launch_small(FusedGemmArgs &a, hipStream_t s, bool
     a.nss_out = a.h >> 4;
     a.n_part = sp.groups;
     if (a.J > 1 && (size_t)a.J * a.part_rows * a.Ntot * sizeof(float) > a.partial_bytes) return hipErrorInvalidValue;
+    if (EPI != FEPI_RESID && EPI != FEPI_STORE && a.J == 1 && a.nss_in > small_row_sums(kpw)) return hipErrorInvalidValue;
     const dim3 grid(groups * a.J * sp.rh), block(PW * 64);
     if (groups * sp.rh > a.tail_slots) a.tail_count = nullptr;   // no counter for every group: epilogue launch
     const bool one = Unit<EPI>::TILES == 1 && a.upw == 1;   // one tile per workgroup

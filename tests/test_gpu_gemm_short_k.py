@@ -48,3 +48,25 @@ def test_uneven_tiles(tiles, K, M):
     N = 16 * tiles
     assert sv.sssd_op_gemm_kernel_of(M, N, K) == "pgemm_kernel"
     check(N, K, M)
+
+
+# The largest unsplit K of one, two, four, seven and eight k-tiles per wave, and K just past it (1040, the two-tile form's, above; past 4096
+# K is split): the row scales of the second layer add up a sum of squares per 16 columns, as many as a row of these widths has.  3568
+# ends inside its last k-tile.
+@pytest.mark.parametrize("hidden", [512, 528, 1024, 2048, 2064, 3568, 3584, 3600, 4096, 4112])
+@pytest.mark.parametrize("B,k", [(1, 4), (2, 7), (2, 12)])     # 5, 16 and 26 rows
+def test_row_scales_of_the_widest_rows(hidden, B, k):
+    print(f"row scales h={hidden} B={B} k={k}", flush=True)
+    s = SimpleNamespace(name="edge", n_layers=2, hidden=hidden, n_q_heads=2, n_kv_heads=1, head_dim=64, ffn=144, vocab=528, rms_eps=1e-5,
+                        rope_base=10000.0)
+    p = Pair(s, seed=75, max_batch=B, max_k=k, max_seq=64, unit_gains=False)
+    lens = uniform_int(76, B * 64 + k, (B,), 0, 64 - k - 1)
+    for b in range(B):
+        p.prefill_random_kv(77, b, int(lens[b]), oracle_slot=b)
+    tokens = uniform_int(78, B * 64 + k, (B, k + 1), 0, s.vocab - 1)
+    ref = p.oracle.verify_step(tokens, lens.to(torch.int32), return_hidden=True)
+    gpu = p.step(tokens, lens.to(torch.int32))
+    compare_step(gpu, ref, tokens)
+    herr = (gpu["hidden"] - ref["hidden"]).abs().max().item() / ref["hidden"].abs().max().item()
+    assert herr < 5e-3      # a bf16 rounding of a new K or V element may fall the other way: 2^-9 of it
+    p.ctx.sssd_verify_destroy()
