@@ -288,6 +288,14 @@ int sssd_verify_plan_check(const sssd_model_config *cfg, int32_t B, int32_t k)
     const int kin[5] = {D.h, D.qd, D.h, D.f, D.h};
     for (int i = 0; i < 5; ++i)
         if (stream_gemm_launch_bytes(M, (int)ntot[i], kin[i]) > W.partial_bytes) return SSSD_ECAPACITY;
+    // ... and of the room for what their workgroups hand over
+    for (int i = 0; i < 5; ++i)
+        if (stream_gemm_hand_bytes(M, (int)ntot[i], kin[i]) > HAND_PARTS) return SSSD_ECAPACITY;
+    if (HAND_PARTS + HAND_WORDS > W.staging_bytes) return SSSD_ECAPACITY;
+    // sums of squares and arg-max partials per row, laid out behind ssq1 and part_val / part_idx
+    if (embed_row_sums(D.h) > D.h / 16 || stream_gemm_row_values(M, D.h, D.qd, false) > D.h / 16 ||
+        stream_gemm_row_values(M, D.h, D.f, false) > D.h / 16 || stream_gemm_row_values(M, D.V, D.h, true) > D.V / 16)
+        return SSSD_ECAPACITY;
     // attention partial slots: [kv heads][B][segments] x q_rows_pad rows, laid out behind part_o / part_ml
     if ((size_t)D.nkv * B * attention_plan(D, B, k).share > W.attn_slots) return SSSD_ECAPACITY;
     return SSSD_OK;
@@ -401,10 +409,10 @@ int sssd_verify_init(const sssd_model_config *cfg, const sssd_weights *w, void *
         c->n_cu = prop.multiProcessorCount;
     }
     // Workgroups hand results over within a die where all of a device's eight are there and take the workgroups in turn.
-    c->hand = Hand{nullptr, (float *)(c->W.staging + ((size_t)1 << 20)), flags & SSSD_NO_WAIT ? 0 : HAND_POLLS};
+    c->hand = Hand{nullptr, (float *)(c->W.staging + HAND_WORDS), flags & SSSD_NO_WAIT ? 0 : HAND_POLLS};
     {
-        static_assert(HAND_GROUPS * HAND_STRIDE * sizeof(uint32_t) <= (size_t)1 << 20, "the words lie in front of the parts");
-        if (c->W.staging_bytes < HAND_PARTS + ((size_t)1 << 20)) INIT_RC(SSSD_ECAPACITY);
+        static_assert(HAND_GROUPS * HAND_STRIDE * sizeof(uint32_t) <= HAND_WORDS, "the words lie in front of the parts");
+        if (c->W.staging_bytes < HAND_PARTS + HAND_WORDS) INIT_RC(SSSD_ECAPACITY);
         uint32_t *words = (uint32_t *)c->W.staging, strays = 0;
         INIT_TRY(hipMemsetAsync(words, 0, HAND_GROUPS * HAND_STRIDE * sizeof(uint32_t), s));
         INIT_TRY(launch_die_check(words, s));

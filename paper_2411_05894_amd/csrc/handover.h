@@ -22,7 +22,7 @@ constexpr int HAND_STRIDE = 32, HAND_GROUPS = 256;   // ... groups of a launch a
 constexpr uint32_t HAND_ARRIVE = 1u, HAND_LEAVE = 1u << 8, HAND_SLOW = 1u << 16, HAND_GONE = 1u << 24;
 constexpr int HAND_POLLS = 400;   // 0.6 us each: past every difference between workgroups that start together
 
-constexpr size_t HAND_PARTS = (size_t)40 << 20;
+constexpr size_t HAND_WORDS = (size_t)1 << 20, HAND_PARTS = (size_t)40 << 20;   // bytes for the words, and for the parts behind them
 
 struct Hand {            // of a launch
     uint32_t *words;     // HAND_GROUPS * HAND_STRIDE, or null: no hand-over

@@ -104,6 +104,8 @@ const char *stream_gemm_kernel_name(int M, int N, int K);   // the kernel that s
 size_t stream_gemm_partial_bytes(const Dims &D, int M);
 size_t stream_gemm_launch_bytes(int M, int N, int K);    // one GEMM of them
 size_t stream_gemm_scratch_bytes(int M, int N, int K);   // one GEMM (kernel-level entry point)
+int stream_gemm_row_values(int M, int N, int K, bool lm);   // sums of squares (arg-max partials) per row that a GEMM leaves at most
+size_t stream_gemm_hand_bytes(int M, int N, int K);         // of HAND_PARTS that its workgroups use
 // Launches the weight-streaming kernel and records its plan (J, part_rows, ...) in `a`; when
 // *needs_epilogue comes back true the results are split-K partials and launch_stream_epilogue
 // must follow with the same `a`.  With t0/t1 non-null the dispatch stamps them at the kernel's own

@@ -1001,8 +1001,9 @@ __device__ __forceinline__ void qgemm16_rows(const FusedGemmArgs a, int NT16, in
                     const int n_units = first < UW ? e.by_J(UW - 1 - first) + 1 : 0, count = way == HAND_ALL ? UW : n_units;
                     for (int x = threadIdx.x; x < count * 16 * RH; x += QW * 64) {
                         const int k = x / (16 * RH), h = x / 16 % RH, v = first + k * step, m = m_base + 16 * (h * MTW + v / NP) + (x & 15);
-                        const size_t to = (size_t)m * (EPI == FEPI_LM ? e.n_part : e.nss_out) + grp * NP + v % NP;
-                        if (m >= e.M) continue;
+                        const int per_row = EPI == FEPI_LM ? e.n_part : e.nss_out, place = grp * NP + v % NP;
+                        if (m >= e.M || place >= per_row) continue;   // the second pair where there is only one
+                        const size_t to = (size_t)m * per_row + place;
                         float2 all = row_s[k][h * CW][x & 15];
                         if (EPI == FEPI_LM) {
                             Best best{all.x, __float_as_int(all.y)};
@@ -1177,9 +1178,8 @@ __host__ bool is_small(int M, int Ntot, int K)
 // output in memory.  With row blocks no more than the plan above: they fill the device already.
 // Against partial sums and an epilogue launch, us a step: 70B layer at 144 rows 588 -> 570; two 8B layers at 36 rows 443 -> 428, 160 rows
 // 558 -> 544, 512 rows 968 -> 950; layer and head at 91 rows 402 -> 394.
-__host__ bool die_plan(QPlan &p, int KT, int RB, const Hand &hand)
+__host__ bool die_plan(QPlan &p, int KT, int RB)
 {
-    if (!hand.words) return false;
     const int per_die = (p.groups + 7) / 8 * RB;   // workgroups of a die for one slice
     int J = 32 / per_die;
     if (J > KT / 8) J = KT / 8;
@@ -1191,23 +1191,50 @@ __host__ bool die_plan(QPlan &p, int KT, int RB, const Hand &hand)
     return true;
 }
 
+struct LargePlan {
+    QPlan p;
+    RowBlocks rows;
+    bool die;            // slices summed inside the launch
+    int sums, maxima;    // values per row: RESID sums of squares, LM arg-max partials
+    size_t hand_bytes;   // of Hand's parts
+};
+
+// `hand`: the launch has words for a hand-over.  Summed inside the launch every group of columns leaves a value per pair of tiles that its
+// waves hold, two with row blocks -- but no more than there are pairs: one column tile is one pair, and the buffers behind the values
+// have room for one per 16 columns.
+__host__ LargePlan large_plan(int Ntot, int KT, int M, bool hand)
+{
+    const int mt16 = (M + 15) / 16, pairs = (Ntot / 16 + 1) / 2;
+    LargePlan l;
+    l.p = q_plan(Ntot, KT * 32, M);
+    l.rows = row_blocks(mt16);
+    l.die = hand && l.p.J > 1 && die_plan(l.p, KT, l.rows.RB);
+    const int values = l.p.groups * (l.rows.RB > 1 ? 2 : 1);
+    l.sums = l.die && values < pairs ? values : pairs;
+    l.maxima = l.die ? l.sums : l.p.groups;
+    const int units = l.rows.RB > 1 ? 8 : (mt16 < 2 ? 2 : mt16);   // a wave has room for
+    l.hand_bytes = l.die ? (size_t)l.p.groups * l.rows.RB * l.p.J * l.p.qw * units * 2048 : 0;
+    return l;
+}
+
 template <int EPI> hipError_t launch_large(FusedGemmArgs &a, hipStream_t s, bool *needs_epilogue, hipEvent_t t0, hipEvent_t t1)
 {
     const int NT16 = a.Ntot / 16;
-    QPlan p = q_plan(a.Ntot, a.KT * 32, a.M);
+    const LargePlan plan = large_plan(a.Ntot, a.KT, a.M, a.hand.words != nullptr);
+    const QPlan &p = plan.p;
     const int mt16 = (a.M + 15) / 16;
-    const RowBlocks rows = row_blocks(mt16);
-    const bool die = p.J > 1 && die_plan(p, a.KT, rows.RB, a.hand);
+    const RowBlocks &rows = plan.rows;
+    const bool die = plan.die;
     a.J = p.J;
     a.kps = p.kps;
     a.by_J = Div(p.J);
     a.by_RB = Div(rows.RB);
     a.part_rows = round_up(a.M, 16);
     a.epi = EPI;
-    const int halves = rows.RB > 1 ? 2 : 1;   // pairs of column tiles per wave
-    a.nss_out = die ? p.groups * halves : (NT16 + 1) / 2;   // read where this launch leaves them (RESID)
-    a.n_part = die ? p.groups * halves : p.groups;
+    a.nss_out = plan.sums;   // read where this launch leaves them (RESID)
+    a.n_part = plan.maxima;
     *needs_epilogue = a.J > 1 && !die;   // an unsplit K: the kernel applies the epilogue itself
+    if (plan.hand_bytes > HAND_PARTS) return hipErrorInvalidValue;
     if (EPI == FEPI_QKV) { a.seg0 = a.nq * (a.d >> 4); a.seg1 = a.nkv * (a.d >> 4); }
     else if (EPI == FEPI_SWIGLU) { a.seg0 = a.NT; a.seg1 = a.NT; }
     else { a.seg0 = NT16; a.seg1 = 0; }
@@ -1364,6 +1391,28 @@ size_t stream_gemm_partial_bytes(const Dims &D, int M)
         consider(rows, D.V, D.h);
     }
     return most;
+}
+
+// Values per row that a GEMM of M rows leaves at most, whichever form it takes: sums of squares (RESID) or arg-max partials (LM).
+int stream_gemm_row_values(int M, int N, int K, bool lm)
+{
+    const int KT = (K + 31) / 32;
+    if (is_small(M, N, KT * 32)) return N / 16;
+    int most = 0;
+    for (bool hand : {false, true}) {
+        const LargePlan l = large_plan(N, KT, M, hand);
+        const int epi_blocks = l.p.J > 1 && !l.die ? ((N + 31) / 32 + 3) / 4 : 0;   // epi_kernel's: four column blocks per workgroup at least
+        for (int n : {epi_blocks, lm ? l.maxima : l.sums})
+            if (n > most) most = n;
+    }
+    return most;
+}
+
+// Room for what the workgroups of a GEMM of M rows hand over to each other.
+size_t stream_gemm_hand_bytes(int M, int N, int K)
+{
+    const int KT = (K + 31) / 32;
+    return is_small(M, N, KT * 32) ? 0 : large_plan(N, KT, M, true).hand_bytes;
 }
 
 // What the kernel-level entry points ask for.  qgemm16_kernel applies the epilogue of a whole K itself and touches no scratch, but one

@@ -65,6 +65,7 @@ static void sweep_plans()
         {{80, 8192, 64, 8, 128, 28672, 128256, 1e-5f, 500000.f, 16, 8, 2057}, "70b"},
         {{2, 1040, 5, 5, 64, 2064, 4112, 1e-5f, 10000.f, 3, 7, 77}, "odd widths"},
         {{1, 64, 1, 1, 64, 16, 16, 1e-5f, 10000.f, 1, 0, 1}, "smallest"},
+        {{1, 16, 2, 1, 64, 512, 16, 1e-5f, 10000.f, 16, 31, 64}, "one tile"},
         {{2, 4096, 32, 8, 128, 14336, 128256, 1e-5f, 500000.f, 4, 8, 32777}, "long context"},
     };
     for (const Case &cs : cases) {

@@ -95,3 +95,16 @@ def test_workspace_holds_no_copy_of_logits_that_no_launch_splits_without_gpu():
     ws = [sv.sssd_verify_sizes(sv.make_config(SimpleNamespace(**{**base, "vocab": v}), 16, 31, 512))[1] for v in (1024, 128256)]
     rows = 640                                    # 16 * 32 in blocks of 160
     assert ws[1] - ws[0] <= 8 * rows * (128256 - 1024) // 16 + 1024
+
+
+def test_plans_fit_models_of_a_single_column_tile_without_gpu():
+    """A hidden size or a vocabulary of 16 leaves one sum of squares or arg-max partial per row, and the buffers hold no more: with row
+    blocks (more than 160 rows) and a K split over workgroups, too."""
+    from types import SimpleNamespace
+    for hidden, ffn, vocab in ((512, 48, 16), (1040, 48, 16), (16, 512, 528), (16, 4096, 16), (32, 1024, 32), (272, 512, 272)):
+        s = SimpleNamespace(n_layers=1, hidden=hidden, n_q_heads=2, n_kv_heads=1, head_dim=64, ffn=ffn, vocab=vocab, rms_eps=1e-5,
+                            rope_base=10000.0)
+        cfg = sv.make_config(s, 16, 31, 64)
+        for B in range(1, 17):
+            for k in range(32):
+                assert sv.lib().sssd_verify_plan_check(C.byref(cfg), B, k) == sv.SSSD_OK, (hidden, ffn, vocab, B, k)

@@ -90,3 +90,23 @@ def test_split_gemms_summed_inside_the_launch(hidden, nq, nkv, d, ffn, vocab, B,
             for name in ("logits", "hidden", "that", "accepted_len", "next_token"):
                 assert torch.equal(got[name], first[name]), (name, i, pair is late)
         pair.ctx.sssd_verify_destroy()
+
+
+# One column tile, so one arg-max partial or sum of squares per row, in row blocks whose waves hold two pairs of tiles
+@pytest.mark.parametrize("hidden,ffn,vocab", [(512, 48, 16), (16, 512, 528)])
+@pytest.mark.parametrize("B,k", [(11, 15), (16, 31)])   # 176 and 512 rows
+def test_a_single_column_tile(hidden, ffn, vocab, B, k):
+    s = SimpleNamespace(name="edge", n_layers=2, hidden=hidden, n_q_heads=2, n_kv_heads=1, head_dim=64, ffn=ffn, vocab=vocab, rms_eps=1e-5,
+                        rope_base=10000.0)
+    print(f"single column tile h={hidden} ffn={ffn} vocab={vocab} B={B} k={k}", flush=True)
+    p = Pair(s, seed=81, max_batch=B, max_k=k, max_seq=96, unit_gains=False)
+    lens = uniform_int(82, B * 64 + k, (B,), 0, 96 - k - 1).to(torch.int32)
+    for b in range(B):
+        p.prefill_random_kv(83, b, int(lens[b]), oracle_slot=b)
+    tokens = uniform_int(84, B * 64 + k, (B, k + 1), 0, s.vocab - 1)
+    ref = p.oracle.verify_step(tokens, lens, return_hidden=True)
+    got = p.step(tokens, lens)
+    compare_step(got, ref, tokens)
+    herr = (got["hidden"] - ref["hidden"]).abs().max().item() / ref["hidden"].abs().max().item()
+    assert herr < 5e-3   # a bf16 rounding of a new K or V element may fall the other way: 2^-9 of it
+    p.ctx.sssd_verify_destroy()
