@@ -265,6 +265,13 @@ int sssd_debug_logits(sssd_ctx *ctx, float *logits);
  * step.  This is the vector the acceptance walk consumes, so a test can hold it against an
  * independent arg-max row by row.  NULL switches the store off. */
 int sssd_debug_argmax(sssd_ctx *ctx, int32_t *that);
+/* Which launches of a step of B sequences x k drafts add up their workgroups' partial results
+ * inside the launch (else a second launch does, or there are none): bits 0..4 of *launches are the
+ * QKV, O, gate/up, down and LM-head products, bit 5 is attention.  *late: how many groups of
+ * workgroups have not waited for each other since sssd_verify_init (SSSD_NO_WAIT: all of them);
+ * waits for `stream`.  launches and late are host pointers; either may be NULL. */
+int sssd_debug_handover(sssd_ctx *ctx, int32_t B, int32_t k, uint32_t *launches, uint32_t *late,
+                        void *stream);
 
 /*
  * Copy cache rows in (e.g. a prefilled prompt) or out, enqueued on `stream`.

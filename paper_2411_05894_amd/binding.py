@@ -88,6 +88,7 @@ def lib() -> C.CDLL:
         l.sssd_debug_outputs.argtypes = [vp, vp, vp]
         l.sssd_debug_logits.argtypes = [vp, vp]
         l.sssd_debug_argmax.argtypes = [vp, vp]
+        l.sssd_debug_handover.argtypes = [vp, i32, i32, vp, vp, vp]
         l.sssd_kv_import.argtypes = [vp, i32, i32, i32, i32, vp, vp, vp]
         l.sssd_kv_export.argtypes = [vp, i32, i32, i32, i32, vp, vp, vp]
         l.sssd_profile_enable.argtypes = [vp, i32]
@@ -237,6 +238,12 @@ class VerifyContext:
 
     def sssd_debug_argmax(self, that: Optional[torch.Tensor]) -> None:
         _check(lib().sssd_debug_argmax(self.handle, _ptr(that)), "sssd_debug_argmax")
+
+    def sssd_debug_handover(self, B: int, k: int):
+        """(launches of a step that add up partial results inside the launch, groups of workgroups that did not wait so far)"""
+        launches, late = C.c_uint32(), C.c_uint32()
+        _check(lib().sssd_debug_handover(self.handle, B, k, C.byref(launches), C.byref(late), _stream()), "sssd_debug_handover")
+        return launches.value, late.value
 
     def sssd_kv_import(self, layer: int, b: int, t0: int, k_src: torch.Tensor, v_src: torch.Tensor) -> None:
         assert k_src.dtype == torch.bfloat16 and k_src.shape == v_src.shape

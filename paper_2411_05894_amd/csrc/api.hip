@@ -411,10 +411,10 @@ int sssd_verify_init(const sssd_model_config *cfg, const sssd_weights *w, void *
     // Workgroups hand results over within a die where all of a device's eight are there and take the workgroups in turn.
     c->hand = Hand{nullptr, (float *)(c->W.staging + HAND_WORDS), flags & SSSD_NO_WAIT ? 0 : HAND_POLLS};
     {
-        static_assert(HAND_GROUPS * HAND_STRIDE * sizeof(uint32_t) <= HAND_WORDS, "the words lie in front of the parts");
+        static_assert(HAND_WORD_COUNT * sizeof(uint32_t) <= HAND_WORDS, "the words lie in front of the parts");
         if (c->W.staging_bytes < HAND_PARTS + HAND_WORDS) INIT_RC(SSSD_ECAPACITY);
         uint32_t *words = (uint32_t *)c->W.staging, strays = 0;
-        INIT_TRY(hipMemsetAsync(words, 0, HAND_GROUPS * HAND_STRIDE * sizeof(uint32_t), s));
+        INIT_TRY(hipMemsetAsync(words, 0, HAND_WORD_COUNT * sizeof(uint32_t), s));
         INIT_TRY(launch_die_check(words, s));
         INIT_TRY(hipMemcpyAsync(&strays, words, sizeof(strays), hipMemcpyDeviceToHost, s));
         INIT_TRY(hipMemsetAsync(words, 0, sizeof(uint32_t), s));
@@ -458,6 +458,27 @@ int sssd_debug_argmax(sssd_ctx *c, int32_t *that)
 {
     if (!valid(c)) return SSSD_EINVAL;
     c->dbg_that = that;
+    return SSSD_OK;
+}
+
+int sssd_debug_handover(sssd_ctx *c, int32_t B, int32_t k, uint32_t *launches, uint32_t *late, void *stream)
+{
+    if (!valid(c) || B <= 0 || k < 0) return SSSD_EINVAL;
+    const Dims &D = c->D;
+    if (B > D.max_batch || k > D.max_k) return SSSD_ECAPACITY;
+    uint32_t on = 0, n = 0;
+    if (c->hand.words) {
+        const int M = B * (k + 1), ntot[5] = {D.qd + 2 * D.kd, D.h, 2 * D.f, D.h, D.V}, kin[5] = {D.h, D.qd, D.h, D.f, D.h};
+        for (int i = 0; i < 5; ++i) on |= (uint32_t)stream_gemm_hands_over(M, ntot[i], kin[i]) << i;
+        on |= (uint32_t)attention_hands_over(D, attention_plan(D, B, k), B) << 5;
+        if (late) {
+            hipStream_t s = (hipStream_t)stream;
+            HIP_TRY(hipMemcpyAsync(&n, c->hand.words + HAND_LATE, sizeof(n), hipMemcpyDeviceToHost, s));
+            HIP_TRY(hipStreamSynchronize(s));
+        }
+    }
+    if (launches) *launches = on;
+    if (late) *late = n;
     return SSSD_OK;
 }
 

@@ -662,6 +662,10 @@ static bool attention_in_die(const Dims &D, const AttnPlan &p, int B)
     return B * D.nkv % 8 == 0 && groups <= HAND_GROUPS && groups * p.share <= 512;
 }
 
+static bool attention_merges(const Dims &D, const AttnPlan &p) { return p.share > 1 && D.blocks_per_seq > ATTN_WHOLE_BLOCKS; }
+
+bool attention_hands_over(const Dims &D, const AttnPlan &p, int B) { return attention_merges(D, p) && attention_in_die(D, p, B); }
+
 // Most partial results that any step of up to B sequences leaves, all kv heads.
 size_t attention_slots(const Dims &D, int B)
 {
@@ -684,8 +688,8 @@ hipError_t launch_attention(const Dims &D, const AttnArgs &a_in, hipStream_t s)
     a.by_share = Div(a.plan.share);
     a.by_nkv = Div(D.nkv);
     a.by_g = Div(D.g);
-    const bool merge = a.plan.share > 1 && D.blocks_per_seq > ATTN_WHOLE_BLOCKS;
-    if (!merge || !attention_in_die(D, a.plan, a.B)) a.hand.words = nullptr;
+    const bool merge = attention_merges(D, a.plan);
+    if (!attention_hands_over(D, a.plan, a.B)) a.hand.words = nullptr;
     hipError_t e = D.d == 128 ? launch_partial<128>(D, a, q_rows_pad, s) : launch_partial<64>(D, a, q_rows_pad, s);
     if (e != hipSuccess) return e;
     // No merge where no sequence can have two segments.  With every workgroup of the merge returning at once the launch still

@@ -8,11 +8,11 @@
 // launch that reads them; with 64 KB 2.7, 8.0 and 5.8 us.
 //
 // Nothing here relies on where a workgroup runs or on all of them running at once:
-//  - a workgroup that finds itself on another die than its block index says, or that has polled `polls` times for the others, gives
-//    the fast way up for its whole group (HAND_GONE); that succeeds only while not everybody has arrived, so the group's workgroups
-//    agree on the way taken;
+//  - a workgroup that finds itself on another die than its block index says, that may not wait (no `polls`), or that has polled `polls`
+//    times for the others, gives the fast way up for its whole group (HAND_GONE); that succeeds only while not everybody has arrived, so
+//    the group's workgroups agree on the way taken;
 //  - then each makes its stores visible to the device (a release fence, about 20 us) and counts itself in a second time, and the last
-//    one to do so does the whole group's work.  No wait is without a bound, and nobody waits for a workgroup that has not started.
+//    one to do so does the whole group's work.  So no wait is without a bound.
 #pragma once
 #include "common.h"
 
@@ -21,13 +21,14 @@
 constexpr int HAND_STRIDE = 32, HAND_GROUPS = 256;   // ... groups of a launch at most (of up to 255 workgroups)
 constexpr uint32_t HAND_ARRIVE = 1u, HAND_LEAVE = 1u << 8, HAND_SLOW = 1u << 16, HAND_GONE = 1u << 24;
 constexpr int HAND_POLLS = 400;   // 0.6 us each: past every difference between workgroups that start together
+constexpr int HAND_LATE = HAND_GROUPS * HAND_STRIDE, HAND_WORD_COUNT = HAND_LATE + 1;   // behind the groups' words: how many groups went the slow way
 
 constexpr size_t HAND_WORDS = (size_t)1 << 20, HAND_PARTS = (size_t)40 << 20;   // bytes for the words, and for the parts behind them
 
 struct Hand {            // of a launch
-    uint32_t *words;     // HAND_GROUPS * HAND_STRIDE, or null: no hand-over
+    uint32_t *words;     // HAND_WORD_COUNT, or null: no hand-over
     float *parts;        // HAND_PARTS bytes for what GEMMs hand over: 256 workgroups of ten units of 2 KiB in each of eight waves
-    int polls;           // HAND_POLLS, or 0: nobody waits, and most groups go the slow way
+    int polls;           // HAND_POLLS, or 0: nobody waits, every group goes the slow way
 };
 
 enum HandWay {
@@ -50,7 +51,7 @@ __device__ __forceinline__ uint32_t hand_arrive(const Hand &h, int group)
     __syncthreads();
     if (threadIdx.x != 0) return 0;
     uint32_t *word = h.words + (size_t)group * HAND_STRIDE;
-    if (on_own_die()) return __hip_atomic_fetch_add(word, HAND_ARRIVE, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + HAND_ARRIVE;
+    if (h.polls > 0 && on_own_die()) return __hip_atomic_fetch_add(word, HAND_ARRIVE, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + HAND_ARRIVE;
     // not counted in: the others cannot all arrive
     return __hip_atomic_fetch_or(word, HAND_GONE, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) | HAND_GONE;
 }
@@ -82,6 +83,7 @@ __device__ __forceinline__ HandWay hand_turn_in(const Hand &h, int group, int n,
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
         const uint32_t old = __hip_atomic_fetch_add(word, HAND_SLOW, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         const bool last = (int)(old >> 16 & 0xFFu) == n - 1;
+        if (last) atomicAdd(h.words + HAND_LATE, 1u);
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
         *way_s = last ? HAND_ALL : HAND_NOTHING;
     }

@@ -106,6 +106,7 @@ size_t stream_gemm_launch_bytes(int M, int N, int K);    // one GEMM of them
 size_t stream_gemm_scratch_bytes(int M, int N, int K);   // one GEMM (kernel-level entry point)
 int stream_gemm_row_values(int M, int N, int K, bool lm);   // sums of squares (arg-max partials) per row that a GEMM leaves at most
 size_t stream_gemm_hand_bytes(int M, int N, int K);         // of HAND_PARTS that its workgroups use
+bool stream_gemm_hands_over(int M, int N, int K);           // its slices are summed inside the launch, where that has words for it
 // Launches the weight-streaming kernel and records its plan (J, part_rows, ...) in `a`; when
 // *needs_epilogue comes back true the results are split-K partials and launch_stream_epilogue
 // must follow with the same `a`.  With t0/t1 non-null the dispatch stamps them at the kernel's own
@@ -178,4 +179,6 @@ struct AttnArgs {
 };
 // Partial slots of a step of B sequences, all kv heads (sizes the buffers).
 size_t attention_slots(const Dims &D, int B);
+// Segments of a step are merged inside the launch, where that has words for it.
+bool attention_hands_over(const Dims &D, const AttnPlan &p, int B);
 hipError_t launch_attention(const Dims &D, const AttnArgs &a, hipStream_t s);

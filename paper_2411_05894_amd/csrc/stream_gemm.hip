@@ -1408,7 +1408,13 @@ int stream_gemm_row_values(int M, int N, int K, bool lm)
     return most;
 }
 
-// Room for what the workgroups of a GEMM of M rows hand over to each other.
+// Whether a GEMM of M rows, in a launch that has words for it, sums its slices inside the launch; room for what its workgroups hand over.
+bool stream_gemm_hands_over(int M, int N, int K)
+{
+    const int KT = (K + 31) / 32;
+    return !is_small(M, N, KT * 32) && large_plan(N, KT, M, true).die;
+}
+
 size_t stream_gemm_hand_bytes(int M, int N, int K)
 {
     const int KT = (K + 31) / 32;

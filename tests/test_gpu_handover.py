@@ -1,6 +1,7 @@
-"""Partial results handed over between the workgroups of one launch (one die's workgroups share its L2).  A context created with
-SSSD_NO_WAIT never waits for the others, so its last workgroups do whole groups' work: the way taken when workgroups do not arrive in
-time.  Both ways must give the reference and the same bits, launch after launch (the words between them are zero again)."""
+"""Partial results handed over between the workgroups of one launch (one die's workgroups share its L2).  In a context created with
+SSSD_NO_WAIT nobody waits for the others, so the last workgroup of every group does all of its work: the way taken when workgroups do not
+arrive in time.  Both ways must give the reference and the same bits, launch after launch (the words between them are zero again); the
+context says which launches hand over and how many groups took the slow way."""
 from types import SimpleNamespace
 
 import pytest
@@ -14,6 +15,7 @@ from sssd_synth import MODEL_SHAPES, global_weight_specs, layer_weight_specs, no
 from test_gpu_attention_segments import reference
 
 DEV = "cuda:0"
+QKV, O, GATE_UP, DOWN, LM, ATTENTION = (1 << i for i in range(6))   # bits of sssd_debug_handover
 
 
 def attention_context(shape_name, B, k, max_seq, no_wait):
@@ -30,11 +32,12 @@ def attention_context(shape_name, B, k, max_seq, no_wait):
     ("8b", 0, [5000], 5001),               # four rows for 32 segments: most have nothing to merge
     ("8b", 17, [700, 12345], 12400),       # five row tiles, two passes
     ("8b", 31, [1500, 40, 3000], 3100),    # a sequence of one segment beside merged ones
-    ("8b", 12, [900 + 100 * i for i in range(14)], 4000),   # passes of two tiles, two workgroups per compute unit
+    ("8b", 12, [900 + 100 * i for i in range(8)], 4000),    # two passes of two tiles
+    ("8b", 31, [900 + 100 * i for i in range(9)], 4000),    # two passes of four tiles, up to two workgroups per compute unit
     ("tiny", 4, [300, 2000, 5, 1000], 2100)])               # two kv heads, head size 64
 def test_attention_merged_inside_the_launch(shape_name, k, lens, max_seq):
     B, sq = len(lens), k + 1
-    outs = []
+    outs, late = [], []
     for no_wait in (False, True):
         s, ctx = attention_context(shape_name, B, k, max_seq, no_wait=no_wait)
         q = (normal_bf16(51, 1, (B, sq, s.n_q_heads, s.head_dim), 1.0, device=DEV).float() * 1.28).contiguous()
@@ -48,6 +51,12 @@ def test_attention_merged_inside_the_launch(shape_name, k, lens, max_seq):
             ctx.sssd_op_attention(0, q, torch.tensor(lens, dtype=torch.int32, device=DEV), out)
             assert ctx.sssd_verify_sync() == 0
             outs.append(out.clone())
+            launches, n = ctx.sssd_debug_handover(B, k)
+            assert launches & ATTENTION, "merged by a second launch"
+            if i == 0: groups = n        # of sequences of more than one segment
+            if no_wait: assert n == (i + 1) * groups > 0
+        late.append(n)
+    assert late[0] < late[1]
     got = outs[0].view(B, sq, s.n_q_heads, s.head_dim)
     for b in range(B):   # as test_gpu_attention_segments: operands in bf16 pairs, ~2^-17 relative
         assert (got[b] - reference(q[b], *kv[b], lens[b], s.n_q_heads // s.n_kv_heads)).abs().max().item() <= 1e-4, b
@@ -55,7 +64,7 @@ def test_attention_merged_inside_the_launch(shape_name, k, lens, max_seq):
         assert torch.equal(o, outs[0])
 
 
-# K in two slices and more everywhere but in the QKV and gate/up projections of the smaller model: 24 and 65 k-tiles (slices of unequal
+# K in two slices and more everywhere but in the O projection of the smaller model: 17 to 65 k-tiles (slices of unequal
 # length), units of one to ten row tiles shared out over as few as two and as many as eight slices, blocks of eight and six row tiles, column groups
 # that end inside the matrix, more slices than units; an LM head of few columns
 @pytest.mark.parametrize("hidden,nq,nkv,d,ffn,vocab", [(768, 6, 2, 128, 2064, 1040), (528, 4, 4, 64, 1120, 4112)])
@@ -76,7 +85,7 @@ def test_split_gemms_summed_inside_the_launch(hidden, nq, nkv, d, ffn, vocab, B,
         late.prefill_random_kv(63, b, int(lens[b]))
     tokens = uniform_int(64, B * 64 + k, (B, k + 1), 0, s.vocab - 1)
     ref = p.oracle.verify_step(tokens, lens, return_hidden=True)
-    first = None
+    first, slow = None, []
     for pair in (p, late):
         print(f"hand-over step h={hidden} ffn={ffn} B={B} k={k} no_wait={pair is late}", flush=True)
         for i in range(4):
@@ -89,7 +98,13 @@ def test_split_gemms_summed_inside_the_launch(hidden, nq, nkv, d, ffn, vocab, B,
                 assert herr < 5e-3   # a bf16 rounding of a new K or V element may fall the other way: 2^-9 of it
             for name in ("logits", "hidden", "that", "accepted_len", "next_token"):
                 assert torch.equal(got[name], first[name]), (name, i, pair is late)
+            launches, n = pair.ctx.sssd_debug_handover(B, k)
+            assert launches == QKV | GATE_UP | DOWN | LM | (O if hidden == 768 else 0)
+            if i == 0: groups = n
+            if pair is late: assert n == (i + 1) * groups > 0
+        slow.append(n)
         pair.ctx.sssd_verify_destroy()
+    assert slow[0] < slow[1]
 
 
 # One column tile, so one arg-max partial or sum of squares per row, in row blocks whose waves hold two pairs of tiles
