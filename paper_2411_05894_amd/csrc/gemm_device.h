@@ -374,7 +374,8 @@ __device__ __forceinline__ void lm8(const FusedGemmArgs &a, int m, int n0, float
 
 // ---- four columns per lane ----
 // qgemm16_kernel multiplies weights x activations, so a lane holds columns 4*(l/16)..+3 of row l%16 of every 16 x 16 tile: the
-// epilogues below work on the accumulators as they are.  What they read from memory can be requested ahead.
+// epilogues below work on the accumulators as they are.  What they read from memory can be requested ahead.  Args: the fields of
+// FusedGemmArgs that they read.
 struct QuadIn {
     f32x4 x0, x1;       // RESID: residual of both tiles; QKV: (cos, sin) of channels 0, 1 and of 2, 3
     uint2 g0, g1;       // RESID: gains of both tiles
@@ -408,7 +409,7 @@ __device__ __forceinline__ float row_sum4(float x)
 
 // RESID: X += v, packed X * gamma at columns col..col+3 of row m.  Returns the sum of squares of the updated columns.
 // (m, col / 8) are the same in the two lanes of a pair, and both call it: so with all below.
-__device__ __forceinline__ float resid4(const FusedGemmArgs &a, int m, int col, const f32x4 &v, const f32x4 &x, const uint2 &gamma)
+template <typename Args> __device__ __forceinline__ float resid4(const Args &a, int m, int col, const f32x4 &v, const f32x4 &x, const uint2 &gamma)
 {
     const f32x4 xn = x + v;
     const f32x4 g = {bits_f32(gamma.x << 16), bits_f32(gamma.x & 0xFFFF0000u), bits_f32(gamma.y << 16), bits_f32(gamma.y & 0xFFFF0000u)};
@@ -421,7 +422,7 @@ __device__ __forceinline__ float resid4(const FusedGemmArgs &a, int m, int col, 
 }
 
 // QKV: v0 at channels ch..ch+3 of the first half of a head, v1 at the same channels of the second half.
-__device__ __forceinline__ void qkv4(const FusedGemmArgs &a, int m, int head, int ch, float rs, f32x4 v0, f32x4 v1, const QuadIn &in)
+template <typename Args> __device__ __forceinline__ void qkv4(const Args &a, int m, int head, int ch, float rs, f32x4 v0, f32x4 v1, const QuadIn &in)
 {
     const int half = a.d >> 1;
     const int b = a.by_k1(m), j = m - b * (a.k + 1);
@@ -458,7 +459,7 @@ __device__ __forceinline__ void qkv4(const FusedGemmArgs &a, int m, int head, in
 }
 
 // SWIGLU: gate v0, up v1 at columns col..col+3 of the FFN.
-__device__ __forceinline__ void swiglu4(const FusedGemmArgs &a, int m, int col, float rs, const f32x4 &v0, const f32x4 &v1)
+template <typename Args> __device__ __forceinline__ void swiglu4(const Args &a, int m, int col, float rs, const f32x4 &v0, const f32x4 &v1)
 {
     f32x4 hv;
 #pragma unroll
@@ -473,7 +474,7 @@ __device__ __forceinline__ void swiglu4(const FusedGemmArgs &a, int m, int col, 
 }
 
 // LM: logits (if asked for), and columns n0..n0+3 of row m into the row's running arg-max.
-__device__ __forceinline__ void lm4(const FusedGemmArgs &a, int m, int n0, float rs, f32x4 v, Best &best)
+template <typename Args> __device__ __forceinline__ void lm4(const Args &a, int m, int n0, float rs, f32x4 v, Best &best)
 {
     v *= rs;
 #pragma unroll

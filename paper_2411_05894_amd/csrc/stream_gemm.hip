@@ -504,12 +504,12 @@ template <int ROWS, int QW> struct RowScales {
             }
         }
     }
-    __device__ __forceinline__ void add(const FusedGemmArgs &a, int t0, float (&sum)[TURNS])
+    __device__ __forceinline__ void add(int n, int t0, float (&sum)[TURNS])
     {
 #pragma unroll
         for (int i = 0; i < TURNS; ++i)
 #pragma unroll
-            for (int u = 0; u < U; ++u) sum[i] += t0 + (int)(threadIdx.x & 15) + 16 * u < a.nss_in ? v[i][u] : 0.f;
+            for (int u = 0; u < U; ++u) sum[i] += t0 + (int)(threadIdx.x & 15) + 16 * u < n ? v[i][u] : 0.f;
     }
     // Without `scaled` (no sums to read) it loads activations for nothing: under a branch the first sum, and so the wait for it, comes
     // before the first operands are requested (1 us of 1B..70B gate/up launches).
@@ -517,15 +517,15 @@ template <int ROWS, int QW> struct RowScales {
     {
         load(scaled ? a.ssq_in : reinterpret_cast<const float *>(a.A_hi), scaled ? a.nss_in : 1, a.M, m0, 0);
     }
-    __device__ __forceinline__ void finish(const FusedGemmArgs &a, int m0, float *rstd_s)
+    template <typename Args> __device__ __forceinline__ void finish(const Args &a, int m0, float *rstd_s)
     {
         float sum[TURNS];
 #pragma unroll
         for (int i = 0; i < TURNS; ++i) sum[i] = 0.f;
-        add(a, 0, sum);
+        add(a.nss_in, 0, sum);
         for (int t0 = 16 * U; t0 < a.nss_in; t0 += 16 * U) {
             load(a.ssq_in, a.nss_in, a.M, m0, t0);
-            add(a, t0, sum);
+            add(a.nss_in, t0, sum);
         }
 #pragma unroll
         for (int i = 0; i < TURNS; ++i) {
@@ -581,33 +581,46 @@ template <int MT16, int QW, bool BLOCKS, int FORM> struct QShape {
     static constexpr int LDS = RING > STAGE ? RING : STAGE;
 };
 
-// What the epilogues read of the launch's first argument, loaded where it is called: loaded in front of the main loop, as the compiler does
-// by itself, these sixty scalars are moved into vector registers and back (130 instructions in front of the first load).
-__device__ __forceinline__ FusedGemmArgs epilogue_arguments()
+// What qgemm16_kernel's epilogues read of FusedGemmArgs, its first argument: these fields and no others, so an epilogue that needs one more
+// does not compile before it is named here.
+#define SSSD_EPILOGUE_VALUES(V)                                                                                                        \
+    V(M) V(h) V(d) V(nq) V(nkv) V(k) V(q_rows_pad) V(vocab) V(eps) V(nss_in) V(nss_out) V(KT_out) V(n_part) V(Ntot) V(J) V(epi)
+#define SSSD_EPILOGUE_POINTERS(P)                                                                                                      \
+    P(X) P(ssq_out) P(out_hi) P(out_lo) P(Qp) P(Qp_lo) P(Kc) P(Vc) P(logits) P(part_val) P(part_idx) P(out) P(ssq_in) P(gamma_next)    \
+    P(rope_cs) P(pos_base) P(rope_pos)
+struct EpilogueArgs {
+#define SSSD_FIELD(f) decltype(FusedGemmArgs::f) f;
+    SSSD_EPILOGUE_VALUES(SSSD_FIELD)
+    SSSD_EPILOGUE_POINTERS(SSSD_FIELD)
+#undef SSSD_FIELD
+    Div by_J, by_k1, by_g;
+    KvGeom kv;
+    Hand hand;
+};
+
+// Loaded where it is called: loaded in front of the main loop, as the compiler does by itself, these sixty scalars are moved into
+// vector registers and back (130 instructions in front of the first load).
+__device__ __forceinline__ EpilogueArgs epilogue_arguments()
 {
     using Constant = const __attribute__((address_space(4))) FusedGemmArgs;
     Constant *p = (Constant *)__builtin_amdgcn_kernarg_segment_ptr();
     asm volatile("" : "+s"(p));   // not before
-    FusedGemmArgs e{};
-#define SSSD_VALUE(f) e.f = p->f
-#define SSSD_POINTER(f) e.f = (decltype(e.f))(__attribute__((address_space(1))) void *)(void *)p->f
-    SSSD_VALUE(M); SSSD_VALUE(h); SSSD_VALUE(d); SSSD_VALUE(nq); SSSD_VALUE(nkv); SSSD_VALUE(k); SSSD_VALUE(q_rows_pad); SSSD_VALUE(vocab);
-    SSSD_VALUE(eps); SSSD_VALUE(nss_in); SSSD_VALUE(nss_out); SSSD_VALUE(KT_out); SSSD_VALUE(n_part); SSSD_VALUE(Ntot); SSSD_VALUE(J); SSSD_VALUE(epi);
-    SSSD_VALUE(by_J.d); SSSD_VALUE(by_J.m); SSSD_VALUE(by_k1.d); SSSD_VALUE(by_k1.m); SSSD_VALUE(by_g.d); SSSD_VALUE(by_g.m);
-    SSSD_VALUE(kv.blocks_per_seq); SSSD_VALUE(kv.n_pages); SSSD_VALUE(kv.nkv); SSSD_VALUE(kv.d); SSSD_VALUE(hand.polls);
-    SSSD_POINTER(X); SSSD_POINTER(ssq_out); SSSD_POINTER(out_hi); SSSD_POINTER(out_lo); SSSD_POINTER(Qp); SSSD_POINTER(Qp_lo);
-    SSSD_POINTER(Kc); SSSD_POINTER(Vc); SSSD_POINTER(logits); SSSD_POINTER(part_val); SSSD_POINTER(part_idx); SSSD_POINTER(out);
-    SSSD_POINTER(hand.words); SSSD_POINTER(hand.parts);
-    e.ssq_in = (const float *)(__attribute__((address_space(1))) const void *)(const void *)p->ssq_in;
-    e.gamma_next = (const uint16_t *)(__attribute__((address_space(1))) const void *)(const void *)p->gamma_next;
-    e.rope_cs = (const float *)(__attribute__((address_space(1))) const void *)(const void *)p->rope_cs;
-    e.pos_base = (const int32_t *)(__attribute__((address_space(1))) const void *)(const void *)p->pos_base;
-    e.rope_pos = (const int32_t *)(__attribute__((address_space(1))) const void *)(const void *)p->rope_pos;
-    e.kv.table = (const int32_t *)(__attribute__((address_space(1))) const void *)(const void *)p->kv.table;
+    EpilogueArgs e;
+#define SSSD_VALUE(f) e.f = p->f;
+#define SSSD_POINTER(f) e.f = (decltype(e.f))(__attribute__((address_space(1))) const void *)(const void *)p->f;
+    SSSD_EPILOGUE_VALUES(SSSD_VALUE)
+    SSSD_EPILOGUE_POINTERS(SSSD_POINTER)
+    // member by member, all of them: there is no copy out of constant memory
+    static_assert(sizeof(Div) == 8 && sizeof(KvGeom) == 24 && sizeof(Hand) == 24, "every member is loaded below");
+    SSSD_VALUE(by_J.d) SSSD_VALUE(by_J.m) SSSD_VALUE(by_k1.d) SSSD_VALUE(by_k1.m) SSSD_VALUE(by_g.d) SSSD_VALUE(by_g.m)
+    SSSD_POINTER(kv.table) SSSD_VALUE(kv.blocks_per_seq) SSSD_VALUE(kv.n_pages) SSSD_VALUE(kv.nkv) SSSD_VALUE(kv.d)
+    SSSD_POINTER(hand.words) SSSD_POINTER(hand.parts) SSSD_VALUE(hand.polls)
 #undef SSSD_VALUE
 #undef SSSD_POINTER
     return e;
 }
+#undef SSSD_EPILOGUE_VALUES
+#undef SSSD_EPILOGUE_POINTERS
 
 // Rows 16 * tile0 .. 16 * (tile0 + MT16) - 1, column group grp, slice j; set: the group of workgroups that hand over to each other (DIE).
 template <int MT16, int QW, bool BLOCKS, int FORM>
@@ -778,7 +791,7 @@ __device__ __forceinline__ void qgemm16_rows(const FusedGemmArgs a, int NT16, in
         }
         return;
     }
-    const FusedGemmArgs e = epilogue_arguments();
+    const EpilogueArgs e = epilogue_arguments();
     // A unit is a wave's pair p of column tiles on row tile i: an epilogue unit (rotary partners, gate and up) or 32 columns.
     constexpr int NP = NC / 2, UW = MTW * NP;
     const int qkv_bits = e.d == 128 ? 2 : 1;   // QKV: rotary pairs of tiles per head, 4 or 2
@@ -886,7 +899,7 @@ __device__ __forceinline__ void qgemm16_rows(const FusedGemmArgs a, int NT16, in
             in[0] = inputs(min(j, UW - 1) / NP, min(j, UW - 1) % NP);   // of the first two units of its share
             in[1] = inputs(min(j + J, UW - 1) / NP, min(j + J, UW - 1) % NP);
             if (SCALED) {
-                scales.request(e, m_base, true);
+                scales.load(e.ssq_in, e.nss_in, e.M, m_base, 0);
                 scales.finish(e, m_base, rstd_s);   // published by the barrier of hand_wait
             }
             int *way_s = reinterpret_cast<int *>(rstd_s + 16 * MT16);
