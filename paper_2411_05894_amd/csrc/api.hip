@@ -411,15 +411,15 @@ int sssd_verify_init(const sssd_model_config *cfg, const sssd_weights *w, void *
     // Workgroups hand results over within a die where all of a device's eight are there and take the workgroups in turn.
     c->hand = Hand{nullptr, (float *)(c->W.staging + HAND_WORDS), flags & SSSD_NO_WAIT ? 0 : HAND_POLLS};
     {
-        static_assert(HAND_WORD_COUNT * sizeof(uint32_t) <= HAND_WORDS, "the words lie in front of the parts");
+        static_assert(HAND_WORD_COUNT * sizeof(uint64_t) <= HAND_WORDS, "the words lie in front of the parts");
         if (c->W.staging_bytes < HAND_PARTS + HAND_WORDS) INIT_RC(SSSD_ECAPACITY);
-        uint32_t *words = (uint32_t *)c->W.staging, strays = 0;
-        INIT_TRY(hipMemsetAsync(words, 0, HAND_WORD_COUNT * sizeof(uint32_t), s));
+        uint64_t *words = (uint64_t *)c->W.staging, found = 0;
+        INIT_TRY(hipMemsetAsync(words, 0, HAND_WORD_COUNT * sizeof(uint64_t), s));
         INIT_TRY(launch_die_check(words, s));
-        INIT_TRY(hipMemcpyAsync(&strays, words, sizeof(strays), hipMemcpyDeviceToHost, s));
-        INIT_TRY(hipMemsetAsync(words, 0, sizeof(uint32_t), s));
+        INIT_TRY(hipMemcpyAsync(&found, words, sizeof(found), hipMemcpyDeviceToHost, s));
+        INIT_TRY(hipMemsetAsync(words, 0, sizeof(found), s));
         INIT_TRY(hipStreamSynchronize(s));
-        if (c->n_cu == 256 && strays == 0) c->hand.words = words;
+        if (c->n_cu == 256 && found != 0 && (found & (found - 1)) == 0 && !(found >> 63)) c->hand.words = words;
     }
     INIT_TRY(hipStreamSynchronize(s));
     c->magic = MAGIC;
@@ -466,7 +466,8 @@ int sssd_debug_handover(sssd_ctx *c, int32_t B, int32_t k, uint32_t *launches, u
     if (!valid(c) || B <= 0 || k < 0) return SSSD_EINVAL;
     const Dims &D = c->D;
     if (B > D.max_batch || k > D.max_k) return SSSD_ECAPACITY;
-    uint32_t on = 0, n = 0;
+    uint32_t on = 0;
+    uint64_t n = 0;
     if (c->hand.words) {
         const int M = B * (k + 1), ntot[5] = {D.qd + 2 * D.kd, D.h, 2 * D.f, D.h, D.V}, kin[5] = {D.h, D.qd, D.h, D.f, D.h};
         for (int i = 0; i < 5; ++i) on |= (uint32_t)stream_gemm_hands_over(M, ntot[i], kin[i]) << i;
@@ -478,7 +479,7 @@ int sssd_debug_handover(sssd_ctx *c, int32_t B, int32_t k, uint32_t *launches, u
         }
     }
     if (launches) *launches = on;
-    if (late) *late = n;
+    if (late) *late = (uint32_t)n;
     return SSSD_OK;
 }
 

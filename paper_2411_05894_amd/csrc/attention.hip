@@ -552,7 +552,7 @@ __global__ __launch_bounds__(NWAVE * 64) __attribute__((amdgpu_waves_per_eu(2, 2
     const int group = (turn * D.nkv + kvh) * passes + pass;   // by turn, not by sequence: both count to B
     HandWay way = hand_wait(a.hand, group, cut.n, hand_arrive(a.hand, group), &way_s);
     if (way == HAND_TURN_IN) way = hand_turn_in(a.hand, group, cut.n, &way_s);
-    uint32_t left = way == HAND_SHARE ? hand_leave(a.hand, group) : 0;   // under way while the shares are done
+    uint64_t left = way == HAND_SHARE ? hand_leave(a.hand, group) : 0;   // under way while the shares are done
     if (way != HAND_NOTHING) {   // the rows of this pass shared out over the waves of all segments
         const int r_end = min(D.g * (a.k + 1), (rt0 + RT) * 16), step = (way == HAND_ALL ? 1 : cut.n) * NWAVE;
         int r = rt0 * 16 + (way == HAND_ALL ? wave : wave * cut.n + segment);

@@ -539,16 +539,17 @@ __global__ __launch_bounds__(256) void stream_read_kernel(const u32x4 *src, size
     if (threadIdx.x == 0) sink[blockIdx.x] = part[0] ^ part[1] ^ part[2] ^ part[3];
 }
 
-__global__ __launch_bounds__(64) void die_check_kernel(uint32_t *strays)
+__global__ __launch_bounds__(64) void die_check_kernel(uint64_t *found)
 {
-    if (threadIdx.x == 0 && !on_own_die()) atomicAdd(strays, 1u);
+    const uint32_t die = own_die();
+    if (threadIdx.x == 0) __hip_atomic_fetch_or(found, die > 7 ? (uint64_t)1 << 63 : (uint64_t)1 << ((die - blockIdx.x) & 7), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 }  // namespace
 
-hipError_t launch_die_check(uint32_t *strays, hipStream_t s)
+hipError_t launch_die_check(uint64_t *found, hipStream_t s)
 {
-    hipLaunchKernelGGL(die_check_kernel, dim3(512), dim3(64), 0, s, strays);
+    hipLaunchKernelGGL(die_check_kernel, dim3(512), dim3(64), 0, s, found);
     return hipGetLastError();
 }
 

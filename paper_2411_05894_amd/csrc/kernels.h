@@ -145,8 +145,8 @@ hipError_t launch_kv_compact(const Dims &D, const KvGeom &kv, uint16_t *Kc, uint
 hipError_t launch_kv_copy(const Dims &D, const KvGeom &kv, uint16_t *Kc_layer, uint16_t *Vc_layer, int b, int t0, int n_rows,
                           uint16_t *k_ext, uint16_t *v_ext, bool import, int32_t *err_flag, hipStream_t s);
 
-// Counts workgroups that do not run on the die their block index names into *strays.
-hipError_t launch_die_check(uint32_t *strays, hipStream_t s);
+// Sets bit (die - block index) modulo 8 of *found for every workgroup of a launch: one bit where eight dies take them in turn.
+hipError_t launch_die_check(uint64_t *found, hipStream_t s);
 
 // Kernel-level entry points only (parity tests, micro-benchmarks).
 hipError_t launch_pack_act(const float *X, int M, int K, uint16_t *A_hi, uint16_t *A_lo, hipStream_t s);

@@ -894,7 +894,7 @@ __device__ __forceinline__ void qgemm16_rows(const FusedGemmArgs a, int NT16, in
                 }
             };
             put(false);
-            const uint32_t seen = hand_arrive(e.hand, set);
+            const uint64_t seen = hand_arrive(e.hand, set);
             QuadIn in[2];
             in[0] = inputs(min(j, UW - 1) / NP, min(j, UW - 1) % NP);   // of the first two units of its share
             in[1] = inputs(min(j + J, UW - 1) / NP, min(j + J, UW - 1) % NP);
@@ -904,7 +904,7 @@ __device__ __forceinline__ void qgemm16_rows(const FusedGemmArgs a, int NT16, in
             }
             int *way_s = reinterpret_cast<int *>(rstd_s + 16 * MT16);
             HandWay way = hand_wait(e.hand, set, J, seen, way_s);
-            uint32_t left = way == HAND_SHARE ? hand_leave(e.hand, set) : 0;
+            uint64_t left = way == HAND_SHARE ? hand_leave(e.hand, set) : 0;
             if (way == HAND_TURN_IN) {
                 put(true);
                 way = hand_turn_in(e.hand, set, J, way_s);

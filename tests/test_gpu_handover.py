@@ -125,3 +125,41 @@ def test_a_single_column_tile(hidden, ffn, vocab, B, k):
     herr = (got["hidden"] - ref["hidden"]).abs().max().item() / ref["hidden"].abs().max().item()
     assert herr < 5e-3   # a bf16 rounding of a new K or V element may fall the other way: 2^-9 of it
     p.ctx.sssd_verify_destroy()
+
+
+def edge_pair(seed, B, k, max_seq=700):
+    s = SimpleNamespace(name="edge", n_layers=2, hidden=768, n_q_heads=6, n_kv_heads=2, head_dim=128, ffn=2064, vocab=1040, rms_eps=1e-5,
+                        rope_base=10000.0)
+    p = Pair(s, seed=seed, max_batch=B, max_k=k, max_seq=max_seq, unit_gains=False, oracle_batch=1)
+    lens = uniform_int(seed + 1, B * 64 + k, (B,), max_seq // 2, max_seq - k - 1).to(torch.int32)
+    for b in range(B):
+        p.prefill_random_kv(seed + 2, b, int(lens[b]))
+    tokens = uniform_int(seed + 3, B * 64 + k, (B, k + 1), 0, s.vocab - 1)
+    assert p.ctx.sssd_debug_handover(B, k)[0] == QKV | O | GATE_UP | DOWN | LM | ATTENTION
+    return p, tokens.to(DEV, torch.int32), lens.to(DEV), [torch.empty(B, dtype=torch.int32, device=DEV) for _ in range(2)]
+
+
+def test_on_every_stream():
+    """The dies that take a launch's workgroups depend on the stream's hardware queue; contexts made and steps run on any of them hand over."""
+    B, k = 4, 8
+    streams = [torch.cuda.Stream() for _ in range(9)]
+    for s in streams:
+        with torch.cuda.stream(s):
+            torch.zeros(64, device=DEV)
+    torch.cuda.synchronize()
+    p, tokens, lens, ints = edge_pair(121, B, k)
+    p.ctx.sssd_verify_step(tokens, lens, *ints)
+    assert p.ctx.sssd_verify_sync() == 0
+    want = [t.clone() for t in (p.logits, p.hidden, p.that, *ints)]
+    groups = 2 * (8 + 4 * 2)     # of a step, at least: 8 of attention and the column groups of four products in two layers
+    for i, s in enumerate(streams):
+        print(f"hand-over on stream {i}", flush=True)
+        with torch.cuda.stream(s):
+            before = p.ctx.sssd_debug_handover(B, k)[1]
+            for _ in range(8):
+                p.ctx.sssd_verify_step(tokens, lens, *ints)
+            late = p.ctx.sssd_debug_handover(B, k)[1] - before
+            assert p.ctx.sssd_verify_sync() == 0
+        assert late < groups, "workgroups that found themselves on other dies than expected"   # of 8 steps: most groups waited for each other
+        assert all(torch.equal(a, b) for a, b in zip((p.logits, p.hidden, p.that, *ints), want)), i
+    p.ctx.sssd_verify_destroy()
