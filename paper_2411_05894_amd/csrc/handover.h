@@ -17,6 +17,11 @@
 //    group (HAND_GONE); that succeeds only while not everybody has arrived, so the group's workgroups agree on the way taken;
 //  - where the fast way is given up, or leads over several dies, each makes its stores visible to the device (a release fence, about
 //    20 us) and counts itself in a second time, and the last one to do so does the whole group's work.  So no wait is without a bound.
+// Beside other work on the device: a launch's workgroups start in the order of their indexes, and a group's lie next to each other, so of each
+// launch at most one group per die waits for workgroups that have not started, while the groups in front of it finish and make room.
+// Two contexts stepping on two streams, a pair of steps of two 8B layers without / with hand-over, us: 9 rows 350 / 348, 36 rows 604 / 548,
+// 160 rows 802 / 779, 512 rows 1774 / 1789; two processes, a step of each: 351 / 344, 466 / 441, 804 / 786, 1772 / 1772; a step beside two
+// products of 4096 x 4096 x 4096 on another stream: 423 / 414, 503 / 476, 665 / 628, 1143 / 1120.
 #pragma once
 #include "common.h"
 

@@ -19,7 +19,7 @@ DEV = "cuda:0"
 
 @pytest.mark.parametrize("B,k", [(1, 8), (2, 12), (6, 7)])
 def test_replayed_step_equals_the_eager_step(B, k):
-    """M = 9 (small-step kernels), 26 (row halves), 48 (large-M kernels with their epilogue launches)."""
+    """M = 9 (small-step kernels), 26 (row halves), 48 (large-M kernels; the down projection sums its slices inside the launch)."""
     s = MODEL_SHAPES["tiny"]
     p = Pair(s, seed=9, max_batch=B, max_k=k, max_seq=160)
     ctxs = [int(c) for c in uniform_int(31, B * 100 + k, (B,), 0, 100)]

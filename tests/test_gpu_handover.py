@@ -139,6 +139,70 @@ def edge_pair(seed, B, k, max_seq=700):
     return p, tokens.to(DEV, torch.int32), lens.to(DEV), [torch.empty(B, dtype=torch.int32, device=DEV) for _ in range(2)]
 
 
+# Every product and the attention of a step hand over: 36, 144 and 512 rows, segments of sequences of 350..700 positions
+ROWS = pytest.mark.parametrize("B,k", [(4, 8), (16, 8), (16, 31)])
+
+
+@ROWS
+def test_replayed_hand_over(B, k):
+    """Under graph capture, with the program's own steps and synchronisations between the replays."""
+    p, tokens, lens, ints = edge_pair(91, B, k)
+    print(f"replayed hand-over B={B} k={k}", flush=True)
+
+    def outputs():
+        assert p.ctx.sssd_verify_sync() == 0
+        return [p.logits.clone(), p.hidden.clone(), p.that.clone()] + [t.clone() for t in ints]
+
+    def eager(t):
+        p.ctx.sssd_verify_step(t, lens, *ints)
+        return outputs()
+
+    want, other = eager(tokens), (tokens + 1) % 1040
+    side, g = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        with torch.cuda.graph(g, stream=side):
+            p.ctx.sssd_verify_step(tokens, lens, *ints)
+    torch.cuda.current_stream().wait_stream(side)
+    for rep in range(4):
+        for t in (p.logits, p.hidden, p.that, *ints):
+            t.fill_(-5)
+        g.replay()
+        assert all(torch.equal(a, b) for a, b in zip(outputs(), want)), rep
+        eager(other)
+        assert all(torch.equal(a, b) for a, b in zip(eager(tokens), want)), rep
+    p.ctx.sssd_verify_destroy()
+
+
+@ROWS
+def test_two_contexts_at_once(B, k):
+    """Two contexts on two streams: workgroups of one hold compute units that the other's wait for.  Each gives what it gives alone."""
+    both = [edge_pair(seed, B, k) for seed in (101, 111)]
+    streams = [torch.cuda.Stream() for _ in both]
+    want = []
+    for p, tokens, lens, ints in both:
+        p.ctx.sssd_verify_step(tokens, lens, *ints)
+        assert p.ctx.sssd_verify_sync() == 0
+        want.append([t.clone() for t in (p.logits, p.hidden, p.that, *ints)])
+    for turn in range(4):
+        print(f"two contexts B={B} k={k} turn {turn}", flush=True)
+        for p, _, _, ints in both:
+            for t in (p.logits, p.hidden, p.that, *ints):
+                t.fill_(-5)
+        torch.cuda.synchronize()
+        for _ in range(12):
+            for s, (p, tokens, lens, ints) in zip(streams, both):
+                with torch.cuda.stream(s):
+                    p.ctx.sssd_verify_step(tokens, lens, *ints)
+        torch.cuda.synchronize()
+        for (p, _, _, ints), w in zip(both, want):
+            assert all(torch.equal(a, b) for a, b in zip((p.logits, p.hidden, p.that, *ints), w)), turn
+    print("groups that did not wait:", [p.ctx.sssd_debug_handover(B, k)[1] for p, _, _, _ in both], flush=True)
+    for p, _, _, _ in both:
+        assert p.ctx.sssd_verify_sync() == 0
+        p.ctx.sssd_verify_destroy()
+
+
 def test_on_every_stream():
     """The dies that take a launch's workgroups depend on the stream's hardware queue; contexts made and steps run on any of them hand over."""
     B, k = 4, 8
