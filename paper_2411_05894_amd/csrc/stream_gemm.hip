@@ -1050,10 +1050,10 @@ __device__ __forceinline__ void qgemm16_rows(const FusedGemmArgs a, int NT16, in
 // BLOCKS: RB blocks of rows, of MT16 tiles, or (MT16 = 0) the first n8 of eight tiles and the others of six.  Blocks of one
 // size have kernels of their own: in the mixed one they are 2 % slower.
 template <int MT16, int QW, bool BLOCKS, int FORM>
-// Registers: two workgroups of four waves per compute unit up to nine tiles (tiny shape with a vocabulary of 128256, 144 rows:
-// 276 registers and one workgroup 69 us, 256 and two 66), which at three tiles costs more than it gives (8B gate/up at 33 rows
-// 44.4 -> 45.2); four waves per SIMD up to two tiles.
-__global__ __launch_bounds__(QW * 64) __attribute__((amdgpu_waves_per_eu(FORM == DIE ? 1 : (!BLOCKS && MT16 <= 2 ? 4 : (QW == 4 && MT16 >= 4 && MT16 <= (FORM == WHOLE ? 8 : 9) ? 2 : 1))))) void qgemm16_kernel(FusedGemmArgs a, int RB, int n8, int NT16, int pairs)
+// Registers: two workgroups of four waves per compute unit up to nine tiles (tiny shape with a vocabulary of 128256, a step of 144 rows:
+// 324 registers and one workgroup 138 us, 256, six of them spilled, and two 116), which at three tiles costs more than it gives (8B
+// gate/up at 33 rows 44.4 -> 45.2); four waves per SIMD up to two tiles; summed inside the launch one workgroup, which is all it has.
+__global__ __launch_bounds__(QW * 64) __attribute__((amdgpu_waves_per_eu(FORM == DIE ? 1 : (!BLOCKS && MT16 <= 2 ? 4 : (QW == 4 && MT16 >= 4 && MT16 <= 9 ? 2 : 1))))) void qgemm16_kernel(FusedGemmArgs a, int RB, int n8, int NT16, int pairs)
 {
     constexpr int MOST = MT16 ? MT16 : 8;   // row tiles of a workgroup at most
     __shared__ u32x4 lds[QShape<MOST, QW, BLOCKS, FORM>::LDS];

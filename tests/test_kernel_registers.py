@@ -1,6 +1,7 @@
-"""Registers of the built kernels whose grids or plans assume how many workgroups fit a compute unit: four of the split-K
-epilogue kernel (four waves each, 512 registers per SIMD lane: at most 128), two of the attention kernel (at most 256); none
-keeps anything in scratch memory."""
+"""Registers of the built kernels whose grids or plans assume how many workgroups fit a compute unit (512 registers per SIMD lane): four of
+the split-K epilogue kernel, of four waves each, at most 128; two of the attention kernel, at most 256; neither keeps anything in scratch
+memory.  Of the pipelined GEMM two workgroups of four waves at four to nine row tiles, but for the form that sums its slices inside the
+launch, and one of eight, at most 256; the small-step GEMM's sixteen waves, at most 128."""
 import os
 import re
 import shutil
@@ -36,3 +37,17 @@ def test_registers_leave_room_for_the_workgroups_the_launch_assumes(source, name
     assert len(mine) == count, sorted(mine)
     for k, (registers, spilled, scratch) in mine.items():
         assert registers <= most and spilled == 0 and scratch == 0, (k, registers, spilled, scratch)
+
+
+def test_registers_of_the_gemm_kernels(tmp_path):
+    found = kernels("stream_gemm", tmp_path)
+    small = {k: v for k, v in found.items() if "pgemm_kernel" in k}
+    large = {tuple(int(x) for x in re.search(r"qgemm16_kernelILi(\d+)ELi(\d+)ELb(\d)ELi(\d)E", k).groups()): v for k, v in found.items() if "qgemm16_kernel" in k}
+    assert len(small) == 112 and len(large) == 63
+    for k, (registers, _, scratch) in small.items():
+        # 8B and 70B QKV: the row scales' sums beside the first two tiles
+        assert registers <= 128 and scratch <= (32 if "ILi0ELi8ELb0E" in k else 0), (k, registers, scratch)
+    spilled = {(0, 8, 1, 2): 20, (9, 4, 0, 0): 20, (9, 4, 0, 1): 28}   # bytes of scratch a lane: blocks of eight and six tiles; nine tiles, two workgroups
+    for (tiles, waves, blocks, form), (registers, _, scratch) in large.items():
+        limit = 256 if waves == 8 or (4 <= tiles <= 9 and form != 2) else 512
+        assert registers <= limit and scratch <= spilled.get((tiles, waves, blocks, form), 0), (tiles, waves, blocks, form, registers, scratch)
