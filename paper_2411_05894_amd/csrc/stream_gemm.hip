@@ -50,9 +50,9 @@ constexpr __host__ __device__ int small_row_sums(int kpw) { return (PW * kpw * 2
 
 // A row of operand tiles as a buffer: the tile's place in it is a scalar, the lane's record the only vector part of the address.  With
 // 64-bit vector addresses the first loads of a wave held forty registers.
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t tile_row(const void *p, int KT)
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t tile_row(const void *p, int bytes)
 {
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, KT * 1024, 0x00027000);
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, bytes, 0x00027000);
 }
 // Weight tile load.  One reader per byte (RH == 1): streaming, the line is not worth keeping.  Two
 // workgroups of a die reading the same tiles (RH == 2): an ordinary load, so that the line is still in
@@ -126,15 +126,18 @@ __global__ __launch_bounds__(PW * 64) void pgemm_kernel(FusedGemmArgs a)
     const int n_mine = RUNS ? (u_begin + a.upw < a.n_units ? a.upw : a.n_units - u_begin) : (a.n_units - grp + groups - 1) / groups;
     const int n_steps = n_mine * TPU;
 
-    // k-tiles past the matrix (ragged K split) contribute zero activations and re-read the last tile.
+    // k-tiles past the matrix (ragged K split) contribute zero activations and re-read the last tile; a wave that has no others reads
+    // through buffers without records, which return zeros at once: of a K of 1040, 33 k-tiles, seven of sixteen waves (LM head of 128256
+    // at two rows 47.6 -> 41.8 us).
+    const int row_bytes = kt0 < KT ? KT * 1024 : 0;
     int koff[KPW];
 #pragma unroll
     for (int i = 0; i < KPW; ++i) koff[i] = (kt0 + i < KT ? kt0 + i : KT - 1) * 1024;
 
     constexpr bool SCALED = EPI != FEPI_RESID && EPI != FEPI_STORE;
     u32x4 w[KPW], ah[KPW], al[KPW];
-    const auto wp = tile_row(tile_weights<EPI>(a, unit_tile<EPI>(a, u_begin, 0)), KT);
-    const auto hi = tile_row(a.A_hi + (size_t)rt * KT * 64, KT), lo = tile_row(a.A_lo + (size_t)rt * KT * 64, KT);
+    const auto wp = tile_row(tile_weights<EPI>(a, unit_tile<EPI>(a, u_begin, 0)), row_bytes);
+    const auto hi = tile_row(a.A_hi + (size_t)rt * KT * 64, row_bytes), lo = tile_row(a.A_lo + (size_t)rt * KT * 64, row_bytes);
     // Weights and activations of a k-tile together, in the order of their use: its products, and with them the request for the next
     // tile's weights, need not wait for the others.  No activation load under a branch: every wait would cover all of them.
 #pragma unroll
@@ -189,7 +192,7 @@ __global__ __launch_bounds__(PW * 64) void pgemm_kernel(FusedGemmArgs a)
         constexpr bool SCALES = decltype(first)::value && SCALED && !SPLIT, MORE = decltype(more)::value;
         const int unit = u_begin + (s / TPU) * u_stride, part = s % TPU;
         const int next = MORE && s + 1 < n_steps ? s + 1 : s;
-        const auto wn = tile_row(tile_weights<EPI>(a, unit_tile<EPI>(a, u_begin + (next / TPU) * u_stride, next % TPU)), KT);
+        const auto wn = tile_row(tile_weights<EPI>(a, unit_tile<EPI>(a, u_begin + (next / TPU) * u_stride, next % TPU)), row_bytes);
         const f32x4 acc = stream_tile<KPW, MORE, RH>(ah, al, w, wn, koff, lane);
         if (SCALES) scales();
         float *rb = &red[s & 1][0][0];
