@@ -1209,15 +1209,25 @@ __host__ bool is_small(int M, int Ntot, int K)
 // output in memory.  With row blocks no more than the plan above: they fill the device already.
 // Against partial sums and an epilogue launch, us a step: 70B layer at 144 rows 588 -> 570; two 8B layers at 36 rows 443 -> 428, 160 rows
 // 558 -> 544, 512 rows 968 -> 950; layer and head at 91 rows 402 -> 394.
-__host__ bool die_plan(QPlan &p, int KT, int RB)
+//
+// Row blocks and a number of column groups that eight dies cannot share evenly leave dies with fewer workgroups, and fewer slices
+// than the plan above: not where the k-tiles that every workgroup then has more cost more (0.099 us a row tile, as in q_plan) than an epilogue
+// launch and its partial sums (5 us and 0.13 us per MB).  18944 x 3584 at 300 rows, 14 groups, five slices instead of six: 94.5 us inside
+// the launch, 77.4 and 9.2 with partial sums; 3584 x 4608, 18 groups, three instead of four: 42.1, 28.1 and 12.4.
+// Steps of two layers at 512 rows without / with this line, us: hidden 5120, FFN 13824 1208 / 1143; 3072, 24576 1075 / 1032; 4608, 18432
+// 1482 / 1401; 2560, 9728 644 / 621.
+__host__ bool die_plan(QPlan &p, int KT, const RowBlocks &rows, size_t slice_bytes)
 {
+    const int RB = rows.RB;
     const int per_die = (p.groups + 7) / 8 * RB;   // workgroups of a die for one slice
     int J = 32 / per_die;
     if (J > KT / 8) J = KT / 8;
     if (J > 16) J = 16;
     if (RB > 1 && J > p.J) J = p.J;
     if (J < 2 || round_up(p.groups, 8) * RB > HAND_GROUPS) return false;
-    p.kps = (KT + J - 1) / J;
+    const int kps = (KT + J - 1) / J;
+    if (RB > 1 && (kps - p.kps) * ((8.0 * rows.n8 + 6.0 * (RB - rows.n8)) / RB) * 0.099 > 5.0 + 0.13e-6 * (double)slice_bytes * p.J) return false;
+    p.kps = kps;
     p.J = (KT + p.kps - 1) / p.kps;
     return true;
 }
@@ -1239,7 +1249,7 @@ __host__ LargePlan large_plan(int Ntot, int KT, int M, bool hand)
     LargePlan l;
     l.p = q_plan(Ntot, KT * 32, M);
     l.rows = row_blocks(mt16);
-    l.die = hand && l.p.J > 1 && die_plan(l.p, KT, l.rows.RB);
+    l.die = hand && l.p.J > 1 && die_plan(l.p, KT, l.rows, (size_t)mt16 * 16 * Ntot * sizeof(float));
     const int values = l.p.groups * (l.rows.RB > 1 ? 2 : 1);
     l.sums = l.die && values < pairs ? values : pairs;
     l.maxima = l.die ? l.sums : l.p.groups;

@@ -227,3 +227,17 @@ def test_on_every_stream():
         assert late < groups, "workgroups that found themselves on other dies than expected"   # of 8 steps: most groups waited for each other
         assert all(torch.equal(a, b) for a, b in zip((p.logits, p.hidden, p.that, *ints), want)), i
     p.ctx.sssd_verify_destroy()
+
+
+# Nine groups of 256 columns: one die gets two, so a launch that sums its 256 k-tiles inside has half the slices of one that does not.
+# Sixteen share out evenly.
+@pytest.mark.parametrize("hidden,inside", [(2304, False), (4096, True)])
+def test_row_blocks_whose_column_groups_do_not_share_out_evenly(hidden, inside):
+    s = SimpleNamespace(name="edge", n_layers=1, hidden=hidden, n_q_heads=2, n_kv_heads=1, head_dim=64, ffn=8192, vocab=16, rms_eps=1e-5, rope_base=10000.0)
+    layers = [{n: torch.zeros(shp, dtype=torch.bfloat16, device=DEV) for n, _, shp in layer_weight_specs(s)}]
+    g = {n: torch.zeros(shp, dtype=torch.bfloat16, device=DEV) for n, _, shp in global_weight_specs(s)}
+    ctx = sv.VerifyContext(sv.make_config(s, 16, 31, 64), layers, g)
+    for B, k in ((11, 28), (16, 31)):   # 319 and 512 rows
+        assert bool(ctx.sssd_debug_handover(B, k)[0] & DOWN) == inside, (B, k)
+    assert ctx.sssd_debug_handover(16, 8)[0] & DOWN   # one row block: the weights' stream bounds it
+    ctx.sssd_verify_destroy()
