@@ -507,8 +507,9 @@ int run_step(sssd_ctx *c, int32_t B, int32_t k, const int32_t *tokens, const int
     const int M = B * (k + 1);
     StepIO io{tokens, lens, accepted_len, next_token, B, k, parents, path};
 
-    // Per layer QKV, attention, the merge of its segments (where a sequence can have two), O, gate/up, down, and an
-    // epilogue launch after every GEMM on the pipelined kernel whose K is split.
+    // Per layer QKV, attention, O, gate/up, down; a merge of attention's segments and an epilogue launch after a GEMM on the pipelined
+    // kernel whose K is split only where the workgroups of the launch do not hand their results over to each other (attention_hands_over,
+    // stream_gemm_hands_over, a context without words).
     {
         Prof p(c, s, SSSD_PROF_ELEM);
         HIP_TRY(launch_fused_embed(D, io, kv_geom(c), c->embed, c->layers[0].attn_norm, W.X, W.Ah_hi, W.Ah_lo, W.ssq1, W.pos_base,
@@ -574,7 +575,6 @@ int run_step(sssd_ctx *c, int32_t B, int32_t k, const int32_t *tokens, const int
         g.W0 = (const u32x4 *)c->lm_head; g.NT = D.V / 16;
         g.n_units = g.NT; g.Ntot = D.V;
     };
-    // Per layer: QKV, attention and its merge, O, gate/up, down; then the LM head.
     set_qkv(f, 0);
     HIP_TRY(fgemm(FEPI_QKV));
     for (int l = 0; l < D.L; ++l) {

@@ -160,7 +160,8 @@ __global__ __launch_bounds__(PW * 64) void pgemm_kernel(FusedGemmArgs a)
     // first products, 7-10 us of a 9-25 us launch.  The operands of a k-tile are therefore requested together and in the order of use, none
     // under a branch, and nothing else in front of them: 8B step of nine rows 3295 -> 3261 us.
     // The row scales are needed by the first epilogue only: their sums (wave w: of row w) are requested behind the operands and added up
-    // behind the first tile's products, so no load of the first tiles waits for them.
+    // behind the first tile's products, so no load of the first tiles waits for them.  (QKV at eight k-tiles per wave, four sums per lane: seven
+    // registers spilled at the limit of 128, ten accesses in a workgroup's life; 13.6 us, 14.4 with the sums added up in front and four spilled.)
     constexpr int SV = small_row_sums(KPW) / 64;   // per lane
     float sv[SV];
     const int ms = m_base + wave < a.M ? m_base + wave : a.M - 1;
@@ -582,7 +583,9 @@ template <int ROWS, int QW> struct RowScales {
 // of the rows: half the operand reads per MFMA for a second fetch of the weights from the die's L2 (8B gate/up at 512 rows
 // 235 -> 220 us, but 84 -> 100 us at 160 rows, which are still bound by what a compute unit can fetch).
 // What becomes of a workgroup's sums: they are stored for epi_kernel, they are whole and go through the epilogue here, or they are
-// handed over to the workgroups of the same columns and rows, which share the units of the epilogue out.
+// handed over to the workgroups of the same columns and rows, which share the units of the epilogue out.  The last form holds four
+// epilogues, each for a share and for the whole of the work, unrolled: 8-21 thousand instructions, run through once, with 70-200 scalars kept in
+// vector registers; 4-9 us lie between a workgroup's last product and its last store.
 enum QForm { PARTS, WHOLE, DIE };
 template <int MT16, int QW, bool BLOCKS, int FORM> struct QShape {
     static constexpr int QDW = BLOCKS ? 3 : 4;                  // k-tiles in flight
